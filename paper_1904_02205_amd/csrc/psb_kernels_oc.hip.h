@@ -58,17 +58,7 @@ struct Keys {
 __device__ __forceinline__ u32x4 philox_rounds_3_to_9(u32x4 c, const Keys& key)
 {
 #pragma unroll
-    for (int r = 0; r < 7; ++r) {
-        uint32_t hi_a, lo_a, hi_b, lo_b;
-        mulhilo(kMulA, c.x, hi_a, lo_a);
-        mulhilo(kMulB, c.z, hi_b, lo_b);
-        u32x4 t;
-        t.x = hi_b ^ c.y ^ key.k0[r + 3];
-        t.y = lo_b;
-        t.z = hi_a ^ c.w ^ key.k1[r + 3];
-        t.w = lo_a;
-        c = t;
-    }
+    for (int r = 3; r < 10; ++r) c = philox_round(c, key.k0[r], key.k1[r]);
     return c;
 }
 

@@ -31,13 +31,13 @@ constexpr int kUnroll = 8;      // operations per chain per loop iteration
 constexpr int kIters = 1024;
 
 enum Op {
-    OP_XOR_E32, OP_XOR_E64, OP_ADD, OP_ADD3, OP_LSHL_ADD, OP_AND_OR, OP_XAD, OP_BFI, OP_ALIGNBIT, OP_LSHR,
+    OP_XOR_E32, OP_XOR_E64, OP_ADD, OP_ADD3, OP_BITOP3, OP_BITOP3_SGPR, OP_LSHL_ADD, OP_AND_OR, OP_XAD, OP_BFI, OP_ALIGNBIT, OP_LSHR,
     OP_MAD64, OP_MULHI, OP_MULLO, OP_MAD24, OP_MUL24, OP_MULHI24,
     OP_CMP_VCC, OP_CMP_SGPR, OP_ADDC, OP_CMP_ADDC, OP_SUB_LSHR_ADD, OP_CNDMASK,
     OP_PHILOX_ROUND, OP_MAD64_SGPR, OP_XOR_SGPR, OP_PHILOX7_COUNT, OP_PHILOX10, OP_COUNT
 };
 static const char* kNames[OP_COUNT] = {
-    "v_xor_b32 (VOP2)", "v_xor_b32_e64 (VOP3)", "v_add_u32", "v_add3_u32", "v_lshl_add_u32", "v_and_or_b32",
+    "v_xor_b32 (VOP2)", "v_xor_b32_e64 (VOP3)", "v_add_u32", "v_add3_u32", "v_bitop3_b32", "v_bitop3_b32 v, v, v, sgpr", "v_lshl_add_u32", "v_and_or_b32",
     "v_xad_u32", "v_bfi_b32", "v_alignbit_b32", "v_lshrrev_b32",
     "v_mad_u64_u32", "v_mul_hi_u32", "v_mul_lo_u32", "v_mad_i32_i24", "v_mul_i32_i24", "v_mul_hi_u32_u24",
     "v_cmp_lt_u32 -> vcc", "v_cmp_lt_u32_e64 -> sgpr", "v_addc_co_u32", "v_cmp_lt_u32 + v_addc_co_u32",
@@ -56,6 +56,10 @@ __device__ __forceinline__ void step(uint32_t& a, uint32_t& b, uint32_t m)
         asm volatile("v_add_u32_e32 %0, %1, %0" : "+v"(a) : "v"(m));
     } else if constexpr (OP == OP_ADD3) {
         asm volatile("v_add3_u32 %0, %0, %1, %2" : "+v"(a) : "v"(m), "v"(b));
+    } else if constexpr (OP == OP_BITOP3) {
+        asm volatile("v_bitop3_b32 %0, %0, %1, %2 bitop3:0x96" : "+v"(a) : "v"(m), "v"(b));
+    } else if constexpr (OP == OP_BITOP3_SGPR) {
+        asm volatile("v_bitop3_b32 %0, %0, %2, %1 bitop3:0x96" : "+v"(a) : "s"(m), "v"(b));
     } else if constexpr (OP == OP_LSHL_ADD) {
         asm volatile("v_lshl_add_u32 %0, %0, 1, %1" : "+v"(a) : "v"(m));
     } else if constexpr (OP == OP_AND_OR) {
@@ -199,7 +203,8 @@ __global__ void __launch_bounds__(256) k_rate(uint32_t* out, uint32_t m, int ite
 // One generator round (two wide multiplies, four xors on their results) on the eight chains, in three instruction
 // orders: 0 = chain by chain (the "philox round" row above), 1 = the sixteen multiplies, then the 32 xors,
 // 2 = the multiplies of chain c between the xors of chain c - 1.  A mixed stream issues more slowly than its
-// parts, and the order moves it by some 10 %.
+// parts, and the order moves it by some 10 %.  3 = chain by chain with the four xors as two v_bitop3_b32: every
+// instruction of the round has the same cost then.
 template <int ORDER>
 __global__ void __launch_bounds__(256) k_rate_round(uint32_t* out, uint32_t m, int iters, unsigned long long* ticks)
 {
@@ -211,6 +216,10 @@ __global__ void __launch_bounds__(256) k_rate_round(uint32_t* out, uint32_t m, i
     }
     auto mul = [&](uint64_t& p, uint32_t v) { asm volatile("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(p) : "v"(v), "v"(m) : "vcc"); };
     auto x2 = [&](uint32_t& x, uint32_t y) {
+        if constexpr (ORDER == 3) {
+            asm volatile("v_bitop3_b32 %0, %0, %1, %2 bitop3:0x96" : "+v"(x) : "v"(y), "v"(m));
+            return;
+        }
         asm volatile("v_xor_b32_e32 %0, %1, %0" : "+v"(x) : "v"(y));
         asm volatile("v_xor_b32_e32 %0, %1, %0" : "+v"(x) : "v"(m));
     };
@@ -218,7 +227,7 @@ __global__ void __launch_bounds__(256) k_rate_round(uint32_t* out, uint32_t m, i
     const unsigned long long w0 = wall_clock64();
     for (int it = 0; it < iters * kUnroll; ++it) {
         uint64_t pa[kChains], pb[kChains];
-        if constexpr (ORDER == 0) {
+        if constexpr (ORDER == 0 || ORDER == 3) {
 #pragma unroll
             for (int c = 0; c < kChains; ++c) {
                 mul(pa[c], a[c]);
@@ -363,14 +372,16 @@ int main(int argc, char** argv)
     for (int i = 0; i < 4; ++i)
         if (run_all<0>(out, ticks, simds, wps[i], all[i])) return 2;
 
-    static const char* kOrderNames[3] = {"round, chain by chain: M M x x x x", "round, all multiplies, then all xors",
-                                         "round, multiplies of chain c between the xors of c-1"};
-    Result orders[4][3];
+    static const char* kOrderNames[4] = {"round, chain by chain: M M x x x x", "round, all multiplies, then all xors",
+                                         "round, multiplies of chain c between the xors of c-1",
+                                         "round, chain by chain, three-input xors: M M b b"};
+    Result orders[4][4];
     for (int i = 0; i < 4; ++i) {
         const int blocks = simds * wps[i] / 4;
         if (run_round<0>(out, ticks, blocks, wps[i], &orders[i][0])) return 2;
         if (run_round<1>(out, ticks, blocks, wps[i], &orders[i][1])) return 2;
         if (run_round<2>(out, ticks, blocks, wps[i], &orders[i][2])) return 2;
+        if (run_round<3>(out, ticks, blocks, wps[i], &orders[i][3])) return 2;
     }
 
     if (json) {
@@ -381,7 +392,7 @@ int main(int argc, char** argv)
                         kNames[op], all[0][op].ns, all[1][op].ns, all[2][op].ns, all[3][op].ns, all[2][op].clock_ghz);
         }
         std::printf("}, \"round_orders\": {");
-        for (int o = 0; o < 3; ++o)
+        for (int o = 0; o < 4; ++o)
             std::printf("%s\"%s\": {\"ns\": [%.4f, %.4f, %.4f, %.4f], \"measured_clock_ghz\": %.3f}", o ? ", " : "",
                         kOrderNames[o], orders[0][o].ns, orders[1][o].ns, orders[2][o].ns, orders[3][o].ns, orders[2][o].clock_ghz);
         std::printf("}}\n");
@@ -392,7 +403,7 @@ int main(int argc, char** argv)
             std::printf("%-40s %7.3f %7.3f %7.3f %7.3f   clock %.3f GHz  -> %6.2f cycles\n", kNames[op], all[0][op].ns,
                         all[1][op].ns, all[2][op].ns, all[3][op].ns, all[2][op].clock_ghz,
                         all[2][op].ns * all[2][op].clock_ghz);
-        for (int o = 0; o < 3; ++o)
+        for (int o = 0; o < 4; ++o)
             std::printf("%-52s %7.3f %7.3f %7.3f %7.3f   clock %.3f GHz  -> %6.2f cycles\n", kOrderNames[o], orders[0][o].ns,
                         orders[1][o].ns, orders[2][o].ns, orders[3][o].ns, orders[2][o].clock_ghz,
                         orders[2][o].ns * orders[2][o].clock_ghz);
