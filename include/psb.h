@@ -152,9 +152,8 @@ int psb_weights_export(const psb_weights_t* q, uint32_t* packed_host);
 
 /* Release a handle (NULL is allowed).  The caller must make sure no layer call
  * using it is still running.
- * A handle also owns a device word with which the layer kernel hands out work to its
- * workgroups (every call resets it on its stream before the kernel starts) and the
- * workspaces named below.  Layer calls that use the SAME handle must therefore not
+ * A handle also owns the workspaces named below; those in which partial sums meet are
+ * zero between calls (every call leaves them so).  Layer calls that use the SAME handle must therefore not
  * overlap in time (same stream, or ordered by events); calls on different handles may
  * run concurrently. */
 void psb_weights_destroy(psb_weights_t* q);
@@ -302,11 +301,10 @@ int psb_conv2d_requant(const psb_weights_t* q, const int8_t* x_dev, const psb_co
  * psb_conv2d_requant for callers that cannot allocate device memory: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  It is psb_conv2d_requant with acc_dev = NULL and shared = 0 (per-product
  * mode, requantised activations and/or rescaled values out, no accumulators handed out), element for element, but
- * the scratch memory of its kernels - the ticket counter of the persistent layer kernel and the accumulators in
- * which the partial sums of a split tap reduction meet - is a fixed array inside the library's device code instead
- * of memory owned by the handle.  The call issues no hipMalloc, no hipFree and no synchronisation.
+ * the scratch memory of its kernels - the accumulators in which the partial sums of a split tap reduction meet -
+ * is a fixed array inside the library's device code instead of memory owned by the handle.  The call issues no hipMalloc, no hipFree and no synchronisation.
  *  - Limit: n * OH * OW * (oc rounded up to a multiple of 64) <= PSB_STATIC_MAX_OUTPUTS (the array holds that many
- *    int32 accumulators, 32 MiB, plus 256 bytes; each GPU the library runs on holds it until the process ends).
+ *    int32 accumulators, 32 MiB; each GPU the library runs on holds it until the process ends).
  *    Larger calls return TOO_LARGE and launch nothing.
  *  - All calls on one GPU share that GPU's array, and it keeps the last call's contents; the call clears what it
  *    needs (in a kernel, not a memset, so it can be captured).  Two such calls that overlap in time on one GPU -

@@ -29,6 +29,8 @@ struct shared_workspace {
     uint32_t* present_dev = nullptr; // 256 flags: budget values that occur
     int32_t* acc_dev = nullptr;      // accumulators of calls that do not hand any out but combine partial sums
     size_t acc_bytes = 0;
+    int32_t* acc_cl_dev = nullptr;   // per-product mode: partial sums of a split reduction, zero between calls
+    size_t acc_cl_bytes = 0;
     // digit planes sampled ahead of the call by psb_shared_prepare_filters; the next matching call consumes them
     bool ready = false;
     uint64_t ready_seed = 0;
@@ -53,14 +55,36 @@ int32_t* scratch_acc(shared_workspace* ws, size_t bytes, hipStream_t stream)
     return ws->acc_dev;
 }
 
-// Scratch memory of psb_conv2d_requant_static: the ticket counter of the persistent layer kernel (first word of a
-// 256-byte head) and the accumulators in which the partial sums of a split tap reduction meet.  A file-scope device
-// array, so that the entry point never allocates; every GPU the library runs on holds its own copy at its own
-// address until the process ends.  Host code never uses the array's name as an address: the per-device pointer
+// The accumulators in which the partial sums of the channel-lane kernel meet (grown on demand).  Cleared here once, with a
+// kernel; every call leaves them at zero.
+int32_t* scratch_acc_cl(shared_workspace* ws, size_t bytes, hipStream_t stream)
+{
+    if (ws->acc_cl_bytes < bytes) {
+        if (ws->acc_cl_dev) {
+            if (hipStreamSynchronize(stream) != hipSuccess) return nullptr;   // an earlier call may still use it
+            (void)hipFree(ws->acc_cl_dev);
+            ws->acc_cl_dev = nullptr;
+            ws->acc_cl_bytes = 0;
+        }
+        if (hipMalloc(&ws->acc_cl_dev, bytes) != hipSuccess) return nullptr;
+        const int64_t words = (int64_t)(bytes / sizeof(int32_t));
+        hipLaunchKernelGGL(psb::k_fill_zero, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 8192)), dim3(256), 0, stream,
+                           ws->acc_cl_dev, words);
+        if (hipGetLastError() != hipSuccess) {
+            (void)hipFree(ws->acc_cl_dev);
+            ws->acc_cl_dev = nullptr;
+            return nullptr;
+        }
+        ws->acc_cl_bytes = bytes;
+    }
+    return ws->acc_cl_dev;
+}
+
+// Scratch memory of psb_conv2d_requant_static: the accumulators in which the partial sums of a split tap
+// reduction meet.  A file-scope device array, so that the entry point never allocates; every GPU the library runs on holds its own copy at its own address until the process ends.  Host code never uses the array's name as an address: the per-device pointer
 // comes from hipGetSymbolAddress (static_scratch() below).
-constexpr size_t kStaticHeadWords = 64;
 constexpr size_t kStaticAccWords = (size_t)PSB_STATIC_MAX_OUTPUTS;
-static __device__ __align__(256) uint32_t scratch[kStaticHeadWords + kStaticAccWords];
+static __device__ __align__(256) uint32_t scratch[kStaticAccWords];
 
 struct psb_weights {
     psb_wshape shape;
@@ -73,7 +97,6 @@ struct psb_weights {
     uint2* tile_dev;         // [K][oc_pad] {threshold, unit}
     uint32_t* live_idx_dev;  // [OC][K]: live taps of each channel first, any order
     uint32_t* live_cnt_dev;  // [OC]
-    uint32_t* sched_dev;     // ticket counter and finish counter of the persistent kernel (both 0 between calls)
     shared_workspace* ws;    // shared-filter mode
 };
 
@@ -217,6 +240,7 @@ void fill_geometry(const psb_weights* q, const psb_conv_geom* g, int32_t OH, int
     p.s_max = q->s_max; p.prob_bits = q->prob_bits;
     p.default_mult = std::ldexp(1.0f, q->info.e_min);
     p.max_shift = q->info.e_top - q->info.e_min;
+    p.inv_OW = psb::inverse_of((uint32_t)OW); p.inv_OH = psb::inverse_of((uint32_t)OH);
 }
 
 int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, int32_t S,
@@ -245,22 +269,28 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
 
     const int mapping = pick_mapping(q, p);
     if (mapping < 0) return mapping;
-    uint32_t* sched = q->sched_dev;
     // the channel-lane kernel combines the partial sums of a split tap reduction in scratch accumulators
     const bool split = mapping == 2 && psb::oc_lane_chunks(p).n_chunks > 1;
-    if (use_static_scratch) {           // ticket counter and accumulators in the static array: nothing is allocated
+    if (use_static_scratch) {           // the accumulators lie in the static array: nothing is allocated
         uint32_t* base = nullptr;
         rc = static_scratch(dev, &base);
         if (rc != PSB_OK) return rc;
-        sched = base;
-        if (split) p.acc_cl = reinterpret_cast<int32_t*>(base + kStaticHeadWords);
+        if (split) {
+            // all handles of a GPU share the array: cleared before every call, so that calls that overlapped against
+            // the contract cannot harm later ones
+            p.acc_cl = reinterpret_cast<int32_t*>(base);
+            const int64_t words = (int64_t)p.N * OH * OW * p.oc_pad;
+            hipLaunchKernelGGL(psb::k_fill_zero, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 8192)), dim3(256), 0, stream,
+                               p.acc_cl, words);
+            PSB_HIP_TRY(hipGetLastError());
+        }
     } else if (split) {
-        p.acc_cl = scratch_acc(q->ws, (size_t)p.N * OH * OW * (size_t)p.oc_pad * sizeof(int32_t), stream);
+        p.acc_cl = scratch_acc_cl(q->ws, (size_t)p.N * OH * OW * (size_t)p.oc_pad * sizeof(int32_t), stream);
         if (!p.acc_cl) return PSB_ERR_ALLOC;
     }
 
     if (mapping == 2) {
-        rc = psb::launch_oc_lane(p, sched, stream, profile_begin, profile_end);
+        rc = psb::launch_oc_lane(p, stream, profile_begin, profile_end);
         if (rc != 0) { tl_last_device_error = rc; return PSB_ERR_DEVICE; }
     } else if (mapping == 3) {
         rc = psb::launch_product_list(p, q->live_idx_dev, q->live_cnt_dev, stream, profile_begin, profile_end);
@@ -819,11 +849,9 @@ int psb_quantize_weights(const float* w_dev, const psb_wshape* shape, int32_t pr
     if (hipMalloc(&q->packed_dev, (size_t)nw * sizeof(uint32_t)) != hipSuccess) return fail(PSB_ERR_ALLOC, hipSuccess);
     if (hipMalloc(&q->tile_dev, (size_t)oc_pad * K * sizeof(uint2)) != hipSuccess)
         return fail(PSB_ERR_ALLOC, hipSuccess);
-    if (hipMalloc(&q->sched_dev, 2 * sizeof(uint32_t)) != hipSuccess) return fail(PSB_ERR_ALLOC, hipSuccess);
     if (hipMalloc(&q->live_idx_dev, (size_t)nw * sizeof(uint32_t)) != hipSuccess) return fail(PSB_ERR_ALLOC, hipSuccess);
     if (hipMalloc(&q->live_cnt_dev, (size_t)OC * sizeof(uint32_t)) != hipSuccess) return fail(PSB_ERR_ALLOC, hipSuccess);
     QTRY(hipMemsetAsync(scratch, 0, scratch_words * sizeof(uint32_t), stream));
-    QTRY(hipMemsetAsync(q->sched_dev, 0, 2 * sizeof(uint32_t), stream));
 
     // 1. largest exponent, NaN/Inf detection
     {
@@ -900,7 +928,6 @@ void psb_weights_destroy(psb_weights_t* q)
     if (!q) return;
     if (q->packed_dev) (void)hipFree(q->packed_dev);
     if (q->tile_dev) (void)hipFree(q->tile_dev);
-    if (q->sched_dev) (void)hipFree(q->sched_dev);
     if (q->live_idx_dev) (void)hipFree(q->live_idx_dev);
     if (q->live_cnt_dev) (void)hipFree(q->live_cnt_dev);
     if (q->ws) {
@@ -910,6 +937,7 @@ void psb_weights_destroy(psb_weights_t* q)
         if (q->ws->present_dev) (void)hipFree(q->ws->present_dev);
         if (q->ws->qmap_dev) (void)hipFree(q->ws->qmap_dev);
         if (q->ws->acc_dev) (void)hipFree(q->ws->acc_dev);
+        if (q->ws->acc_cl_dev) (void)hipFree(q->ws->acc_cl_dev);
         delete q->ws;
     }
     delete q;

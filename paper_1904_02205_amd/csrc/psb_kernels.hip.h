@@ -159,6 +159,18 @@ __global__ void __launch_bounds__(256) k_pack(const uint32_t* __restrict__ w_bit
 // Layer kernels
 // ---------------------------------------------------------------------------------
 
+// x / d and x % d for any 32-bit x, given inv = floor(2^32 / d) (0xFFFFFFFF for d = 1): the product's high word
+// is the quotient or one less.
+__host__ __device__ inline uint32_t inverse_of(uint32_t d) { return d <= 1u ? 0xFFFFFFFFu : (uint32_t)(0x100000000ull / d); }
+__device__ __forceinline__ uint32_t div_mod(uint32_t x, uint32_t d, uint32_t inv, uint32_t& rem)
+{
+    uint32_t q = __umulhi(x, inv);
+    uint32_t r = x - q * d;
+    if (r >= d) { ++q; r -= d; }
+    rem = r;
+    return q;
+}
+
 // Optional second output of a layer call: the next layer's 8-bit activations, made from the rescaled value in
 // the same kernel (suppl. "ReLU, Batch-Norm, and Pooling": ReLU as a gate on the sign; "Activations and
 // Accumulation": fixed-point activations):  x = clamp(rint(g(y [+ r]) * inv_step), lo, hi).
@@ -194,6 +206,7 @@ struct LayerParams {
     uint32_t key0, key1, layer_id;
     float default_mult;        // 2^e_min
     int max_shift;             // largest shift of a live weight
+    uint32_t inv_OW, inv_OH;   // inverse_of(OW), inverse_of(OH): pixel indices are decomposed by multiplication
     Requant rq;
 };
 
@@ -224,6 +237,15 @@ __device__ __forceinline__ uint32_t count_below(uint32_t o, uint32_t k, uint32_t
 __device__ __forceinline__ uint32_t not_below7(uint32_t word, uint32_t thr4, uint32_t valid)
 {
     return (uint32_t)__popc(((word | 0x80808080u) - thr4) & valid);
+}
+
+// n + the bytes whose uniform IS below the threshold: (127 - u) + t has bit 7 set exactly when u < t, and no byte
+// carries into its neighbour.  (Assembly: the compiler would count into zero and add afterwards.)
+__device__ __forceinline__ uint32_t add_below7(uint32_t n, uint32_t word, uint32_t thr4, uint32_t valid)
+{
+    uint32_t sum;
+    asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(sum) : "v"(((~word & 0x7F7F7F7Fu) + thr4) & valid), "v"(n));
+    return sum;
 }
 
 // 0x80 in byte b of word w of block j for every sample 16j + 4w + b inside [from, to)

@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
                         for (int j = 0; j < NB; ++j) {
                             const uint2 pb = pix_blk[pl][j];
                             const uint2 tb = tap_blk[slot][j];
-                            cnt[u] += sample_block<4, P7>(thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j, 0, 0);
+                            cnt[u] = sample_block<4, P7>(cnt[u], thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j, 0, 0);
                         }
                     } else {
                         const uint32_t ou = o_s[ent[u] & 0xFFu];

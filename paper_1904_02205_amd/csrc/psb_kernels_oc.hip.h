@@ -14,7 +14,7 @@
 // sums are combined with int32 atomic adds, which is exact in any order because the
 // accumulator arithmetic is modulo 2^32.  They meet in scratch accumulators laid out
 // [N*OH*OW][OC padded to 64], where the 64 adds of a wave are consecutive words; a last
-// pass turns them into the [N][OC][OH][OW] outputs.
+// pass turns them into the [N][OC][OH][OW] outputs and leaves the scratch at zero for the next call.
 //
 // Philox work saved without changing a bit of the result.  Counter = (o, k, j, layer).
 // Round 0 multiplies o and j; o is fixed per lane and pixel, j is a literal.  Round 1
@@ -32,13 +32,25 @@
 
 namespace psb {
 
-constexpr int kOcWaves = 4;     // waves per workgroup
-constexpr int kOcMaxTaps = 64;  // taps per LDS tile: 64 * 64 channels * 8 B = 32 KB
+constexpr int kOcWaves = 16;    // waves per workgroup
+constexpr int kOcMaxTaps = 64;  // taps per step of a wave: one activation per lane
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
-// a*b + c with 24-bit signed a, b (full-rate v_mad_i32_i24)
-__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c) { return __mul24(a, b) + c; }
+// x * n and a * b + c with 24-bit signed factors.  Inline assembly: through __mul24 the compiler turns the product with
+// an activation byte into a 32-bit multiply, a shift and another multiply.
+__device__ __forceinline__ int32_t mul24(int32_t x /* scalar */, int32_t n)
+{
+    int32_t d;
+    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(d) : "s"(x), "v"(n));
+    return d;
+}
+__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c)
+{
+    int32_t d;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
 
 struct PixelHoist {
     uint32_t lo_a;    // low half of MulA * o                          (round 0, word 3)
@@ -46,10 +58,7 @@ struct PixelHoist {
     uint32_t y2k;     // low half of the same product, xor round-2 key 0
 };
 
-// Round keys and multipliers.  Everything here is wave-uniform and stays in scalar registers.  (An instruction
-// stream in which EVERY two-operand VALU instruction has a scalar-register source issues at half rate on gfx950 -
-// 4.2 vs 2.4 cycles per wave64 - but in this loop only the key xors and the multiplies by the two constants have
-// one, and copies of the keys (16 registers) or of the two multipliers in vector registers measured no gain.)
+// Round keys of a call: wave-uniform, computed once per wave.
 struct Keys {
     uint32_t k0[10], k1[10];
 };
@@ -72,14 +81,14 @@ __device__ __forceinline__ TapScalars tap_scalars(uint32_t s_x1, const Keys& key
     return TapScalars{s_hi ^ key.k1[1], s_lo};
 }
 
-// Number of samples of block j of one product that are below thr.  P7: the block holds sixteen 7-bit
+// n + the number of samples of block j of one product that are below thr.  P7: the block holds sixteen 7-bit
 // uniforms and thr the 7-bit threshold in each byte; otherwise four 32-bit uniforms.
 // VALID = 4: every sample of the block counts; 1..3: the first VALID samples count with 32-bit uniforms, the first
 // 4 VALID (whole words) with 7-bit uniforms (the last block of a range that starts on a block boundary);
 // 0: the range [from,to) is checked at run time.
 // state after round 1: (.., .., ts.sz ^ lo_a, ts.s_lo); words 0 and 1 were used in the per-pixel set-up.
 template <int VALID, bool P7>
-__device__ __forceinline__ uint32_t sample_block(uint32_t thr, TapScalars ts, const PixelHoist& h, uint32_t hz,
+__device__ __forceinline__ uint32_t sample_block(uint32_t n, uint32_t thr, TapScalars ts, const PixelHoist& h, uint32_t hz,
                                                  uint32_t lo2, const Keys& key, int j, int from, int to)
 {
     const uint32_t z2 = ts.sz ^ h.lo_a;
@@ -92,20 +101,19 @@ __device__ __forceinline__ uint32_t sample_block(uint32_t thr, TapScalars ts, co
     c.z = hz ^ ts.s_lo;
     c.w = lo2;
     c = philox_rounds_3_to_9(c, key);
-    uint32_t n = 0;
     if constexpr (P7) {
         if constexpr (VALID > 0) {       // the first 4 VALID samples of the block: its first VALID words, whole
             const uint32_t all = 0x80808080u;
-            uint32_t not_below = not_below7(c.x, thr, all);
-            if (VALID > 1) not_below += not_below7(c.y, thr, all);
-            if (VALID > 2) not_below += not_below7(c.z, thr, all);
-            if (VALID > 3) not_below += not_below7(c.w, thr, all);
-            return (uint32_t)(4 * VALID) - not_below;
+            n = add_below7(n, c.x, thr, all);
+            if (VALID > 1) n = add_below7(n, c.y, thr, all);
+            if (VALID > 2) n = add_below7(n, c.z, thr, all);
+            if (VALID > 3) n = add_below7(n, c.w, thr, all);
+            return n;
         }
-        const int lo = max(from, 16 * j), hi = min(to, 16 * j + 16);
-        return (uint32_t)(hi - lo) -
-               (not_below7(c.x, thr, valid_bytes7(j, 0, from, to)) + not_below7(c.y, thr, valid_bytes7(j, 1, from, to)) +
-                not_below7(c.z, thr, valid_bytes7(j, 2, from, to)) + not_below7(c.w, thr, valid_bytes7(j, 3, from, to)));
+        n = add_below7(n, c.x, thr, valid_bytes7(j, 0, from, to));
+        n = add_below7(n, c.y, thr, valid_bytes7(j, 1, from, to));
+        n = add_below7(n, c.z, thr, valid_bytes7(j, 2, from, to));
+        return add_below7(n, c.w, thr, valid_bytes7(j, 3, from, to));
     } else if constexpr (VALID > 0) {
         n += (c.x < thr) ? 1u : 0u;
         if (VALID > 1) n += (c.y < thr) ? 1u : 0u;
@@ -135,357 +143,264 @@ __device__ __forceinline__ void block_setup(const PixelHoist& h, const Keys& key
     lo2 = lo_a2;
 }
 
-// Entry i of the wave's compacted tap list; the list lives in one VGPR (lane i = entry i).
-__device__ __forceinline__ uint32_t list_entry(uint32_t mylist, int i)
-{
-    return (uint32_t)__builtin_amdgcn_readlane((int)mylist, i);
-}
+// One step of a wave: a pixel and up to 64 consecutive taps.
+struct Step {
+    unsigned long long mask;      // taps whose product needs sampling (scalar)
+    int32_t xv;                   // lane t: activation of tap t of the step
+    const char* w;                // weights of the step's first tap and of the ticket's first channel (scalar)
+    uint32_t w_stride;            // bytes between the weights of consecutive taps (scalar)
+    uint32_t k0;                  // the step's first tap (scalar)
+};
 
-// All products of one pixel's compacted tap list, NB generator blocks per product
-// (NB = 0: run-time number of blocks).  Returns this lane's partial accumulator.
-// mylist: lane i holds entry i = (tap index inside the tile << 8) | activation byte, and 0
-// beyond cnt (entry 0 addresses tile row 0, so reading one group ahead is always in bounds).
-// VALID: see sample_block; with NB > 1 it applies to every block (only 4 is used then).
+// All products of one step for NB consecutive generator blocks, the first being block j0.  Returns this lane's
+// partial accumulator: the sum over the products of x * unit * (nsamp + count), nsamp = number of samples counted.
+// VALID: see sample_block; with NB > 1 it applies to every block (only 4 is used then).  VALID = 0: the samples of
+// block j0 inside [from, to).
+// Nothing is compacted: the next product's tap is the lowest bit left in the mask, its activation that lane's value,
+// and its weights - 512 consecutive bytes, which the waves of a CU share through L1 and L2 - are requested one product
+// ahead.  One generator call after the other: eight waves per SIMD hide each other's latencies, and a call costs a
+// SIMD 63 ns then, against 69 ns with four waves that interleave two or four calls each.
 template <int NB, int VALID, bool P7>
-__device__ __forceinline__ int32_t process_list(uint32_t mylist, int cnt, const uint2* __restrict__ w_tile,
-                                                int lane, uint32_t k0, int j0, int nb_rt, int from, int to,
-                                                const PixelHoist& h, const Keys& key)
+__device__ __forceinline__ int32_t process_step(const Step& s, int lane, int j0, int from, int to, const PixelHoist& h,
+                                                const Keys& key)
 {
-    const uint32_t nsamp = (uint32_t)(to - from);
+    const uint32_t nsamp = VALID > 0 ? (uint32_t)(NB * VALID * (P7 ? 4 : 1)) : (uint32_t)(to - from);
     int32_t acc = 0;
-    if constexpr (NB == 0) {
-        for (int i = 0; i < cnt; ++i) {
-            const uint32_t entry = list_entry(mylist, i);
-            const uint32_t kl = entry >> 8;
-            const int32_t xs = (int32_t)(int8_t)(entry & 0xFFu);
-            const uint2 wt = w_tile[kl * 64 + lane];
-            uint32_t n = nsamp;
-            for (int jj = 0; jj < nb_rt; ++jj) {
-                uint32_t s_hib, hz, lo2;
-                block_setup(h, key, j0 + jj, s_hib, hz, lo2);
-                n += sample_block<0, P7>(wt.x, tap_scalars(s_hib ^ (k0 + kl), key), h, hz, lo2, key, j0 + jj, from, to);
-            }
-            acc = mad24(__mul24(xs, (int32_t)n), (int32_t)wt.y, acc);
-        }
-        return acc;
-    } else {
-        constexpr int E = (NB >= 4) ? 1 : 4 / NB;   // products in flight: keep four generator calls independent
-        uint32_t s_hib[NB], hz[NB], lo2[NB];
+    uint32_t s_hib[NB], hz[NB], lo2[NB];
 #pragma unroll
-        for (int jj = 0; jj < NB; ++jj) block_setup(h, key, j0 + jj, s_hib[jj], hz[jj], lo2[jj]);
+    for (int jj = 0; jj < NB; ++jj) block_setup(h, key, j0 + jj, s_hib[jj], hz[jj], lo2[jj]);
 
-        // Software pipeline: while group g is sampled, the list entries of group g+1 are read, their
-        // weights fetched from LDS and the scalar half of their generator calls computed.
-        uint32_t ent_next[E];
-        uint2 wt_next[E];
-        TapScalars ts_next[E][NB];
+    struct Product { uint32_t t; uint2 wt; };
+    unsigned long long rest = s.mask;
+    uint32_t last = 0;
+    auto take = [&]() {               // the next tap and its weights; the same tap again when none is left
+        uint32_t f;
+        asm("s_ff1_i32_b64 %0, %1" : "=s"(f) : "s"(rest));
+        last = rest != 0ull ? f : last;
+        asm("s_bitset0_b64 %0, %1" : "+s"(rest) : "s"(last));
+        // a scalar address and the lane's constant offset: no address arithmetic in vector registers
+        typedef const __attribute__((address_space(1))) char* GlobalPtr;
+        typedef const __attribute__((address_space(1))) unsigned long long* GlobalEntry;
+        GlobalPtr row = (GlobalPtr)s.w + (uint64_t)last * s.w_stride;
+        uint32_t at = (uint32_t)lane * 8u;
+        asm("" : "+s"(row), "+v"(at));
+        const unsigned long long e = *(GlobalEntry)(row + at);
+        return Product{last, make_uint2((uint32_t)e, (uint32_t)(e >> 32))};
+    };
+    auto sample = [&](const Product& q) {
+        const int32_t x = __builtin_amdgcn_readlane(s.xv, (int)q.t);
+        uint32_t n = nsamp;
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            ent_next[e] = list_entry(mylist, e);
-            wt_next[e] = w_tile[(ent_next[e] >> 8) * 64 + lane];
-#pragma unroll
-            for (int jj = 0; jj < NB; ++jj) ts_next[e][jj] = tap_scalars(s_hib[jj] ^ (k0 + (ent_next[e] >> 8)), key);
+        for (int jj = 0; jj < NB; ++jj) {
+            n = sample_block<VALID, P7>(n, q.wt.x, tap_scalars(s_hib[jj] ^ (s.k0 + q.t), key), h, hz[jj], lo2[jj], key, j0 + jj, from, to);
+            __builtin_amdgcn_sched_barrier(0);     // one call after the other: interleaved calls only take more registers
         }
-        int i = 0;
-        for (; i + E <= cnt; i += E) {
-            uint2 wt[E];
-            int32_t xs[E];
-            TapScalars ts[E][NB];
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                xs[e] = (int32_t)(int8_t)(ent_next[e] & 0xFFu);
-                wt[e] = wt_next[e];
-#pragma unroll
-                for (int jj = 0; jj < NB; ++jj) ts[e][jj] = ts_next[e][jj];
-            }
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                ent_next[e] = list_entry(mylist, (i + E + e) & 63);
-                wt_next[e] = w_tile[(ent_next[e] >> 8) * 64 + lane];
-#pragma unroll
-                for (int jj = 0; jj < NB; ++jj)
-                    ts_next[e][jj] = tap_scalars(s_hib[jj] ^ (k0 + (ent_next[e] >> 8)), key);
-            }
-            // the counts of the blocks are independent of each other: no serial chain over the samples
-            uint32_t cnt_b[E][NB];
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-#pragma unroll
-                for (int jj = 0; jj < NB; ++jj)
-                    cnt_b[e][jj] = sample_block<VALID, P7>(wt[e].x, ts[e][jj], h, hz[jj], lo2[jj], key, j0 + jj, from, to);
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                uint32_t n = nsamp;
-#pragma unroll
-                for (int jj = 0; jj < NB; ++jj) n += cnt_b[e][jj];
-                acc = mad24(__mul24(xs[e], (int32_t)n), (int32_t)wt[e].y, acc);
-            }
-        }
-        if constexpr (E > 1) {
-            for (; i < cnt; ++i) {      // fewer than E products left
-                const uint32_t entry = list_entry(mylist, i);
-                const uint2 wt = w_tile[(entry >> 8) * 64 + lane];
-                uint32_t n = nsamp;
-#pragma unroll
-                for (int jj = 0; jj < NB; ++jj)
-                    n += sample_block<VALID, P7>(wt.x, tap_scalars(s_hib[jj] ^ (k0 + (entry >> 8)), key), h, hz[jj], lo2[jj],
-                                            key, j0 + jj, from, to);
-                acc = mad24(__mul24((int32_t)(int8_t)(entry & 0xFFu), (int32_t)n), (int32_t)wt.y, acc);
-            }
-        }
-        return acc;
+        acc = mad24(mul24(x, (int32_t)n), (int32_t)q.wt.y, acc);
+    };
+    int left = __popcll(s.mask);
+    Product a = take();
+    for (; left >= 2; left -= 2) {    // two at a time, so that the weights requested ahead need not change registers
+        const Product b = take();
+        sample(a);
+        a = take();
+        sample(b);
     }
+    if (left) sample(a);
+    return acc;
 }
 
-// Persistent kernel.  A ticket is one (channel block, tap chunk, group of WAVES * ppw pixels:
-// ppw per wave); tickets are numbered so that consecutive tickets are consecutive pixel groups
-// of the same (channel block, chunk).  Workgroups draw tickets from a device counter until none is left:
-// the grid is only as large as the chip can hold at once, there is no launch gap between
-// work items, and the tail at the end of the kernel is at most one ticket long.
-//   sched[0] = number of tickets drawn from the counter; the launcher sets it to 0 on the stream before
-//   every launch (in the kernel that zero-fills the accumulators, where there is one).
-// FIXED_P7: the layer uses 7-bit uniforms (prob_bits < 23); each kernel is compiled for one of the two.
+// How the launcher cuts a call into tickets.
+struct OcPlan {
+    int n_chunks, kc;             // the taps are cut into n_chunks chunks of kc taps, none empty
+    int ppw;                      // consecutive pixels of a ticket
+    uint32_t pixel_groups;        // groups of ppw pixels
+    uint32_t n_tickets;           // pixel_groups * n_chunks * channel blocks
+    uint32_t rounds;              // rounds in which every workgroup takes a whole batch of tickets
+    uint32_t inv_groups, inv_chunks, inv_KHW, inv_KW;     // inverse_of()
+};
+
+// Workgroup b of a grid of n runs on XCD b mod 8: its position when the workgroups of an XCD are next to each other.
+__device__ __forceinline__ uint32_t xcd_grouped(uint32_t b, uint32_t n)
+{
+    const uint32_t xcd = b & 7u, per = n >> 3, more = n & 7u;
+    return xcd * per + min(xcd, more) + (b >> 3);
+}
+
+// The kernel's arguments, read again from the argument segment: the compiler would keep the fields of a 300-byte
+// parameter block in scalar registers (and spill them to vector registers, of which eight waves per SIMD have 64
+// each); loaded where they are used they cost a few scalar loads per pixel.
+struct OcArgs {
+    LayerParams p;
+    OcPlan plan;
+};
+__device__ __forceinline__ const OcArgs& reload_args()
+{
+    auto ptr = __builtin_amdgcn_kernarg_segment_ptr();       // points to constant memory: scalar loads
+    asm volatile("" : "+s"(ptr));
+    return *(const OcArgs*)ptr;
+}
+
+// Persistent kernel of independent waves: two workgroups of sixteen per CU, eight waves per SIMD.  A ticket is one
+// (channel block, tap chunk, group of ppw pixels); tickets are numbered so that consecutive tickets are consecutive pixel
+// groups of the same (channel block, chunk), whose weights all waves then share in the caches.  Sixteen consecutive
+// tickets are a batch; the workgroups take the batches in turn (an XCD's workgroups next to each other; what does not
+// fill a round is dealt ticket by ticket), and inside a workgroup a wave that is done draws the next ticket from a
+// counter in LDS.  The waves never wait for each other.
+// (One counter in memory for the whole chip hands out a ticket every 14 to 46 ns, which is all the time that 8192
+// waves have for one.)
+// FIXED_P7: the layer uses 7-bit uniforms (prob_bits < 8); each kernel is compiled for one of the two.
 // FIXED_NB > 0: every pixel draws generator blocks 0 .. FIXED_NB-1 completely (a call with one S everywhere that is
-// a whole number of blocks).  Only that path of the sampling loop is compiled then, which
-// takes 76 vector registers instead of 110 and measured 3 % faster than the kernel that can do everything.
+// a whole number of blocks).  Only that path of the sampling loop is compiled then.
 // FIXED_VALID < 4 (with FIXED_NB = 1, 7-bit uniforms): every pixel draws the first 4 FIXED_VALID samples of block 0
 // (S = 4, 8 or 12: a 16-sample block is more than such a call needs).
-// ppw: pixels per wave and ticket.
-template <int WAVES, int FIXED_NB = 0, bool FIXED_P7 = false, int FIXED_VALID = 4>
-__global__ void __launch_bounds__(WAVES * 64) k_layer_oc_lane(const LayerParams p, int n_chunks, int kc,
-                                                              uint32_t pixel_groups, uint32_t n_tickets,
-                                                              uint32_t* __restrict__ sched, int ppw)
+template <int FIXED_NB = 0, bool FIXED_P7 = false, int FIXED_VALID = 4>
+__global__ void __launch_bounds__(kOcWaves * 64, 8) k_layer_oc_lane(const OcArgs args)
 {
-    __shared__ uint2 w_tile[kOcMaxTaps * 64];
-    __shared__ int2 tap_tab[kOcMaxTaps];
-    __shared__ uint32_t lists[WAVES][kOcMaxTaps];
-    __shared__ uint32_t s_ticket;
-
     const int lane = threadIdx.x & 63;
-    const int wave = (int)uniform_u32(threadIdx.x >> 6);
-
     Keys key;
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        key.k0[r] = p.key0 + (uint32_t)r * kWeyl0;
-        key.k1[r] = p.key1 + (uint32_t)r * kWeyl1;
+        key.k0[r] = args.p.key0 + (uint32_t)r * kWeyl0;
+        key.k1[r] = args.p.key1 + (uint32_t)r * kWeyl1;
+        // the keys of rounds 3..9 stay in vector registers: a three-input xor with a scalar operand issues at half rate
+        if (r >= 3) {
+            asm("v_mov_b32 %0, %1" : "=v"(key.k0[r]) : "s"(key.k0[r]));
+            asm("v_mov_b32 %0, %1" : "=v"(key.k1[r]) : "s"(key.k1[r]));
+        }
     }
-
-    const int64_t npix = (int64_t)p.N * p.OH * p.OW;
-    uint32_t* list = lists[wave];
-    uint32_t staged = 0xFFFFFFFFu;   // (channel block, chunk) whose weights are in w_tile
-
-    // The first ticket of a workgroup is its index (the grid never exceeds the number of tickets); only
-    // later ones come from the counter, so the launch does not start with every workgroup hitting one address.
-    bool first = true;
+    __shared__ uint32_t s_next;
+    if (threadIdx.x == 0) s_next = 0;
+    __syncthreads();
     for (;;) {
-        uint32_t ticket;
-        if (first) {
-            ticket = blockIdx.x;
-            first = false;
-        } else {
-            if (threadIdx.x == 0) s_ticket = gridDim.x + atomicAdd(&sched[0], 1u);
-            __syncthreads();
-            ticket = s_ticket;
-        }
-        if (ticket >= n_tickets) break;   // uniform over the workgroup
-        const uint32_t combo = ticket / pixel_groups;
-        const uint32_t pgroup = ticket - combo * pixel_groups;
-        const int chunk = (int)(combo % (uint32_t)n_chunks);
-        const int ocb = (int)(combo / (uint32_t)n_chunks);
-        const int k0 = chunk * kc;
-        const int kn = min(kc, p.K - k0);   // > 0: the launcher sizes n_chunks so that no chunk is empty
+        uint32_t drawn = 0;
+        if (lane == 0) drawn = atomicAdd(&s_next, 1u);
+        drawn = uniform_u32(drawn);
+        const uint32_t mine = xcd_grouped(blockIdx.x, gridDim.x), rounds = args.plan.rounds;
+        const uint32_t ticket = drawn < rounds * kOcWaves
+                                    ? ((drawn / kOcWaves) * gridDim.x + mine) * kOcWaves + drawn % kOcWaves
+                                    : (rounds * kOcWaves + (drawn - rounds * kOcWaves)) * gridDim.x + mine;
+        if (ticket >= args.plan.n_tickets) break;            // later draws of this workgroup lie beyond it, too
 
-        if (combo != staged) {
-            // stage this chunk's weights (taps k0..k0+kn-1, channels ocb*64..+63): coalesced 512 B rows
-            for (int i = threadIdx.x; i < kn * 64; i += WAVES * 64)
-                w_tile[i] = p.tile[(int64_t)(k0 + (i >> 6)) * p.oc_pad + ocb * 64 + (i & 63)];
-            // tap table: offset of the tap inside one image relative to (iy0, ix0), and (kh, kw)
-            for (int t = threadIdx.x; t < kn; t += WAVES * 64) {
-                const int k = k0 + t;
-                const int khw = p.KH * p.KW;
-                const int ci = k / khw;
-                const int r = k - ci * khw;
-                const int kh = r / p.KW;
-                const int kw = r - kh * p.KW;
-                tap_tab[t] = make_int2((ci * p.H + kh) * p.W + kw, kh | (kw << 16));
-            }
-            staged = combo;
+        uint32_t pgroup, chunk, ocb;
+        int k_begin, k_end, ppw;
+        {
+            const OcArgs& a = reload_args();
+            const uint32_t combo = div_mod(ticket, a.plan.pixel_groups, a.plan.inv_groups, pgroup);
+            ocb = div_mod(combo, (uint32_t)a.plan.n_chunks, a.plan.inv_chunks, chunk);
+            k_begin = (int)chunk * a.plan.kc;
+            k_end = min(k_begin + a.plan.kc, a.p.K);
+            ppw = a.plan.ppw;
         }
-        __syncthreads();
+        const int oc = (int)ocb * 64 + lane;
+        // this lane's tap of the chunk (a chunk has at most 64 taps): its offset inside an image relative to tap (0, 0)
+        // of channel 0, and its row and column; the same for every pixel of the ticket
+        const bool has_tap = k_begin + lane < k_end;
+        uint32_t tap_off, tap_at;
+        const char* weights;
+        {
+            const OcArgs& a = reload_args();
+            uint32_t r, kw;
+            const uint32_t ci = div_mod((uint32_t)(k_begin + lane), (uint32_t)(a.p.KH * a.p.KW), a.plan.inv_KHW, r);
+            const uint32_t kh = div_mod(r, (uint32_t)a.p.KW, a.plan.inv_KW, kw);
+            tap_off = (ci * (uint32_t)a.p.H + kh) * (uint32_t)a.p.W + kw;
+            tap_at = kh | (kw << 16);                               // below 2^15 each
+            weights = reinterpret_cast<const char*>(a.p.tile + ((int64_t)k_begin * a.p.oc_pad + (int64_t)ocb * 64));
+        }
 
-        const int oc = ocb * 64 + lane;
-        // This lane's tap of the chunk (a chunk has at most 64 taps: one per lane) is the same for every pixel of
-        // the ticket.  The activation of the NEXT pixel is requested before the current one is sampled, so that the
-        // load's latency falls into the sampling loop.
-        static_assert(kOcMaxTaps <= 64, "one tap per lane");
-        const bool has_tap = lane < kn;
-        const int2 info = has_tap ? tap_tab[lane] : make_int2(0, 0);
-        struct Pixel { bool valid; int ox, oy, n; uint32_t pix; };
-        auto locate = [&](int pp) {
-            const int64_t pix = ((int64_t)pgroup * ppw + pp) * WAVES + wave;       // wave-uniform
-            Pixel q;
-            q.valid = pix < npix;
-            const uint32_t pc = q.valid ? (uint32_t)pix : 0u;      // the number of outputs fits 32 bits
-            q.pix = pc;
-            const uint32_t row = pc / (uint32_t)p.OW;
-            q.ox = (int)(pc - row * (uint32_t)p.OW);
-            q.n = (int)(row / (uint32_t)p.OH);
-            q.oy = (int)(row - (uint32_t)q.n * (uint32_t)p.OH);
-            return q;
-        };
-        auto request = [&](const Pixel& q) {
-            int32_t xv = 0;
-            const int iy0 = q.oy * p.stride_h - p.pad_h, ix0 = q.ox * p.stride_w - p.pad_w;
-            const int iy = iy0 + (info.y & 0xFFFF), ix = ix0 + (info.y >> 16);
-            if (q.valid && has_tap && (unsigned)iy < (unsigned)p.H && (unsigned)ix < (unsigned)p.W)
-                xv = p.x[((int64_t)q.n * p.C * p.H + iy0) * p.W + ix0 + info.x];
-            return xv;
-        };
-        // the pixel's sample range travels with its activation (a load between two pixels would make the wave wait
-        // for the next pixel's activation as well); kernels for a fixed block count have no budget maps
-        auto budget = [&](const Pixel& q, int pp, int& to_raw, int& from_raw) {
-            if constexpr (FIXED_NB == 0) {
-                const int64_t pix = ((int64_t)pgroup * ppw + pp) * WAVES + wave;
-                to_raw = (q.valid && p.budget_to) ? (int)p.budget_to[pix] : p.S;
-                from_raw = (q.valid && p.budget_from) ? (int)p.budget_from[pix] : 0;
-            }
-        };
-        Pixel next = locate(0);
-        int32_t xv_next = request(next);
-        int to_next = 0, from_next = 0;
-        budget(next, 0, to_next, from_next);
         for (int pp = 0; pp < ppw; ++pp) {
-        const Pixel me = next;
-        const int32_t xv = xv_next;
-        const int to_raw = to_next, from_raw = from_next;
-        if (pp + 1 < ppw) {
-            next = locate(pp + 1);
-            xv_next = request(next);
-            budget(next, pp + 1, to_next, from_next);
-        }
-        if (me.valid) {   // wave-uniform
-            const int ox = me.ox, oy = me.oy, n = me.n;
-
-            int to, from;
-            if constexpr (FIXED_NB > 0) {
-                to = min(p.S, p.s_max);
-                from = 0;
-            } else {
-                to = min(to_raw, p.s_max);
-                from = min(from_raw, to);
-                to = (int)uniform_u32((uint32_t)to);
-                from = (int)uniform_u32((uint32_t)from);
+            // everything about a pixel but its activations is scalar
+            const LayerParams& p = reload_args().p;
+            const uint32_t hw = (uint32_t)(p.OH * p.OW);
+            const uint64_t at64 = (uint64_t)pgroup * (uint32_t)ppw + (uint32_t)pp;
+            if (at64 >= (uint32_t)p.N * hw) break;           // the number of outputs fits 32 bits
+            const uint32_t pix = (uint32_t)at64;
+            uint32_t ox, oy;
+            const uint32_t row = div_mod(pix, (uint32_t)p.OW, p.inv_OW, ox);
+            const uint32_t n = div_mod(row, (uint32_t)p.OH, p.inv_OH, oy);
+            int to = min(p.S, p.s_max), from = 0;
+            if constexpr (FIXED_NB == 0) {
+                if (p.budget_to) to = min((int)uniform_u32(p.budget_to[pix]), p.s_max);
+                if (p.budget_from) from = min((int)uniform_u32(p.budget_from[pix]), to);
             }
+            const int iy0 = (int)oy * p.stride_h - p.pad_h, ix0 = (int)ox * p.stride_w - p.pad_w;
+            const uint32_t x_base = (n * (uint32_t)(p.C * p.H) + (uint32_t)iy0) * (uint32_t)p.W + (uint32_t)ix0;
 
-            const uint32_t o = (uint32_t)((((int64_t)n * p.OC + oc) * p.OH + oy) * p.OW + ox);
+            // ((n OC + oc) OH + oy) OW + ox, with pix = (n OH + oy) OW + ox
+            const uint32_t o = pix + n * (uint32_t)(p.OC - 1) * hw + (uint32_t)oc * hw;
+            PixelHoist h;
+            uint32_t hi_a, lo_b1;
+            mulhilo(kMulA, o, hi_a, h.lo_a);                       // round 0: MulA * o
+            const uint32_t z1 = hi_a ^ p.layer_id ^ key.k1[0];      // state word 2 after round 0
+            mulhilo(kMulB, z1, h.hi_b1, lo_b1);                    // round 1: MulB * z1
+            h.y2k = lo_b1 ^ key.k0[2];
+
             int32_t total = 0;
-
             if (to > from) {
-                // keep the non-zero ones of this pixel's taps of the chunk
-                int cnt = 0;
-                {
-                    const int t = lane;
-                    const unsigned long long mask = __ballot(xv != 0);
-                    const int pos = cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                    if (xv != 0) list[pos] = ((uint32_t)t << 8) | ((uint32_t)xv & 0xFFu);
-                    cnt += __popcll(mask);
-                }
-                // the list is written and read by this wave only: order the LDS accesses
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-                if (cnt > 0) {
-                    const uint32_t mylist = (lane < cnt) ? list[lane] : 0u;
-                    PixelHoist h;
-                    uint32_t hi_a;
-                    mulhilo(kMulA, o, hi_a, h.lo_a);                       // round 0: MulA * o
-                    const uint32_t z1 = hi_a ^ p.layer_id ^ key.k1[0];      // state word 2 after round 0
-                    uint32_t lo_b1;
-                    mulhilo(kMulB, z1, h.hi_b1, lo_b1);                    // round 1: MulB * z1
-                    h.y2k = lo_b1 ^ key.k0[2];
-
-                    // generator blocks serve 4 samples (32-bit uniforms) or 16 (7-bit uniforms)
-                    constexpr bool p7 = FIXED_P7;
-                    constexpr int lg = p7 ? 4 : 2;
-                    const int j0 = from >> lg;
-                    const int nb = ((to + (1 << lg) - 1) >> lg) - j0;
-                    const bool full = ((from | to) & ((1 << lg) - 1)) == 0;
-                    const uint32_t kbase = (uint32_t)k0;
-#define PSB_LIST(NB_, VALID_, P7_) \
-    total = process_list<NB_, VALID_, P7_>(mylist, cnt, w_tile, lane, kbase, j0, nb, from, to, h, key)
+                int32_t xv = 0;
+                if (has_tap && (unsigned)(iy0 + (int)(tap_at & 0xFFFFu)) < (unsigned)p.H && (unsigned)(ix0 + (int)(tap_at >> 16)) < (unsigned)p.W)
+                    xv = p.x[x_base + tap_off];                     // modulo 2^32: the element exists
+                const Step step{__ballot(xv != 0), xv, weights, (uint32_t)p.oc_pad * 8u, (uint32_t)k_begin};
+                if (step.mask != 0ull) {
+#define PSB_STEP(NB_, VALID_, J0_, FROM_, TO_) \
+    total += process_step<NB_, VALID_, FIXED_P7>(step, lane, J0_, FROM_, TO_, h, key)
                     if constexpr (FIXED_NB > 0) {
-                        PSB_LIST(FIXED_NB, FIXED_VALID, FIXED_P7);
-                    } else if constexpr (p7) {
-                        if (full && nb == 1) PSB_LIST(1, 4, true);
-                        else if (full && nb == 2) PSB_LIST(2, 4, true);
-                        else if (nb == 1 && (from & 15) == 0 && ((to - from) & 3) == 0) {
-                            // one block, its first whole words
-                            switch ((to - from) >> 2) {
-                                case 1: PSB_LIST(1, 1, true); break;
-                                case 2: PSB_LIST(1, 2, true); break;
-                                default: PSB_LIST(1, 3, true); break;
-                            }
-                        } else if (nb == 1) PSB_LIST(1, 0, true);
-                        else PSB_LIST(0, 0, true);
+                        PSB_STEP(FIXED_NB, FIXED_VALID, 0, 0, 0);
                     } else {
-                    if (full) {
-                        switch (nb) {
-                            case 1: PSB_LIST(1, 4, false); break;
-                            case 2: PSB_LIST(2, 4, false); break;
-                            case 4: PSB_LIST(4, 4, false); break;
-                            case 8: PSB_LIST(8, 4, false); break;
-                            default: PSB_LIST(0, 0, false); break;
+                        // Any range: a first block that is not drawn from its start, whole blocks, a last block that is not
+                        // drawn to its end.  Every part is compiled for its number of blocks and goes over the mask once.
+                        constexpr int kPer = FIXED_P7 ? 16 : 4;       // samples of a generator block
+                        int at = from;
+                        if (at & (kPer - 1)) {
+                            const int end = min(to, (at | (kPer - 1)) + 1);
+                            PSB_STEP(1, 0, at / kPer, at, end);
+                            at = end;
                         }
-                    } else if (nb == 1 && (from & 3) == 0) {
-                        // one block, its first to - from samples: fewer comparisons, no range checks
-                        switch (to - from) {
-                            case 1: PSB_LIST(1, 1, false); break;
-                            case 2: PSB_LIST(1, 2, false); break;
-                            default: PSB_LIST(1, 3, false); break;
+                        for (; to - at >= 2 * kPer; at += 2 * kPer) PSB_STEP(2, 4, at / kPer, 0, 0);
+                        if (to - at >= kPer) {
+                            PSB_STEP(1, 4, at / kPer, 0, 0);
+                            at += kPer;
                         }
-                    } else if (nb == 1) {
-                        PSB_LIST(1, 0, false);
-                    } else {
-                        PSB_LIST(0, 0, false);
+                        const int left = to - at;                      // the first samples of block at / kPer
+                        if constexpr (FIXED_P7) {
+                            if (left & 3) PSB_STEP(1, 0, at / kPer, at, to);
+                            else if (left == 4) PSB_STEP(1, 1, at / kPer, 0, 0);
+                            else if (left == 8) PSB_STEP(1, 2, at / kPer, 0, 0);
+                            else if (left == 12) PSB_STEP(1, 3, at / kPer, 0, 0);
+                        } else {
+                            if (left == 1) PSB_STEP(1, 1, at / kPer, 0, 0);
+                            else if (left == 2) PSB_STEP(1, 2, at / kPer, 0, 0);
+                            else if (left == 3) PSB_STEP(1, 3, at / kPer, 0, 0);
+                        }
                     }
-                    }
-#undef PSB_LIST
+#undef PSB_STEP
                 }
             }
-
-            if (oc < p.OC) {
-                if (n_chunks == 1) {
-                    if (p.budget_from) total += p.acc[o];
-                    if (p.acc) p.acc[o] = total;
-                    emit(p, o, oc, total, to);
+            const OcArgs& a = reload_args();
+            const LayerParams& pe = a.p;
+            if (oc < pe.OC) {
+                if (a.plan.n_chunks == 1) {
+                    if (pe.budget_from) total += pe.acc[o];
+                    if (pe.acc) pe.acc[o] = total;
+                    emit(pe, o, oc, total, to);
                 } else if (total != 0) {
                     // the 64 channels of the wave are 64 consecutive words: the adds of a wave are one or two
                     // requests of whole lines (in [N][OC][OH][OW] order they would be 64 lines, one plane apart,
                     // which the memory side takes 16 times more slowly)
-                    atomicAdd(&p.acc_cl[(int64_t)me.pix * p.oc_pad + oc], total);
+                    atomicAdd(&pe.acc_cl[(int64_t)pix * pe.oc_pad + oc], total);
                 }
             }
         }
-        }   // pixels of this wave in the ticket
-        // all waves are done with the tile, the lists and s_ticket before the next ticket is drawn
-        __syncthreads();
     }
-
 }
 
-// acc[i] = 0 and, if given, the ticket counter of the persistent kernel = 0  (a plain store kernel: safe inside a
-// captured graph, unlike a memset node)
-__global__ void __launch_bounds__(256) k_fill_zero(int32_t* __restrict__ acc, int64_t n, uint32_t* __restrict__ sched = nullptr)
+// acc[i] = 0  (a plain store kernel: safe inside a captured graph, unlike a memset node)
+__global__ void __launch_bounds__(256) k_fill_zero(int32_t* __restrict__ acc, int64_t n)
 {
-    if (sched && blockIdx.x == 0 && threadIdx.x == 0) sched[0] = 0u;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         acc[i] = 0;
 }
 
-// Rescaled value and/or requantised activation for layers whose accumulators were combined with atomics.
+// Rescaled value and/or requantised activation for layers whose accumulators were combined with atomics in p.acc.
 __global__ void __launch_bounds__(256) k_rescale(const LayerParams p)
 {
     const int64_t total = (int64_t)p.N * p.OC * p.OH * p.OW;
@@ -495,52 +410,72 @@ __global__ void __launch_bounds__(256) k_rescale(const LayerParams p)
         const int64_t pix = (i / (hw * p.OC)) * hw + (i % hw);
         int to = p.budget_to ? (int)p.budget_to[pix] : p.S;
         to = min(to, p.s_max);
-        int32_t v;
-        if (p.acc_cl) {     // partial sums of the channel-lane kernel, channels last (small layers: see below)
-            v = p.acc_cl[pix * p.oc_pad + oc];
-            if (p.budget_from) v += p.acc[i];
-            if (p.acc) p.acc[i] = v;
-        } else {
-            v = p.acc[i];
-        }
-        emit(p, i, oc, v, to);
+        emit(p, i, oc, p.acc[i], to);
     }
 }
 
-// The same for the channel-lane kernel's split reduction, whose partial sums met in acc_cl [N*OH*OW][oc_pad]:
+// The last pass of the channel-lane kernel's split reduction, whose partial sums met in acc_cl [N*OH*OW][oc_pad]:
 // acc (if given; with budget_from it holds the earlier samples' sums and the new ones are added), rescaled value
-// and/or requantised activation, all [N][OC][OH][OW].  A workgroup moves a tile of 64 pixels x 64 channels through
-// LDS, so that it reads whole rows of channels and writes runs of 64 pixels.  (Layers whose partial sums fit the L2
-// several times over take k_rescale instead: one output per thread, more workgroups.)
+// and/or requantised activation, all [N][OC][OH][OW].  acc_cl is left at zero, as the next call wants to find it: one
+// launch less per call than clearing it there (linear 512->256, batch 64: 24.1 -> 22 us), and the lines are at hand.
+// A workgroup moves a tile of PX pixels x 64 channels through LDS, so that it reads whole rows of channels and writes
+// runs of PX pixels; 64 where that leaves a few workgroups per CU, else 16.
+template <int PX>
 __global__ void __launch_bounds__(256) k_rescale_channels_last(const LayerParams p)
 {
-    __shared__ int32_t tile[64][65];
-    const int64_t npix = (int64_t)p.N * p.OH * p.OW;
-    const int64_t pix0 = (int64_t)blockIdx.x * 64;
-    const int oc0 = blockIdx.y * 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll 4
-    for (int r = 0; r < 16; ++r) {
-        const int px = r * 4 + wave;
-        tile[lane][px] = (pix0 + px < npix) ? p.acc_cl[(pix0 + px) * p.oc_pad + oc0 + lane] : 0;
+    __shared__ int32_t tile[64][PX + 1];
+    const uint32_t hw = (uint32_t)(p.OH * p.OW);
+    const uint32_t npix = (uint32_t)p.N * hw;                    // the number of outputs fits 32 bits
+    const uint32_t pix0 = blockIdx.x * (uint32_t)PX;
+    const uint32_t oc0 = blockIdx.y * 64u;
+    {
+        const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+#pragma unroll
+        for (uint32_t r = 0; r < PX / 4; ++r) {
+            const uint32_t px = r * 4u + wave;
+            if (pix0 + px < npix) {
+                int32_t* const at = p.acc_cl + ((uint64_t)(pix0 + px) * (uint32_t)p.oc_pad + oc0 + lane);
+                tile[lane][px] = *at;
+                *at = 0;
+            }
+        }
     }
     __syncthreads();
-    const int64_t pix = pix0 + lane;
+    const uint32_t px = threadIdx.x % PX, group = threadIdx.x / PX, pix = pix0 + px;
+    constexpr uint32_t kGroups = 256 / PX;
     if (pix >= npix) return;
-    const int64_t hw = (int64_t)p.OH * p.OW;
-    const int64_t n = pix / hw, rem = pix - n * hw;
+    uint32_t ox, oy;
+    const uint32_t row = div_mod(pix, (uint32_t)p.OW, p.inv_OW, ox);
+    const uint32_t n = div_mod(row, (uint32_t)p.OH, p.inv_OH, oy);
     int to = p.budget_to ? (int)p.budget_to[pix] : p.S;
     to = min(to, p.s_max);
 #pragma unroll 4
-    for (int r = 0; r < 16; ++r) {
-        const int oc = oc0 + r * 4 + wave;
-        if (oc >= p.OC) break;
-        const int64_t o = (n * p.OC + oc) * hw + rem;
-        int32_t v = tile[r * 4 + wave][lane];
+    for (uint32_t r = 0; r < 64 / kGroups; ++r) {
+        const uint32_t c = r * kGroups + group, oc = oc0 + c;
+        if (oc >= (uint32_t)p.OC) break;
+        const uint32_t o = pix + (n * (uint32_t)(p.OC - 1) + oc) * hw;          // ((n OC + oc) OH + oy) OW + ox
+        int32_t v = tile[c][px];
         if (p.budget_from) v += p.acc[o];
         if (p.acc) p.acc[o] = v;
-        emit(p, o, oc, v, to);
+        emit(p, (int64_t)o, (int)oc, v, to);
     }
+}
+
+// The same for 1 x 1 outputs (linear layers), where [N*OH*OW][oc] and [N][OC][OH][OW] run in the same order.
+__global__ void __launch_bounds__(256) k_rescale_rows(const LayerParams p)
+{
+    const uint32_t oc = blockIdx.y * 64u + (threadIdx.x & 63u), n = blockIdx.x * 4u + (threadIdx.x >> 6);
+    if (n >= (uint32_t)p.N) return;
+    int32_t* const at = p.acc_cl + ((uint64_t)n * (uint32_t)p.oc_pad + oc);
+    int32_t v = *at;
+    *at = 0;
+    if (oc >= (uint32_t)p.OC) return;
+    int to = p.budget_to ? (int)p.budget_to[n] : p.S;
+    to = min(to, p.s_max);
+    const uint32_t o = n * (uint32_t)p.OC + oc;
+    if (p.budget_from) v += p.acc[o];
+    if (p.acc) p.acc[o] = v;
+    emit(p, (int64_t)o, (int)oc, v, to);
 }
 
 // The channel-lane kernel needs groups = 1 and products that fit the 24-bit multiplier
@@ -583,39 +518,38 @@ inline int oc_lane_cus()
     return cus;
 }
 
-// resident workgroups per CU: 160 KB of LDS hold four tiles; 512 VGPRs per lane hold four waves per SIMD
-constexpr int kOcWgPerCu = 4;
+// resident waves per CU: the kernel is built for eight per SIMD
+constexpr int kOcWavesPerCu = 32;
 
 // How the launcher cuts the tap reduction of a layer: n_chunks chunks of kc taps (at most kOcMaxTaps), as equal as
-// possible, none empty; a layer too small to give every resident workgroup a ticket gets shorter chunks (down to 16
-// taps) instead of leaving part of the chip idle.  With more than one chunk the partial sums meet in
-// LayerParams::acc_cl, which the caller provides.
+// possible, none empty; a layer too small to give every resident wave a ticket gets shorter chunks (down to 16
+// taps) instead of leaving part of the chip idle.  (Shorter chunks beyond that cost more set-up than they even out: 3x3
+// 64->64 at 56x56, 3.4 tickets of 64 taps per wave, 238 us with 64 and 32 taps, 241 with 24 and 16; 512->512 at 7x7, 7-bit,
+// 1577 / 1663 / 1864 us with 64 / 32 / 16.)  With a budget map the tickets of a call differ by the ratio of its budgets,
+// and 32 taps are better up to 32 tickets per wave (128->128 at 28x28, budgets 2..32, 28 of them: 898 -> 854 us).
+// With more than one chunk the partial sums meet in LayerParams::acc_cl, which the caller provides.
 struct OcChunks { int n_chunks, kc; };
 inline OcChunks oc_lane_chunks(const LayerParams& p)
 {
     int max_taps = oc_tuning().max_taps;
     const int64_t n_ocb = p.oc_pad / 64;
     const int64_t npix = (int64_t)p.N * p.OH * p.OW;
-    const int64_t pixel_groups = (npix + kOcWaves - 1) / kOcWaves;
     OcChunks c;
     for (;;) {
         c.n_chunks = (p.K + max_taps - 1) / max_taps;
         c.kc = (p.K + c.n_chunks - 1) / c.n_chunks;
         c.n_chunks = (p.K + c.kc - 1) / c.kc;
-        if (pixel_groups * c.n_chunks * n_ocb >= (int64_t)oc_lane_cus() * kOcWgPerCu || max_taps <= 16) break;
+        const int64_t waves = (int64_t)oc_lane_cus() * kOcWavesPerCu;
+        const int64_t want = p.budget_to && max_taps > 32 ? 32 * waves : waves;
+        if (npix * c.n_chunks * n_ocb >= want || max_taps <= 16) break;
         max_taps /= 2;
     }
     return c;
 }
 
-inline int launch_oc_lane(const LayerParams& p, uint32_t* sched, hipStream_t stream, ProfileBegin prof_begin,
-                          ProfileEnd prof_end)
+inline int launch_oc_lane(const LayerParams& p, hipStream_t stream, ProfileBegin prof_begin, ProfileEnd prof_end)
 {
     if (!oc_lane_supported(p)) return (int)hipErrorInvalidValue;
-    const OcTuning& tuning = oc_tuning();
-    constexpr int waves = kOcWaves;
-    const int cus = oc_lane_cus();
-    const int wg_per_cu = kOcWgPerCu;
     // one S everywhere, a whole number of generator blocks for which a specialised kernel is built (0: none)
     const bool p7 = p.prob_bits <= 7;
     const int per_block = p7 ? 16 : 4;
@@ -629,69 +563,46 @@ inline int launch_oc_lane(const LayerParams& p, uint32_t* sched, hipStream_t str
     }
     const int n_ocb = p.oc_pad / 64;
     const int64_t npix = (int64_t)p.N * p.OH * p.OW;
-    int64_t pixel_groups = (npix + waves - 1) / waves;
     const OcChunks chunks = oc_lane_chunks(p);
-    const int n_chunks = chunks.n_chunks, kc = chunks.kc;
+    const int n_chunks = chunks.n_chunks;
     if (n_chunks > 1 && !p.acc_cl) return (int)hipErrorInvalidValue;
-    // Pixels per wave and ticket.  A ticket costs a draw, a restaging on small layers, three barriers and one
-    // exposed activation load whatever it holds, so a ticket should hold some 10 us of sampling per wave (estimated
-    // at half of the chunk's taps per pixel and 86 ns per generator call), which products of one or two calls only
-    // reach with several pixels; large layers take four in any case (config 4: 0.66 -> 0.69 of the roofline;
-    // 8 and 16 measured like 4).  Never so many that a resident workgroup would draw fewer than 1.5 tickets on
-    // average (config 2 with its 7 tickets per workgroup and 11 us per ticket keeps one pixel: two measured -4 %;
-    // with 7-bit uniforms, a quarter of the calls, it takes four: +16 %).
-    int ppw = 1;
-    {
-        const double per_wg = (double)(pixel_groups * n_chunks * n_ocb) / ((double)cus * wg_per_cu);
-        const int calls = p.budget_to ? 1 : (p.S + per_block - 1) / per_block;
-        const double ticket_us = 0.5 * kc * calls * 0.086;
-        const int want = (int)std::min(8.0, std::max(1.0, std::floor(11.0 / ticket_us + 0.5)));
-        ppw = std::max(want, per_wg >= 128 ? 4 : per_wg >= 32 ? 2 : 1);
-        while (ppw > 1 && per_wg / ppw < 1.5) --ppw;
-        if (tuning.ppw > 0) ppw = tuning.ppw;
-    }
-    pixel_groups = (npix + (int64_t)waves * ppw - 1) / ((int64_t)waves * ppw);
+    const int64_t waves = (int64_t)oc_lane_cus() * kOcWavesPerCu;
+    OcPlan plan;
+    plan.n_chunks = n_chunks;
+    plan.kc = chunks.kc;
+    // one pixel per ticket (3x3 128->128 at 28x28, batch 8, S = 16: 1686 / 1705 / 1734 / 1759 us with 1 / 2 / 4 / 8), more only
+    // where the ticket numbers would not fit 31 bits
+    plan.ppw = std::max(1, oc_tuning().ppw);
+    while ((npix + plan.ppw - 1) / plan.ppw * n_chunks * n_ocb >= (1ll << 31)) plan.ppw *= 2;
+    const int64_t pixel_groups = (npix + plan.ppw - 1) / plan.ppw;
     const int64_t n_tickets = pixel_groups * n_chunks * n_ocb;
-    if (n_tickets >= (1ll << 32) - 65536) return (int)hipErrorInvalidValue;
-    const int64_t grid = std::min<int64_t>(n_tickets, (int64_t)cus * wg_per_cu);
+    plan.pixel_groups = (uint32_t)pixel_groups;
+    plan.n_tickets = (uint32_t)n_tickets;
+    plan.inv_groups = inverse_of(plan.pixel_groups);
+    plan.inv_chunks = inverse_of((uint32_t)n_chunks);
+    plan.inv_KHW = inverse_of((uint32_t)(p.KH * p.KW));
+    plan.inv_KW = inverse_of((uint32_t)p.KW);
+    const int64_t grid = std::min<int64_t>((n_tickets + kOcWaves - 1) / kOcWaves, waves / kOcWaves);
+    plan.rounds = (uint32_t)(n_tickets / (grid * kOcWaves));
 
-    // the ticket counter starts at 0; partial sums of a split reduction meet in accumulators that start at 0
-    {
-        const bool fill = n_chunks > 1;
-        const int64_t words = npix * p.oc_pad;
-        const int blocks = fill ? (int)std::min<int64_t>((words + 255) / 256, 8192) : 1;
-        hipLaunchKernelGGL(k_fill_zero, dim3(blocks), dim3(fill ? 256 : 64), 0, stream, p.acc_cl, fill ? words : 0, sched);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return (int)e;
-    }
     int slot = 0;
     const bool timed = prof_begin(stream, &slot);
-#define PSB_OC_LAUNCH(WAVES_, NB_, P7_)                                                                           \
-    hipLaunchKernelGGL((k_layer_oc_lane<WAVES_, NB_, P7_>), dim3((unsigned)grid), dim3(WAVES_ * 64), 0, stream, p,   \
-                       n_chunks, kc, (uint32_t)pixel_groups, (uint32_t)n_tickets, sched, ppw)
-    if (p7 && fixed_nb == 1 && fixed_valid < 4) {
-        auto launch_valid = [&](auto valid_c) {
-            hipLaunchKernelGGL((k_layer_oc_lane<4, 1, true, decltype(valid_c)::value>), dim3((unsigned)grid), dim3(4 * 64), 0, stream,
-                               p, n_chunks, kc, (uint32_t)pixel_groups, (uint32_t)n_tickets, sched, ppw);
-        };
-        switch (fixed_valid) {
-            case 1: launch_valid(std::integral_constant<int, 1>{}); break;
-            case 2: launch_valid(std::integral_constant<int, 2>{}); break;
-            default: launch_valid(std::integral_constant<int, 3>{}); break;
-        }
-    } else if (p7) {
-        switch (fixed_nb) {
-            case 1: PSB_OC_LAUNCH(4, 1, true); break;
-            case 2: PSB_OC_LAUNCH(4, 2, true); break;
-            default: PSB_OC_LAUNCH(4, 0, true); break;
-        }
+#define PSB_OC_LAUNCH(NB_, P7_, VALID_)                                                                            \
+    hipLaunchKernelGGL((k_layer_oc_lane<NB_, P7_, VALID_>), dim3((unsigned)grid), dim3(kOcWaves * 64), 0, stream, OcArgs{p, plan})
+    if (p7) {
+        if (fixed_nb == 0) PSB_OC_LAUNCH(0, true, 4);
+        else if (fixed_nb == 2) PSB_OC_LAUNCH(2, true, 4);
+        else if (fixed_valid == 1) PSB_OC_LAUNCH(1, true, 1);
+        else if (fixed_valid == 2) PSB_OC_LAUNCH(1, true, 2);
+        else if (fixed_valid == 3) PSB_OC_LAUNCH(1, true, 3);
+        else PSB_OC_LAUNCH(1, true, 4);
     } else {
         switch (fixed_nb) {
-            case 1: PSB_OC_LAUNCH(4, 1, false); break;
-            case 2: PSB_OC_LAUNCH(4, 2, false); break;
-            case 4: PSB_OC_LAUNCH(4, 4, false); break;
-            case 8: PSB_OC_LAUNCH(4, 8, false); break;
-            default: PSB_OC_LAUNCH(4, 0, false); break;
+            case 1: PSB_OC_LAUNCH(1, false, 4); break;
+            case 2: PSB_OC_LAUNCH(2, false, 4); break;
+            case 4: PSB_OC_LAUNCH(4, false, 4); break;
+            case 8: PSB_OC_LAUNCH(8, false, 4); break;
+            default: PSB_OC_LAUNCH(0, false, 4); break;
         }
     }
 #undef PSB_OC_LAUNCH
@@ -699,12 +610,13 @@ inline int launch_oc_lane(const LayerParams& p, uint32_t* sched, hipStream_t str
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
     if (n_chunks > 1) {
-        if ((npix + 63) / 64 > 2147483647ll) return (int)hipErrorInvalidValue;
-        const int64_t total = npix * p.OC;
-        if (total <= (1 << 20))
-            hipLaunchKernelGGL(k_rescale, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, p);
+        if (p.OH * p.OW == 1)
+            hipLaunchKernelGGL(k_rescale_rows, dim3((unsigned)((npix + 3) / 4), (unsigned)n_ocb), dim3(256), 0, stream, p);
+        else if ((npix + 63) / 64 * n_ocb >= 4 * oc_lane_cus())
+            hipLaunchKernelGGL(k_rescale_channels_last<64>, dim3((unsigned)((npix + 63) / 64), (unsigned)n_ocb), dim3(256), 0,
+                               stream, p);
         else
-            hipLaunchKernelGGL(k_rescale_channels_last, dim3((unsigned)((npix + 63) / 64), (unsigned)n_ocb), dim3(256), 0,
+            hipLaunchKernelGGL(k_rescale_channels_last<16>, dim3((unsigned)((npix + 15) / 16), (unsigned)n_ocb), dim3(256), 0,
                                stream, p);
         e = hipGetLastError();
         if (e != hipSuccess) return (int)e;

@@ -181,18 +181,6 @@ __device__ __forceinline__ uint32_t quad_transpose_bytes(uint32_t d)
     return lo | hi;
 }
 
-// x / d and x % d for any 32-bit x, given inv = floor(2^32 / d) (0xFFFFFFFF for d = 1): the product's high word
-// is the quotient or one less.
-__host__ __device__ inline uint32_t inverse_of(uint32_t d) { return d <= 1u ? 0xFFFFFFFFu : (uint32_t)(0x100000000ull / d); }
-__device__ __forceinline__ uint32_t div_mod(uint32_t x, uint32_t d, uint32_t inv, uint32_t& rem)
-{
-    uint32_t q = __umulhi(x, inv);
-    uint32_t r = x - q * d;
-    if (r >= d) { ++q; r -= d; }
-    rem = r;
-    return q;
-}
-
 // Digit planes in operand order: one thread per (channel, slot) of a 32-channel x 32-slot operand block, padding
 // included (those get zeros, so the buffer needs no clearing), and kPlaneGroup operand blocks per thread, so that
 // the weight words of all of them are in flight before the first is sampled.  Workgroup `block` of the job works
