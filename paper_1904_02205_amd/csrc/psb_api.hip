@@ -221,10 +221,16 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p)
     int mapping = g_mapping;
     if (mapping == 2 && q->shape.groups != 1) return PSB_ERR_SHAPE;
     if (mapping == 0) {
-        // channel lanes pay for every (tap, channel) pair of a tile, live or not: only for mostly dense layers
-        const int64_t n_weights = (int64_t)q->shape.oc * q->K;
-        const bool dense = 2 * q->info.n_live >= n_weights;
-        mapping = (dense && psb::oc_lane_preferred(p)) ? 2 : 3;
+        // Channel lanes pay for every (tap, channel lane) pair, live or not, about 42 instructions a generator call; the
+        // product list pays for live weights only, 50 to 60, and needs a thousand workgroups to fill the chip.  Measured
+        // (3x3 on 64 channels of 28x28, batch 4, S = 8 / 16, product list : channel lanes): 32 of 64 lanes in use 1.8 / 1.3,
+        // 30 % of the weights live on 64 lanes (832 workgroups) 0.9, 20 % 0.6 / 0.4; 16 lanes (208 workgroups) 1.5 / 1.0,
+        // 4 lanes (52 workgroups) 1.5 / 1.0; 37->70 channels, 5x5, 324 pixels, S = 10: 504 us : 60 us.
+        const double in_use = (double)q->info.n_live / ((double)q->oc_pad * q->K);
+        const int64_t list_wgs = ((int64_t)p.N * p.OH * p.OW + psb::kListPixels - 1) / psb::kListPixels * p.OC;
+        const double fill = std::min(1.0, (double)list_wgs / 1024.0);
+        const bool mostly_pruned = 3 * q->info.n_live < (int64_t)q->shape.oc * q->K;
+        mapping = psb::oc_lane_supported(p) && !mostly_pruned && in_use >= 0.45 * fill ? 2 : 3;
     }
     return mapping;
 }
@@ -321,6 +327,8 @@ psb::FilterJob filter_job(const psb_weights* q, int from, int to, uint64_t seed,
     j.pack_KW = 0; j.pack_C = 0; j.n_planes = psb::kMaxPlanes;
     j.C = q->K / j.KHW;
     j.inv_ksteps = psb::inverse_of((uint32_t)n_ksteps); j.inv_CB = psb::inverse_of((uint32_t)CB); j.inv_pack_C = 0xFFFFFFFFu;
+    j.inv_KHW = psb::inverse_of((uint32_t)j.KHW);
+    j.group = psb::kPlaneGroup;
     return j;
 }
 
@@ -403,12 +411,14 @@ int sample_segments(const psb_weights* q, const shared_plan& sp, const int (&lev
     psb::FilterBatch batch;
     std::memset(&batch, 0, sizeof(batch));
     for (int k = 0; k <= psb::kMaxBatchJobs; ++k) batch.first_block[k] = 0xFFFFFFFFu;
-    const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + psb::kPlaneGroup - 1) / psb::kPlaneGroup * 4;
+    const int group = psb::plane_group(q->shape.kh * q->shape.kw, sp.rowpack, false);
+    const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + group - 1) / group * 4;
     if (need * n_seg > 2147483647ll) return PSB_ERR_TOO_LARGE;
     for (int i = 0; i < n_seg; ++i) {
         psb::FilterJob fj = filter_job(q, i == 0 ? 0 : level[i - 1], level[i], seed, layer_id, nullptr,
                                        q->ws->planes_dev + planes_segment_bytes(sp) * i, sp.CB, sp.n_ksteps);
         fj.n_planes = n_planes;
+        fj.group = group;
         if (sp.rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
         batch.jobs[i] = fj;
         batch.first_block[i] = (unsigned)(need * i);
@@ -1123,7 +1133,8 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
         int longest = 0;
         for (int k = 0; k < n_seg; ++k) longest = std::max(longest, level[k] - (k ? level[k - 1] : 0));
         const int n_planes = psb::planes_needed(q->info.e_top - q->info.e_min, longest);
-        const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + psb::kPlaneGroup - 1) / psb::kPlaneGroup * 4;
+        const int group = psb::plane_group(q->shape.kh * q->shape.kw, sp.rowpack, n > 1);
+        const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + group - 1) / group * 4;
         if (need > 2147483647ll) return PSB_ERR_TOO_LARGE;
         for (int k = 0; k < n_seg; ++k) {
             if (n_jobs == psb::kMaxBatchJobs || blocks + need > 2147483647ll) {
@@ -1133,6 +1144,7 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
             psb::FilterJob fj = filter_job(q, k ? level[k - 1] : 0, level[k], seeds[i], layer_ids[i], nullptr,
                                            q->ws->planes_dev + planes_segment_bytes(sp) * k, sp.CB, sp.n_ksteps);
             fj.n_planes = n_planes;
+            fj.group = group;
             if (sp.rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
             batch.jobs[n_jobs] = fj;
             batch.first_block[n_jobs] = (unsigned)blocks;
@@ -1316,7 +1328,7 @@ int psb_attention_budget(const int8_t* act_dev, float step, int32_t n, int32_t c
     const int64_t HW = (int64_t)h * w;
     const int64_t total = (int64_t)n * HW;
     hipStream_t stream = (hipStream_t)hip_stream;
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 65536);
+    const int blocks = (int)std::min<int64_t>((total + psb::kEntropyPixels - 1) / psb::kEntropyPixels, 65536);
     hipLaunchKernelGGL(psb::k_channel_entropy, dim3(blocks), dim3(256), 0, stream, act_dev, step, n, c, HW, entropy_dev);
     PSB_HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(psb::k_attention_mask, dim3((unsigned)n), dim3(256), 0, stream, entropy_dev, HW, budget_lo,

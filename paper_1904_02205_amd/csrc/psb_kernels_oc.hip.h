@@ -2,13 +2,16 @@
 //
 // Mapping: lane = output channel inside a block of 64, wave = one output pixel at a
 // time.  The activation of a tap is then the same for all lanes, so
-//   - taps whose activation is 0 (about half after a ReLU, and all padding) are removed
-//     before the sampling loop by a wave-level compaction (ballot + prefix count) into a
-//     per-wave list in LDS: no lane ever idles on a zero product;
+//   - taps whose activation is 0 (about half after a ReLU, and all padding) are left out: the
+//     wave walks over the bits of the ballot of its non-zero activations, one tap of up to 64 per
+//     lane; no lane ever idles on a zero product;
 //   - the sample range [from,to) of a progressive call is wave-uniform: no divergence;
 //   - everything of the Philox counter that depends on the tap only is scalar work.
-// The weights of one tile of taps x 64 channels are staged in LDS once per workgroup as
-// {threshold, +-2^shift} pairs and read conflict-free (one ds_read_b64 per product).
+// The weights of a tap x 64 channels are {threshold, +-2^shift} pairs, 512 consecutive bytes.
+//
+// Bound by the issue of vector instructions: a generator call takes 41 of them (15 wide multiplies, 14 three-input and 3
+// two-input xors, 4 compares, 4 counts, a share of the product's 4), which a SIMD issues in 63 ns at best (a loop of
+// nothing else, eight waves).  3x3 128->128 at 28x28, batch 32, S = 8: 53.7 k calls per SIMD in 3.38 ms, 63 ns each.
 //
 // The reduction over taps is split into chunks; with more than one chunk the partial
 // sums are combined with int32 atomic adds, which is exact in any order because the
@@ -481,12 +484,6 @@ __global__ void __launch_bounds__(256) k_rescale_rows(const LayerParams p)
 // The channel-lane kernel needs groups = 1 and products that fit the 24-bit multiplier
 // (|x * count| < 2^17, unit <= 2^22).
 inline bool oc_lane_supported(const LayerParams& p) { return p.Cg == p.C && p.max_shift <= 22; }
-
-inline bool oc_lane_preferred(const LayerParams& p)
-{
-    // at least half of the 64 lanes of the last channel block must be real channels
-    return oc_lane_supported(p) && (p.OC % 64 == 0 || p.OC % 64 >= 32 || p.OC >= 256);
-}
 
 // Returns 0 or a hipError_t.
 typedef bool (*ProfileBegin)(hipStream_t, int*);

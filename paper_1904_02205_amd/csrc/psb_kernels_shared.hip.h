@@ -94,14 +94,15 @@ struct FilterJob {
     int pack_KW, pack_C;      // row packing: kernel width and channel count (0: not packed)
     int n_planes;             // digit planes the contraction of this sample range reads
     int C;                    // input channels (K / KHW)
-    uint32_t inv_ksteps, inv_CB, inv_pack_C;   // floor(2^32 / d) of the three divisors of the index arithmetic
+    int group;                // operand blocks a workgroup works on one after the other (see sample_planes_block)
+    uint32_t inv_ksteps, inv_CB, inv_KHW, inv_pack_C;   // floor(2^32 / d) of the divisors of the index arithmetic
     uint32_t key0, key1, layer_id;
     int32_t* w32;             // [OC][K], or null when only the planes are wanted
     int8_t* planes;           // operand-ordered digit planes, or null
 };
 
-// The ten pairs of round keys of a generator key: uniform over a job, so they are computed once per wave and kept
-// in scalar registers instead of being stepped inside every generator call.
+// The ten pairs of round keys of a generator key: uniform over a job, computed once per wave.  Those of rounds 2..9, which
+// go into three-input xors, stay in vector registers (with a scalar operand the instruction issues at half rate).
 struct RoundKeys { uint32_t k0[10], k1[10]; };
 __device__ __forceinline__ RoundKeys round_keys(uint32_t key0, uint32_t key1)
 {
@@ -110,15 +111,19 @@ __device__ __forceinline__ RoundKeys round_keys(uint32_t key0, uint32_t key1)
     for (int r = 0; r < 10; ++r) {
         rk.k0[r] = key0 + (uint32_t)r * kWeyl0;
         rk.k1[r] = key1 + (uint32_t)r * kWeyl1;
+        if (r >= 2) {
+            asm("v_mov_b32 %0, %1" : "=v"(rk.k0[r]) : "s"(rk.k0[r]));
+            asm("v_mov_b32 %0, %1" : "=v"(rk.k1[r]) : "s"(rk.k1[r]));
+        }
     }
     return rk;
 }
 
-// count_below() for the whole generator blocks 0 .. NB - 1 of one weight (samples 0 .. 4 NB - 1): no per-sample
-// range tests, and what the blocks share is computed once - in round 0 the product with the output index, in round 1
-// the product with state word 2 (neither depends on the block number, whose own product is a constant).
+// count_below() for the whole generator blocks j0 .. j0 + NB - 1 of one weight: no per-sample range tests, and what the blocks share is computed once - in round 0 the product with the output index, in round 1
+// the product with state word 2 (neither depends on the block number, whose own product is scalar).
 template <int NB>
-__device__ __forceinline__ uint32_t count_below_blocks(uint32_t o, uint32_t k, uint32_t layer, const RoundKeys& rk, uint32_t thr)
+__device__ __forceinline__ uint32_t count_below_blocks(uint32_t o, uint32_t k, uint32_t j0, uint32_t layer, const RoundKeys& rk,
+                                                       uint32_t thr)
 {
     uint32_t hi_a, lo_a, hi_b1, lo_b1;
     mulhilo(kMulA, o, hi_a, lo_a);
@@ -128,10 +133,10 @@ __device__ __forceinline__ uint32_t count_below_blocks(uint32_t o, uint32_t k, u
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         uint32_t hi_bj, lo_bj, hi_a1, lo_a1;
-        mulhilo(kMulB, (uint32_t)j, hi_bj, lo_bj);             // constants
+        mulhilo(kMulB, j0 + (uint32_t)j, hi_bj, lo_bj);        // scalar
         const uint32_t x1 = hi_bj ^ k ^ rk.k0[0];              // state after round 0: (x1, lo_bj, z1, lo_a)
         mulhilo(kMulA, x1, hi_a1, lo_a1);
-        u32x4 c{hi_b1 ^ lo_bj ^ rk.k0[1], lo_b1, hi_a1 ^ lo_a ^ rk.k1[1], lo_a1};      // after round 1
+        u32x4 c{hi_b1 ^ (lo_bj ^ rk.k0[1]), lo_b1, xor3(hi_a1, lo_a, rk.k1[1]), lo_a1};      // after round 1
 #pragma unroll
         for (int r = 2; r < 10; ++r) c = philox_round(c, rk.k0[r], rk.k1[r]);
         n += (c.x < thr ? 1u : 0u) + (c.y < thr ? 1u : 0u) + (c.z < thr ? 1u : 0u) + (c.w < thr ? 1u : 0u);
@@ -139,18 +144,18 @@ __device__ __forceinline__ uint32_t count_below_blocks(uint32_t o, uint32_t k, u
     return n;
 }
 
-// W[oc][k] for the job's sample range, from the weight's encoded word.  whole_blocks: 1..4 when the range is samples
-// 0 .. 4 whole_blocks - 1 of 32-bit uniforms (the usual call), else 0; rk: round_keys() of the job's key.
+// W[oc][k] for the job's sample range, from the weight's encoded word.  whole_blocks: 1..4 when the range is that many
+// whole blocks of 32-bit uniforms (the usual call), else 0; rk: round_keys() of the job's key.
 __device__ __forceinline__ int32_t sample_word(const FilterJob& j, uint32_t word, int oc, int k, int whole_blocks = 0,
                                                const RoundKeys* rk = nullptr)
 {
     if ((word & 0x7F800000u) == kDeadWord) return 0;
     const uint32_t thr = threshold_of(word & 0x7FFFFFu, j.prob_bits);
     uint32_t cnt;
-    if (whole_blocks == 1) cnt = count_below_blocks<1>((uint32_t)oc, (uint32_t)k, j.layer_id, *rk, thr);
-    else if (whole_blocks == 2) cnt = count_below_blocks<2>((uint32_t)oc, (uint32_t)k, j.layer_id, *rk, thr);
-    else if (whole_blocks == 3) cnt = count_below_blocks<3>((uint32_t)oc, (uint32_t)k, j.layer_id, *rk, thr);
-    else if (whole_blocks == 4) cnt = count_below_blocks<4>((uint32_t)oc, (uint32_t)k, j.layer_id, *rk, thr);
+    if (whole_blocks == 1) cnt = count_below_blocks<1>((uint32_t)oc, (uint32_t)k, (uint32_t)j.from >> 2, j.layer_id, *rk, thr);
+    else if (whole_blocks == 2) cnt = count_below_blocks<2>((uint32_t)oc, (uint32_t)k, (uint32_t)j.from >> 2, j.layer_id, *rk, thr);
+    else if (whole_blocks == 3) cnt = count_below_blocks<3>((uint32_t)oc, (uint32_t)k, (uint32_t)j.from >> 2, j.layer_id, *rk, thr);
+    else if (whole_blocks == 4) cnt = count_below_blocks<4>((uint32_t)oc, (uint32_t)k, (uint32_t)j.from >> 2, j.layer_id, *rk, thr);
     else cnt = j.prob_bits <= 7
         ? count_below7((uint32_t)oc, (uint32_t)k, j.layer_id, j.key0, j.key1, thr, j.from, j.to)
         : count_below((uint32_t)oc, (uint32_t)k, j.layer_id, j.key0, j.key1, thr, j.from, j.to);
@@ -182,63 +187,77 @@ __device__ __forceinline__ uint32_t quad_transpose_bytes(uint32_t d)
 }
 
 // Digit planes in operand order: one thread per (channel, slot) of a 32-channel x 32-slot operand block, padding
-// included (those get zeros, so the buffer needs no clearing), and kPlaneGroup operand blocks per thread, so that
-// the weight words of all of them are in flight before the first is sampled.  Workgroup `block` of the job works
-// on operand blocks (block >> 2) * kPlaneGroup + g, each = (channel block, reduction step) - uniform values, whose
-// divisions run on the scalar unit - and its thread t' = (block & 3) * 256 + thread index on slot (bits 0-3 and
-// 9 of t') of channel (bits 4-8).  The four lanes of a quad hold four consecutive slots; after the byte transpose
-// lane b of the quad stores plane b's four digits as one 32-bit word.
-constexpr int kPlaneGroup = 4;
+// included (those get zeros, so the buffer needs no clearing).  Workgroup `block` of the job works on j.group
+// operand blocks from (block >> 2) * j.group on, kPlaneGroup at a time, so that their weight words are in flight
+// together before the first is sampled; an operand block = (channel block, block of 32 input channels, tap), taps fastest:
+// the 32 channels' words of a tap lie KH * KW words apart, so a line of encoded weights serves all taps while it is in
+// the L1 (with the input channels fastest every line came from the L2 or beyond once per tap: the 21 filters of the
+// ResNet-18 pass, S = 8, 54 us).  A workgroup's thread t' = (block & 3) * 256 + thread index works on slot
+// (bits 0-3 and 9 of t') of channel (bits 4-8).  The four lanes of a quad hold four consecutive slots; after the byte
+// transpose lane b of the quad stores plane b's four digits as one 32-bit word.
+constexpr int kPlaneGroup = 3;
+
+// Operand blocks per workgroup: all taps of a kernel (up to 5 x 5) when many filters are sampled at once; a call that
+// samples one filter spreads over more workgroups instead.
+inline int plane_group(int khw, bool packed, bool batch) { return batch ? (!packed && khw >= 4 && khw <= 25 ? khw : 12) : kPlaneGroup; }
 
 __device__ __forceinline__ void sample_planes_block(const FilterJob& j, uint32_t block)
 {
     const uint32_t t = (block & 3u) * 256u + threadIdx.x;
     const int cl = (int)(t & 15u) + 16 * (int)((t >> 9) & 1u);
     const int ocl = (int)(t >> 4) & 31;
-    const uint32_t n_blk = (uint32_t)((j.OC + 31) >> 5) * (uint32_t)j.n_ksteps;
-    const uint32_t blk0 = (block >> 2) * kPlaneGroup;
-    uint32_t word[kPlaneGroup];
-    int oc_[kPlaneGroup], k_[kPlaneGroup];
-    bool valid[kPlaneGroup];
-#pragma unroll
-    for (int g = 0; g < kPlaneGroup; ++g) {
-        const uint32_t blk = min(blk0 + g, n_blk - 1);     // past the end: the last block again (not stored)
-        uint32_t kstep;
-        const uint32_t ocb = div_mod(blk, (uint32_t)j.n_ksteps, j.inv_ksteps, kstep);
-        const int oc = (int)ocb * 32 + ocl;
-        int c, r;
-        bool ok = oc < j.OC;
-        if (j.pack_KW) {                               // one step per kernel row; slot kw * C + c inside it
-            uint32_t cu;
-            const int kw = (int)div_mod((uint32_t)cl, (uint32_t)j.pack_C, j.inv_pack_C, cu);
-            c = (int)cu;
-            r = (int)kstep * j.pack_KW + kw;
-            ok = ok && kw < j.pack_KW;
-        } else {
-            uint32_t cb;
-            r = (int)div_mod(kstep, (uint32_t)j.CB, j.inv_CB, cb);
-            c = (int)cb * 32 + cl;
-            ok = ok && c < j.C;
-        }
-        oc_[g] = oc;
-        k_[g] = c * j.KHW + r;
-        valid[g] = ok;
-        word[g] = ok ? j.packed[(int64_t)oc * j.K + k_[g]] : kDeadWord;
-    }
     const int plane = (int)(t & 3);
+    const uint32_t n_blk = (uint32_t)((j.OC + 31) >> 5) * (uint32_t)j.n_ksteps;
+    const uint32_t blk_begin = (block >> 2) * (uint32_t)j.group, blk_end = min(blk_begin + (uint32_t)j.group, n_blk);
     const RoundKeys rk = round_keys(j.key0, j.key1);
-    const int whole_blocks = (j.prob_bits > 7 && j.from == 0 && (j.to & 3) == 0 && j.to <= 16) ? j.to >> 2 : 0;   // uniform
+    const int blocks = (j.to - j.from) >> 2;
+    const int whole_blocks = (j.prob_bits > 7 && ((j.from | j.to) & 3) == 0 && blocks <= 4) ? blocks : 0;           // uniform
+    for (uint32_t blk0 = blk_begin; blk0 < blk_end; blk0 += kPlaneGroup) {
+        uint32_t word[kPlaneGroup], at_[kPlaneGroup];
+        int oc_[kPlaneGroup], k_[kPlaneGroup];
+        bool valid[kPlaneGroup];
 #pragma unroll
-    for (int g = 0; g < kPlaneGroup; ++g) {
-        // Balanced base-256 digits d_b in [-128, 127] with v = sum d_b 256^b modulo 2^32, all four at once: adding 128
-        // to every digit gives the ordinary digits (0..255) of v + 0x80808080, and subtracting 128 from a byte
-        // flips its top bit.
-        const uint32_t v = valid[g] ? (uint32_t)sample_word(j, word[g], oc_[g], k_[g], whole_blocks, &rk) : 0u;
-        const uint32_t digits = (v + 0x80808080u) ^ 0x80808080u;
-        const uint32_t out = quad_transpose_bytes(digits);
-        if (plane < j.n_planes && blk0 + g < n_blk)
-            *reinterpret_cast<uint32_t*>(j.planes + (((int64_t)(blk0 + g) * kMaxPlanes + plane) * 64 + ocl + 32 * (cl >> 4)) * 16 +
-                                         (cl & 12)) = out;
+        for (int g = 0; g < kPlaneGroup; ++g) {
+            const uint32_t blk = min(blk0 + g, blk_end - 1);      // past the end: the last block again (not stored)
+            uint32_t in_ocb;
+            const uint32_t ocb = div_mod(blk, (uint32_t)j.n_ksteps, j.inv_ksteps, in_ocb);
+            const int oc = (int)ocb * 32 + ocl;
+            uint32_t kstep;
+            int c, r;
+            bool ok = oc < j.OC;
+            if (j.pack_KW) {                               // one step per kernel row; slot kw * C + c inside it
+                uint32_t cu;
+                const int kw = (int)div_mod((uint32_t)cl, (uint32_t)j.pack_C, j.inv_pack_C, cu);
+                kstep = in_ocb;
+                c = (int)cu;
+                r = (int)kstep * j.pack_KW + kw;
+                ok = ok && kw < j.pack_KW;
+            } else {
+                uint32_t tap;
+                const uint32_t cb = div_mod(in_ocb, (uint32_t)j.KHW, j.inv_KHW, tap);
+                kstep = tap * (uint32_t)j.CB + cb;
+                r = (int)tap;
+                c = (int)cb * 32 + cl;
+                ok = ok && c < j.C;
+            }
+            at_[g] = ocb * (uint32_t)j.n_ksteps + kstep;
+            oc_[g] = oc;
+            k_[g] = c * j.KHW + r;
+            valid[g] = ok;
+            word[g] = ok ? j.packed[(int64_t)oc * j.K + k_[g]] : kDeadWord;
+        }
+#pragma unroll
+        for (int g = 0; g < kPlaneGroup; ++g) {
+            // Balanced base-256 digits d_b in [-128, 127] with v = sum d_b 256^b modulo 2^32, all four at once: adding 128
+            // to every digit gives the ordinary digits (0..255) of v + 0x80808080, and subtracting 128 from a byte
+            // flips its top bit.
+            const uint32_t v = valid[g] ? (uint32_t)sample_word(j, word[g], oc_[g], k_[g], whole_blocks, &rk) : 0u;
+            const uint32_t digits = (v + 0x80808080u) ^ 0x80808080u;
+            const uint32_t out = quad_transpose_bytes(digits);
+            if (plane < j.n_planes && blk0 + g < blk_end)
+                *reinterpret_cast<uint32_t*>(j.planes + (((int64_t)at_[g] * kMaxPlanes + plane) * 64 + ocl + 32 * (cl >> 4)) * 16 +
+                                             (cl & 12)) = out;
+        }
     }
 }
 
@@ -1388,7 +1407,7 @@ inline int window_slots(int kh, int kw, int stride_h, int stride_w, int pad_h, i
 inline WindowPlan window_plan(const SharedParams& p, int planes, int half_tiles, int n_cus)
 {
     WindowPlan w{false, 1, 1};
-    if (p.OH != p.tH || p.OW != p.tW || p.ksplit != 1 || planes < 3) return w;
+    if (p.OH != p.tH || p.OW != p.tW || p.ksplit != 1 || planes < 2) return w;
     const int64_t T = 128 * half_tiles;
     const int slots = window_slots(p.tKH, p.tKW, p.t_stride_h, p.t_stride_w, p.t_pad_h, p.t_pad_w, p.tH, p.tW, half_tiles);
     if (slots == 0) return w;
@@ -1429,7 +1448,8 @@ inline bool launch_window_shape(const SharedParams& p, int half_tiles, const Win
 template <int OUT>
 inline bool launch_window_out(const SharedParams& p, int planes, int half_tiles, const WindowPlan& w, dim3 grid, hipStream_t stream)
 {
-    return planes == 3 ? launch_window_shape<3, OUT>(p, half_tiles, w, grid, stream) : launch_window_shape<4, OUT>(p, half_tiles, w, grid, stream);
+    return planes == 2 ? launch_window_shape<2, OUT>(p, half_tiles, w, grid, stream)
+         : planes == 3 ? launch_window_shape<3, OUT>(p, half_tiles, w, grid, stream) : launch_window_shape<4, OUT>(p, half_tiles, w, grid, stream);
 }
 
 // Half tiles (32 pixels) per wave: two, unless the layer is so small that one-half-tile waves still fit the chip at

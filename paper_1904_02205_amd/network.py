@@ -16,6 +16,10 @@ from . import psb
 from . import resnet_synth as rs
 
 
+class _WithoutCopies(list):
+    """Collector of a pass's activations that leaves out those which would have to be copied to [N, C, H, W]."""
+
+
 class ResNet18:
     def __init__(self, net: rs.Net, s_max=16, prob_bits=23, seed=3, device="cuda"):
         self.net, self.seed, self.device, self.s_max = net, seed, device, s_max
@@ -104,6 +108,8 @@ class ResNet18:
         copies).  Same integers as the layer-by-layer pass."""
         def keep(t, shape=None):
             if collect is None:
+                return
+            if shape is not None and isinstance(collect, _WithoutCopies):
                 return
             if shape is not None:        # diagnostic copy back to [N, C, H, W]
                 n, c, h, w = shape
@@ -245,8 +251,8 @@ class ResNet18:
         """The two-stage scheme of Sect. 4.5: a low-precision pass everywhere, the entropy mask of the last
         convolutional layer, then the network again with s_hi samples inside the mask and s_lo outside, on all
         layers.  Returns (logits, budget map uint8 [batch, h, w] at the last layer's resolution)."""
-        acts = []
+        acts = _WithoutCopies()
         self.forward(S=s_lo, shared=shared, collect=acts)
-        last = acts[-2]                                  # output of the last residual block
+        last = acts[-2]                                  # output of the last residual block, [N, C, H, W] in every pass
         _, _, budget = psb.attention_budget(last, float(np.float32(rs.STEP_BLOCK)), s_lo, s_hi)
         return self.forward(budget=budget, s_fc=s_hi, shared=shared, levels=(s_lo, s_hi)), budget
