@@ -327,8 +327,6 @@ psb::FilterJob filter_job(const psb_weights* q, int from, int to, uint64_t seed,
     j.pack_KW = 0; j.pack_C = 0; j.n_planes = psb::kMaxPlanes;
     j.C = q->K / j.KHW;
     j.inv_ksteps = psb::inverse_of((uint32_t)n_ksteps); j.inv_CB = psb::inverse_of((uint32_t)CB); j.inv_pack_C = 0xFFFFFFFFu;
-    j.inv_KHW = psb::inverse_of((uint32_t)j.KHW);
-    j.group = psb::kPlaneGroup;
     return j;
 }
 
@@ -411,14 +409,12 @@ int sample_segments(const psb_weights* q, const shared_plan& sp, const int (&lev
     psb::FilterBatch batch;
     std::memset(&batch, 0, sizeof(batch));
     for (int k = 0; k <= psb::kMaxBatchJobs; ++k) batch.first_block[k] = 0xFFFFFFFFu;
-    const int group = psb::plane_group(q->shape.kh * q->shape.kw, sp.rowpack, false);
-    const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + group - 1) / group * 4;
+    const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + psb::kPlaneGroup - 1) / psb::kPlaneGroup * 4;
     if (need * n_seg > 2147483647ll) return PSB_ERR_TOO_LARGE;
     for (int i = 0; i < n_seg; ++i) {
         psb::FilterJob fj = filter_job(q, i == 0 ? 0 : level[i - 1], level[i], seed, layer_id, nullptr,
                                        q->ws->planes_dev + planes_segment_bytes(sp) * i, sp.CB, sp.n_ksteps);
         fj.n_planes = n_planes;
-        fj.group = group;
         if (sp.rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
         batch.jobs[i] = fj;
         batch.first_block[i] = (unsigned)(need * i);
@@ -1133,8 +1129,7 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
         int longest = 0;
         for (int k = 0; k < n_seg; ++k) longest = std::max(longest, level[k] - (k ? level[k - 1] : 0));
         const int n_planes = psb::planes_needed(q->info.e_top - q->info.e_min, longest);
-        const int group = psb::plane_group(q->shape.kh * q->shape.kw, sp.rowpack, n > 1);
-        const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + group - 1) / group * 4;
+        const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + psb::kPlaneGroup - 1) / psb::kPlaneGroup * 4;
         if (need > 2147483647ll) return PSB_ERR_TOO_LARGE;
         for (int k = 0; k < n_seg; ++k) {
             if (n_jobs == psb::kMaxBatchJobs || blocks + need > 2147483647ll) {
@@ -1144,7 +1139,6 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
             psb::FilterJob fj = filter_job(q, k ? level[k - 1] : 0, level[k], seeds[i], layer_ids[i], nullptr,
                                            q->ws->planes_dev + planes_segment_bytes(sp) * k, sp.CB, sp.n_ksteps);
             fj.n_planes = n_planes;
-            fj.group = group;
             if (sp.rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
             batch.jobs[n_jobs] = fj;
             batch.first_block[n_jobs] = (unsigned)blocks;

@@ -94,8 +94,7 @@ struct FilterJob {
     int pack_KW, pack_C;      // row packing: kernel width and channel count (0: not packed)
     int n_planes;             // digit planes the contraction of this sample range reads
     int C;                    // input channels (K / KHW)
-    int group;                // operand blocks a workgroup works on one after the other (see sample_planes_block)
-    uint32_t inv_ksteps, inv_CB, inv_KHW, inv_pack_C;   // floor(2^32 / d) of the divisors of the index arithmetic
+    uint32_t inv_ksteps, inv_CB, inv_pack_C;   // floor(2^32 / d) of the three divisors of the index arithmetic
     uint32_t key0, key1, layer_id;
     int32_t* w32;             // [OC][K], or null when only the planes are wanted
     int8_t* planes;           // operand-ordered digit planes, or null
@@ -187,77 +186,64 @@ __device__ __forceinline__ uint32_t quad_transpose_bytes(uint32_t d)
 }
 
 // Digit planes in operand order: one thread per (channel, slot) of a 32-channel x 32-slot operand block, padding
-// included (those get zeros, so the buffer needs no clearing).  Workgroup `block` of the job works on j.group
-// operand blocks from (block >> 2) * j.group on, kPlaneGroup at a time, so that their weight words are in flight
-// together before the first is sampled; an operand block = (channel block, block of 32 input channels, tap), taps fastest:
-// the 32 channels' words of a tap lie KH * KW words apart, so a line of encoded weights serves all taps while it is in
-// the L1 (with the input channels fastest every line came from the L2 or beyond once per tap: the 21 filters of the
-// ResNet-18 pass, S = 8, 54 us).  A workgroup's thread t' = (block & 3) * 256 + thread index works on slot
-// (bits 0-3 and 9 of t') of channel (bits 4-8).  The four lanes of a quad hold four consecutive slots; after the byte
-// transpose lane b of the quad stores plane b's four digits as one 32-bit word.
-constexpr int kPlaneGroup = 3;
-
-// Operand blocks per workgroup: all taps of a kernel (up to 5 x 5) when many filters are sampled at once; a call that
-// samples one filter spreads over more workgroups instead.
-inline int plane_group(int khw, bool packed, bool batch) { return batch ? (!packed && khw >= 4 && khw <= 25 ? khw : 12) : kPlaneGroup; }
+// included (those get zeros, so the buffer needs no clearing), and kPlaneGroup operand blocks per thread, so that
+// the weight words of all of them are in flight before the first is sampled.  Workgroup `block` of the job works
+// on operand blocks (block >> 2) * kPlaneGroup + g, each = (channel block, reduction step) - uniform values, whose
+// divisions run on the scalar unit - and its thread t' = (block & 3) * 256 + thread index on slot (bits 0-3 and
+// 9 of t') of channel (bits 4-8).  The four lanes of a quad hold four consecutive slots; after the byte transpose
+// lane b of the quad stores plane b's four digits as one 32-bit word.
+constexpr int kPlaneGroup = 4;
 
 __device__ __forceinline__ void sample_planes_block(const FilterJob& j, uint32_t block)
 {
     const uint32_t t = (block & 3u) * 256u + threadIdx.x;
     const int cl = (int)(t & 15u) + 16 * (int)((t >> 9) & 1u);
     const int ocl = (int)(t >> 4) & 31;
-    const int plane = (int)(t & 3);
     const uint32_t n_blk = (uint32_t)((j.OC + 31) >> 5) * (uint32_t)j.n_ksteps;
-    const uint32_t blk_begin = (block >> 2) * (uint32_t)j.group, blk_end = min(blk_begin + (uint32_t)j.group, n_blk);
+    const uint32_t blk0 = (block >> 2) * kPlaneGroup;
+    uint32_t word[kPlaneGroup];
+    int oc_[kPlaneGroup], k_[kPlaneGroup];
+    bool valid[kPlaneGroup];
+#pragma unroll
+    for (int g = 0; g < kPlaneGroup; ++g) {
+        const uint32_t blk = min(blk0 + g, n_blk - 1);     // past the end: the last block again (not stored)
+        uint32_t kstep;
+        const uint32_t ocb = div_mod(blk, (uint32_t)j.n_ksteps, j.inv_ksteps, kstep);
+        const int oc = (int)ocb * 32 + ocl;
+        int c, r;
+        bool ok = oc < j.OC;
+        if (j.pack_KW) {                               // one step per kernel row; slot kw * C + c inside it
+            uint32_t cu;
+            const int kw = (int)div_mod((uint32_t)cl, (uint32_t)j.pack_C, j.inv_pack_C, cu);
+            c = (int)cu;
+            r = (int)kstep * j.pack_KW + kw;
+            ok = ok && kw < j.pack_KW;
+        } else {
+            uint32_t cb;
+            r = (int)div_mod(kstep, (uint32_t)j.CB, j.inv_CB, cb);
+            c = (int)cb * 32 + cl;
+            ok = ok && c < j.C;
+        }
+        oc_[g] = oc;
+        k_[g] = c * j.KHW + r;
+        valid[g] = ok;
+        word[g] = ok ? j.packed[(int64_t)oc * j.K + k_[g]] : kDeadWord;
+    }
+    const int plane = (int)(t & 3);
     const RoundKeys rk = round_keys(j.key0, j.key1);
     const int blocks = (j.to - j.from) >> 2;
     const int whole_blocks = (j.prob_bits > 7 && ((j.from | j.to) & 3) == 0 && blocks <= 4) ? blocks : 0;           // uniform
-    for (uint32_t blk0 = blk_begin; blk0 < blk_end; blk0 += kPlaneGroup) {
-        uint32_t word[kPlaneGroup], at_[kPlaneGroup];
-        int oc_[kPlaneGroup], k_[kPlaneGroup];
-        bool valid[kPlaneGroup];
 #pragma unroll
-        for (int g = 0; g < kPlaneGroup; ++g) {
-            const uint32_t blk = min(blk0 + g, blk_end - 1);      // past the end: the last block again (not stored)
-            uint32_t in_ocb;
-            const uint32_t ocb = div_mod(blk, (uint32_t)j.n_ksteps, j.inv_ksteps, in_ocb);
-            const int oc = (int)ocb * 32 + ocl;
-            uint32_t kstep;
-            int c, r;
-            bool ok = oc < j.OC;
-            if (j.pack_KW) {                               // one step per kernel row; slot kw * C + c inside it
-                uint32_t cu;
-                const int kw = (int)div_mod((uint32_t)cl, (uint32_t)j.pack_C, j.inv_pack_C, cu);
-                kstep = in_ocb;
-                c = (int)cu;
-                r = (int)kstep * j.pack_KW + kw;
-                ok = ok && kw < j.pack_KW;
-            } else {
-                uint32_t tap;
-                const uint32_t cb = div_mod(in_ocb, (uint32_t)j.KHW, j.inv_KHW, tap);
-                kstep = tap * (uint32_t)j.CB + cb;
-                r = (int)tap;
-                c = (int)cb * 32 + cl;
-                ok = ok && c < j.C;
-            }
-            at_[g] = ocb * (uint32_t)j.n_ksteps + kstep;
-            oc_[g] = oc;
-            k_[g] = c * j.KHW + r;
-            valid[g] = ok;
-            word[g] = ok ? j.packed[(int64_t)oc * j.K + k_[g]] : kDeadWord;
-        }
-#pragma unroll
-        for (int g = 0; g < kPlaneGroup; ++g) {
-            // Balanced base-256 digits d_b in [-128, 127] with v = sum d_b 256^b modulo 2^32, all four at once: adding 128
-            // to every digit gives the ordinary digits (0..255) of v + 0x80808080, and subtracting 128 from a byte
-            // flips its top bit.
-            const uint32_t v = valid[g] ? (uint32_t)sample_word(j, word[g], oc_[g], k_[g], whole_blocks, &rk) : 0u;
-            const uint32_t digits = (v + 0x80808080u) ^ 0x80808080u;
-            const uint32_t out = quad_transpose_bytes(digits);
-            if (plane < j.n_planes && blk0 + g < blk_end)
-                *reinterpret_cast<uint32_t*>(j.planes + (((int64_t)at_[g] * kMaxPlanes + plane) * 64 + ocl + 32 * (cl >> 4)) * 16 +
-                                             (cl & 12)) = out;
-        }
+    for (int g = 0; g < kPlaneGroup; ++g) {
+        // Balanced base-256 digits d_b in [-128, 127] with v = sum d_b 256^b modulo 2^32, all four at once: adding 128
+        // to every digit gives the ordinary digits (0..255) of v + 0x80808080, and subtracting 128 from a byte
+        // flips its top bit.
+        const uint32_t v = valid[g] ? (uint32_t)sample_word(j, word[g], oc_[g], k_[g], whole_blocks, &rk) : 0u;
+        const uint32_t digits = (v + 0x80808080u) ^ 0x80808080u;
+        const uint32_t out = quad_transpose_bytes(digits);
+        if (plane < j.n_planes && blk0 + g < n_blk)
+            *reinterpret_cast<uint32_t*>(j.planes + (((int64_t)(blk0 + g) * kMaxPlanes + plane) * 64 + ocl + 32 * (cl >> 4)) * 16 +
+                                         (cl & 12)) = out;
     }
 }
 
@@ -1392,6 +1378,8 @@ inline void launch_conv_shared_mfma_resident(const SharedParams& p, int planes, 
 // Whether k_conv3x3_window can take the call, and in which shape.  slots = the longest window of a pixel tile:
 // T - 1 positions between its first and last pixel, one more per image row and W + 1 more per image that the tile
 // crosses, and the taps' reach of 2 (W + 1) + 2 beyond the last pixel.
+// Filters of two digit planes as well (long reductions: the last stage of ResNet-18, 512 channels of 7x7): 18.3 us against
+// 20.7 in the plain kernel, with two budget segments 29 against 35.
 struct WindowPlan { bool ok; int teams, ws; };
 // slots of the longest window of a layer with this geometry, or 0 when the kernel does not take the geometry
 // (the reduction of such a layer is never split over workgroups: the teams do that inside one)
