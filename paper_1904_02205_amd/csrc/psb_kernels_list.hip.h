@@ -9,16 +9,26 @@
 // LDS (ds_add, exact in any order).  Every lane therefore always has a product to work on, whatever the
 // sparsity pattern.  Output index and tap differ per lane, so the parts of the first three generator
 // rounds that depend on only one of the two cannot stay in registers; for calls with the same S everywhere
-// (up to four generator blocks) they are kept in two LDS tables instead - one row per pixel, one per tap
-// of the chunk - and a call costs 15 wide multiplies as in the channel-lane kernel; the other calls run
-// the whole generator per entry (19 multiplies).  No global atomics, no zero-fill: the accumulators leave
+// they are kept in two LDS tables instead, for up to four generator blocks at a time - one row per pixel, one per
+// tap of the chunk - and a call costs 15 wide multiplies as in the channel-lane kernel; a call of more blocks
+// goes over its taps once per four of them, and calls with per-pixel ranges run the whole generator per
+// entry (19 multiplies).  No global atomics, no zero-fill: the accumulators leave
 // LDS once, with the fp32 epilogue fused.
 // The chunk is short on purpose: the list is the largest LDS array, and with 10 taps (23 KB per workgroup
-// with the tables) seven workgroups share a compute unit, whose waves hide each other's list building,
-// table loads and barriers; 24- and 32-tap chunks (4 and 3 workgroups) measured 10 % slower.
+// with the tables) six workgroups share a compute unit, whose waves hide each other's list building,
+// table loads and barriers; 24- and 32-tap chunks (4 and 3 workgroups) measured 10 % slower.  Six and not seven: the
+// round keys of the block kernels then fit vector registers, and the table of (block, pixel) products is laid out so that
+// neighbouring pixels are neighbouring words (pruned 576->160 at 14x14, batch 64, S = 16: 329 -> 311 us, depthwise 3x3 on
+// 576 channels 199 -> 190).  Bound by vector instructions: 53 a generator call for the first of the two, 61 for the
+// second, 41 of them the call itself, the rest the list (14 per tap and pixel), its entries (14) and the tables.  One wave
+// per workgroup with a list of its own and no barriers was slower (337 and 247 us): fewer resident waves, and each
+// waits for its own chain of scalar loads, activations and list.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "psb_kernels.hip.h"
 #include "psb_kernels_oc.hip.h"
@@ -56,38 +66,22 @@ __global__ void __launch_bounds__(256) k_live_index(const uint32_t* __restrict__
     if (threadIdx.x == 0) live_cnt[oc] = count;
 }
 
-// Samples of block j of product (o, k) that are below thr; all arguments per lane.
-__device__ __forceinline__ uint32_t count_block_full(uint32_t o, uint32_t k, uint32_t j, uint32_t layer, uint32_t key0,
-                                                     uint32_t key1, uint32_t thr)
-{
-    const u32x4 r = philox4x32_10(u32x4{o, k, j, layer}, key0, key1);
-    return (r.x < thr ? 1u : 0u) + (r.y < thr ? 1u : 0u) + (r.z < thr ? 1u : 0u) + (r.w < thr ? 1u : 0u);
-}
-
-// Same with sixteen 7-bit uniforms per block, thr4 = the 7-bit threshold in each byte.
-__device__ __forceinline__ uint32_t count_block_full7(uint32_t o, uint32_t k, uint32_t j, uint32_t layer, uint32_t key0,
-                                                      uint32_t key1, uint32_t thr4)
-{
-    const u32x4 r = philox4x32_10(u32x4{o, k, j, layer}, key0, key1);
-    const uint32_t all = 0x80808080u;
-    return 16u - (not_below7(r.x, thr4, all) + not_below7(r.y, thr4, all) + not_below7(r.z, thr4, all) +
-                  not_below7(r.w, thr4, all));
-}
-
-// NB > 0: every pixel draws the samples of generator blocks 0 .. NB-1, all of them (a call with the
-//         same S everywhere, S = NB * samples per block).
+// NB > 0: a call with the same S everywhere, NB (1..4) generator blocks at a time.  MULTI: it takes more than one such pass
+//         over the taps, or draws its last block in part; otherwise blocks 0 .. NB - 1 are all there is, and whole (the
+//         general form costs that call 7 % on depthwise 3 x 3 layers, whose tables are rebuilt for every nine taps).
 // NB = 0: per-pixel ranges [from, to), any values.
 // P7: 7-bit uniforms, 16 samples per block; otherwise 32-bit uniforms, 4 per block.
 // INSIDE: every tap of every output pixel lies inside the image (1 x 1 layers, unpadded layers): no bounds checks.
-template <int NB, bool P7, bool INSIDE>
-__global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const LayerParams p,
+template <int NB, bool P7, bool INSIDE, bool MULTI>
+__global__ void __launch_bounds__(kListPixels, 6) k_layer_product_list(const LayerParams p,
                                                                     const uint32_t* __restrict__ live_idx,
                                                                     const uint32_t* __restrict__ live_cnt,
                                                                     int channels_per_wg)
 {
-    // HOIST: the tap-independent and the pixel-independent parts of generator rounds 0..2 come from tables
-    constexpr bool HOIST = NB >= 1 && NB <= 4;
+    static_assert(NB <= 4, "table rows are kept for four blocks");
+    constexpr bool HOIST = NB >= 1;      // the tap- and the pixel-independent parts of rounds 0..2 come from tables
     constexpr int NBT = HOIST ? NB : 1;
+    constexpr int kPer = P7 ? 16 : 4;    // samples of a block
     __shared__ uint32_t list[kListCap];          // pixel | tap slot << 8 | activation byte << 16
     __shared__ int32_t acc_s[kListPixels];
     __shared__ uint32_t o_s[HOIST ? 1 : kListPixels];      // flat output index of the pixel for this channel
@@ -96,7 +90,7 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
     __shared__ uint2 wtab[kListTaps];            // {threshold, +-2^shift}
     __shared__ int2 tapinfo[kListTaps];          // {offset inside the image group, kh | kw << 16}
     __shared__ uint2 pix_base[HOIST ? kListPixels : 1];    // per pixel: {low half of MulA * o, state word 1 after round 1 ^ key}
-    __shared__ __align__(16) uint2 pix_blk[HOIST ? kListPixels : 1][NBT];   // per (pixel, block): round 2's MulA product
+    __shared__ uint2 pix_blk[NBT][HOIST ? kListPixels : 1];                 // per (block, pixel): round 2's MulA product
     __shared__ __align__(16) uint2 tap_blk[HOIST ? kListTaps : 1][NBT];     // per (tap, block): round 1's MulA product
     __shared__ uint32_t count;
 
@@ -105,6 +99,10 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
     for (int r = 0; r < 10; ++r) {
         key.k0[r] = p.key0 + (uint32_t)r * kWeyl0;
         key.k1[r] = p.key1 + (uint32_t)r * kWeyl1;
+        if (r >= 3 && HOIST) {                       // see k_layer_oc_lane
+            asm("v_mov_b32 %0, %1" : "=v"(key.k0[r]) : "s"(key.k0[r]));
+            asm("v_mov_b32 %0, %1" : "=v"(key.k1[r]) : "s"(key.k1[r]));
+        }
     }
 
     const int tid = threadIdx.x;
@@ -143,6 +141,10 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
     const uint32_t xbase = (uint32_t)((((int64_t)n * p.C + (int64_t)grp * p.Cg) * p.H + iy0) * p.W + ix0);
 
     acc_s[tid] = 0;
+    const int s_uniform = min(p.S, p.s_max);
+    const int n_blocks = MULTI ? (s_uniform + kPer - 1) / kPer : 1;
+    for (int j_at = 0; j_at < n_blocks; j_at += NBT) {
+    const int j0 = MULTI ? j_at : 0;
     if constexpr (HOIST) {
         // rounds 0..2 of this pixel's counter, as far as they go without the tap
         PixelHoist h;
@@ -154,8 +156,8 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
 #pragma unroll
         for (int j = 0; j < NBT; ++j) {
             uint32_t s_hib, hz, lo2;
-            block_setup(h, key, j, s_hib, hz, lo2);
-            pix_blk[tid][j] = make_uint2(hz, lo2);
+            block_setup(h, key, j0 + j, s_hib, hz, lo2);
+            pix_blk[j][tid] = make_uint2(hz, lo2);
         }
     } else {
         o_s[tid] = o;
@@ -180,7 +182,7 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
 #pragma unroll
                 for (int j = 0; j < NBT; ++j) {
                     uint32_t hi_bj, lo_bj;
-                    mulhilo(kMulB, (uint32_t)j, hi_bj, lo_bj);
+                    mulhilo(kMulB, (uint32_t)(j0 + j), hi_bj, lo_bj);
                     const TapScalars ts = tap_scalars(hi_bj ^ key.k0[0] ^ k, key);
                     tap_blk[tid][j] = make_uint2(ts.sz, ts.s_lo);
                 }
@@ -226,8 +228,8 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
             if (i < nk) {
                 const unsigned long long mask = __ballot(xv[i] != 0);
                 if (xv[i] != 0) {
-                    const uint32_t pos = run + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                    const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, run));
                     list[pos] = (uint32_t)tid | ((uint32_t)i << 8) | (xv[i] << 16);
                 }
                 run += (uint32_t)__popcll(mask);
@@ -237,50 +239,53 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
 
         // sample the products, lanes taking entries round-robin
         const uint32_t total = count;
-        if constexpr (NB > 0) {
+        if constexpr (HOIST) {
             constexpr int U = (NB >= 4) ? 1 : 4 / NB;      // entries in flight per lane: four independent calls
-            for (uint32_t e0 = (uint32_t)tid; e0 < total; e0 += (uint32_t)(U * kListPixels)) {
-                uint32_t cnt[U];
-                uint32_t ent[U];
+            auto sample_all = [&](auto whole_c) {          // whole: every block of this pass is drawn to its end
+                constexpr bool WHOLE = decltype(whole_c)::value;
+                const uint32_t nsamp = WHOLE ? (uint32_t)(kPer * NB) : (uint32_t)(s_uniform - kPer * j0);
+                for (uint32_t e0 = (uint32_t)tid; e0 < total; e0 += (uint32_t)(U * kListPixels)) {
+                    uint32_t cnt[U];
+                    uint32_t ent[U];
+                    int32_t unit[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint32_t e = e0 + (uint32_t)(u * kListPixels);
-                    ent[u] = (e < total) ? list[e] : 0xFFFFFFFFu;
-                    cnt[u] = 0;
-                }
+                    for (int u = 0; u < U; ++u) {
+                        const uint32_t e = e0 + (uint32_t)(u * kListPixels);
+                        ent[u] = (e < total) ? list[e] : 0xFFFFFFFFu;
+                        cnt[u] = nsamp;
+                    }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (ent[u] == 0xFFFFFFFFu) continue;
-                    const uint32_t slot = (ent[u] >> 8) & 0xFFu;
-                    const uint32_t thr = wtab[slot].x;
-                    if constexpr (HOIST) {
+                    for (int u = 0; u < U; ++u) {
+                        if (ent[u] == 0xFFFFFFFFu) continue;
+                        const uint32_t slot = (ent[u] >> 8) & 0xFFu;
+                        const uint2 wt = wtab[slot];
+                        const uint32_t thr = wt.x;
+                        unit[u] = (int32_t)wt.y;
                         const uint32_t pl = ent[u] & 0xFFu;
                         const uint2 base = pix_base[pl];
                         const PixelHoist h{base.x, 0u, base.y};
 #pragma unroll
                         for (int j = 0; j < NB; ++j) {
-                            const uint2 pb = pix_blk[pl][j];
+                            const uint2 pb = pix_blk[j][pl];
                             const uint2 tb = tap_blk[slot][j];
-                            cnt[u] = sample_block<4, P7>(cnt[u], thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j, 0, 0);
+                            if (!WHOLE && kPer * (j0 + j) >= s_uniform) break;          // uniform
+                            if (WHOLE || kPer * (j0 + j + 1) <= s_uniform)               // uniform
+                                cnt[u] = sample_block<4, P7>(cnt[u], thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j0 + j, 0, 0);
+                            else
+                                cnt[u] = sample_block<0, P7>(cnt[u], thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j0 + j, 0, s_uniform);
                         }
-                    } else {
-                        const uint32_t ou = o_s[ent[u] & 0xFFu];
-                        const uint32_t ku = ktab[slot];
+                    }
 #pragma unroll
-                        for (int j = 0; j < NB; ++j)
-                            cnt[u] += P7 ? count_block_full7(ou, ku, (uint32_t)j, p.layer_id, p.key0, p.key1, thr)
-                                         : count_block_full(ou, ku, (uint32_t)j, p.layer_id, p.key0, p.key1, thr);
+                    for (int u = 0; u < U; ++u) {
+                        if (ent[u] == 0xFFFFFFFFu) continue;
+                        const int32_t xs = (int32_t)(int8_t)((ent[u] >> 16) & 0xFFu);
+                        const int32_t term = (int32_t)((uint32_t)xs * cnt[u] * (uint32_t)unit[u]);   // modulo 2^32
+                        atomicAdd(&acc_s[ent[u] & 0xFFu], term);
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (ent[u] == 0xFFFFFFFFu) continue;
-                    const int32_t xs = (int32_t)(int8_t)((ent[u] >> 16) & 0xFFu);
-                    const int32_t unit = (int32_t)wtab[(ent[u] >> 8) & 0xFFu].y;
-                    const int32_t term = (int32_t)((uint32_t)xs * ((uint32_t)((P7 ? 16 : 4) * NB) + cnt[u]) * (uint32_t)unit);   // modulo 2^32
-                    atomicAdd(&acc_s[ent[u] & 0xFFu], term);
-                }
-            }
+            };
+            if (!MULTI || kPer * (j0 + NB) <= s_uniform) sample_all(std::true_type{});
+            else if constexpr (MULTI) sample_all(std::false_type{});
         } else {
             for (uint32_t e = (uint32_t)tid; e < total; e += (uint32_t)kListPixels) {
                 const uint32_t entry = list[e];
@@ -297,6 +302,7 @@ __global__ void __launch_bounds__(kListPixels, 7) k_layer_product_list(const Lay
         }
         __syncthreads();   // the tables and the list are rewritten by the next chunk
     }
+    }   // generator blocks
     __syncthreads();       // acc_s is complete (also when the channel has no live tap at all)
 
     if (valid) {
@@ -320,40 +326,44 @@ inline int launch_product_list(const LayerParams& p, const uint32_t* live_idx, c
     const int gy = (p.OC + channels_per_wg - 1) / channels_per_wg;
     if (gx > 2147483647ll || gy > 65535) return (int)hipErrorInvalidValue;
     const dim3 grid((unsigned)gx, (unsigned)gy), block(kListPixels);
-    // compile-time block count only for a uniform S that is a whole number of generator blocks
+    // Uniform S: the blocks of a call in as many passes of up to four as it takes, cut as evenly as possible (five blocks: three
+    // and two; a pass of three costs what it samples, not what it could).
     const bool p7 = p.prob_bits <= 7;
     const int per_block = p7 ? 16 : 4;
     int nb = 0;
-    if (!p.budget_to && p.S % per_block == 0) nb = p.S / per_block;
+    bool multi = false;
+    if (!p.budget_to) {
+        const int blocks = std::max(1, (std::min(p.S, p.s_max) + per_block - 1) / per_block), passes = (blocks + 3) / 4;
+        nb = (blocks + passes - 1) / passes;
+        multi = std::min(p.S, p.s_max) != nb * per_block;
+    }
     int slot = 0;
     const bool timed = prof_begin(stream, &slot);
     const bool inside = p.pad_h == 0 && p.pad_w == 0 && (int64_t)(p.OH - 1) * p.stride_h + p.KH <= p.H &&
                         (int64_t)(p.OW - 1) * p.stride_w + p.KW <= p.W;
-#define PSB_LAUNCH(NB_, P7_)                                                                                      \
-    do {                                                                                                          \
-        if (inside)                                                                                               \
-            hipLaunchKernelGGL((k_layer_product_list<NB_, P7_, true>), grid, block, 0, stream, p, live_idx,       \
-                               live_cnt, channels_per_wg);                                                        \
-        else                                                                                                      \
-            hipLaunchKernelGGL((k_layer_product_list<NB_, P7_, false>), grid, block, 0, stream, p, live_idx,      \
-                               live_cnt, channels_per_wg);                                                        \
-    } while (0)
-    if (p7) {
+    auto launch = [&](auto nb_c, auto p7_c, auto inside_c, auto multi_c) {
+        hipLaunchKernelGGL((k_layer_product_list<decltype(nb_c)::value, decltype(p7_c)::value, decltype(inside_c)::value, decltype(multi_c)::value>),
+                           grid, block, 0, stream, p, live_idx, live_cnt, channels_per_wg);
+    };
+    auto with_inside = [&](auto nb_c, auto p7_c, auto multi_c) {
+        if (inside) launch(nb_c, p7_c, std::true_type{}, multi_c);
+        else launch(nb_c, p7_c, std::false_type{}, multi_c);
+    };
+    auto with_nb = [&](auto p7_c, auto multi_c) {
         switch (nb) {
-            case 1: PSB_LAUNCH(1, true); break;
-            case 2: PSB_LAUNCH(2, true); break;
-            default: PSB_LAUNCH(0, true); break;
+            case 1: with_inside(std::integral_constant<int, 1>{}, p7_c, multi_c); break;
+            case 2: with_inside(std::integral_constant<int, 2>{}, p7_c, multi_c); break;
+            case 3: with_inside(std::integral_constant<int, 3>{}, p7_c, multi_c); break;
+            default: with_inside(std::integral_constant<int, 4>{}, p7_c, multi_c); break;
         }
-    } else {
-        switch (nb) {
-            case 1: PSB_LAUNCH(1, false); break;
-            case 2: PSB_LAUNCH(2, false); break;
-            case 4: PSB_LAUNCH(4, false); break;
-            case 8: PSB_LAUNCH(8, false); break;
-            default: PSB_LAUNCH(0, false); break;
-        }
-    }
-#undef PSB_LAUNCH
+    };
+    auto with_p7 = [&](auto p7_c) {
+        if (nb == 0) with_inside(std::integral_constant<int, 0>{}, p7_c, std::false_type{});
+        else if (multi) with_nb(p7_c, std::true_type{});
+        else with_nb(p7_c, std::false_type{});
+    };
+    if (p7) with_p7(std::true_type{});
+    else with_p7(std::false_type{});
     if (timed) prof_end(stream, slot);
     return (int)hipGetLastError();
 }
