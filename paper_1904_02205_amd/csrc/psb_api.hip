@@ -424,6 +424,20 @@ int sample_segments(const psb_weights* q, const shared_plan& sp, const int (&lev
     return PSB_OK;
 }
 
+// Workgroups of the persistent matrix-core kernel that the chip holds at once (two per CU), 0 to rule that kernel out.
+int resident_workgroups()
+{
+    static const int resident_wgs = [] {
+        if (const char* v = std::getenv("PSB_SHARED_RESIDENT")) { if (std::atoi(v) == 0) return 0; }   // benchmark switch
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+            n = 256;
+        return 2 * n;
+    }();
+    return resident_wgs;
+}
+
 // layout: PSB_BLOCKED_IN | PSB_BLOCKED_OUT | PSB_BLOCKED_RES
 int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, int32_t S, const uint8_t* budget_to,
                   const uint8_t* budget_from, uint64_t seed, uint32_t layer_id, int32_t* acc, float* y,
@@ -469,16 +483,22 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
     int ksplit = 1, half_tiles = 2;
     if (mfma) {
         // Few pixel tiles and a long reduction: cut the reduction so that every SIMD has a wave.  Only then: the
-        // partial sums cost a zero-fill, atomics and a separate rescale pass, which measured slower than the
-        // unsplit kernel as soon as the chip is half full.
+        // partial sums cost a zero-fill, atomics and a separate rescale pass.  Whole call, split : unsplit, us - 3x3
+        // 256->512 stride 2 on 14x14, batch 16 (72 steps) 29.6 : 26.9; linear 1024->256, batch 64 (32) 17.2 : 14.0,
+        // 4096->512 (128) 40.9 : 33.8; 3x3 512->512 stride 2 (144) 37.5 : 39.9; linear 8192->64, batch 16 (256) 19 : 33,
+        // 16384->512, batch 64 (512) 74 : 94.
         half_tiles = psb::shared_half_tiles((int64_t)g->n * OH * OW, n_ocb);
         const int64_t waves = ((int64_t)g->n * OH * OW + 32 * half_tiles - 1) / (32 * half_tiles) * n_ocb;
-        const int64_t want = waves <= 512 ? (1024 + waves - 1) / waves : 1;
+        const int64_t want = waves <= 512 && n_ksteps >= 144 ? (1024 + waves - 1) / waves : 1;
         ksplit = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, 8), n_ksteps / 16));
         // the 3 x 3 kernel with both operands in LDS deals the channel blocks to teams inside a workgroup instead
         if (!rowpack && psb::window_slots(q->shape.kh, q->shape.kw, g->stride_h, g->stride_w, g->pad_h, g->pad_w, g->h, g->w,
                                           half_tiles) > 0)
             ksplit = 1;
+        // Budget levels in one launch: splitting would take the segments one at a time, each with a filter sampled again, a
+        // contraction, and around them a rounded map, a zero-fill and a rescale pass (256->512, 3x3, stride 2 at 14x14, batch 16, two
+        // levels: seven launches of 55 us in all).
+        if (round_down && n_seg > 0 && !budget_from && n_ksteps <= 256 && (int64_t)n_ksteps * 32 * n_seg < (1ll << 17)) ksplit = 1;
     }
     // all segments in one launch, accumulated in registers, epilogue fused
     const bool fused_segments = round_down && mfma && n_seg > 0 && !budget_from && ksplit == 1 &&
@@ -607,15 +627,7 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         int slot = 0;
         const bool timed = profile_begin(stream, &slot);
         if (mfma) {
-            static const int resident_wgs = [] {
-                if (const char* v = std::getenv("PSB_SHARED_RESIDENT")) { if (std::atoi(v) == 0) return 0; }   // benchmark switch
-                int dev = 0, n = 0;
-                if (hipGetDevice(&dev) != hipSuccess ||
-                    hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-                    n = 256;
-                return 2 * n;
-            }();
-            psb::launch_conv_shared_mfma(p, psb::planes_needed(max_shift, n_samples), resident_wgs, half_tiles, stream);
+            psb::launch_conv_shared_mfma(p, psb::planes_needed(max_shift, n_samples), resident_workgroups(), half_tiles, stream);
         } else {
             const int64_t columns = (npix + 255) / 256;
             if (p.Cg == 1 && p.KH == 3 && p.KW == 3) {
@@ -681,7 +693,7 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         p.masked = 0;
         int slot = 0;
         const bool timed = profile_begin(stream, &slot);
-        psb::launch_conv_shared_mfma(p, n_planes, 0, half_tiles, stream);
+        psb::launch_conv_shared_mfma(p, n_planes, resident_workgroups(), half_tiles, stream);
         if (timed) profile_end(stream, slot);
         PSB_HIP_TRY(hipGetLastError());
         return PSB_OK;

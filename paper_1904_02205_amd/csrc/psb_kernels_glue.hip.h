@@ -208,10 +208,10 @@ __global__ void __launch_bounds__(256) k_budget_resample(const uint8_t* __restri
 //     h = sum_c -p_c log p_c = log Z - (sum_c e_c z_c) / Z,   z_c = a_c*step - max_c, e_c = exp(z_c), Z = sum_c e_c.
 // Evaluated in binary64 and rounded once to binary32: sums of hundreds of binary32 terms would lose the digits the
 // threshold needs.  a_c - max is one of 256 integers, so the exponentials come from a table of 256 that a workgroup
-// computes once; it works on 16 consecutive pixels, 16 lanes per pixel, each taking every 16th channel (a channel of
-// 16 pixels is a run of 16 bytes), and adds the lanes' sums in a fixed order.  (One lane per pixel and one exp per
+// computes once; it works on 4 consecutive pixels, 64 threads per pixel, each taking every 64th channel, and adds the
+// threads' sums in a fixed order.  (One lane per pixel and one exp per
 // activation took 170 us for 784 pixels x 512 channels: four workgroups, 512 exponentials after each other.)
-constexpr int kEntropyPixels = 16, kEntropySlices = 16;
+constexpr int kEntropyPixels = 4, kEntropySlices = 64;
 __global__ void __launch_bounds__(256) k_channel_entropy(const int8_t* __restrict__ act, float step, int N, int C,
                                                          int64_t HW, float* __restrict__ entropy)
 {

@@ -903,7 +903,7 @@ __global__ void __launch_bounds__(256, (P == 4 && HT == 2) ? 1 : 2) k_conv_share
 // channels, 1x1 shortcuts, classifiers): a persistent variant.  A workgroup stages the whole block once and then walks
 // over pixel tiles, `columns` apart; inside the walk there is no barrier and no staging, the kernel arguments and
 // the rescale factors are read once, and the four waves run independently of each other.  Unsplit, unmasked calls
-// only.  Dynamic LDS: n_steps * P * 1024 bytes.  gridDim.x is a multiple of 8, columns = the grid the plain kernel
+// only.  Dynamic LDS: n_steps * P * 1024 bytes per segment of the sample axis.  gridDim.x is a multiple of 8, columns = the grid the plain kernel
 // would get.  HT: half tiles of 32 pixels per wave (a tile of the walk is 128 HT pixels).
 template <int P, int OUT, int HT>
 __global__ void __launch_bounds__(256, HT == 1 ? 4 : 2) k_conv_shared_mfma_resident(const SharedParams p, unsigned columns)
@@ -918,10 +918,14 @@ __global__ void __launch_bounds__(256, HT == 1 ? 4 : 2) k_conv_shared_mfma_resid
     const int ocb = blockIdx.y;
     const int CB = p.C_pad >> 5;
     const int n_steps = p.tKH * p.tKW * CB;
-    const int8_t* wblock = p.planes + (int64_t)ocb * p.n_ksteps * (kMaxPlanes * kPlaneStride);
-    for (int i = threadIdx.x; i < n_steps * P * 64; i += 256) {
-        const int step = i / (P * 64), b = (i >> 6) % P;
-        a_all[i] = *reinterpret_cast<const v4i*>(wblock + ((int64_t)(step * kMaxPlanes + b) * 64 + (i & 63)) * 16);
+    const int n_seg = p.n_seg > 0 ? p.n_seg : 1;
+    const int seg_words = n_steps * P * 64;
+    for (int seg = 0; seg < n_seg; ++seg) {
+        const int8_t* wblock = p.planes + (int64_t)seg * (int64_t)p.seg_stride + (int64_t)ocb * p.n_ksteps * (kMaxPlanes * kPlaneStride);
+        for (int i = threadIdx.x; i < seg_words; i += 256) {
+            const int step = i / (P * 64), b = (i >> 6) % P;
+            a_all[seg * seg_words + i] = *reinterpret_cast<const v4i*>(wblock + ((int64_t)(step * kMaxPlanes + b) * 64 + (i & 63)) * 16);
+        }
     }
     if (threadIdx.x < 32) {
         const int oc = ocb * 32 + (int)threadIdx.x;
@@ -952,34 +956,44 @@ __global__ void __launch_bounds__(256, HT == 1 ? 4 : 2) k_conv_shared_mfma_resid
 #pragma unroll
                 for (int q = 0; q < 16; ++q) acc[h][b][q] = 0;
 
-        TapCursor<HT> cur;
-        cur.start(p, 0, CB, cb_stride, row_stride, live, iy0, ix0, origin);
-        v4i opb[kDepth][HT];
-        auto request = [&](int slot) {
+        // one pass over the reduction per segment of the sample axis, as in the plain kernel
+        for (int seg = 0; seg < n_seg; ++seg) {
+            bool lv[2] = {live[0], live[1]};
+            if (p.n_seg > 0) {
 #pragma unroll
-            for (int h = 0; h < HT; ++h) opb[slot][h] = load_operand(xt_rsrc, cur.tap_off[h], cur.cboff);
-            cur.advance(p, n_steps, CB, cb_stride, row_stride, live, iy0, ix0, origin);
-        };
+                for (int h = 0; h < 2; ++h) lv[h] = live[h] && to_[h] >= p.seg_level[seg];
+                if (__ballot(lv[0] || lv[1]) == 0ull) break;     // wave-uniform; levels nest
+            }
+            const v4i* const a_seg = a_all + seg * seg_words;
+            TapCursor<HT> cur;
+            cur.start(p, 0, CB, cb_stride, row_stride, lv, iy0, ix0, origin);
+            v4i opb[kDepth][HT];
+            auto request = [&](int slot) {
 #pragma unroll
-        for (int d = 0; d < kDepth; ++d) request(d);
+                for (int h = 0; h < HT; ++h) opb[slot][h] = load_operand(xt_rsrc, cur.tap_off[h], cur.cboff);
+                cur.advance(p, n_steps, CB, cb_stride, row_stride, lv, iy0, ix0, origin);
+            };
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) request(d);
 
-        v4i a[2][P];
+            v4i a[2][P];
 #pragma unroll
-        for (int b = 0; b < P; ++b) a[0][b] = a_all[b * 64 + lane];
-        for (int s0 = 0; s0 < n_steps; s0 += kDepth) {
+            for (int b = 0; b < P; ++b) a[0][b] = a_seg[b * 64 + lane];
+            for (int s0 = 0; s0 < n_steps; s0 += kDepth) {
 #pragma unroll
-            for (int ks = 0; ks < kDepth; ++ks) {
-                const int nxt = min(s0 + ks + 1, n_steps - 1);       // the operands of the next step, one step ahead
+                for (int ks = 0; ks < kDepth; ++ks) {
+                    const int nxt = min(s0 + ks + 1, n_steps - 1);       // the operands of the next step, one step ahead
 #pragma unroll
-                for (int b = 0; b < P; ++b) a[(ks + 1) & 1][b] = a_all[(nxt * P + b) * 64 + lane];
-                if (s0 + ks < n_steps) {             // wave-uniform
+                    for (int b = 0; b < P; ++b) a[(ks + 1) & 1][b] = a_seg[(nxt * P + b) * 64 + lane];
+                    if (s0 + ks < n_steps) {             // wave-uniform
 #pragma unroll
-                    for (int b = 0; b < P; ++b)
+                        for (int b = 0; b < P; ++b)
 #pragma unroll
-                        for (int h = 0; h < HT; ++h)
-                            acc[h][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks & 1][b], opb[ks][h], acc[h][b], 0, 0, 0);
+                            for (int h = 0; h < HT; ++h)
+                                acc[h][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks & 1][b], opb[ks][h], acc[h][b], 0, 0, 0);
+                    }
+                    request(ks);
                 }
-                request(ks);
             }
         }
         tile_epilogue<P, OUT, HT>(p, acc, live, n_, oy_, ox_, to_, ocb, lane, s_mult, s_bias);
@@ -1454,7 +1468,7 @@ inline void launch_conv_shared_mfma(const SharedParams& p, int planes, int resid
     const unsigned columns = (unsigned)((tiles + 7) / 8 * 8);                        // 8 XCDs
     const unsigned n_ocb = (unsigned)((p.OC + 31) / 32);
     const int n_steps = p.tKH * p.tKW * (p.C_pad >> 5);
-    const size_t lds = (size_t)n_steps * planes * kPlaneStride;
+    const size_t lds = (size_t)n_steps * planes * kPlaneStride * std::max(1, p.n_seg);
     const WindowPlan win = window_plan(p, planes, half_tiles, std::max(resident_wgs, 512) / 2);
     if (win.ok) {
         SharedParams pw = p;
@@ -1469,14 +1483,16 @@ inline void launch_conv_shared_mfma(const SharedParams& p, int planes, int resid
     // worth it when a workgroup gets more than one tile: staging the whole block before the first matrix instruction
     // costs more than the chunked start of the plain kernel
     const unsigned fit = std::max(8u, (unsigned)std::max(resident_wgs, 0) / n_ocb / 8u * 8u);
-    if (half_tiles == 2 && resident_wgs > 0 && !p.masked && p.n_seg == 0 && p.ksplit == 1 && lds <= 65536 && columns > fit) {
+    if (half_tiles == 2 && resident_wgs > 0 && !p.masked && p.ksplit == 1 && lds <= 65536 && columns > fit) {
         // A short reduction leaves the walk bound by the vector instructions of tile set-up and epilogue (the first
         // convolution of a ResNet: ~1000 per tile and wave against 42 matrix instructions), which two waves per SIMD
         // issue at half the rate four do: one half tile per wave then (half the accumulators, four waves per SIMD),
         // when four workgroups' weight blocks fit the LDS of a CU (first convolution of config 4: 45 -> 37 us).
-        if (lds <= 36864) {
+        // (With two budget segments the weight blocks of three workgroups fit, still better than the plain kernel.)
+        if (lds <= (p.n_seg > 0 ? 49152u : 36864u)) {
             const unsigned columns1 = (unsigned)(((npix + 127) / 128 + 7) / 8 * 8);
-            const unsigned fit1 = std::max(8u, 2u * (unsigned)resident_wgs / n_ocb / 8u * 8u);
+            const unsigned wgs1 = lds <= 36864 ? 2u * (unsigned)resident_wgs : 3u * (unsigned)resident_wgs / 2u;
+            const unsigned fit1 = std::max(8u, wgs1 / n_ocb / 8u * 8u);
             const dim3 grid(std::min(fit1, columns1), n_ocb);
             if (p.rq.x_out) launch_conv_shared_mfma_resident<kOutRequant, 1>(p, planes, grid, columns1, lds, stream);
             else launch_conv_shared_mfma_resident<kOutAcc, 1>(p, planes, grid, columns1, lds, stream);

@@ -52,3 +52,37 @@ def test_channel_entropy_remainders(psb, orc, n, c, h, w):
     assert np.all(np.abs(got - ref) <= np.spacing(np.maximum(np.abs(ref), 1e-12).astype(np.float32)) + 1e-13)
     clear = np.abs(ref - ref.mean(axis=(1, 2), keepdims=True)) > 1e-6
     assert np.array_equal(bud.cpu().numpy()[clear], np.where(ref > ref.mean(axis=(1, 2), keepdims=True), 9, 4)[clear])
+
+
+@pytest.mark.parametrize("cin,oc,batch", [(143 * 32, 40, 5), (144 * 32, 40, 5), (257 * 32, 33, 3)])
+def test_shared_long_reductions(psb, orc, cin, oc, batch):
+    """Shared-filter linear layers below, at and beyond the length from which the reduction is split over the grid."""
+    rng = np.random.default_rng(cin)
+    L = synth.Layer("long", synth.he_normal((oc, cin, 1, 1), rng), synth.sparse_relu_int8((batch, cin, 1, 1), rng), S=8, s_max=8,
+                    seed=6, layer_id=1, linear=True)
+    ref, over, _ = helpers.oracle_layer(orc, L, shared=True)
+    for _ in range(2):
+        acc, _ = helpers.gpu_layer(psb, L, shared=True)
+        assert over == 0 and np.array_equal(acc, ref)
+
+
+@pytest.mark.parametrize("oc,k", [(64, 3), (40, 7)])
+def test_shared_levels_in_the_persistent_kernel(psb, orc, oc, k):
+    """A first layer (three channels, packed rows) with more pixel tiles than the chip holds workgroups, budget levels taken in
+    one launch: against the call that takes its segments one at a time, and a sample of it against the oracle."""
+    import torch
+    rng = np.random.default_rng(oc)
+    L = synth.Layer("stem", synth.he_normal((oc, 3, k, k), rng), synth.gaussian_int8((1, 3, 262, 261), rng), pad=(k // 2, k // 2), S=8,
+                    s_max=16, seed=6, layer_id=1)
+    q = helpers.gpu_quantize(psb, L)
+    x = torch.from_numpy(L.x).cuda()
+    bt = torch.from_numpy(rng.choice([0, 3, 8, 16], size=(1, 262, 261)).astype(np.uint8)).cuda()
+    mult = torch.full((oc,), 0.02 * 2.0 ** q.e_min, device="cuda")
+    kw = dict(pad=L.pad, seed=L.seed, layer_id=L.layer_id, mult=mult)
+    acc = torch.empty((1, oc, 262, 261), dtype=torch.int32, device="cuda")
+    one_by_one = psb.conv2d_requant(q, x, 4.0, budget_to=bt, shared=True, acc=acc, **kw)
+    at_once = psb.conv2d_shared_budget_requant_blocked(q, x, tuple(x.shape), 4.0, bt, (3, 8, 16), **kw)
+    assert torch.equal(at_once, one_by_one)
+    points = np.sort(rng.choice(oc * 262 * 261, 4000, replace=False)).astype(np.int64)
+    ref, over, _ = helpers.oracle_layer(orc, L, budget_to=bt.cpu().numpy(), shared=True, points=points)
+    assert over == 0 and np.array_equal(acc.cpu().numpy().ravel()[points], ref)
