@@ -215,22 +215,48 @@ bool choose_window(const std::vector<uint32_t>& hist, int OC, int window, int x_
     return false;
 }
 
+// Workgroups of the persistent matrix-core kernel that the chip holds at once (two per CU), 0 to rule that kernel out.
+int resident_workgroups()
+{
+    static const int resident_wgs = [] {
+        if (const char* v = std::getenv("PSB_SHARED_RESIDENT")) { if (std::atoi(v) == 0) return 0; }   // benchmark switch
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+            n = 256;
+        return 2 * n;
+    }();
+    return resident_wgs;
+}
+
 // Which kernel serves this layer under the current mapping switch (1, 2, 3), or a psb_status.
 int pick_mapping(const psb_weights* q, const psb::LayerParams& p)
 {
     int mapping = g_mapping;
     if (mapping == 2 && q->shape.groups != 1) return PSB_ERR_SHAPE;
     if (mapping == 0) {
-        // Channel lanes pay for every (tap, channel lane) pair, live or not, about 42 instructions a generator call; the
-        // product list pays for live weights only, 50 to 60, and needs a thousand workgroups to fill the chip.  Measured
-        // (3x3 on 64 channels of 28x28, batch 4, S = 8 / 16, product list : channel lanes): 32 of 64 lanes in use 1.8 / 1.3,
-        // 30 % of the weights live on 64 lanes (832 workgroups) 0.9, 20 % 0.6 / 0.4; 16 lanes (208 workgroups) 1.5 / 1.0,
-        // 4 lanes (52 workgroups) 1.5 / 1.0; 37->70 channels, 5x5, 324 pixels, S = 10: 504 us : 60 us.
-        const double in_use = (double)q->info.n_live / ((double)q->oc_pad * q->K);
-        const int64_t list_wgs = ((int64_t)p.N * p.OH * p.OW + psb::kListPixels - 1) / psb::kListPixels * p.OC;
-        const double fill = std::min(1.0, (double)list_wgs / 1024.0);
+        // Time of either kernel in us, from its measured parts (half of the activations zero: that scales both alike).
+        // Channel lanes: a generator call of a wave is 63 ns and they make one for every (tap, channel lane, block), live or
+        // not, on four SIMDs per CU; two launches.  Product list: a workgroup (256 pixels of a channel) walks the live taps
+        // ten at a time, at 2.3 us + 0.45 us per block alone on its CU (a chain of latencies: table, gather, compaction,
+        // barriers) and 0.37 us + 0.30 us more for each further one.  Lanes win dense layers of many channels and small
+        // images, the list few channels on many pixels and pruned weights.  3x3 on 64 channels, list : lanes, us:
+        // 8 channels, 4704 pixels, S = 8 / 16 / 32 184:175 / 240:335 / 400:653, 784 pixels 183:38 / 236:69 / 400:128;
+        // 17 channels, 4704 pixels, S = 16 315:338; 100 channels 884:645; 37->70, 5x5, 324 pixels, S = 10 504:71.
+        const int n_cus = std::max(resident_workgroups(), 512) / 2;
+        const double pixels = (double)p.N * p.OH * p.OW;
+        const int per_block = p.prob_bits <= 7 ? 16 : 4;
+        const int blocks = std::max(1, ((p.budget_to ? p.s_max : std::min(p.S, p.s_max)) + per_block - 1) / per_block);
+        const int passes = (blocks + 3) / 4;
+        const double lanes_us = 12.0 + 0.063 / (4 * n_cus) * 0.5 * p.K * pixels * (p.oc_pad / 64) * blocks;
+        // workgroups per CU (one or two over a full row do not show: 2.004 measures as 2)
+        const double rows = std::max(1.0, std::ceil(std::ceil(pixels / psb::kListPixels) * p.OC / n_cus - 0.25));
+        const double b = (double)blocks / passes;
+        const double chunk_us = passes * (2.3 + 0.45 * b + (rows - 1.0) * (0.37 + 0.30 * b));
+        // per-pixel ranges have no tables: twice the instructions
+        const double list_us = 3.0 + (double)q->info.n_live / p.OC / psb::kListTaps * chunk_us * (p.budget_to ? 2.0 : 1.0);
         const bool mostly_pruned = 3 * q->info.n_live < (int64_t)q->shape.oc * q->K;
-        mapping = psb::oc_lane_supported(p) && !mostly_pruned && in_use >= 0.45 * fill ? 2 : 3;
+        mapping = psb::oc_lane_supported(p) && !mostly_pruned && lanes_us <= list_us ? 2 : 3;
     }
     return mapping;
 }
@@ -299,7 +325,7 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
         rc = psb::launch_oc_lane(p, stream, profile_begin, profile_end);
         if (rc != 0) { tl_last_device_error = rc; return PSB_ERR_DEVICE; }
     } else if (mapping == 3) {
-        rc = psb::launch_product_list(p, q->live_idx_dev, q->live_cnt_dev, stream, profile_begin, profile_end);
+        rc = psb::launch_product_list(p, std::max(resident_workgroups(), 512) / 2, q->live_idx_dev, q->live_cnt_dev, stream, profile_begin, profile_end);
         if (rc != 0) { tl_last_device_error = rc; return PSB_ERR_DEVICE; }
     } else {
         const int64_t npix = (int64_t)p.N * OH * OW;
@@ -424,20 +450,6 @@ int sample_segments(const psb_weights* q, const shared_plan& sp, const int (&lev
     return PSB_OK;
 }
 
-// Workgroups of the persistent matrix-core kernel that the chip holds at once (two per CU), 0 to rule that kernel out.
-int resident_workgroups()
-{
-    static const int resident_wgs = [] {
-        if (const char* v = std::getenv("PSB_SHARED_RESIDENT")) { if (std::atoi(v) == 0) return 0; }   // benchmark switch
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-            n = 256;
-        return 2 * n;
-    }();
-    return resident_wgs;
-}
-
 // layout: PSB_BLOCKED_IN | PSB_BLOCKED_OUT | PSB_BLOCKED_RES
 int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, int32_t S, const uint8_t* budget_to,
                   const uint8_t* budget_from, uint64_t seed, uint32_t layer_id, int32_t* acc, float* y,
@@ -482,14 +494,16 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
     // ksplit and the tile shape decide whether the segments can share one launch: computed before the planes are sized
     int ksplit = 1, half_tiles = 2;
     if (mfma) {
-        // Few pixel tiles and a long reduction: cut the reduction so that every SIMD has a wave.  Only then: the
-        // partial sums cost a zero-fill, atomics and a separate rescale pass.  Whole call, split : unsplit, us - 3x3
-        // 256->512 stride 2 on 14x14, batch 16 (72 steps) 29.6 : 26.9; linear 1024->256, batch 64 (32) 17.2 : 14.0,
-        // 4096->512 (128) 40.9 : 33.8; 3x3 512->512 stride 2 (144) 37.5 : 39.9; linear 8192->64, batch 16 (256) 19 : 33,
-        // 16384->512, batch 64 (512) 74 : 94.
+        // Few pixel tiles and a long reduction: cut the reduction so that every SIMD has a wave.  The partial sums cost a
+        // zero-fill, a separate rescale pass and an atomic per output and part, so only where that is less than the chain
+        // of steps it cuts: reductions of 144 steps on, and of more than 40 where the outputs are few.  Whole call, split :
+        // unsplit, us - linear 1024 inputs (32 steps), batch 91, 32 / 512 outputs 18.0:14.5 / 21.2:17.5; 2048 (64) 16.6:19.1 /
+        // 30.8:25.4, 128 outputs, batch 256 19.6:22.9; 4096 (128) 17.6:26.6 / 47.8:37.6; 3x3 256->512 stride 2 (72) on
+        // 14x14, batch 16 29.6:26.9, batch 1 20.0:20.8; 512->512 stride 2 (144) 37.5:39.9; linear 16384->512 (512) 74:94.
         half_tiles = psb::shared_half_tiles((int64_t)g->n * OH * OW, n_ocb);
         const int64_t waves = ((int64_t)g->n * OH * OW + 32 * half_tiles - 1) / (32 * half_tiles) * n_ocb;
-        const int64_t want = waves <= 512 && n_ksteps >= 144 ? (1024 + waves - 1) / waves : 1;
+        const bool few_outputs = (int64_t)g->n * OH * OW * q->shape.oc <= 40000;
+        const int64_t want = waves <= 512 && (n_ksteps >= 144 || (n_ksteps > 40 && few_outputs)) ? (1024 + waves - 1) / waves : 1;
         ksplit = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(want, 8), n_ksteps / 16));
         // the 3 x 3 kernel with both operands in LDS deals the channel blocks to teams inside a workgroup instead
         if (!rowpack && psb::window_slots(q->shape.kh, q->shape.kw, g->stride_h, g->stride_w, g->pad_h, g->pad_w, g->h, g->w,
@@ -498,7 +512,7 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         // Budget levels in one launch: splitting would take the segments one at a time, each with a filter sampled again, a
         // contraction, and around them a rounded map, a zero-fill and a rescale pass (256->512, 3x3, stride 2 at 14x14, batch 16, two
         // levels: seven launches of 55 us in all).
-        if (round_down && n_seg > 0 && !budget_from && n_ksteps <= 256 && (int64_t)n_ksteps * 32 * n_seg < (1ll << 17)) ksplit = 1;
+        if (round_down && n_seg > 0 && !budget_from && n_ksteps <= 144 && (int64_t)n_ksteps * 32 * n_seg < (1ll << 17)) ksplit = 1;
     }
     // all segments in one launch, accumulated in registers, epilogue fused
     const bool fused_segments = round_down && mfma && n_seg > 0 && !budget_from && ksplit == 1 &&

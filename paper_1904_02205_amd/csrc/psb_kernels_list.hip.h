@@ -66,19 +66,19 @@ __global__ void __launch_bounds__(256) k_live_index(const uint32_t* __restrict__
     if (threadIdx.x == 0) live_cnt[oc] = count;
 }
 
-// NB > 0: a call with the same S everywhere, NB (1..4) generator blocks at a time.  MULTI: it takes more than one such pass
+// NB > 0: a call with the same S everywhere, NB (1..4, 8) generator blocks at a time.  MULTI: it takes more than one such pass
 //         over the taps, or draws its last block in part; otherwise blocks 0 .. NB - 1 are all there is, and whole (the
 //         general form costs that call 7 % on depthwise 3 x 3 layers, whose tables are rebuilt for every nine taps).
 // NB = 0: per-pixel ranges [from, to), any values.
 // P7: 7-bit uniforms, 16 samples per block; otherwise 32-bit uniforms, 4 per block.
 // INSIDE: every tap of every output pixel lies inside the image (1 x 1 layers, unpadded layers): no bounds checks.
 template <int NB, bool P7, bool INSIDE, bool MULTI>
-__global__ void __launch_bounds__(kListPixels, 6) k_layer_product_list(const LayerParams p,
+__global__ void __launch_bounds__(kListPixels, NB > 4 ? 4 : 6) k_layer_product_list(const LayerParams p,
                                                                     const uint32_t* __restrict__ live_idx,
                                                                     const uint32_t* __restrict__ live_cnt,
                                                                     int channels_per_wg)
 {
-    static_assert(NB <= 4, "table rows are kept for four blocks");
+    static_assert(NB <= 8, "table rows are kept for eight blocks");
     constexpr bool HOIST = NB >= 1;      // the tap- and the pixel-independent parts of rounds 0..2 come from tables
     constexpr int NBT = HOIST ? NB : 1;
     constexpr int kPer = P7 ? 16 : 4;    // samples of a block
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(kListPixels, 6) k_layer_product_list(const Lay
 }
 
 // Returns 0 or a hipError_t.
-inline int launch_product_list(const LayerParams& p, const uint32_t* live_idx, const uint32_t* live_cnt,
+inline int launch_product_list(const LayerParams& p, int n_cus, const uint32_t* live_idx, const uint32_t* live_cnt,
                                hipStream_t stream, bool (*prof_begin)(hipStream_t, int*),
                                void (*prof_end)(hipStream_t, int))
 {
@@ -336,6 +336,10 @@ inline int launch_product_list(const LayerParams& p, const uint32_t* live_idx, c
         const int blocks = std::max(1, (std::min(p.S, p.s_max) + per_block - 1) / per_block), passes = (blocks + 3) / 4;
         nb = (blocks + passes - 1) / passes;
         multi = std::min(p.S, p.s_max) != nb * per_block;
+        // Eight whole blocks and no more than a workgroup per CU: all in one pass, which walks the taps - a chain of
+        // latencies that nothing else on the CU hides - once (576 taps, S = 32, 152 workgroups: 364 us against 481 in two
+        // passes).  With more workgroups two passes and their smaller tables are as fast.
+        if (blocks == 8 && gx * gy <= n_cus && std::min(p.S, p.s_max) == 8 * per_block) { nb = 8; multi = false; }
     }
     int slot = 0;
     const bool timed = prof_begin(stream, &slot);
@@ -359,6 +363,7 @@ inline int launch_product_list(const LayerParams& p, const uint32_t* live_idx, c
     };
     auto with_p7 = [&](auto p7_c) {
         if (nb == 0) with_inside(std::integral_constant<int, 0>{}, p7_c, std::false_type{});
+        else if (nb == 8) with_inside(std::integral_constant<int, 8>{}, p7_c, std::false_type{});
         else if (multi) with_nb(p7_c, std::true_type{});
         else with_nb(p7_c, std::false_type{});
     };

@@ -579,7 +579,9 @@ inline int launch_oc_lane(const LayerParams& p, hipStream_t stream, ProfileBegin
     plan.inv_chunks = inverse_of((uint32_t)n_chunks);
     plan.inv_KHW = inverse_of((uint32_t)(p.KH * p.KW));
     plan.inv_KW = inverse_of((uint32_t)p.KW);
-    const int64_t grid = std::min<int64_t>((n_tickets + kOcWaves - 1) / kOcWaves, waves / kOcWaves);
+    // Two workgroups per CU; when one per CU is enough, one on every CU, though it has tickets for some of its waves only
+    // (as few full workgroups as possible would leave CUs idle: 1x1 128->32 at 14x14, S = 32, 1568 tickets, 29.1 -> 21.1 us).
+    const int64_t grid = std::min<int64_t>(n_tickets, n_tickets > waves / 2 ? waves / kOcWaves : waves / kOcWaves / 2);
     plan.rounds = (uint32_t)(n_tickets / (grid * kOcWaves));
 
     int slot = 0;

@@ -35,6 +35,20 @@ def test_automatic_choice(psb, orc, oc, prune, hw, S):
     psb.set_mapping(psb.MAPPING_AUTO)
 
 
+@pytest.mark.parametrize("oc,prob_bits,S", [(256, 23, 32), (257, 23, 32), (2, 4, 128), (2, 23, 28)])
+def test_product_list_eight_blocks(psb, orc, oc, prob_bits, S):
+    """Eight generator blocks in one pass (as many workgroups as CUs) and in two (one more), seven in two."""
+    rng = np.random.default_rng(S)
+    L = synth.Layer("blocks", synth.he_normal((oc, 8, 3, 3), rng), synth.sparse_relu_int8((1, 8, 4, 5), rng), pad=(1, 1), S=S, s_max=S,
+                    seed=4, layer_id=1)
+    qo, qg = helpers.oracle_quantize(orc, L, prob_bits=prob_bits), helpers.gpu_quantize(psb, L, prob_bits=prob_bits)
+    ref, over, _ = helpers.oracle_layer(orc, L, qo)
+    psb.set_mapping(psb.MAPPING_PRODUCT_LIST)
+    acc, _ = helpers.gpu_layer(psb, L, qg)
+    psb.set_mapping(psb.MAPPING_AUTO)
+    assert over == 0 and np.array_equal(acc, ref)
+
+
 @pytest.mark.parametrize("n,c,h,w", [(1, 1, 1, 1), (2, 15, 3, 5), (1, 17, 4, 4), (3, 40, 7, 7), (1, 512, 1, 17)])
 def test_channel_entropy_remainders(psb, orc, n, c, h, w):
     """Fewer channels than lanes per pixel, pixels that leave a last tile in part; the whole range of activations.  Both sides
@@ -54,9 +68,10 @@ def test_channel_entropy_remainders(psb, orc, n, c, h, w):
     assert np.array_equal(bud.cpu().numpy()[clear], np.where(ref > ref.mean(axis=(1, 2), keepdims=True), 9, 4)[clear])
 
 
-@pytest.mark.parametrize("cin,oc,batch", [(143 * 32, 40, 5), (144 * 32, 40, 5), (257 * 32, 33, 3)])
+@pytest.mark.parametrize("cin,oc,batch", [(40 * 32, 40, 5), (41 * 32, 40, 5), (143 * 32, 333, 121), (144 * 32, 40, 5), (257 * 32, 33, 3)])
 def test_shared_long_reductions(psb, orc, cin, oc, batch):
-    """Shared-filter linear layers below, at and beyond the length from which the reduction is split over the grid."""
+    """Shared-filter linear layers around the lengths from which the reduction is split over the grid, with few outputs and
+    with many."""
     rng = np.random.default_rng(cin)
     L = synth.Layer("long", synth.he_normal((oc, cin, 1, 1), rng), synth.sparse_relu_int8((batch, cin, 1, 1), rng), S=8, s_max=8,
                     seed=6, layer_id=1, linear=True)
