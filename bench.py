@@ -16,14 +16,14 @@ metric  sampled MACs/s: one sampled MAC = one (output element, live tap inside t
 roofline  bound "alu": the sampling kernel is limited by integer VALU issue.  Unit: simple int32 lane-operations
         (a two-operand VALU instruction on vector registers, e.g. v_xor_b32, v_add_u32).  peak = 256 CUs x 4 SIMDs
         x 32 lanes/clock x 2.4 GHz = 78.6 T lane-ops/s (the integer twin of the 157.3 TFLOP/s fp32 vector figure;
-        measured: 2.4 cycles per wave64).  Instructions that multiply, take three operands or produce/consume a lane
+        measured: 2.4 cycles per wave64).  Instructions that multiply, take three operands (v_bitop3_b32 excepted) or produce/consume a lane
         mask (v_mad_u64_u32, v_mul_*, v_cmp, v_addc_co) issue at half that rate (measured 4.2-4.5 cycles) and
         count as 2 units.  `achieved` prices only what the method cannot avoid under this keying: per generator
-        call (4 samples) 15 wide multiplies, 31 two-input xors (gfx950 has no three-input xor), 4 compares and
-        4 carry-adds = 77 units; per product a 24-bit multiply and multiply-add = 4 units; and only for products
+        call (4 samples) 15 wide multiplies, 14 three-input xors (v_bitop3_b32 on vector registers: 2.45 cycles, one
+        unit) and 3 two-input ones, 4 compares and 4 carry-adds = 63 units; per product a 24-bit multiply and multiply-add = 4 units; and only for products
         that need sampling (live weight, tap inside the image, activation != 0).  With --prob-bits 1..7 a
         generator call serves 16 samples and its counting is 4 x (or, subtract, and, bit count) + 1 = 17 units
-        instead of 16: 78 units per call.  The kernel time is measured live: the library brackets every sampling
+        instead of 16: 64 units per call.  The kernel time is measured live: the library brackets every sampling
         kernel with HIP events on the stream it launches on.
         `traffic`: HBM bytes per launch of the sampling kernel from the rocprofv3 counter summary that is tracked
         under profiles/ for the workload (named in `traffic_source`), null when there is none.
@@ -59,8 +59,8 @@ TRAFFIC_PROFILES = {("c4", "product", 23): "profiles/k_layer_oc_lane_config4.md"
 CUS, SIMDS_PER_CU, LANES_PER_SIMD_CLK, CLOCK_HZ = 256, 4, 32, 2.4e9
 PEAK_TIOPS = CUS * SIMDS_PER_CU * LANES_PER_SIMD_CLK * CLOCK_HZ / 1e12     # 78.64 T simple int32 lane-ops/s
 WIDE = 2                   # units of a half-rate instruction (multiply, three operands, lane-mask producer/consumer)
-CALL_UNITS = 15 * WIDE + 31 + 4 * WIDE + 4 * WIDE                          # 77 per generator call (4 samples)
-CALL_UNITS_7BIT = 15 * WIDE + 31 + 1                                       # 62 per generator call (16 samples) ...
+CALL_UNITS = 15 * WIDE + 17 + 4 * WIDE + 4 * WIDE                          # 63 per generator call (4 samples)
+CALL_UNITS_7BIT = 15 * WIDE + 17 + 1                                       # 48 per generator call (16 samples) ...
 WORD_UNITS_7BIT = 4                                                        # ... + 4 per word of four samples it needs
 PRODUCT_UNITS = 2 * WIDE                                                   # v_mul_i32_i24 + v_mad_i32_i24
 KERNEL_NAMES = {1: "k_layer_pixel_lane", 2: "k_layer_oc_lane", 3: "k_layer_product_list"}

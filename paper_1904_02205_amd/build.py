@@ -19,7 +19,7 @@ DEPS = [SRC,
         os.path.join(os.path.dirname(HERE), "include", "psb.h")]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-         # packed FP32 instructions are disabled on purpose (see the build notes of this machine pool)
+         # packed FP32 instructions are disabled on purpose: some forms have given wrong results on this hardware
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-ffp-contract=off", "-Wall", "-Wno-unused-function"]
 
