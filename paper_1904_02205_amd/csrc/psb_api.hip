@@ -31,6 +31,7 @@ struct shared_workspace {
     size_t acc_bytes = 0;
     int32_t* acc_cl_dev = nullptr;   // per-product mode: partial sums of a split reduction, zero between calls
     size_t acc_cl_bytes = 0;
+    bool acc_cl_clean = false;        // all zero once the launches of the calls so far have run
     // digit planes sampled ahead of the call by psb_shared_prepare_filters; the next matching call consumes them
     bool ready = false;
     uint64_t ready_seed = 0;
@@ -55,9 +56,17 @@ int32_t* scratch_acc(shared_workspace* ws, size_t bytes, hipStream_t stream)
     return ws->acc_dev;
 }
 
-// The accumulators in which the partial sums of the channel-lane kernel meet (grown on demand).  Cleared here once, with a
-// kernel; every call leaves them at zero.
-int32_t* scratch_acc_cl(shared_workspace* ws, size_t bytes, hipStream_t stream)
+// Clears the accumulators in which the partial sums of the channel-lane kernel meet, with a kernel.
+bool clear_acc_cl(int32_t* acc_cl, int64_t words, hipStream_t stream)
+{
+    hipLaunchKernelGGL(psb::k_fill_zero, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 8192)), dim3(256), 0, stream, acc_cl, words);
+    return hipGetLastError() == hipSuccess;
+}
+
+// These accumulators, grown on demand.  Every call leaves them at zero, so they are cleared only when that is not known: new,
+// or after a call that failed half way (acc_cl_clean is set by the caller when all its launches succeeded).  A call that is
+// captured always records the clearing: what the replays find is not known at that time, and its own clearing has not run.
+int32_t* scratch_acc_cl(shared_workspace* ws, size_t bytes, bool capturing, hipStream_t stream)
 {
     if (ws->acc_cl_bytes < bytes) {
         if (ws->acc_cl_dev) {
@@ -66,17 +75,17 @@ int32_t* scratch_acc_cl(shared_workspace* ws, size_t bytes, hipStream_t stream)
             ws->acc_cl_dev = nullptr;
             ws->acc_cl_bytes = 0;
         }
-        if (hipMalloc(&ws->acc_cl_dev, bytes) != hipSuccess) return nullptr;
-        const int64_t words = (int64_t)(bytes / sizeof(int32_t));
-        hipLaunchKernelGGL(psb::k_fill_zero, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 8192)), dim3(256), 0, stream,
-                           ws->acc_cl_dev, words);
-        if (hipGetLastError() != hipSuccess) {
-            (void)hipFree(ws->acc_cl_dev);
-            ws->acc_cl_dev = nullptr;
+        ws->acc_cl_clean = false;
+        if (hipMalloc(&ws->acc_cl_dev, bytes) != hipSuccess) {
+            (void)hipGetLastError();
             return nullptr;
         }
         ws->acc_cl_bytes = bytes;
     }
+    if (capturing ? !clear_acc_cl(ws->acc_cl_dev, (int64_t)(bytes / sizeof(int32_t)), stream)
+                  : !ws->acc_cl_clean && !clear_acc_cl(ws->acc_cl_dev, (int64_t)(ws->acc_cl_bytes / sizeof(int32_t)), stream))
+        return nullptr;
+    if (!capturing) ws->acc_cl_clean = false;          // until this call's launches are known to be out
     return ws->acc_cl_dev;
 }
 
@@ -256,7 +265,8 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p)
         // per-pixel ranges have no tables: twice the instructions
         const double list_us = 3.0 + (double)q->info.n_live / p.OC / psb::kListTaps * chunk_us * (p.budget_to ? 2.0 : 1.0);
         const bool mostly_pruned = 3 * q->info.n_live < (int64_t)q->shape.oc * q->K;
-        mapping = psb::oc_lane_supported(p) && !mostly_pruned && lanes_us <= list_us ? 2 : 3;
+        // (the list's grid holds 65535 channels)
+        mapping = psb::oc_lane_supported(p) && ((!mostly_pruned && lanes_us <= list_us) || p.OC > 65535) ? 2 : 3;
     }
     return mapping;
 }
@@ -299,10 +309,11 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
     PSB_HIP_TRY(hipGetDevice(&dev));
     if (dev != q->device) return PSB_ERR_DEVICE;
 
-    const int mapping = pick_mapping(q, p);
+    int mapping = pick_mapping(q, p);
     if (mapping < 0) return mapping;
     // the channel-lane kernel combines the partial sums of a split tap reduction in scratch accumulators
-    const bool split = mapping == 2 && psb::oc_lane_chunks(p).n_chunks > 1;
+    bool split = mapping == 2 && psb::oc_lane_chunks(p).n_chunks > 1;
+    bool capturing = false;
     if (use_static_scratch) {           // the accumulators lie in the static array: nothing is allocated
         uint32_t* base = nullptr;
         rc = static_scratch(dev, &base);
@@ -317,13 +328,25 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
             PSB_HIP_TRY(hipGetLastError());
         }
     } else if (split) {
-        p.acc_cl = scratch_acc_cl(q->ws, (size_t)p.N * OH * OW * (size_t)p.oc_pad * sizeof(int32_t), stream);
-        if (!p.acc_cl) return PSB_ERR_ALLOC;
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+        capturing = status != hipStreamCaptureStatusNone;
+        const size_t bytes = (size_t)p.N * OH * OW * (size_t)p.oc_pad * sizeof(int32_t);
+        // Nothing is allocated under capture; the product list needs no scratch and has the same results, so an automatic choice
+        // falls back to it, there and when memory is short.
+        const bool listable = g_mapping == 0 && p.OC <= 65535;
+        if (!(listable && capturing && q->ws->acc_cl_bytes < bytes)) p.acc_cl = scratch_acc_cl(q->ws, bytes, capturing, stream);
+        if (!p.acc_cl) {
+            if (!listable) return PSB_ERR_ALLOC;
+            mapping = 3;
+            split = false;
+        }
     }
 
     if (mapping == 2) {
         rc = psb::launch_oc_lane(p, stream, profile_begin, profile_end);
         if (rc != 0) { tl_last_device_error = rc; return PSB_ERR_DEVICE; }
+        if (split && !use_static_scratch && !capturing) q->ws->acc_cl_clean = true;
     } else if (mapping == 3) {
         rc = psb::launch_product_list(p, std::max(resident_workgroups(), 512) / 2, q->live_idx_dev, q->live_cnt_dev, stream, profile_begin, profile_end);
         if (rc != 0) { tl_last_device_error = rc; return PSB_ERR_DEVICE; }

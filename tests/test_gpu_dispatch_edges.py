@@ -49,6 +49,31 @@ def test_product_list_eight_blocks(psb, orc, oc, prob_bits, S):
     assert over == 0 and np.array_equal(acc, ref)
 
 
+@pytest.mark.parametrize("warm", [False, True])
+def test_split_reduction_in_a_graph(psb, orc, warm):
+    """A captured call of a layer whose partial sums meet in scratch, on a handle that has none yet (nothing is allocated under
+    capture) and on one that has: eager calls before the first replay and between replays, every result exact."""
+    import torch
+    rng = np.random.default_rng(8)
+    L = synth.Layer("graph", synth.he_normal((64, 40, 3, 3), rng), synth.sparse_relu_int8((1, 40, 14, 14), rng), pad=(1, 1), S=8, s_max=8,
+                    seed=4, layer_id=1)
+    ref, over, _ = helpers.oracle_layer(orc, L)
+    q, x = helpers.gpu_quantize(psb, L), torch.from_numpy(L.x).cuda()
+    acc = torch.zeros((1, 64, 14, 14), dtype=torch.int32, device="cuda")
+    call = lambda: psb.conv2d(q, x, L.S, pad=L.pad, seed=L.seed, layer_id=L.layer_id, acc=acc)
+    if warm:
+        call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for eager in (True, False, True, False, False):
+        acc.zero_()
+        call() if eager else graph.replay()
+        torch.cuda.synchronize()
+        assert over == 0 and np.array_equal(acc.cpu().numpy(), ref), eager
+
+
 @pytest.mark.parametrize("n,c,h,w", [(1, 1, 1, 1), (2, 15, 3, 5), (1, 17, 4, 4), (3, 40, 7, 7), (1, 512, 1, 17)])
 def test_channel_entropy_remainders(psb, orc, n, c, h, w):
     """Fewer channels than lanes per pixel, pixels that leave a last tile in part; the whole range of activations.  Both sides
