@@ -259,11 +259,15 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p)
         const int passes = (blocks + 3) / 4;
         const double lanes_us = 12.0 + 0.063 / (4 * n_cus) * 0.5 * p.K * pixels * (p.oc_pad / 64) * blocks;
         // workgroups per CU (one or two over a full row do not show: 2.004 measures as 2)
-        const double rows = std::max(1.0, std::ceil(std::ceil(pixels / psb::kListPixels) * p.OC / n_cus - 0.25));
+        const int channels = psb::list_channels_per_wg(p.K);
+        const double list_wgs = std::ceil(pixels / psb::kListPixels) * ((p.OC + channels - 1) / channels);
+        const double rows = std::max(1.0, std::ceil(list_wgs / n_cus - 0.25));
         const double b = (double)blocks / passes;
         const double chunk_us = passes * (2.3 + 0.45 * b + (rows - 1.0) * (0.37 + 0.30 * b));
         // per-pixel ranges have no tables: twice the instructions
-        const double list_us = 3.0 + (double)q->info.n_live / p.OC / psb::kListTaps * chunk_us * (p.budget_to ? 2.0 : 1.0);
+        // (short reductions: a workgroup walks several channels one after the other; 1x1 21->49, 792 pixels, S = 8 27.7:17.0)
+        const double chunks = channels * std::ceil((double)q->info.n_live / p.OC / psb::kListTaps);
+        const double list_us = 3.0 + chunks * chunk_us * (p.budget_to ? 2.0 : 1.0);
         const bool mostly_pruned = 3 * q->info.n_live < (int64_t)q->shape.oc * q->K;
         // (the list's grid holds 65535 channels)
         mapping = psb::oc_lane_supported(p) && ((!mostly_pruned && lanes_us <= list_us) || p.OC > 65535) ? 2 : 3;

@@ -314,6 +314,9 @@ __global__ void __launch_bounds__(kListPixels, NB > 4 ? 4 : 6) k_layer_product_l
     }   // channels of this workgroup (acc_s and o_s are only touched by their own lane between the barriers)
 }
 
+// enough channels per workgroup for about 64 taps of work per pixel, at most 8
+inline int list_channels_per_wg(int K) { return std::min(8, std::max(1, 64 / std::max(1, K))); }
+
 // Returns 0 or a hipError_t.
 inline int launch_product_list(const LayerParams& p, int n_cus, const uint32_t* live_idx, const uint32_t* live_cnt,
                                hipStream_t stream, bool (*prof_begin)(hipStream_t, int*),
@@ -321,8 +324,7 @@ inline int launch_product_list(const LayerParams& p, int n_cus, const uint32_t* 
 {
     const int64_t npix = (int64_t)p.N * p.OH * p.OW;
     const int64_t gx = (npix + kListPixels - 1) / kListPixels;
-    // enough channels per workgroup for about 64 taps of work per pixel, at most 8
-    const int channels_per_wg = (int)std::min<int64_t>(8, std::max<int64_t>(1, 64 / std::max(1, p.K)));
+    const int channels_per_wg = list_channels_per_wg(p.K);
     const int gy = (p.OC + channels_per_wg - 1) / channels_per_wg;
     if (gx > 2147483647ll || gy > 65535) return (int)hipErrorInvalidValue;
     const dim3 grid((unsigned)gx, (unsigned)gy), block(kListPixels);
