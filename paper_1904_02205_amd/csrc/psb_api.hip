@@ -265,7 +265,7 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p)
         const double b = (double)blocks / passes;
         const double chunk_us = passes * (2.3 + 0.45 * b + (rows - 1.0) * (0.37 + 0.30 * b));
         // per-pixel ranges have no tables: twice the instructions
-        // (short reductions: a workgroup walks several channels one after the other; 1x1 21->49, 792 pixels, S = 8 27.7:17.0)
+        // (short reductions: a workgroup walks several channels one after the other; 1x1 21->49, 792 pixels, S = 8 27.7:15.1)
         const double chunks = channels * std::ceil((double)q->info.n_live / p.OC / psb::kListTaps);
         const double list_us = 3.0 + chunks * chunk_us * (p.budget_to ? 2.0 : 1.0);
         const bool mostly_pruned = 3 * q->info.n_live < (int64_t)q->shape.oc * q->K;
