@@ -155,7 +155,10 @@ int psb_weights_export(const psb_weights_t* q, uint32_t* packed_host);
  * A handle also owns the workspaces named below; those in which partial sums meet are
  * zero between calls (every call leaves them so).  Layer calls that use the SAME handle must therefore not
  * overlap in time (same stream, or ordered by events); calls on different handles may
- * run concurrently. */
+ * run concurrently.
+ * Workspaces grow with the calls.  One that a captured call has used stays allocated until the
+ * handle is destroyed, also when a later, larger call makes a new one: a graph may be replayed
+ * until then (it counts as a layer call using the handle), whatever calls the handle has served since. */
 void psb_weights_destroy(psb_weights_t* q);
 
 /* Output height/width of a convolution, on the host, with the validation every

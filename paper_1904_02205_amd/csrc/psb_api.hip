@@ -16,22 +16,19 @@
 #include "psb_kernels_list.hip.h"
 #include "psb_kernels_shared.hip.h"
 #include "psb_kernels_glue.hip.h"
+#include "psb_workspace.h"
 
-// Device memory of the shared-filter mode; allocated on first use, grown on demand, owned by the handle.
-struct shared_workspace {
+// Device memory that a handle's calls work in; allocated on first use, grown on demand, owned by the handle.
+struct workspace {
+    psb::WorkspaceMemory memory;
     int32_t* w32_dev = nullptr;      // [OC][K] sampled integer filter
-    int8_t* planes_dev = nullptr;    // digit planes in matrix-core operand order, one buffer per segment of the sample axis
-    int planes_segments = 0;         // segments the allocation holds
-    uint8_t* qmap_dev = nullptr;     // a budget map rounded down to announced levels (calls that cannot take them in one launch)
-    size_t qmap_bytes = 0;
-    int8_t* xt_dev = nullptr;        // blocked channels-last copy of the activations
-    size_t xt_bytes = 0;
     uint32_t* present_dev = nullptr; // 256 flags: budget values that occur
-    int32_t* acc_dev = nullptr;      // accumulators of calls that do not hand any out but combine partial sums
-    size_t acc_bytes = 0;
-    int32_t* acc_cl_dev = nullptr;   // per-product mode: partial sums of a split reduction, zero between calls
-    size_t acc_cl_bytes = 0;
-    bool acc_cl_clean = false;        // all zero once the launches of the calls so far have run
+    psb::GrownBuffer planes;         // digit planes in matrix-core operand order, one buffer per segment of the sample axis
+    psb::GrownBuffer qmap;           // a budget map rounded down to announced levels (calls that cannot take them in one launch)
+    psb::GrownBuffer xt;             // blocked channels-last copy of the activations
+    psb::GrownBuffer acc;            // accumulators of calls that do not hand any out but combine partial sums
+    psb::GrownBuffer acc_cl;         // per-product mode: partial sums of a split reduction, zero between calls
+    bool acc_cl_clean = false;       // all zero once the launches of the calls so far have run
     // digit planes sampled ahead of the call by psb_shared_prepare_filters; the next matching call consumes them
     bool ready = false;
     uint64_t ready_seed = 0;
@@ -40,20 +37,39 @@ struct shared_workspace {
     int ready_level[4] = {0, 0, 0, 0};
 };
 
-// Accumulator scratch of a handle for psb_conv2d_requant calls without acc_dev (grown on demand).
-int32_t* scratch_acc(shared_workspace* ws, size_t bytes, hipStream_t stream)
-{
-    if (ws->acc_bytes < bytes) {
-        if (ws->acc_dev) {
-            if (hipStreamSynchronize(stream) != hipSuccess) return nullptr;   // an earlier call may still use it
-            (void)hipFree(ws->acc_dev);
-            ws->acc_dev = nullptr;
-            ws->acc_bytes = 0;
-        }
-        if (hipMalloc(&ws->acc_dev, bytes) != hipSuccess) return nullptr;
-        ws->acc_bytes = bytes;
+static thread_local int tl_last_device_error = 0;
+
+// psb::WorkspaceMemory's allocator; waits for the calls on one stream
+struct stream_device {
+    hipStream_t stream;
+    bool allocate(void** ptr, size_t bytes)
+    {
+        if (hipMalloc(ptr, bytes) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
     }
-    return ws->acc_dev;
+    void release(void* ptr) { (void)hipFree(ptr); }
+    bool wait()
+    {
+        const hipError_t e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) tl_last_device_error = (int)e;
+        return e == hipSuccess;
+    }
+};
+
+// At least `bytes` in a buffer of the handle, or a psb_status.
+static int reserve(workspace* ws, psb::GrownBuffer& b, size_t bytes, bool capturing, hipStream_t stream)
+{
+    stream_device device{stream};
+    const psb::Grow r = ws->memory.reserve(b, bytes, capturing, device);
+    return r == psb::Grow::ok ? PSB_OK : r == psb::Grow::wait_failed ? PSB_ERR_DEVICE : PSB_ERR_ALLOC;
+}
+
+static bool is_capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+    return status != hipStreamCaptureStatusNone;
 }
 
 // Clears the accumulators in which the partial sums of the channel-lane kernel meet, with a kernel.
@@ -66,27 +82,16 @@ bool clear_acc_cl(int32_t* acc_cl, int64_t words, hipStream_t stream)
 // These accumulators, grown on demand.  Every call leaves them at zero, so they are cleared only when that is not known: new,
 // or after a call that failed half way (acc_cl_clean is set by the caller when all its launches succeeded).  A call that is
 // captured always records the clearing: what the replays find is not known at that time, and its own clearing has not run.
-int32_t* scratch_acc_cl(shared_workspace* ws, size_t bytes, bool capturing, hipStream_t stream)
+int32_t* scratch_acc_cl(workspace* ws, size_t bytes, bool capturing, hipStream_t stream)
 {
-    if (ws->acc_cl_bytes < bytes) {
-        if (ws->acc_cl_dev) {
-            if (hipStreamSynchronize(stream) != hipSuccess) return nullptr;   // an earlier call may still use it
-            (void)hipFree(ws->acc_cl_dev);
-            ws->acc_cl_dev = nullptr;
-            ws->acc_cl_bytes = 0;
-        }
-        ws->acc_cl_clean = false;
-        if (hipMalloc(&ws->acc_cl_dev, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        ws->acc_cl_bytes = bytes;
-    }
-    if (capturing ? !clear_acc_cl(ws->acc_cl_dev, (int64_t)(bytes / sizeof(int32_t)), stream)
-                  : !ws->acc_cl_clean && !clear_acc_cl(ws->acc_cl_dev, (int64_t)(ws->acc_cl_bytes / sizeof(int32_t)), stream))
+    if (ws->acc_cl.bytes < bytes) ws->acc_cl_clean = false;
+    if (reserve(ws, ws->acc_cl, bytes, capturing, stream) != PSB_OK) return nullptr;
+    int32_t* const acc_cl = static_cast<int32_t*>(ws->acc_cl.ptr);
+    if (capturing ? !clear_acc_cl(acc_cl, (int64_t)(bytes / sizeof(int32_t)), stream)
+                  : !ws->acc_cl_clean && !clear_acc_cl(acc_cl, (int64_t)(ws->acc_cl.bytes / sizeof(int32_t)), stream))
         return nullptr;
     if (!capturing) ws->acc_cl_clean = false;          // until this call's launches are known to be out
-    return ws->acc_cl_dev;
+    return acc_cl;
 }
 
 // Scratch memory of psb_conv2d_requant_static: the accumulators in which the partial sums of a split tap
@@ -106,12 +111,11 @@ struct psb_weights {
     uint2* tile_dev;         // [K][oc_pad] {threshold, unit}
     uint32_t* live_idx_dev;  // [OC][K]: live taps of each channel first, any order
     uint32_t* live_cnt_dev;  // [OC]
-    shared_workspace* ws;    // shared-filter mode
+    workspace* ws;
 };
 
 namespace {
 
-thread_local int tl_last_device_error = 0;
 // budget values announced by psb_shared_budget_levels for the thread's next shared-filter call with a budget map
 // (n = 0: none, the call reads them back from its maps)
 thread_local int tl_levels_n = 0;
@@ -332,14 +336,12 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
             PSB_HIP_TRY(hipGetLastError());
         }
     } else if (split) {
-        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
-        capturing = status != hipStreamCaptureStatusNone;
+        capturing = is_capturing(stream);
         const size_t bytes = (size_t)p.N * OH * OW * (size_t)p.oc_pad * sizeof(int32_t);
         // Nothing is allocated under capture; the product list needs no scratch and has the same results, so an automatic choice
         // falls back to it, there and when memory is short.
         const bool listable = g_mapping == 0 && p.OC <= 65535;
-        if (!(listable && capturing && q->ws->acc_cl_bytes < bytes)) p.acc_cl = scratch_acc_cl(q->ws, bytes, capturing, stream);
+        if (!(listable && capturing && q->ws->acc_cl.bytes < bytes)) p.acc_cl = scratch_acc_cl(q->ws, bytes, capturing, stream);
         if (!p.acc_cl) {
             if (!listable) return PSB_ERR_ALLOC;
             mapping = 3;
@@ -422,23 +424,13 @@ size_t planes_segment_bytes(const shared_plan& sp)
 
 // The digit-plane buffer of a handle for n_seg segments (allocated on first use, grown when a call has more
 // segments than any before; growing synchronises the stream first: an earlier call may still read the old buffer).
-int ensure_planes(const psb_weights* q, const shared_plan& sp, int n_seg, hipStream_t stream)
+int ensure_planes(const psb_weights* q, const shared_plan& sp, int n_seg, bool capturing, hipStream_t stream)
 {
     // each digit plane is summed in int32: 128 * 128 * (padded reduction length) must stay below 2^31
     if ((int64_t)sp.n_ksteps * 32 * n_seg >= (1ll << 17)) return PSB_ERR_TOO_LARGE;
-    shared_workspace* ws = q->ws;
-    if (ws->planes_segments < n_seg) {
-        if (ws->planes_dev) {
-            PSB_HIP_TRY(hipStreamSynchronize(stream));
-            (void)hipFree(ws->planes_dev);
-            ws->planes_dev = nullptr;
-            ws->planes_segments = 0;
-            ws->ready = false;
-        }
-        if (hipMalloc(&ws->planes_dev, planes_segment_bytes(sp) * n_seg) != hipSuccess) return PSB_ERR_ALLOC;   // written whole by every sampling
-        ws->planes_segments = n_seg;
-    }
-    return PSB_OK;
+    const size_t bytes = planes_segment_bytes(sp) * n_seg;      // written whole by every sampling
+    if (q->ws->planes.bytes < bytes) q->ws->ready = false;
+    return reserve(q->ws, q->ws->planes, bytes, capturing, stream);
 }
 
 // Sorted distinct non-zero levels, clamped to s_max; at most 4 are taken in one launch (more: returns -1).
@@ -466,7 +458,7 @@ int sample_segments(const psb_weights* q, const shared_plan& sp, const int (&lev
     if (need * n_seg > 2147483647ll) return PSB_ERR_TOO_LARGE;
     for (int i = 0; i < n_seg; ++i) {
         psb::FilterJob fj = filter_job(q, i == 0 ? 0 : level[i - 1], level[i], seed, layer_id, nullptr,
-                                       q->ws->planes_dev + planes_segment_bytes(sp) * i, sp.CB, sp.n_ksteps);
+                                       static_cast<int8_t*>(q->ws->planes.ptr) + planes_segment_bytes(sp) * i, sp.CB, sp.n_ksteps);
         fj.n_planes = n_planes;
         if (sp.rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
         batch.jobs[i] = fj;
@@ -513,7 +505,8 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
     if (mfma && !rowpack && g->h == 1 && g->w == 1 && q->shape.cin % 32 == 0 && ((uintptr_t)x & 15u) == 0)
         in_blocked = true;
 
-    shared_workspace* ws = q->ws;
+    workspace* ws = q->ws;
+    const bool capturing = is_capturing(stream);
     const int64_t nw = (int64_t)q->shape.oc * q->K;
     if (!mfma && !ws->w32_dev && hipMalloc(&ws->w32_dev, (size_t)nw * sizeof(int32_t)) != hipSuccess)
         return PSB_ERR_ALLOC;
@@ -545,23 +538,16 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
     const bool fused_segments = round_down && mfma && n_seg > 0 && !budget_from && ksplit == 1 &&
                                 (int64_t)n_ksteps * 32 * n_seg < (1ll << 17);
     if (mfma) {
-        rc = ensure_planes(q, sp, fused_segments ? n_seg : 1, stream);
+        rc = ensure_planes(q, sp, fused_segments ? n_seg : 1, capturing, stream);
         if (rc != PSB_OK) return rc;
     }
     if (round_down && !fused_segments) {
         // This call takes the segments one launch at a time (direct kernel, split reduction, more than four
         // levels): round the map down to the levels first, then it is a map that holds only announced values.
         const size_t need = (size_t)g->n * OH * OW;
-        if (ws->qmap_bytes < need) {
-            if (ws->qmap_dev) {
-                PSB_HIP_TRY(hipStreamSynchronize(stream));
-                (void)hipFree(ws->qmap_dev);
-                ws->qmap_dev = nullptr;
-                ws->qmap_bytes = 0;
-            }
-            if (hipMalloc(&ws->qmap_dev, need) != hipSuccess) return PSB_ERR_ALLOC;
-            ws->qmap_bytes = need;
-        }
+        rc = reserve(ws, ws->qmap, need, capturing, stream);
+        if (rc != PSB_OK) return rc;
+        uint8_t* const qmap = static_cast<uint8_t*>(ws->qmap.ptr);
         uint8_t all[256];
         int n_all = 0;
         {
@@ -575,32 +561,28 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
             for (int i = 0; i < 4; ++i) bl.level[i] = i < n_all ? all[i] : 0;
             const int blocks = (int)std::min<int64_t>(((int64_t)need + 255) / 256, 1024);
             hipLaunchKernelGGL(psb::k_budget_round_down, dim3(blocks), dim3(256), 0, stream, budget_to, (int64_t)need,
-                               q->s_max, bl, ws->qmap_dev);
+                               q->s_max, bl, qmap);
             PSB_HIP_TRY(hipGetLastError());
         } else {
             return PSB_ERR_VALUE;           // more than four levels
         }
-        budget_to = ws->qmap_dev;
+        budget_to = qmap;
         n_announced = n_all;
         std::memcpy(announced, all, (size_t)n_all);
     }
     // blocked channels-last copy (row-packed: one 32-byte block per input row and output column)
     const size_t xt_need = (size_t)g->n * g->h * (rowpack ? OW : g->w) * C_pad;
     if (mfma && xt_need >= (1ull << 31)) return PSB_ERR_TOO_LARGE;      // the kernel addresses it with 32-bit offsets
-    if (mfma && !in_blocked && ws->xt_bytes < xt_need) {
-        if (ws->xt_dev) {
-            PSB_HIP_TRY(hipStreamSynchronize(stream));     // an earlier call may still read the old buffer
-            (void)hipFree(ws->xt_dev);
-            ws->xt_dev = nullptr;
-            ws->xt_bytes = 0;
-        }
-        if (hipMalloc(&ws->xt_dev, xt_need) != hipSuccess) return PSB_ERR_ALLOC;
-        ws->xt_bytes = xt_need;
+    if (mfma && !in_blocked) {
+        rc = reserve(ws, ws->xt, xt_need, capturing, stream);
+        if (rc != PSB_OK) return rc;
     }
+    int8_t* const xt = static_cast<int8_t*>(ws->xt.ptr);
+    int8_t* const planes = static_cast<int8_t*>(ws->planes.ptr);
 
     psb::SharedParams p;
     std::memset(&p, 0, sizeof(p));
-    p.x = x; p.xt = in_blocked ? x : ws->xt_dev; p.planes = ws->planes_dev; p.w32 = ws->w32_dev;
+    p.x = x; p.xt = in_blocked ? x : xt; p.planes = planes; p.w32 = ws->w32_dev;
     p.budget_to = budget_to; p.budget_from = budget_from;
     p.acc = acc; p.y = y; p.mult = mult; p.bias = bias;
     if (rq) p.rq = *rq;
@@ -634,7 +616,7 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
     std::memset(&tj, 0, sizeof(tj));
     int64_t transpose_blocks = 0;
     if (mfma && !in_blocked) {
-        tj.x = x; tj.C = p.C; tj.H = p.H; tj.W = p.W; tj.C_pad = C_pad; tj.xt = ws->xt_dev;
+        tj.x = x; tj.C = p.C; tj.H = p.H; tj.W = p.W; tj.C_pad = C_pad; tj.xt = xt;
         tj.wide = ((int64_t)g->h * g->w) % 4 == 0 && ((uintptr_t)x & 3u) == 0;
         const int per_tile = tj.wide ? psb::kWideTilePositions : 64;
         tj.N = g->n; tj.tiles_p = (int)(((int64_t)g->h * g->w + per_tile - 1) / per_tile); tj.rows = (int64_t)g->n * g->h;
@@ -654,7 +636,7 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         if (filter_blocks + transpose_blocks > 2147483647ll) return PSB_ERR_TOO_LARGE;
         if (filter_blocks + transpose_blocks == 0) return PSB_OK;
         psb::FilterJob fj = filter_job(q, from, to, seed, layer_id, mfma ? nullptr : ws->w32_dev,
-                                       mfma ? ws->planes_dev : nullptr, CB, n_ksteps);
+                                       mfma ? planes : nullptr, CB, n_ksteps);
         fj.n_planes = psb::planes_needed(max_shift, to - from);
         if (rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
         hipLaunchKernelGGL(psb::k_shared_prologue, dim3((unsigned)(filter_blocks + transpose_blocks)), dim3(256), 0,
@@ -689,8 +671,8 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
 
     const int64_t total = npix * p.OC;
     if (!acc && !fused_segments && (p.ksplit > 1 || budget_to)) {      // partial sums meet in the accumulators
-        acc = scratch_acc(ws, (size_t)total * sizeof(int32_t), stream);
-        if (!acc) return PSB_ERR_ALLOC;
+        if (reserve(ws, ws->acc, (size_t)total * sizeof(int32_t), capturing, stream) != PSB_OK) return PSB_ERR_ALLOC;
+        acc = static_cast<int32_t*>(ws->acc.ptr);
         p.acc = acc;
     }
     auto rescale_pass = [&]() -> int {
@@ -878,7 +860,7 @@ int psb_quantize_weights(const float* w_dev, const psb_wshape* shape, int32_t pr
     if (!q) return PSB_ERR_ALLOC;
     std::memset(q, 0, sizeof(*q));
     q->shape = *shape; q->K = (int32_t)K; q->oc_pad = oc_pad;
-    q->ws = new (std::nothrow) shared_workspace;
+    q->ws = new (std::nothrow) workspace;
     if (!q->ws) { delete q; return PSB_ERR_ALLOC; }
     q->prob_bits = prob_bits; q->exp_bits = exp_bits; q->x_absmax = x_absmax; q->s_max = s_max;
 
@@ -990,13 +972,12 @@ void psb_weights_destroy(psb_weights_t* q)
     if (q->live_idx_dev) (void)hipFree(q->live_idx_dev);
     if (q->live_cnt_dev) (void)hipFree(q->live_cnt_dev);
     if (q->ws) {
-        if (q->ws->w32_dev) (void)hipFree(q->ws->w32_dev);
-        if (q->ws->planes_dev) (void)hipFree(q->ws->planes_dev);
-        if (q->ws->xt_dev) (void)hipFree(q->ws->xt_dev);
-        if (q->ws->present_dev) (void)hipFree(q->ws->present_dev);
-        if (q->ws->qmap_dev) (void)hipFree(q->ws->qmap_dev);
-        if (q->ws->acc_dev) (void)hipFree(q->ws->acc_dev);
-        if (q->ws->acc_cl_dev) (void)hipFree(q->ws->acc_cl_dev);
+        workspace* const ws = q->ws;
+        if (ws->w32_dev) (void)hipFree(ws->w32_dev);
+        if (ws->present_dev) (void)hipFree(ws->present_dev);
+        stream_device device{nullptr};
+        for (psb::GrownBuffer* b : {&ws->planes, &ws->qmap, &ws->xt, &ws->acc, &ws->acc_cl}) ws->memory.release(*b, device);
+        ws->memory.release_retired(device);
         delete q->ws;
     }
     delete q;
@@ -1151,6 +1132,7 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
 {
     int dev = 0;
     PSB_HIP_TRY(hipGetDevice(&dev));
+    const bool capturing = is_capturing(stream);
     psb::FilterBatch batch;
     int n_jobs = 0;
     int64_t blocks = 0;
@@ -1177,7 +1159,7 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
         const int n_seg = normalise_levels(levels, n_levels, q->s_max, level);
         if (n_seg <= 0) return PSB_ERR_VALUE;   // no level above 0, or more than four
         if ((int64_t)sp.n_ksteps * 32 * n_seg >= (1ll << 17)) continue;    // the call takes its segments one at a time
-        int rc = ensure_planes(q, sp, n_seg, stream);
+        int rc = ensure_planes(q, sp, n_seg, capturing, stream);
         if (rc != PSB_OK) return rc;
         int longest = 0;
         for (int k = 0; k < n_seg; ++k) longest = std::max(longest, level[k] - (k ? level[k - 1] : 0));
@@ -1190,7 +1172,7 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
                 if (rc != PSB_OK) return rc;
             }
             psb::FilterJob fj = filter_job(q, k ? level[k - 1] : 0, level[k], seeds[i], layer_ids[i], nullptr,
-                                           q->ws->planes_dev + planes_segment_bytes(sp) * k, sp.CB, sp.n_ksteps);
+                                           static_cast<int8_t*>(q->ws->planes.ptr) + planes_segment_bytes(sp) * k, sp.CB, sp.n_ksteps);
             fj.n_planes = n_planes;
             if (sp.rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
             batch.jobs[n_jobs] = fj;

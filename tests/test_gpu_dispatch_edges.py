@@ -126,3 +126,55 @@ def test_shared_levels_in_the_persistent_kernel(psb, orc, oc, k):
     points = np.sort(rng.choice(oc * 262 * 261, 4000, replace=False)).astype(np.int64)
     ref, over, _ = helpers.oracle_layer(orc, L, budget_to=bt.cpu().numpy(), shared=True, points=points)
     assert over == 0 and np.array_equal(acc.cpu().numpy().ravel()[points], ref)
+
+
+@pytest.mark.parametrize("kind", ["split", "split_few_channels", "shared_accumulators", "shared_levels"])
+def test_a_graph_outlives_larger_calls(psb, orc, kind):
+    """Capture a small call, run a larger one on the same handle eagerly - every workspace it uses grows - and replay: the graph's
+    own workspace must still be there.  Memory allocated after the growth must not be written by the replay."""
+    import torch
+    rng = np.random.default_rng(11)
+    cin, oc = (40, 12) if kind == "split_few_channels" else (40, 64)
+    small = synth.Layer("small", synth.he_normal((oc, cin, 3, 3), rng), synth.sparse_relu_int8((1, cin, 9, 7), rng), pad=(1, 1), S=8,
+                        s_max=16, seed=4, layer_id=1, budget_to=None if kind.startswith("split") else
+                        rng.choice([2, 5, 8], size=(1, 9, 7)).astype(np.uint8))
+    shared = not kind.startswith("split")
+    ref, over, _ = helpers.oracle_layer(orc, small, shared=shared)
+    assert over == 0
+    q = helpers.gpu_quantize(psb, small)
+    mult = torch.full((oc,), 0.02 * 2.0 ** q.e_min, device="cuda")
+    kw = dict(pad=(1, 1), seed=4, layer_id=1, mult=mult)
+
+    def run(x, bt, levels):
+        if not shared:
+            return psb.conv2d(q, x, 8, **kw)
+        if kind == "shared_accumulators":
+            psb.shared_budget_levels(levels)
+            return psb.conv2d_requant(q, x, 4.0, budget_to=bt, shared=True, want_acc=False, **kw)
+        return psb.conv2d_shared_budget_requant_blocked(q, x, tuple(x.shape), 4.0, bt, levels, **kw)
+
+    x = torch.from_numpy(small.x).cuda()
+    bt = None if small.budget_to is None else torch.from_numpy(small.budget_to).cuda()
+    big_x = torch.from_numpy(synth.sparse_relu_int8((4, cin, 21, 23), rng)).cuda()
+    big_bt = torch.from_numpy(rng.choice([2, 5, 8, 11], size=(4, 21, 23)).astype(np.uint8)).cuda()
+    if kind == "split_few_channels":
+        psb.set_mapping(psb.MAPPING_CHANNEL_LANE)
+    expect = run(x, bt, (2, 5, 8))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = run(x, bt, (2, 5, 8))
+    for _ in range(2):
+        first = run(big_x, big_bt, (2, 5, 8, 11))
+        torch.cuda.synchronize()
+        canary = [torch.full((1 << 14,), 7, dtype=torch.int32, device="cuda") for _ in range(64)]
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, expect)
+        if not shared:
+            assert np.array_equal(out.cpu().numpy(), ref)
+        assert all(bool((c == 7).all()) for c in canary)
+        assert torch.equal(run(big_x, big_bt, (2, 5, 8, 11)), first)
+    psb.set_mapping(psb.MAPPING_AUTO)
