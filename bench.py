@@ -214,7 +214,8 @@ def prepare(workload, args, torch, psb, dev):
     for L in layers:
         w = torch.from_numpy(L.w).to(dev)
         q = psb.Weights(w, groups=L.groups, x_absmax=L.x_absmax, s_max=L.s_max, prob_bits=args.prob_bits)
-        name = KERNEL_NAMES[psb.query_mapping(q, (L.x.shape[0], L.x.shape[2], L.x.shape[3]) + L.stride + L.pad)]
+        geom = (L.x.shape[0], L.x.shape[2], L.x.shape[3]) + L.stride + L.pad
+        name = KERNEL_NAMES[psb.query_mapping(q, geom, S=L.S, budget_map=L.budget_to is not None)]
         if shared:
             # matrix-core contraction: 3 x 3 / stride 1 / padding 1 layers normally run in k_conv3x3_window (both operands
             # from LDS), the others in k_conv_shared_mfma; the library's timer covers whichever it launched

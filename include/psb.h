@@ -446,10 +446,20 @@ const char* psb_build_id(void);
  * Returns the previous value. */
 int psb_set_mapping(int mapping);
 
-/* The mapping (1, 2 or 3) a layer call with this handle and geometry would run with under the
- * current psb_set_mapping value; negative psb_status on invalid arguments (NULL, SHAPE,
- * TOO_LARGE; SHAPE also when mapping 2 is forced on a grouped layer).  Host only: no device work. */
+/* The mapping (1, 2 or 3) a per-product layer call with this handle and geometry would run with under the
+ * current psb_set_mapping value: a call with S samples everywhere, 1 <= S <= s_max, or one with a budget map
+ * (budget_map not 0; S is not looked at).  Negative psb_status on invalid arguments (NULL, SHAPE, TOO_LARGE, VALUE;
+ * SHAPE also when mapping 2 is forced on a grouped layer).  Host only: no device work.
+ * An automatic choice of 2 that needs scratch memory which cannot be had - no memory left, or the call is
+ * captured on a handle that has served no such call before - runs as 3 instead: psb_last_mapping tells. */
+int psb_query_mapping_call(const psb_weights_t* q, const psb_conv_geom* geom, int32_t S, int32_t budget_map);
+
+/* The same for a call with S = s_max samples everywhere, s_max being the handle's. */
 int psb_query_mapping(const psb_weights_t* q, const psb_conv_geom* geom);
+
+/* The mapping with which the calling thread's last successful per-product layer call was launched (or captured);
+ * 0 before the first. */
+int psb_last_mapping(void);
 
 /* Shared-filter mode, host only (no device work; for tests): the number of 16-byte slots per half plane that the
  * 3 x 3 kernel with both operands in LDS reserves for the input window of one pixel tile (128 * half_tiles consecutive

@@ -121,6 +121,7 @@ namespace {
 thread_local int tl_levels_n = 0;
 thread_local uint8_t tl_levels[256];
 int g_mapping = 0;
+thread_local int tl_last_mapping = 0;        // mapping of the thread's last per-product layer call, 0: none yet
 
 // optional timing of the sampling kernels (psb_profile_enable / psb_profile_read)
 constexpr int kMaxProfilePairs = 4096;
@@ -242,8 +243,9 @@ int resident_workgroups()
     return resident_wgs;
 }
 
-// Which kernel serves this layer under the current mapping switch (1, 2, 3), or a psb_status.
-int pick_mapping(const psb_weights* q, const psb::LayerParams& p)
+// Which kernel serves a call on this layer under the current mapping switch (1, 2, 3), or a psb_status: a call with S samples
+// everywhere, or (budget_map) with a budget per pixel.
+int pick_mapping(const psb_weights* q, const psb::LayerParams& p, int32_t S, bool budget_map)
 {
     int mapping = g_mapping;
     if (mapping == 2 && q->shape.groups != 1) return PSB_ERR_SHAPE;
@@ -259,7 +261,7 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p)
         const int n_cus = std::max(resident_workgroups(), 512) / 2;
         const double pixels = (double)p.N * p.OH * p.OW;
         const int per_block = p.prob_bits <= 7 ? 16 : 4;
-        const int blocks = std::max(1, ((p.budget_to ? p.s_max : std::min(p.S, p.s_max)) + per_block - 1) / per_block);
+        const int blocks = std::max(1, ((budget_map ? p.s_max : std::min(S, p.s_max)) + per_block - 1) / per_block);
         const int passes = (blocks + 3) / 4;
         const double lanes_us = 12.0 + 0.063 / (4 * n_cus) * 0.5 * p.K * pixels * (p.oc_pad / 64) * blocks;
         // workgroups per CU (one or two over a full row do not show: 2.004 measures as 2)
@@ -271,7 +273,7 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p)
         // per-pixel ranges have no tables: twice the instructions
         // (short reductions: a workgroup walks several channels one after the other; 1x1 21->49, 792 pixels, S = 8 27.7:15.1)
         const double chunks = channels * std::ceil((double)q->info.n_live / p.OC / psb::kListTaps);
-        const double list_us = 3.0 + chunks * chunk_us * (p.budget_to ? 2.0 : 1.0);
+        const double list_us = 3.0 + chunks * chunk_us * (budget_map ? 2.0 : 1.0);
         const bool mostly_pruned = 3 * q->info.n_live < (int64_t)q->shape.oc * q->K;
         // (the list's grid holds 65535 channels)
         mapping = psb::oc_lane_supported(p) && ((!mostly_pruned && lanes_us <= list_us) || p.OC > 65535) ? 2 : 3;
@@ -317,7 +319,7 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
     PSB_HIP_TRY(hipGetDevice(&dev));
     if (dev != q->device) return PSB_ERR_DEVICE;
 
-    int mapping = pick_mapping(q, p);
+    int mapping = pick_mapping(q, p, S, budget_to != nullptr);
     if (mapping < 0) return mapping;
     // the channel-lane kernel combines the partial sums of a split tap reduction in scratch accumulators
     bool split = mapping == 2 && psb::oc_lane_chunks(p).n_chunks > 1;
@@ -366,6 +368,7 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
         if (timed) profile_end(stream, slot);
         PSB_HIP_TRY(hipGetLastError());
     }
+    tl_last_mapping = mapping;
     return PSB_OK;
 }
 
@@ -800,13 +803,21 @@ int psb_shared_window_slots(int32_t kh, int32_t kw, const psb_conv_geom* geom, i
 
 int psb_query_mapping(const psb_weights_t* q, const psb_conv_geom* geom)
 {
+    return q && geom ? psb_query_mapping_call(q, geom, q->s_max, 0) : PSB_ERR_NULL;
+}
+
+int psb_last_mapping(void) { return tl_last_mapping; }
+
+int psb_query_mapping_call(const psb_weights_t* q, const psb_conv_geom* geom, int32_t S, int32_t budget_map)
+{
     if (!q || !geom) return PSB_ERR_NULL;
+    if (!budget_map && (S <= 0 || S > q->s_max)) return PSB_ERR_VALUE;
     int32_t OH = 0, OW = 0;
     const int rc = check_geom(&q->shape, geom, &OH, &OW);
     if (rc != PSB_OK) return rc;
     psb::LayerParams p;
     fill_geometry(q, geom, OH, OW, p);
-    return pick_mapping(q, p);
+    return pick_mapping(q, p, S, budget_map != 0);
 }
 
 int psb_profile_enable(int on)

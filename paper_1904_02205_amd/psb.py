@@ -22,7 +22,7 @@ SYMBOLS = ["psb_quantize_weights", "psb_weights_info", "psb_weights_export", "ps
            "psb_conv2d_out_dims", "psb_linear", "psb_conv2d", "psb_conv2d_progressive",
            "psb_sample_filter", "psb_linear_shared", "psb_conv2d_shared", "psb_conv2d_progressive_shared",
            "psb_conv2d_requant", "psb_conv2d_requant_static", "psb_conv2d_shared_requant_blocked", "psb_shared_prepare_filters", "psb_shared_prepare_filters_levels", "psb_conv2d_shared_budget_requant_blocked", "psb_shared_budget_levels", "psb_requantize", "psb_maxpool2d_i8", "psb_maxpool2d_i8_blocked", "psb_global_avgpool_requantize", "psb_budget_resample",
-           "psb_attention_budget", "psb_last_device_error", "psb_build_id", "psb_set_mapping", "psb_query_mapping", "psb_shared_window_slots", "psb_profile_enable",
+           "psb_attention_budget", "psb_last_device_error", "psb_build_id", "psb_set_mapping", "psb_query_mapping", "psb_query_mapping_call", "psb_last_mapping", "psb_shared_window_slots", "psb_profile_enable",
            "psb_profile_read"]
 
 
@@ -105,6 +105,8 @@ def lib():
         L.psb_last_device_error.argtypes = []
         L.psb_set_mapping.argtypes = [C.c_int]
         L.psb_query_mapping.argtypes = [vp, C.POINTER(ConvGeom)]
+        L.psb_query_mapping_call.argtypes = [vp, C.POINTER(ConvGeom), i32, i32]
+        L.psb_last_mapping.argtypes = []
         L.psb_shared_window_slots.argtypes = [i32, i32, C.POINTER(ConvGeom), i32]
         L.psb_profile_enable.argtypes = [C.c_int]
         L.psb_profile_read.argtypes = [C.POINTER(C.c_double), C.POINTER(C.c_int64)]
@@ -165,12 +167,22 @@ def set_mapping(mapping):
     return lib().psb_set_mapping(int(mapping))
 
 
-def query_mapping(q, geom):
-    """Mapping (1, 2, 3) a layer call on handle q with geom = (n, h, w, stride_h, stride_w, pad_h, pad_w) would use."""
-    rc = lib().psb_query_mapping(q._h, C.byref(ConvGeom(*geom)))
+def query_mapping(q, geom, S=None, budget_map=False):
+    """Mapping (1, 2, 3) a per-product call on handle q with geom = (n, h, w, stride_h, stride_w, pad_h, pad_w) would use, with S
+    samples everywhere (default: the handle's s_max) or with a budget map."""
+    g = C.byref(ConvGeom(*geom))
+    if S is None and not budget_map:
+        rc = lib().psb_query_mapping(q._h, g)
+    else:
+        rc = lib().psb_query_mapping_call(q._h, g, 0 if S is None else int(S), 1 if budget_map else 0)
     if rc < 0:
         raise PsbError(rc, "psb_query_mapping")
     return rc
+
+
+def last_mapping():
+    """Mapping this thread's last per-product layer call was launched with, 0 before the first."""
+    return lib().psb_last_mapping()
 
 
 def shared_window_slots(kernel, geom, half_tiles):

@@ -146,6 +146,9 @@ def test_query_mapping_null_arguments(psb):
     g = psb.ConvGeom(1, 8, 8, 1, 1, 1, 1)
     assert L.psb_query_mapping(None, C.byref(g)) == psb.ERR_NULL
     assert L.psb_query_mapping(C.c_void_p(16), None) == psb.ERR_NULL
+    assert L.psb_query_mapping_call(None, C.byref(g), 8, 0) == psb.ERR_NULL
+    assert L.psb_query_mapping_call(C.c_void_p(16), None, 8, 0) == psb.ERR_NULL
+    assert L.psb_last_mapping() == 0
 
 
 def test_mapping_switch(psb):

@@ -32,7 +32,43 @@ def test_automatic_choice(psb, orc, oc, prune, hw, S):
         psb.set_mapping(mapping)
         acc, _ = helpers.gpu_layer(psb, L, q)
         assert over == 0 and np.array_equal(acc, ref), mapping
+        assert psb.last_mapping() == (mapping or psb.query_mapping(q, (1,) + hw + (1, 1, 1, 1), S=S))
     psb.set_mapping(psb.MAPPING_AUTO)
+
+
+def test_query_names_the_kernel_that_was_launched(psb):
+    """The query against what layer calls report, over sample counts and with a budget map; the choice depends on both (few
+    channels on many pixels: lanes for few samples, the list for many).  A call captured on a handle without scratch runs on the
+    list whatever the query says."""
+    import torch
+    rng = np.random.default_rng(12)
+    seen = set()
+    for oc, cin, hw, groups in [(8, 64, (56, 60), 1), (20, 24, (60, 56), 1), (64, 16, (9, 9), 1), (70, 8, (30, 30), 1), (24, 24, (9, 9), 24)]:
+        L = synth.Layer("query", synth.he_normal((oc, cin // groups, 3, 3), rng), synth.sparse_relu_int8((1, cin) + hw, rng), pad=(1, 1),
+                        groups=groups, S=32, s_max=32)
+        q, x = helpers.gpu_quantize(psb, L), torch.from_numpy(L.x).cuda()
+        geom = (1,) + hw + (1, 1, 1, 1)
+        for S in (1, 4, 8, 11, 16, 32):
+            asked = psb.query_mapping(q, geom, S=S)
+            psb.conv2d(q, x, S, pad=(1, 1))
+            assert psb.last_mapping() == asked, (oc, S)
+            seen.add((oc, asked))
+        assert psb.query_mapping(q, geom) == asked                     # S = s_max
+        asked = psb.query_mapping(q, geom, budget_map=True)
+        psb.conv2d_progressive(q, x, torch.full((1,) + hw, 5, dtype=torch.uint8, device="cuda"), None, pad=(1, 1))
+        assert psb.last_mapping() == asked
+    assert (64, psb.MAPPING_CHANNEL_LANE) in seen and (24, psb.MAPPING_PRODUCT_LIST) in seen
+    assert {(8, psb.MAPPING_CHANNEL_LANE), (8, psb.MAPPING_PRODUCT_LIST)} <= seen or {(20, psb.MAPPING_CHANNEL_LANE), (20, psb.MAPPING_PRODUCT_LIST)} <= seen
+    with pytest.raises(psb.PsbError) as ei:
+        psb.query_mapping(q, geom, S=33)
+    assert ei.value.code == psb.ERR_VALUE
+    L = synth.Layer("cold", synth.he_normal((64, 40, 3, 3), rng), synth.sparse_relu_int8((1, 40, 14, 14), rng), pad=(1, 1), S=8, s_max=8)
+    q, x = helpers.gpu_quantize(psb, L), torch.from_numpy(L.x).cuda()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        psb.conv2d(q, x, 8, pad=(1, 1))
+    assert psb.query_mapping(q, (1, 14, 14, 1, 1, 1, 1)) == psb.MAPPING_CHANNEL_LANE and psb.last_mapping() == psb.MAPPING_PRODUCT_LIST
 
 
 @pytest.mark.parametrize("oc,prob_bits,S", [(256, 23, 32), (257, 23, 32), (2, 4, 128), (2, 23, 28)])
