@@ -19,7 +19,8 @@
 // table loads and barriers; 24- and 32-tap chunks (4 and 3 workgroups) measured 10 % slower.  Six and not seven: the
 // round keys of the block kernels then fit vector registers, and the table of (block, pixel) products is laid out so that
 // neighbouring pixels are neighbouring words (pruned 576->160 at 14x14, batch 64, S = 16: 329 -> 311 us, depthwise 3x3 on
-// 576 channels 199 -> 190).  Bound by vector instructions: 53 a generator call for the first of the two, 61 for the
+// 576 channels 199 -> 190).  (Four blocks, and three in the general form, spill one or two registers; keeping some
+// keys scalar instead measures between 2 % slower and 2 % faster.)  Bound by vector instructions: 53 a generator call for the first of the two, 61 for the
 // second, 41 of them the call itself, the rest the list (14 per tap and pixel), its entries (14) and the tables.  One wave
 // per workgroup with a list of its own and no barriers was slower (337 and 247 us): fewer resident waves, and each
 // waits for its own chain of scalar loads, activations and list.
@@ -240,7 +241,11 @@ __global__ void __launch_bounds__(kListPixels, NB > 4 ? 4 : 6) k_layer_product_l
         // sample the products, lanes taking entries round-robin
         const uint32_t total = count;
         if constexpr (HOIST) {
-            constexpr int U = (NB >= 4) ? 1 : 4 / NB;      // entries in flight per lane: four independent calls
+            // Entries in flight per lane.  Six waves per SIMD hide a call's latency, and more calls in flight only cost registers:
+            // four made calls of one and two blocks spill (pruned 576->160, depthwise 3x3 on 576, both batch 64, S = 1: 153 and
+            // 112 us, 148 and 103 with one; S = 4: 149 and 102, 143 and 98).  Two fit where a call is cheapest to count (S = 16 of
+            // 7 bits: 153 and 103 us, one 159 and 105).
+            constexpr int U = P7 && NB == 1 && !MULTI ? 2 : 1;
             auto sample_all = [&](auto whole_c) {          // whole: every block of this pass is drawn to its end
                 constexpr bool WHOLE = decltype(whole_c)::value;
                 const uint32_t nsamp = WHOLE ? (uint32_t)(kPer * NB) : (uint32_t)(s_uniform - kPer * j0);

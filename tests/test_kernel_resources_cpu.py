@@ -1,0 +1,38 @@
+"""Registers of the kernels as hipcc reports them: the ones that are built to stay out of scratch memory do."""
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_1904_02205_amd import build
+
+
+def _resources(tmp_path, header, kernel, instances):
+    """{template arguments: (scratch bytes per lane, spilled vector registers)} of the instances of a kernel that the header's
+    launcher can launch, e.g. "<1, true, false>"; `instances` = how many there have to be at least."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("no hipcc")
+    src = tmp_path / "kernels.hip"
+    src.write_text('#include "%s"\n' % header)
+    flags = [f for f in build.FLAGS if f not in ("-shared", "-Wall")]
+    r = subprocess.run(["hipcc", *flags, "-I", build.HERE + "/csrc", "--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage",
+                        str(src), "-o", "/dev/null"], capture_output=True, text=True, check=True)
+    names = re.findall(r"Function Name: (\S+)", r.stderr)
+    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)]
+    spills = [int(v) for v in re.findall(r"VGPRs Spill: (\d+)", r.stderr)]
+    assert len(names) == len(scratch) == len(spills)
+    found = {}
+    for name, s, v in zip(names, scratch, spills):
+        m = re.match(r"_ZN3psb\d+%sI((?:L[ib]\d+E)+)E" % kernel, name)
+        if m:
+            args = [("false", "true")[int(n)] if t == "b" else n for t, n in re.findall(r"L([ib])(\d+)E", m.group(1))]
+            found["<%s>" % ", ".join(args)] = (s, v)
+    assert len(found) >= instances, names
+    return found
+
+
+def test_product_list_of_one_and_two_blocks_does_not_spill(tmp_path):
+    found = _resources(tmp_path, "psb_kernels_list.hip.h", "k_layer_product_list", 40)
+    few = {k: v for k, v in found.items() if k.startswith(("<1,", "<2,"))}
+    assert len(few) == 16 and set(few.values()) == {(0, 0)}, few
