@@ -904,8 +904,12 @@ __global__ void __launch_bounds__(256, (P == 4 && HT == 2) ? 1 : 2) k_conv_share
 // over pixel tiles, `columns` apart; inside the walk there is no barrier and no staging, the kernel arguments and
 // the rescale factors are read once, and the four waves run independently of each other.  Unsplit, unmasked calls
 // only.  Dynamic LDS: n_steps * P * 1024 bytes per segment of the sample axis.  gridDim.x is a multiple of 8, columns = the grid the plain kernel
-// would get.  HT: half tiles of 32 pixels per wave (a tile of the walk is 128 HT pixels).
-template <int P, int OUT, int HT>
+// would get.  HT: half tiles of 32 pixels per wave (a tile of the walk is 128 HT pixels).  SEG: the call may have
+// segments of the sample axis (p.n_seg > 0).  Calls that write accumulators or rescaled values without segments have a form
+// of their own: the loop over segments costs them 2 to 5 % (1x1 64->256 at 56x56, batch 32: 31.1 us with the loop, 29.4
+// without).  Calls that requantise are better with it (7x7 3->64, stride 2 at 224x224, batch 32: 55.8 us, 56.7 without; four digit
+// planes spill 17 vector registers instead of 150).
+template <int P, int OUT, int HT, bool SEG>
 __global__ void __launch_bounds__(256, HT == 1 ? 4 : 2) k_conv_shared_mfma_resident(const SharedParams p, unsigned columns)
 {
     extern __shared__ v4i a_all[];                 // [n_steps][P][64]
@@ -918,7 +922,7 @@ __global__ void __launch_bounds__(256, HT == 1 ? 4 : 2) k_conv_shared_mfma_resid
     const int ocb = blockIdx.y;
     const int CB = p.C_pad >> 5;
     const int n_steps = p.tKH * p.tKW * CB;
-    const int n_seg = p.n_seg > 0 ? p.n_seg : 1;
+    const int n_seg = SEG && p.n_seg > 0 ? p.n_seg : 1;
     const int seg_words = n_steps * P * 64;
     for (int seg = 0; seg < n_seg; ++seg) {
         const int8_t* wblock = p.planes + (int64_t)seg * (int64_t)p.seg_stride + (int64_t)ocb * p.n_ksteps * (kMaxPlanes * kPlaneStride);
@@ -959,7 +963,7 @@ __global__ void __launch_bounds__(256, HT == 1 ? 4 : 2) k_conv_shared_mfma_resid
         // one pass over the reduction per segment of the sample axis, as in the plain kernel
         for (int seg = 0; seg < n_seg; ++seg) {
             bool lv[2] = {live[0], live[1]};
-            if (p.n_seg > 0) {
+            if (SEG && p.n_seg > 0) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) lv[h] = live[h] && to_[h] >= p.seg_level[seg];
                 if (__ballot(lv[0] || lv[1]) == 0ull) break;     // wave-uniform; levels nest
@@ -1381,12 +1385,17 @@ inline void launch_conv_shared_mfma_resident(const SharedParams& p, int planes, 
                                              hipStream_t stream)
 {
     const dim3 block(256);
-    switch (planes) {
-        case 1: hipLaunchKernelGGL((k_conv_shared_mfma_resident<1, OUT, HT>), grid, block, lds, stream, p, columns); break;
-        case 2: hipLaunchKernelGGL((k_conv_shared_mfma_resident<2, OUT, HT>), grid, block, lds, stream, p, columns); break;
-        case 3: hipLaunchKernelGGL((k_conv_shared_mfma_resident<3, OUT, HT>), grid, block, lds, stream, p, columns); break;
-        default: hipLaunchKernelGGL((k_conv_shared_mfma_resident<4, OUT, HT>), grid, block, lds, stream, p, columns); break;
-    }
+    auto with_seg = [&](auto seg_c) {
+        constexpr bool SEG = decltype(seg_c)::value;
+        switch (planes) {
+            case 1: hipLaunchKernelGGL((k_conv_shared_mfma_resident<1, OUT, HT, SEG>), grid, block, lds, stream, p, columns); break;
+            case 2: hipLaunchKernelGGL((k_conv_shared_mfma_resident<2, OUT, HT, SEG>), grid, block, lds, stream, p, columns); break;
+            case 3: hipLaunchKernelGGL((k_conv_shared_mfma_resident<3, OUT, HT, SEG>), grid, block, lds, stream, p, columns); break;
+            default: hipLaunchKernelGGL((k_conv_shared_mfma_resident<4, OUT, HT, SEG>), grid, block, lds, stream, p, columns); break;
+        }
+    };
+    if (OUT == kOutRequant || p.n_seg > 0) with_seg(std::true_type{});
+    else if constexpr (OUT != kOutRequant) with_seg(std::false_type{});
 }
 
 // Whether k_conv3x3_window can take the call, and in which shape.  slots = the longest window of a pixel tile:

@@ -36,3 +36,11 @@ def test_product_list_of_one_and_two_blocks_does_not_spill(tmp_path):
     found = _resources(tmp_path, "psb_kernels_list.hip.h", "k_layer_product_list", 40)
     few = {k: v for k, v in found.items() if k.startswith(("<1,", "<2,"))}
     assert len(few) == 16 and set(few.values()) == {(0, 0)}, few
+
+
+def test_persistent_shared_kernel_without_segments_does_not_spill(tmp_path):
+    """Calls that write accumulators, one to three digit planes, one and two half tiles, no segments of the sample axis."""
+    found = _resources(tmp_path, "psb_kernels_shared.hip.h", "k_conv_shared_mfma_resident", 24)
+    for planes in (1, 2, 3):
+        for half_tiles in (1, 2):
+            assert found["<%d, 1, %d, false>" % (planes, half_tiles)] == (0, 0)
