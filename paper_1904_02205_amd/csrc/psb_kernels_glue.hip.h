@@ -8,6 +8,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <type_traits>
+
 #include "psb_kernels.hip.h"
 
 namespace psb {
@@ -208,31 +211,31 @@ __global__ void __launch_bounds__(256) k_budget_resample(const uint8_t* __restri
 //     h = sum_c -p_c log p_c = log Z - (sum_c e_c z_c) / Z,   z_c = a_c*step - max_c, e_c = exp(z_c), Z = sum_c e_c.
 // Evaluated in binary64 and rounded once to binary32: sums of hundreds of binary32 terms would lose the digits the
 // threshold needs.  a_c - max is one of 256 integers, so the exponentials come from a table of 256 that a workgroup
-// computes once; it works on 4 consecutive pixels, 64 threads per pixel, each taking every 64th channel, and adds the
-// threads' sums in a fixed order.  (One lane per pixel and one exp per
-// activation took 170 us for 784 pixels x 512 channels: four workgroups, 512 exponentials after each other.)
-constexpr int kEntropyPixels = 4, kEntropySlices = 64;
+// computes once; it works on PX consecutive pixels, 256 / PX threads per pixel, each taking every (256 / PX)th channel, and adds
+// the threads' sums in a fixed order.
+template <int PX>
 __global__ void __launch_bounds__(256) k_channel_entropy(const int8_t* __restrict__ act, float step, int N, int C,
                                                          int64_t HW, float* __restrict__ entropy)
 {
+    constexpr int kSlices = 256 / PX;
     __shared__ double tab[256];                                   // exp(-d * step)
-    __shared__ double part_z[kEntropySlices][kEntropyPixels], part_t[kEntropySlices][kEntropyPixels];
-    __shared__ int part_max[kEntropySlices][kEntropyPixels];
+    __shared__ double part_z[kSlices][PX], part_t[kSlices][PX];
+    __shared__ int part_max[kSlices][PX];
     tab[threadIdx.x] = exp(-(double)(int)threadIdx.x * (double)step);
     const int64_t total = (int64_t)N * HW;
-    const int px = threadIdx.x % kEntropyPixels, slice = threadIdx.x / kEntropyPixels;
-    for (int64_t i0 = (int64_t)blockIdx.x * kEntropyPixels; i0 < total; i0 += (int64_t)gridDim.x * kEntropyPixels) {   // uniform
+    const int px = threadIdx.x % PX, slice = threadIdx.x / PX;
+    for (int64_t i0 = (int64_t)blockIdx.x * PX; i0 < total; i0 += (int64_t)gridDim.x * PX) {   // uniform
         const int64_t i = min(i0 + px, total - 1);
         const int64_t n = i / HW;
         const int8_t* src = act + n * C * HW + (i - n * HW);
         int amax = -128;
-        for (int c = slice; c < C; c += kEntropySlices) amax = max(amax, (int)src[(int64_t)c * HW]);
+        for (int c = slice; c < C; c += kSlices) amax = max(amax, (int)src[(int64_t)c * HW]);
         part_max[slice][px] = amax;
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kEntropySlices; ++k) amax = max(amax, part_max[k][px]);
+        for (int k = 0; k < kSlices; ++k) amax = max(amax, part_max[k][px]);
         double Z = 0.0, T = 0.0;
-        for (int c = slice; c < C; c += kEntropySlices) {
+        for (int c = slice; c < C; c += kSlices) {
             const int d = amax - (int)src[(int64_t)c * HW];           // 0..255
             const double e = tab[d];
             Z += e;
@@ -244,10 +247,38 @@ __global__ void __launch_bounds__(256) k_channel_entropy(const int8_t* __restric
         if (slice == 0 && i0 + px < total) {
             Z = T = 0.0;
 #pragma unroll
-            for (int k = 0; k < kEntropySlices; ++k) { Z += part_z[k][px]; T += part_t[k][px]; }
+            for (int k = 0; k < kSlices; ++k) { Z += part_z[k][px]; T += part_t[k][px]; }
             entropy[i] = (float)(log(Z) - T / Z);
         }
         __syncthreads();                                          // the partial sums are rewritten by the next pixels
+    }
+}
+
+// Pixels per workgroup (PX): few where there are few pixels, so that every CU has a workgroup and a thread few channels; many
+// where there are many, so that a workgroup has few barriers per pixel and reads whole lines.  The form with the least estimated
+// time: a workgroup takes 3 us plus 0.3 us per channel of a thread for PX pixels, and eight share a CU.  Call with the mask, us, PX = 4 /
+// 16 / 64 / 256 (16.6 is the two launches): 784 pixels x 512 channels 17 / 17 / 35 / 107; 3136 x 2048 28 / 83 / 128 / 473; 100352 x 64
+// 66 / 22 / 16 / 24; 401408 x 16 172 / 51 / 31 / 28.  (One lane per pixel and one exp per activation: 131, 597, 27 and 33.)
+inline void launch_channel_entropy(const int8_t* act, float step, int N, int C, int64_t HW, float* entropy, int n_cus, hipStream_t stream)
+{
+    const int64_t total = (int64_t)N * HW, resident = (int64_t)8 * n_cus;
+    int px = 0;
+    double best = 0.0;
+    for (int candidate = 4; candidate <= 256; candidate *= 4) {
+        const double rounds = (double)((total + candidate * resident - 1) / (candidate * resident));
+        const double us = rounds * (3.0 + 0.3 * (double)(((int64_t)C * candidate + 255) / 256));
+        if (px == 0 || us < best) { px = candidate; best = us; }
+    }
+    auto launch = [&](auto px_c) {
+        constexpr int PX = decltype(px_c)::value;
+        const int blocks = (int)std::min<int64_t>((total + PX - 1) / PX, resident);
+        hipLaunchKernelGGL(k_channel_entropy<PX>, dim3(blocks), dim3(256), 0, stream, act, step, N, C, HW, entropy);
+    };
+    switch (px) {
+        case 4: launch(std::integral_constant<int, 4>{}); break;
+        case 16: launch(std::integral_constant<int, 16>{}); break;
+        case 64: launch(std::integral_constant<int, 64>{}); break;
+        default: launch(std::integral_constant<int, 256>{}); break;
     }
 }
 

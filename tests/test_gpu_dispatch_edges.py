@@ -110,10 +110,11 @@ def test_split_reduction_in_a_graph(psb, orc, warm):
         assert over == 0 and np.array_equal(acc.cpu().numpy(), ref), eager
 
 
-@pytest.mark.parametrize("n,c,h,w", [(1, 1, 1, 1), (2, 15, 3, 5), (1, 17, 4, 4), (3, 40, 7, 7), (1, 512, 1, 17)])
+@pytest.mark.parametrize("n,c,h,w", [(1, 1, 1, 1), (2, 15, 3, 5), (1, 17, 4, 4), (3, 40, 7, 7), (1, 512, 1, 17),
+                                     (1, 20, 91, 97), (1, 5, 190, 181), (2, 2, 263, 251)])
 def test_channel_entropy_remainders(psb, orc, n, c, h, w):
-    """Fewer channels than lanes per pixel, pixels that leave a last tile in part; the whole range of activations.  Both sides
-    evaluate in binary64 and round once, so at most one binary32 ulp apart; the mask may differ only at its threshold."""
+    """Fewer channels than lanes per pixel, pixels that leave a last tile in part, 4, 16, 64 and 256 pixels a workgroup; the whole range of
+    activations.  Both sides evaluate in binary64 and round once, so at most one binary32 ulp apart; the mask may differ only at its threshold."""
     import torch
     rng = np.random.default_rng(c)
     act = rng.integers(-128, 128, size=(n, c, h, w)).astype(np.int8)
