@@ -356,7 +356,7 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
         if (rc != 0) { tl_last_device_error = rc; return PSB_ERR_DEVICE; }
         if (split && !use_static_scratch && !capturing) q->ws->acc_cl_clean = true;
     } else if (mapping == 3) {
-        rc = psb::launch_product_list(p, std::max(resident_workgroups(), 512) / 2, q->live_idx_dev, q->live_cnt_dev, stream, profile_begin, profile_end);
+        rc = psb::launch_product_list(p, q->live_idx_dev, q->live_cnt_dev, stream, profile_begin, profile_end);
         if (rc != 0) { tl_last_device_error = rc; return PSB_ERR_DEVICE; }
     } else {
         const int64_t npix = (int64_t)p.N * OH * OW;

@@ -9,9 +9,9 @@
 // LDS (ds_add, exact in any order).  Every lane therefore always has a product to work on, whatever the
 // sparsity pattern.  Output index and tap differ per lane, so the parts of the first three generator
 // rounds that depend on only one of the two cannot stay in registers; for calls with the same S everywhere
-// they are kept in two LDS tables instead, for up to four generator blocks at a time - one row per pixel, one per
+// they are kept in two LDS tables instead, for up to eight generator blocks at a time - one row per pixel, one per
 // tap of the chunk - and a call costs 15 wide multiplies as in the channel-lane kernel; a call of more blocks
-// goes over its taps once per four of them, and calls with per-pixel ranges run the whole generator per
+// goes over its taps once per eight of them, and calls with per-pixel ranges run the whole generator per
 // entry (19 multiplies).  No global atomics, no zero-fill: the accumulators leave
 // LDS once, with the fp32 epilogue fused.
 // The chunk is short on purpose: the list is the largest LDS array, and with 10 taps (23 KB per workgroup
@@ -67,14 +67,14 @@ __global__ void __launch_bounds__(256) k_live_index(const uint32_t* __restrict__
     if (threadIdx.x == 0) live_cnt[oc] = count;
 }
 
-// NB > 0: a call with the same S everywhere, NB (1..4, 8) generator blocks at a time.  MULTI: it takes more than one such pass
+// NB > 0: a call with the same S everywhere, NB (1..8) generator blocks at a time.  MULTI: it takes more than one such pass
 //         over the taps, or draws its last block in part; otherwise blocks 0 .. NB - 1 are all there is, and whole (the
 //         general form costs that call 7 % on depthwise 3 x 3 layers, whose tables are rebuilt for every nine taps).
 // NB = 0: per-pixel ranges [from, to), any values.
 // P7: 7-bit uniforms, 16 samples per block; otherwise 32-bit uniforms, 4 per block.
 // INSIDE: every tap of every output pixel lies inside the image (1 x 1 layers, unpadded layers): no bounds checks.
 template <int NB, bool P7, bool INSIDE, bool MULTI>
-__global__ void __launch_bounds__(kListPixels, NB > 4 ? 4 : 6) k_layer_product_list(const LayerParams p,
+__global__ void __launch_bounds__(kListPixels, NB > 6 ? 5 : NB > 4 ? 4 : 6) k_layer_product_list(const LayerParams p,
                                                                     const uint32_t* __restrict__ live_idx,
                                                                     const uint32_t* __restrict__ live_cnt,
                                                                     int channels_per_wg)
@@ -323,7 +323,7 @@ __global__ void __launch_bounds__(kListPixels, NB > 4 ? 4 : 6) k_layer_product_l
 inline int list_channels_per_wg(int K) { return std::min(8, std::max(1, 64 / std::max(1, K))); }
 
 // Returns 0 or a hipError_t.
-inline int launch_product_list(const LayerParams& p, int n_cus, const uint32_t* live_idx, const uint32_t* live_cnt,
+inline int launch_product_list(const LayerParams& p, const uint32_t* live_idx, const uint32_t* live_cnt,
                                hipStream_t stream, bool (*prof_begin)(hipStream_t, int*),
                                void (*prof_end)(hipStream_t, int))
 {
@@ -333,20 +333,19 @@ inline int launch_product_list(const LayerParams& p, int n_cus, const uint32_t* 
     const int gy = (p.OC + channels_per_wg - 1) / channels_per_wg;
     if (gx > 2147483647ll || gy > 65535) return (int)hipErrorInvalidValue;
     const dim3 grid((unsigned)gx, (unsigned)gy), block(kListPixels);
-    // Uniform S: the blocks of a call in as many passes of up to four as it takes, cut as evenly as possible (five blocks: three
-    // and two; a pass of three costs what it samples, not what it could).
+    // Uniform S: the blocks of a call in as many passes of up to eight as it takes, cut as evenly as possible (ten blocks: twice
+    // five; a pass costs what it samples, not what it could).  A pass builds the lists again, which is most of its time where few
+    // activations are left: with at most four blocks a pass, depthwise 3x3 on 576 channels at batch 64, S = 32, took 189 / 378 / 629 us
+    // for 10 / 50 / 100 % of the activations not zero, with eight 128 / 316 / 560 (S = 20: 168 / 295 / 460, 103 / 221 / 373).  The tables
+    // of eight blocks leave five workgroups a CU instead of six.
     const bool p7 = p.prob_bits <= 7;
     const int per_block = p7 ? 16 : 4;
     int nb = 0;
     bool multi = false;
     if (!p.budget_to) {
-        const int blocks = std::max(1, (std::min(p.S, p.s_max) + per_block - 1) / per_block), passes = (blocks + 3) / 4;
+        const int blocks = std::max(1, (std::min(p.S, p.s_max) + per_block - 1) / per_block), passes = (blocks + 7) / 8;
         nb = (blocks + passes - 1) / passes;
         multi = std::min(p.S, p.s_max) != nb * per_block;
-        // Eight whole blocks and no more than a workgroup per CU: all in one pass, which walks the taps - a chain of
-        // latencies that nothing else on the CU hides - once (576 taps, S = 32, 152 workgroups: 364 us against 481 in two
-        // passes).  With more workgroups two passes and their smaller tables are as fast.
-        if (blocks == 8 && gx * gy <= n_cus && std::min(p.S, p.s_max) == 8 * per_block) { nb = 8; multi = false; }
     }
     int slot = 0;
     const bool timed = prof_begin(stream, &slot);
@@ -365,12 +364,15 @@ inline int launch_product_list(const LayerParams& p, int n_cus, const uint32_t* 
             case 1: with_inside(std::integral_constant<int, 1>{}, p7_c, multi_c); break;
             case 2: with_inside(std::integral_constant<int, 2>{}, p7_c, multi_c); break;
             case 3: with_inside(std::integral_constant<int, 3>{}, p7_c, multi_c); break;
-            default: with_inside(std::integral_constant<int, 4>{}, p7_c, multi_c); break;
+            case 4: with_inside(std::integral_constant<int, 4>{}, p7_c, multi_c); break;
+            case 5: with_inside(std::integral_constant<int, 5>{}, p7_c, multi_c); break;
+            case 6: with_inside(std::integral_constant<int, 6>{}, p7_c, multi_c); break;
+            case 7: with_inside(std::integral_constant<int, 7>{}, p7_c, multi_c); break;
+            default: with_inside(std::integral_constant<int, 8>{}, p7_c, multi_c); break;
         }
     };
     auto with_p7 = [&](auto p7_c) {
         if (nb == 0) with_inside(std::integral_constant<int, 0>{}, p7_c, std::false_type{});
-        else if (nb == 8) with_inside(std::integral_constant<int, 8>{}, p7_c, std::false_type{});
         else if (multi) with_nb(p7_c, std::true_type{});
         else with_nb(p7_c, std::false_type{});
     };

@@ -71,9 +71,9 @@ def test_query_names_the_kernel_that_was_launched(psb):
     assert psb.query_mapping(q, (1, 14, 14, 1, 1, 1, 1)) == psb.MAPPING_CHANNEL_LANE and psb.last_mapping() == psb.MAPPING_PRODUCT_LIST
 
 
-@pytest.mark.parametrize("oc,prob_bits,S", [(256, 23, 32), (257, 23, 32), (2, 4, 128), (2, 23, 28)])
+@pytest.mark.parametrize("oc,prob_bits,S", [(256, 23, 32), (257, 23, 32), (2, 4, 128), (2, 23, 28), (2, 23, 58), (2, 4, 200)])
 def test_product_list_eight_blocks(psb, orc, oc, prob_bits, S):
-    """Eight generator blocks in one pass (as many workgroups as CUs) and in two (one more), seven in two."""
+    """Eight generator blocks in one pass and seven; fifteen in two passes, the last one drawn in part, and thirteen of 7 bits."""
     rng = np.random.default_rng(S)
     L = synth.Layer("blocks", synth.he_normal((oc, 8, 3, 3), rng), synth.sparse_relu_int8((1, 8, 4, 5), rng), pad=(1, 1), S=S, s_max=S,
                     seed=4, layer_id=1)

@@ -32,7 +32,7 @@ def test_every_sample_count(psb, orc, prob_bits, mapping):
     L = _layer()
     qo, qg = helpers.oracle_quantize(orc, L, prob_bits=prob_bits), helpers.gpu_quantize(psb, L, prob_bits=prob_bits)
     psb.set_mapping(mapping)
-    for S in list(range(1, 25)) + [31, 32, 33, 40]:
+    for S in list(range(1, 25)) + [26, 28, 31, 32, 33, 36, 37, 40]:
         ref, over, _ = helpers.oracle_layer(orc, L, qo, S=S)
         acc, _ = helpers.gpu_layer(psb, L, qg, S=S)
         assert over == 0 and np.array_equal(acc, ref), S

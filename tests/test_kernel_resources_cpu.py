@@ -33,7 +33,7 @@ def _resources(tmp_path, header, kernel, instances):
 
 
 def test_product_list_of_one_and_two_blocks_does_not_spill(tmp_path):
-    found = _resources(tmp_path, "psb_kernels_list.hip.h", "k_layer_product_list", 40)
+    found = _resources(tmp_path, "psb_kernels_list.hip.h", "k_layer_product_list", 68)
     few = {k: v for k, v in found.items() if k.startswith(("<1,", "<2,"))}
     assert len(few) == 16 and set(few.values()) == {(0, 0)}, few
 
