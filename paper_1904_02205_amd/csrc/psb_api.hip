@@ -258,7 +258,7 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p, int32_t S, boo
         // images, the list few channels on many pixels and pruned weights.  3x3 on 64 channels, list : lanes, us:
         // 8 channels, 4704 pixels, S = 8 / 16 / 32 184:175 / 240:335 / 400:653, 784 pixels 183:38 / 236:69 / 400:128;
         // 17 channels, 4704 pixels, S = 16 315:338; 100 channels 884:645; 37->70, 5x5, 324 pixels, S = 10 504:71.
-        const int n_cus = std::max(resident_workgroups(), 512) / 2;
+        const int n_cus = psb::oc_lane_cus();
         const double pixels = (double)p.N * p.OH * p.OW;
         const int per_block = p.prob_bits <= 7 ? 16 : 4;
         const int blocks = std::max(1, ((budget_map ? p.s_max : std::min(S, p.s_max)) + per_block - 1) / per_block);
