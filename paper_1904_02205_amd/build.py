@@ -17,6 +17,7 @@ DEPS = [SRC,
         os.path.join(HERE, "csrc", "psb_kernels_glue.hip.h"),
         os.path.join(HERE, "csrc", "psb_philox.hip.h"),
         os.path.join(HERE, "csrc", "psb_workspace.h"),
+        os.path.join(HERE, "csrc", "psb_choice.h"),
         os.path.join(os.path.dirname(HERE), "include", "psb.h")]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

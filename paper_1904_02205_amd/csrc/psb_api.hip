@@ -16,6 +16,7 @@
 #include "psb_kernels_list.hip.h"
 #include "psb_kernels_shared.hip.h"
 #include "psb_kernels_glue.hip.h"
+#include "psb_choice.h"
 #include "psb_workspace.h"
 
 // Device memory that a handle's calls work in; allocated on first use, grown on demand, owned by the handle.
@@ -250,33 +251,21 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p, int32_t S, boo
     int mapping = g_mapping;
     if (mapping == 2 && q->shape.groups != 1) return PSB_ERR_SHAPE;
     if (mapping == 0) {
-        // Time of either kernel in us, from its measured parts (half of the activations zero: that scales both alike).
-        // Channel lanes: a generator call of a wave is 63 ns and they make one for every (tap, channel lane, block), live or
-        // not, on four SIMDs per CU; two launches.  Product list: a workgroup (256 pixels of a channel) walks the live taps
-        // ten at a time, at 2.3 us + 0.45 us per block alone on its CU (a chain of latencies: table, gather, compaction,
-        // barriers) and 0.37 us + 0.30 us more for each further one.  Lanes win dense layers of many channels and small
-        // images, the list few channels on many pixels and pruned weights.  3x3 on 64 channels, list : lanes, us:
-        // 8 channels, 4704 pixels, S = 8 / 16 / 32 184:175 / 240:335 / 400:653, 784 pixels 183:38 / 236:69 / 400:128;
-        // 17 channels, 4704 pixels, S = 16 315:338; 100 channels 884:645; 37->70, 5x5, 324 pixels, S = 10 504:71.
-        const int n_cus = psb::oc_lane_cus();
-        const double pixels = (double)p.N * p.OH * p.OW;
         const int per_block = p.prob_bits <= 7 ? 16 : 4;
-        const int blocks = std::max(1, ((budget_map ? p.s_max : std::min(S, p.s_max)) + per_block - 1) / per_block);
-        const int passes = (blocks + 3) / 4;
-        const double lanes_us = 12.0 + 0.063 / (4 * n_cus) * 0.5 * p.K * pixels * (p.oc_pad / 64) * blocks;
-        // workgroups per CU (one or two over a full row do not show: 2.004 measures as 2)
-        const int channels = psb::list_channels_per_wg(p.K);
-        const double list_wgs = std::ceil(pixels / psb::kListPixels) * ((p.OC + channels - 1) / channels);
-        const double rows = std::max(1.0, std::ceil(list_wgs / n_cus - 0.25));
-        const double b = (double)blocks / passes;
-        const double chunk_us = passes * (2.3 + 0.45 * b + (rows - 1.0) * (0.37 + 0.30 * b));
-        // per-pixel ranges have no tables: twice the instructions
-        // (short reductions: a workgroup walks several channels one after the other; 1x1 21->49, 792 pixels, S = 8 27.7:15.1)
-        const double chunks = channels * std::ceil((double)q->info.n_live / p.OC / psb::kListTaps);
-        const double list_us = 3.0 + chunks * chunk_us * (budget_map ? 2.0 : 1.0);
+        const int samples = budget_map ? p.s_max : std::min(S, p.s_max);
+        const psb::OcChunks chunks = psb::oc_lane_chunks(p, budget_map);
+        psb::LayerWork work;
+        work.K = p.K; work.OC = p.OC; work.n_live = q->info.n_live;
+        work.pixels = (double)p.N * p.OH * p.OW;
+        work.blocks = std::max(1, (samples + per_block - 1) / per_block);
+        work.budget_map = budget_map;
+        work.lane_chunks = chunks.n_chunks; work.lane_taps = chunks.kc;
+        work.list_channels = psb::list_channels_per_wg(p.K);
+        work.list_pixels = psb::kListPixels; work.list_taps = psb::kListTaps;
         const bool mostly_pruned = 3 * q->info.n_live < (int64_t)q->shape.oc * q->K;
         // (the list's grid holds 65535 channels)
-        mapping = psb::oc_lane_supported(p) && ((!mostly_pruned && lanes_us <= list_us) || p.OC > 65535) ? 2 : 3;
+        const bool lanes = (!mostly_pruned && psb::prefer_channel_lanes(work, psb::oc_lane_cus())) || p.OC > 65535;
+        mapping = lanes && psb::oc_lane_supported(p) ? 2 : 3;
     }
     return mapping;
 }
@@ -322,7 +311,7 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
     int mapping = pick_mapping(q, p, S, budget_to != nullptr);
     if (mapping < 0) return mapping;
     // the channel-lane kernel combines the partial sums of a split tap reduction in scratch accumulators
-    bool split = mapping == 2 && psb::oc_lane_chunks(p).n_chunks > 1;
+    bool split = mapping == 2 && psb::oc_lane_chunks(p, budget_to != nullptr).n_chunks > 1;
     bool capturing = false;
     if (use_static_scratch) {           // the accumulators lie in the static array: nothing is allocated
         uint32_t* base = nullptr;

@@ -526,7 +526,7 @@ constexpr int kOcWavesPerCu = 32;
 // and 32 taps are better up to 32 tickets per wave (128->128 at 28x28, budgets 2..32, 28 of them: 898 -> 854 us).
 // With more than one chunk the partial sums meet in LayerParams::acc_cl, which the caller provides.
 struct OcChunks { int n_chunks, kc; };
-inline OcChunks oc_lane_chunks(const LayerParams& p)
+inline OcChunks oc_lane_chunks(const LayerParams& p, bool budget_map)
 {
     int max_taps = oc_tuning().max_taps;
     const int64_t n_ocb = p.oc_pad / 64;
@@ -537,7 +537,7 @@ inline OcChunks oc_lane_chunks(const LayerParams& p)
         c.kc = (p.K + c.n_chunks - 1) / c.n_chunks;
         c.n_chunks = (p.K + c.kc - 1) / c.kc;
         const int64_t waves = (int64_t)oc_lane_cus() * kOcWavesPerCu;
-        const int64_t want = p.budget_to && max_taps > 32 ? 32 * waves : waves;
+        const int64_t want = budget_map && max_taps > 32 ? 32 * waves : waves;
         if (npix * c.n_chunks * n_ocb >= want || max_taps <= 16) break;
         max_taps /= 2;
     }
@@ -560,7 +560,7 @@ inline int launch_oc_lane(const LayerParams& p, hipStream_t stream, ProfileBegin
     }
     const int n_ocb = p.oc_pad / 64;
     const int64_t npix = (int64_t)p.N * p.OH * p.OW;
-    const OcChunks chunks = oc_lane_chunks(p);
+    const OcChunks chunks = oc_lane_chunks(p, p.budget_to != nullptr);
     const int n_chunks = chunks.n_chunks;
     if (n_chunks > 1 && !p.acc_cl) return (int)hipErrorInvalidValue;
     const int64_t waves = (int64_t)oc_lane_cus() * kOcWavesPerCu;
