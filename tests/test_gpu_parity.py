@@ -270,11 +270,9 @@ def test_progressive_constant_map_equals_plain_call(psb):
     assert np.array_equal(plain, prog)
 
 
-def test_several_pixels_per_wave_and_ticket(psb, orc):
-    """Large layers hand a wave several pixels per ticket; here the count is forced (benchmark override of the
-    channel-lane launcher) on layers small enough for the oracle, with pixel counts that leave a ragged last group:
-    the kernel variants for a fixed number of generator blocks, 7-bit uniforms, and per-pixel budgets."""
-    import os
+def _several_pixels_per_ticket(psb, orc):
+    """The kernel variants for a fixed number of generator blocks, 7-bit uniforms, and per-pixel budgets, with pixel counts that
+    leave a ragged last group."""
     rng = np.random.default_rng(260)
     cases = [(_layer(rng, 3, 20, 70, (9, 11), 3, pad=1, S=8), 23, False),           # 297 pixels, 3 chunks, 2 channel blocks
              (_layer(rng, 1, 24, 64, (7, 9), 1, S=16), 23, False),                    # single chunk: fused epilogue
@@ -289,13 +287,26 @@ def test_several_pixels_per_wave_and_ticket(psb, orc):
             qg = helpers.gpu_quantize(psb, L, prob_bits=prob_bits)
             ref, over, _ = helpers.oracle_layer(orc, L, qo, budget_to=to)
             assert over == 0
-            for ppw in (1, 2, 3, 5, 64):
-                os.environ["PSB_OC_PPW"] = str(ppw)
-                acc, _ = helpers.gpu_layer(psb, L, qg, budget_to=to)
-                assert np.array_equal(acc, ref), (L.name, prob_bits, ppw)
+            acc, _ = helpers.gpu_layer(psb, L, qg, budget_to=to)
+            assert np.array_equal(acc, ref), (L.name, prob_bits)
     finally:
-        os.environ.pop("PSB_OC_PPW", None)
         psb.set_mapping(psb.MAPPING_AUTO)
+
+
+@pytest.mark.parametrize("ppw", [1, 2, 5, 64])
+def test_several_pixels_per_wave_and_ticket(psb, orc, ppw):
+    """Calls of more than 2^31 tickets hand a wave several pixels per ticket; here the count is forced (benchmark override of the
+    channel-lane launcher, which a process reads once: so each count has a process of its own)."""
+    import os
+    import subprocess
+    import sys
+    if ppw == 1:
+        return _several_pixels_per_ticket(psb, orc)
+    tests = os.path.dirname(os.path.abspath(__file__))
+    program = ("import sys; sys.path[:0] = [%r, %r]\nimport test_gpu_parity as t\nfrom paper_1904_02205_amd import psb\n"
+               "from oracle import binding as orc\nt._several_pixels_per_ticket(psb, orc)\nprint('equal')" % (tests, os.path.dirname(tests)))
+    r = subprocess.run([sys.executable, "-c", program], env=dict(os.environ, PSB_OC_PPW=str(ppw)), capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.endswith("equal\n"), r.stderr[-2000:]
 
 
 # ------------------------------------------------------------------ fp32 rescale
