@@ -68,6 +68,7 @@ static int reserve(workspace* ws, psb::GrownBuffer& b, size_t bytes, bool captur
 
 static bool is_capturing(hipStream_t stream)
 {
+    if (!stream) return false;                  // the legacy default stream cannot be captured
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
     return status != hipStreamCaptureStatusNone;
