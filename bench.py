@@ -22,7 +22,7 @@ roofline  bound "alu": the sampling kernel is limited by integer VALU issue.  Un
         call (4 samples) 15 wide multiplies, 14 three-input xors (v_bitop3_b32 on vector registers: 2.45 cycles, one
         unit) and 3 two-input ones, 4 compares and 4 carry-adds = 63 units; per product a 24-bit multiply and multiply-add = 4 units; and only for products
         that need sampling (live weight, tap inside the image, activation != 0).  With --prob-bits 1..7 a
-        generator call serves 16 samples and its counting is 4 x (or, subtract, and, bit count) + 1 = 17 units
+        generator call serves 16 samples and its counting is 4 x (complement and mask, add, mask, bit count) + 1 = 17 units
         instead of 16: 64 units per call.  The kernel time is measured live: the library brackets every sampling
         kernel with HIP events on the stream it launches on.
         `traffic`: HBM bytes per launch of the sampling kernel from the rocprofv3 counter summary that is tracked

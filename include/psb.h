@@ -305,12 +305,13 @@ int psb_conv2d_requant(const psb_weights_t* q, const int8_t* x_dev, const psb_co
  * loops, harnesses that forbid hipMalloc.  It is psb_conv2d_requant with acc_dev = NULL and shared = 0 (per-product
  * mode, requantised activations and/or rescaled values out, no accumulators handed out), element for element, but
  * the scratch memory of its kernels - the accumulators in which the partial sums of a split tap reduction meet -
- * is a fixed array inside the library's device code instead of memory owned by the handle.  The call issues no hipMalloc, no hipFree and no synchronisation.
+ * is a fixed array inside the library's device code instead of memory owned by the handle.  The call issues no
+ * hipMalloc, no hipFree and no synchronisation.
  *  - Limit: n * OH * OW * (oc rounded up to a multiple of 64) <= PSB_STATIC_MAX_OUTPUTS (the array holds that many
  *    int32 accumulators, 32 MiB; each GPU the library runs on holds it until the process ends).
  *    Larger calls return TOO_LARGE and launch nothing.
- *  - All calls on one GPU share that GPU's array, and it keeps the last call's contents; the call clears what it
- *    needs (in a kernel, not a memset, so it can be captured).  Two such calls that overlap in time on one GPU -
+ *  - All calls on one GPU share that GPU's array, and a call clears the part it
+ *    needs before it starts (in a kernel, not a memset, so it can be captured).  Two such calls that overlap in time on one GPU -
  *    different streams without ordering - race on it; same-stream calls are ordered and safe.
  *  - The array's device address is looked up once per GPU, by psb_quantize_weights (any handle of that GPU), which
  *    therefore has to have run outside the capture - it allocates and synchronises anyway.

@@ -96,8 +96,9 @@ int32_t* scratch_acc_cl(workspace* ws, size_t bytes, bool capturing, hipStream_t
     return acc_cl;
 }
 
-// Scratch memory of psb_conv2d_requant_static: the accumulators in which the partial sums of a split tap
-// reduction meet.  A file-scope device array, so that the entry point never allocates; every GPU the library runs on holds its own copy at its own address until the process ends.  Host code never uses the array's name as an address: the per-device pointer
+// Scratch memory of psb_conv2d_requant_static: the accumulators in which the partial sums of a split tap reduction meet.  A
+// file-scope device array, so that the entry point never allocates; every GPU the library runs on holds its own copy at its own
+// address until the process ends.  Host code never uses the array's name as an address: the per-device pointer
 // comes from hipGetSymbolAddress (static_scratch() below).
 constexpr size_t kStaticAccWords = (size_t)PSB_STATIC_MAX_OUTPUTS;
 static __device__ __align__(256) uint32_t scratch[kStaticAccWords];
@@ -513,6 +514,7 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         // unsplit, us - linear 1024 inputs (32 steps), batch 91, 32 / 512 outputs 18.0:14.5 / 21.2:17.5; 2048 (64) 16.6:19.1 /
         // 30.8:25.4, 128 outputs, batch 256 19.6:22.9; 4096 (128) 17.6:26.6 / 47.8:37.6; 3x3 256->512 stride 2 (72) on
         // 14x14, batch 16 29.6:26.9, batch 1 20.0:20.8; 512->512 stride 2 (144) 37.5:39.9; linear 16384->512 (512) 74:94.
+        // (144 steps is the shortest reduction of many outputs that measured better split; none was measured between 128 and 144.)
         half_tiles = psb::shared_half_tiles((int64_t)g->n * OH * OW, n_ocb);
         const int64_t waves = ((int64_t)g->n * OH * OW + 32 * half_tiles - 1) / (32 * half_tiles) * n_ocb;
         const bool few_outputs = (int64_t)g->n * OH * OW * q->shape.oc <= 40000;
@@ -524,7 +526,8 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
             ksplit = 1;
         // Budget levels in one launch: splitting would take the segments one at a time, each with a filter sampled again, a
         // contraction, and around them a rounded map, a zero-fill and a rescale pass (256->512, 3x3, stride 2 at 14x14, batch 16, two
-        // levels: seven launches of 55 us in all).
+        // levels: seven launches of 55 us in all).  Longer reductions than 144 steps were not measured that way and keep
+        // their segments apart.
         if (round_down && n_seg > 0 && !budget_from && n_ksteps <= 144 && (int64_t)n_ksteps * 32 * n_seg < (1ll << 17)) ksplit = 1;
     }
     // all segments in one launch, accumulated in registers, epilogue fused

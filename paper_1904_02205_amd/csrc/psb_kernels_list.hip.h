@@ -20,10 +20,10 @@
 // round keys of the block kernels then fit vector registers, and the table of (block, pixel) products is laid out so that
 // neighbouring pixels are neighbouring words (pruned 576->160 at 14x14, batch 64, S = 16: 329 -> 311 us, depthwise 3x3 on
 // 576 channels 199 -> 190).  (Four blocks, and three in the general form, spill one or two registers; keeping some
-// keys scalar instead measures between 2 % slower and 2 % faster.)  Bound by vector instructions: 53 a generator call for the first of the two, 61 for the
-// second, 41 of them the call itself, the rest the list (14 per tap and pixel), its entries (14) and the tables.  One wave
-// per workgroup with a list of its own and no barriers was slower (337 and 247 us): fewer resident waves, and each
-// waits for its own chain of scalar loads, activations and list.
+// keys scalar instead measures between 2 % slower and 2 % faster.)  Bound by vector instructions: 52 a generator call for the
+// first of the two, 58 for the second, 41 of them the call itself, the rest the list (14 per tap and pixel), its entries (14) and
+// the tables.  One wave per workgroup with a list of its own and no barriers was slower (337 and 247 us): fewer resident waves,
+// and each waits for its own chain of scalar loads, activations and list.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
