@@ -524,11 +524,16 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         if (!rowpack && psb::window_slots(q->shape.kh, q->shape.kw, g->stride_h, g->stride_w, g->pad_h, g->pad_w, g->h, g->w,
                                           half_tiles) > 0)
             ksplit = 1;
-        // Budget levels in one launch: splitting would take the segments one at a time, each with a filter sampled again, a
-        // contraction, and around them a rounded map, a zero-fill and a rescale pass (256->512, 3x3, stride 2 at 14x14, batch 16, two
-        // levels: seven launches of 55 us in all).  Longer reductions than 144 steps were not measured that way and keep
-        // their segments apart.
-        if (round_down && n_seg > 0 && !budget_from && n_ksteps <= 144 && (int64_t)n_ksteps * 32 * n_seg < (1ll << 17)) ksplit = 1;
+        // Budget levels in one launch: splitting takes the segments one at a time, each with a filter sampled again, a
+        // contraction, and around them a rounded map, a zero-fill and a rescale pass, seven launches for two levels; one launch walks
+        // the whole reduction once per level.  The latter for reductions of up to 64 steps, and for longer ones where the filter is so
+        // large (2^20 weights) that sampling it is most of either.  Two levels, one launch : split, us - 50 steps, 64 channels 27:29;
+        // 64 steps, linear 2048->100, batch 16 23:28; 72, 256->64 30:29, 256->512 (2^20 weights) 39:41; 100, 105->6 35:28; 128, linear
+        // 4096->100 38:31, 4096->512, batch 64 55:70; 144, 512->64 46:30, 512->512 62:55.
+        const bool large_filter = (int64_t)q->shape.oc * q->K >= (1ll << 20);
+        if (round_down && n_seg > 0 && !budget_from && (n_ksteps <= 64 || (n_ksteps < 144 && large_filter)) &&
+            (int64_t)n_ksteps * 32 * n_seg < (1ll << 17))
+            ksplit = 1;
     }
     // all segments in one launch, accumulated in registers, epilogue fused
     const bool fused_segments = round_down && mfma && n_seg > 0 && !budget_from && ksplit == 1 &&

@@ -215,3 +215,23 @@ def test_a_graph_outlives_larger_calls(psb, orc, kind):
         assert all(bool((c == 7).all()) for c in canary)
         assert torch.equal(run(big_x, big_bt, (2, 5, 8, 11)), first)
     psb.set_mapping(psb.MAPPING_AUTO)
+
+
+@pytest.mark.parametrize("cin,k,oc,hw", [(64, 5, 8, (7, 6)), (2048, 1, 9, (3, 2)), (2080, 1, 9, (3, 2)), (105, 5, 6, (9, 8)), (4096, 1, 256, (1, 1)),
+                                         (4064, 1, 256, (2, 1)), (4608, 1, 8, (2, 2))])
+def test_shared_levels_of_long_reductions(psb, orc, cin, k, oc, hw):
+    """Budget levels given with the call around the lengths and filter sizes from which a reduction is split over the grid: against
+    the call that reads them from the map, whose accumulators are the oracle's."""
+    import torch
+    rng = np.random.default_rng(cin)
+    L = synth.Layer("levels", synth.he_normal((oc, cin, k, k), rng), synth.sparse_relu_int8((2, cin) + hw, rng), pad=(k // 2, k // 2), S=8,
+                    s_max=16, seed=6, layer_id=1, budget_to=rng.choice([0, 3, 8, 16], size=(2,) + hw).astype(np.uint8))
+    ref, over, _ = helpers.oracle_layer(orc, L, shared=True)
+    q, x, bt = helpers.gpu_quantize(psb, L), torch.from_numpy(L.x).cuda(), torch.from_numpy(L.budget_to).cuda()
+    mult = torch.full((oc,), 0.02 * 2.0 ** q.e_min, device="cuda")
+    kw = dict(pad=L.pad, seed=L.seed, layer_id=L.layer_id, mult=mult)
+    acc = torch.empty((2, oc) + hw, dtype=torch.int32, device="cuda")
+    one_by_one = psb.conv2d_requant(q, x, 4.0, budget_to=bt, shared=True, acc=acc, **kw)
+    assert over == 0 and np.array_equal(acc.cpu().numpy(), ref)
+    for _ in range(2):
+        assert torch.equal(psb.conv2d_shared_budget_requant_blocked(q, x, tuple(x.shape), 4.0, bt, (3, 8, 16), **kw), one_by_one)
