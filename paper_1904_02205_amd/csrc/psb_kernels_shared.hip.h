@@ -1402,7 +1402,7 @@ inline void launch_conv_shared_mfma_resident(const SharedParams& p, int planes, 
 // T - 1 positions between its first and last pixel, one more per image row and W + 1 more per image that the tile
 // crosses, and the taps' reach of 2 (W + 1) + 2 beyond the last pixel.
 // Filters of two digit planes as well (long reductions: the last stage of ResNet-18, 512 channels of 7x7): 18.3 us against
-// 20.7 in the plain kernel, with two budget segments 29 against 35.
+// 20.7 in the plain kernel, with two budget segments 29 against 35; not all of them, see below.
 struct WindowPlan { bool ok; int teams, ws; };
 // slots of the longest window of a layer with this geometry, or 0 when the kernel does not take the geometry
 // (the reduction of such a layer is never split over workgroups: the teams do that inside one)
@@ -1429,6 +1429,11 @@ inline WindowPlan window_plan(const SharedParams& p, int planes, int half_tiles,
     const int CB = p.C_pad >> 5;
     // two teams when the layer has at most one workgroup per CU: then every SIMD still gets two waves
     w.teams = (half_tiles == 1 && CB % 2 == 0 && CB >= 4 && wgs <= n_cus) ? 2 : 1;
+    // Two digit planes and a single team that has its CU to itself: the boundary of a channel block, which nothing hides, costs more
+    // than the plain kernel's operand loads when the blocks are many.  Plain : window, us, 7x7, batch 17 - 5 / 9 / 13 / 15 / 25 blocks, 64
+    // channels 14.2:14.2 / 17.6:17.7 / 20.7:22.0 / 22.7:24.4 / 31.6:34.8 (two budget segments 20.5:20.3 / 28.4:29.3 / 34.5:37.9); 512 channels, whose
+    // workgroups of a pixel tile share an XCD's cache, 7 / 11 / 13 blocks 19.5:18.2 / 26.8:25.3 / 29.3:28.4 (33.5:32.4 / 45.6:45.9 / 50.7:52.0).
+    if (planes == 2 && w.teams == 1 && wgs <= n_cus && CB > (p.OC > 480 ? 11 : 5)) return w;
     w.ok = true;
     return w;
 }

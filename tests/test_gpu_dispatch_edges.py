@@ -235,3 +235,18 @@ def test_shared_levels_of_long_reductions(psb, orc, cin, k, oc, hw):
     assert over == 0 and np.array_equal(acc.cpu().numpy(), ref)
     for _ in range(2):
         assert torch.equal(psb.conv2d_shared_budget_requant_blocked(q, x, tuple(x.shape), 4.0, bt, (3, 8, 16), **kw), one_by_one)
+
+
+@pytest.mark.parametrize("cin,oc,hw", [(160, 9, (7, 7)), (192, 9, (7, 7)), (224, 9, (7, 7)), (352, 484, (5, 6)), (384, 484, (5, 6)), (416, 484, (5, 6))])
+def test_shared_two_digit_planes(psb, orc, cin, oc, hw):
+    """3 x 3 layers whose filter needs two digit planes, around the numbers of channel blocks from which the window kernel with a
+    single team leaves them to the plain one (even numbers have two teams)."""
+    rng = np.random.default_rng(cin)
+    L = synth.Layer("planes", synth.he_normal((oc, cin, 3, 3), rng), synth.sparse_relu_int8((1, cin) + hw, rng), pad=(1, 1), S=8, s_max=8,
+                    seed=6, layer_id=1)
+    qo, qg = helpers.oracle_quantize(orc, L, exp_bits=2), helpers.gpu_quantize(psb, L, exp_bits=2)
+    assert 2 ** 8 < 2 * 8 * 2 ** (qg.e_top - qg.e_min) * 4 <= 2 ** 16          # two balanced base-256 digits with two guard bits
+    points = np.sort(rng.choice(oc * hw[0] * hw[1], 441, replace=False)).astype(np.int64)
+    ref, over, _ = helpers.oracle_layer(orc, L, qo, shared=True, points=points)
+    acc, _ = helpers.gpu_layer(psb, L, qg, shared=True)
+    assert over == 0 and np.array_equal(acc.ravel()[points], ref)
