@@ -241,11 +241,12 @@ __global__ void __launch_bounds__(kListPixels, NB > 6 ? 5 : NB > 4 ? 4 : 6) k_la
         // sample the products, lanes taking entries round-robin
         const uint32_t total = count;
         if constexpr (HOIST) {
-            // Entries in flight per lane.  Six waves per SIMD hide a call's latency, and more calls in flight only cost registers:
-            // four made calls of one and two blocks spill (pruned 576->160, depthwise 3x3 on 576, both batch 64, S = 1: 153 and
-            // 112 us, 148 and 103 with one; S = 4: 149 and 102, 143 and 98).  Two fit where a call is cheapest to count (S = 16 of
-            // 7 bits: 153 and 103 us, one 159 and 105).
-            constexpr int U = P7 && NB == 1 && !MULTI ? 2 : 1;
+            // Entries in flight per lane.  Six waves per SIMD hide a call's latency, and more calls in flight cost registers: four
+            // made calls of one and two blocks spill (pruned 576->160, depthwise 3x3 on 576, both batch 64, S = 1: 153 and
+            // 112 us, 148 and 103 with two or one; S = 4: 149 and 102, 143 and 98).  Two calls of one block fit, and hide some
+            // latency where few workgroups share a CU (grouped 26->182 at 14x14, S = 1 / 4: 33.0 / 31.9 us with four, 32.8 / 31.6 with two,
+            // 34.5 / 32.8 with one); of two blocks one fits (S = 8 there: 35.7 us with two, 35.1 with one).
+            constexpr int U = NB == 1 ? 2 : 1;
             auto sample_all = [&](auto whole_c) {          // whole: every block of this pass is drawn to its end
                 constexpr bool WHOLE = decltype(whole_c)::value;
                 const uint32_t nsamp = WHOLE ? (uint32_t)(kPer * NB) : (uint32_t)(s_uniform - kPer * j0);
