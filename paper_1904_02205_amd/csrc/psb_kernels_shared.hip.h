@@ -118,8 +118,9 @@ __device__ __forceinline__ RoundKeys round_keys(uint32_t key0, uint32_t key1)
     return rk;
 }
 
-// count_below() for the whole generator blocks j0 .. j0 + NB - 1 of one weight: no per-sample range tests, and what the blocks share is computed once - in round 0 the product with the output index, in round 1
-// the product with state word 2 (neither depends on the block number, whose own product is scalar).
+// count_below() for the whole generator blocks j0 .. j0 + NB - 1 of one weight: no per-sample range tests, and what the blocks
+// share is computed once - in round 0 the product with the output index, in round 1 the product with state word 2 (neither
+// depends on the block number, whose own product is scalar).
 template <int NB>
 __device__ __forceinline__ uint32_t count_below_blocks(uint32_t o, uint32_t k, uint32_t j0, uint32_t layer, const RoundKeys& rk,
                                                        uint32_t thr)
