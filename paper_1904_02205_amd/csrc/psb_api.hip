@@ -369,11 +369,11 @@ psb::FilterJob filter_job(const psb_weights* q, int from, int to, uint64_t seed,
                           int8_t* planes, int CB, int n_ksteps)
 {
     psb::FilterJob j;
-    j.packed = q->packed_dev; j.OC = q->shape.oc; j.K = q->K; j.KHW = q->shape.kh * q->shape.kw;
+    j.packed = q->packed_dev; j.tile = q->tile_dev; j.oc_pad = q->oc_pad; j.OC = q->shape.oc; j.K = q->K; j.KHW = q->shape.kh * q->shape.kw;
     j.CB = CB; j.n_ksteps = n_ksteps; j.prob_bits = q->prob_bits; j.from = from; j.to = to;
     j.key0 = (uint32_t)(seed & 0xFFFFFFFFull); j.key1 = (uint32_t)(seed >> 32); j.layer_id = layer_id;
     j.w32 = w32; j.planes = planes;
-    j.pack_KW = 0; j.pack_C = 0; j.n_planes = psb::kMaxPlanes;
+    j.pack_KW = 0; j.pack_C = 0; j.n_planes = psb::kMaxPlanes; j.taps = 4;
     j.C = q->K / j.KHW;
     j.inv_ksteps = psb::inverse_of((uint32_t)n_ksteps); j.inv_CB = psb::inverse_of((uint32_t)CB); j.inv_pack_C = 0xFFFFFFFFu;
     return j;
@@ -409,6 +409,10 @@ shared_plan plan_shared(const psb_weights* q)
     s.n_ocb = (q->shape.oc + 31) / 32;
     return s;
 }
+
+// Blocks of 64 channels x reduction steps of one sampling of a handle's digit planes, and its workgroups.
+int64_t sampling_steps(const shared_plan& sp) { return (int64_t)((sp.n_ocb + 1) / 2) * sp.n_ksteps; }
+int64_t sampling_blocks(const shared_plan& sp, int taps) { return sampling_steps(sp) * (8 / taps); }
 
 // Bytes of the digit planes of one segment (one chunk of padding: the kernel stages whole chunks of reduction steps).
 size_t planes_segment_bytes(const shared_plan& sp)
@@ -448,12 +452,14 @@ int sample_segments(const psb_weights* q, const shared_plan& sp, const int (&lev
     psb::FilterBatch batch;
     std::memset(&batch, 0, sizeof(batch));
     for (int k = 0; k <= psb::kMaxBatchJobs; ++k) batch.first_block[k] = 0xFFFFFFFFu;
-    const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + psb::kPlaneGroup - 1) / psb::kPlaneGroup * 4;
+    const int taps = psb::plane_taps(sampling_steps(sp) * n_seg);
+    const int64_t need = sampling_blocks(sp, taps);
     if (need * n_seg > 2147483647ll) return PSB_ERR_TOO_LARGE;
     for (int i = 0; i < n_seg; ++i) {
         psb::FilterJob fj = filter_job(q, i == 0 ? 0 : level[i - 1], level[i], seed, layer_id, nullptr,
                                        static_cast<int8_t*>(q->ws->planes.ptr) + planes_segment_bytes(sp) * i, sp.CB, sp.n_ksteps);
         fj.n_planes = n_planes;
+        fj.taps = taps;
         if (sp.rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
         batch.jobs[i] = fj;
         batch.first_block[i] = (unsigned)(need * i);
@@ -628,17 +634,19 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         }
     }
     auto prepare = [&](int from, int to) -> int {
-        // matrix cores: one thread per slot of the operand-ordered planes; otherwise one per weight
+        // matrix cores: the operand-ordered planes; otherwise one thread per weight
         // planes sampled ahead of this call (psb_shared_prepare_filters) are used once
         const bool have = mfma && ws->ready && ws->ready_seed == seed && ws->ready_layer == layer_id && from == 0 &&
                           ws->ready_n_seg == 1 && to == ws->ready_level[0];
         ws->ready = false;
-        const int64_t filter_blocks = have ? 0 : mfma ? ((int64_t)n_ocb * n_ksteps + psb::kPlaneGroup - 1) / psb::kPlaneGroup * 4 : (nw + 255) / 256;
+        const int taps = psb::plane_taps(sampling_steps(sp));
+        const int64_t filter_blocks = have ? 0 : mfma ? sampling_blocks(sp, taps) : (nw + 255) / 256;
         if (filter_blocks + transpose_blocks > 2147483647ll) return PSB_ERR_TOO_LARGE;
         if (filter_blocks + transpose_blocks == 0) return PSB_OK;
         psb::FilterJob fj = filter_job(q, from, to, seed, layer_id, mfma ? nullptr : ws->w32_dev,
                                        mfma ? planes : nullptr, CB, n_ksteps);
         fj.n_planes = psb::planes_needed(max_shift, to - from);
+        fj.taps = taps;
         if (rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
         hipLaunchKernelGGL(psb::k_shared_prologue, dim3((unsigned)(filter_blocks + transpose_blocks)), dim3(256), 0,
                            stream, fj, tj, (unsigned)filter_blocks);
@@ -1159,6 +1167,12 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
         return PSB_OK;
     };
     reset();
+    int64_t steps = 0;
+    for (int i = 0; i < n; ++i) {
+        const shared_plan sp = plan_shared(handles[i]);
+        if (sp.mfma) steps += sampling_steps(sp);
+    }
+    const int taps = psb::plane_taps(steps);
     for (int i = 0; i < n; ++i) {
         const psb_weights* q = handles[i];
         if (q->device != dev) return PSB_ERR_DEVICE;
@@ -1173,7 +1187,7 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
         int longest = 0;
         for (int k = 0; k < n_seg; ++k) longest = std::max(longest, level[k] - (k ? level[k - 1] : 0));
         const int n_planes = psb::planes_needed(q->info.e_top - q->info.e_min, longest);
-        const int64_t need = ((int64_t)sp.n_ocb * sp.n_ksteps + psb::kPlaneGroup - 1) / psb::kPlaneGroup * 4;
+        const int64_t need = sampling_blocks(sp, taps);
         if (need > 2147483647ll) return PSB_ERR_TOO_LARGE;
         for (int k = 0; k < n_seg; ++k) {
             if (n_jobs == psb::kMaxBatchJobs || blocks + need > 2147483647ll) {
@@ -1183,6 +1197,7 @@ static int prepare_filters(const psb_weights_t* const* handles, int32_t n, const
             psb::FilterJob fj = filter_job(q, k ? level[k - 1] : 0, level[k], seeds[i], layer_ids[i], nullptr,
                                            static_cast<int8_t*>(q->ws->planes.ptr) + planes_segment_bytes(sp) * k, sp.CB, sp.n_ksteps);
             fj.n_planes = n_planes;
+            fj.taps = taps;
             if (sp.rowpack) { fj.pack_KW = q->shape.kw; fj.pack_C = q->shape.cin; fj.inv_pack_C = psb::inverse_of((uint32_t)q->shape.cin); }
             batch.jobs[n_jobs] = fj;
             batch.first_block[n_jobs] = (unsigned)blocks;

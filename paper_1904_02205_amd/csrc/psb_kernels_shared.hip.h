@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "psb_kernels.hip.h"
+#include "psb_kernels_oc.hip.h"
 
 namespace psb {
 
@@ -89,8 +90,10 @@ struct SharedParams {
 
 // Filter sampling: count and filter value of one weight; digit planes for the matrix cores.
 struct FilterJob {
-    const uint32_t* packed;   // [OC][K]
-    int OC, K, KHW, CB, n_ksteps, prob_bits, from, to;
+    const uint32_t* packed;   // [OC][K]                         (int32 filter)
+    const uint2* tile;        // [K][oc_pad] {threshold, unit}   (digit planes)
+    int OC, K, oc_pad, KHW, CB, n_ksteps, prob_bits, from, to;
+    int taps;                 // slots per wave, plane_taps()
     int pack_KW, pack_C;      // row packing: kernel width and channel count (0: not packed)
     int n_planes;             // digit planes the contraction of this sample range reads
     int C;                    // input channels (K / KHW)
@@ -100,63 +103,12 @@ struct FilterJob {
     int8_t* planes;           // operand-ordered digit planes, or null
 };
 
-// The ten pairs of round keys of a generator key: uniform over a job, computed once per wave.  Those of rounds 2..9, which
-// go into three-input xors, stay in vector registers (with a scalar operand the instruction issues at half rate).
-struct RoundKeys { uint32_t k0[10], k1[10]; };
-__device__ __forceinline__ RoundKeys round_keys(uint32_t key0, uint32_t key1)
-{
-    RoundKeys rk;
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        rk.k0[r] = key0 + (uint32_t)r * kWeyl0;
-        rk.k1[r] = key1 + (uint32_t)r * kWeyl1;
-        if (r >= 2) {
-            asm("v_mov_b32 %0, %1" : "=v"(rk.k0[r]) : "s"(rk.k0[r]));
-            asm("v_mov_b32 %0, %1" : "=v"(rk.k1[r]) : "s"(rk.k1[r]));
-        }
-    }
-    return rk;
-}
-
-// count_below() for the whole generator blocks j0 .. j0 + NB - 1 of one weight: no per-sample range tests, and what the blocks
-// share is computed once - in round 0 the product with the output index, in round 1 the product with state word 2 (neither
-// depends on the block number, whose own product is scalar).
-template <int NB>
-__device__ __forceinline__ uint32_t count_below_blocks(uint32_t o, uint32_t k, uint32_t j0, uint32_t layer, const RoundKeys& rk,
-                                                       uint32_t thr)
-{
-    uint32_t hi_a, lo_a, hi_b1, lo_b1;
-    mulhilo(kMulA, o, hi_a, lo_a);
-    const uint32_t z1 = hi_a ^ layer ^ rk.k1[0];               // state word 2 after round 0
-    mulhilo(kMulB, z1, hi_b1, lo_b1);
-    uint32_t n = 0;
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        uint32_t hi_bj, lo_bj, hi_a1, lo_a1;
-        mulhilo(kMulB, j0 + (uint32_t)j, hi_bj, lo_bj);        // scalar
-        const uint32_t x1 = hi_bj ^ k ^ rk.k0[0];              // state after round 0: (x1, lo_bj, z1, lo_a)
-        mulhilo(kMulA, x1, hi_a1, lo_a1);
-        u32x4 c{hi_b1 ^ (lo_bj ^ rk.k0[1]), lo_b1, xor3(hi_a1, lo_a, rk.k1[1]), lo_a1};      // after round 1
-#pragma unroll
-        for (int r = 2; r < 10; ++r) c = philox_round(c, rk.k0[r], rk.k1[r]);
-        n += (c.x < thr ? 1u : 0u) + (c.y < thr ? 1u : 0u) + (c.z < thr ? 1u : 0u) + (c.w < thr ? 1u : 0u);
-    }
-    return n;
-}
-
-// W[oc][k] for the job's sample range, from the weight's encoded word.  whole_blocks: 1..4 when the range is that many
-// whole blocks of 32-bit uniforms (the usual call), else 0; rk: round_keys() of the job's key.
-__device__ __forceinline__ int32_t sample_word(const FilterJob& j, uint32_t word, int oc, int k, int whole_blocks = 0,
-                                               const RoundKeys* rk = nullptr)
+// W[oc][k] for the job's sample range, from the weight's encoded word.
+__device__ __forceinline__ int32_t sample_word(const FilterJob& j, uint32_t word, int oc, int k)
 {
     if ((word & 0x7F800000u) == kDeadWord) return 0;
     const uint32_t thr = threshold_of(word & 0x7FFFFFu, j.prob_bits);
-    uint32_t cnt;
-    if (whole_blocks == 1) cnt = count_below_blocks<1>((uint32_t)oc, (uint32_t)k, (uint32_t)j.from >> 2, j.layer_id, *rk, thr);
-    else if (whole_blocks == 2) cnt = count_below_blocks<2>((uint32_t)oc, (uint32_t)k, (uint32_t)j.from >> 2, j.layer_id, *rk, thr);
-    else if (whole_blocks == 3) cnt = count_below_blocks<3>((uint32_t)oc, (uint32_t)k, (uint32_t)j.from >> 2, j.layer_id, *rk, thr);
-    else if (whole_blocks == 4) cnt = count_below_blocks<4>((uint32_t)oc, (uint32_t)k, (uint32_t)j.from >> 2, j.layer_id, *rk, thr);
-    else cnt = j.prob_bits <= 7
+    const uint32_t cnt = j.prob_bits <= 7
         ? count_below7((uint32_t)oc, (uint32_t)k, j.layer_id, j.key0, j.key1, thr, j.from, j.to)
         : count_below((uint32_t)oc, (uint32_t)k, j.layer_id, j.key0, j.key1, thr, j.from, j.to);
     const uint32_t mag = ((uint32_t)(j.to - j.from) + cnt) << ((word >> 23) & 0xFFu);   // < 2^31 by the overflow rule
@@ -186,65 +138,128 @@ __device__ __forceinline__ uint32_t quad_transpose_bytes(uint32_t d)
     return lo | hi;
 }
 
-// Digit planes in operand order: one thread per (channel, slot) of a 32-channel x 32-slot operand block, padding
-// included (those get zeros, so the buffer needs no clearing), and kPlaneGroup operand blocks per thread, so that
-// the weight words of all of them are in flight before the first is sampled.  Workgroup `block` of the job works
-// on operand blocks (block >> 2) * kPlaneGroup + g, each = (channel block, reduction step) - uniform values, whose
-// divisions run on the scalar unit - and its thread t' = (block & 3) * 256 + thread index on slot (bits 0-3 and
-// 9 of t') of channel (bits 4-8).  The four lanes of a quad hold four consecutive slots; after the byte transpose
-// lane b of the quad stores plane b's four digits as one 32-bit word.
-constexpr int kPlaneGroup = 4;
+// byte b of w[i] -> byte i of out[b]
+__device__ __forceinline__ void transpose_bytes_4x4(const uint32_t (&w)[4], uint32_t (&out)[4])
+{
+    const uint32_t t0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);
+    const uint32_t t1 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+    const uint32_t t2 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);
+    const uint32_t t3 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+    out[0] = __builtin_amdgcn_perm(t1, t0, 0x05040100u);
+    out[1] = __builtin_amdgcn_perm(t1, t0, 0x07060302u);
+    out[2] = __builtin_amdgcn_perm(t3, t2, 0x05040100u);
+    out[3] = __builtin_amdgcn_perm(t3, t2, 0x07060302u);
+}
+
+// Digit planes in operand order.  lane = output channel of a block of 64 (two operand blocks of 32), a wave = TAPS
+// consecutive slots of a reduction step: the tap index is wave-uniform as in the channel-lane layer kernel, whose
+// generator steps are used here (15 wide multiplies a call; what depends on the channel only, or on channel and block, is
+// computed once for the TAPS weights), the {threshold, unit} pairs of a tap are 512 consecutive bytes, and a lane's
+// digits of a plane are TAPS consecutive bytes of its operand.  Padding slots and channels get zeros, so the buffer needs
+// no clearing.  Workgroup `block` of the job: 32 / (4 TAPS) of them serve one (channel block, reduction step).
+template <int TAPS, bool P7>
+__device__ __forceinline__ void sample_planes_slots(const FilterJob& j, uint32_t block)
+{
+    static_assert(TAPS == 4 || TAPS == 8, "a lane stores one or two words per plane");
+    constexpr uint32_t kWgs = 32 / (4 * TAPS);              // workgroups per (channel block, reduction step)
+    constexpr int kPer = P7 ? 16 : 4;                       // samples of a generator block
+    const int lane = threadIdx.x & 63;
+    const uint32_t slot0 = ((block % kWgs) * 4u + uniform_u32(threadIdx.x >> 6)) * TAPS;      // scalar, like all but the lane's channel
+    uint32_t kstep;
+    const uint32_t ocb = div_mod(block / kWgs, (uint32_t)j.n_ksteps, j.inv_ksteps, kstep);
+    const uint32_t oc = ocb * 64u + (uint32_t)lane;
+    uint32_t k[TAPS];
+    uint2 wt[TAPS];
+    uint32_t cb = 0;
+    const uint32_t r = j.pack_KW ? 0u : div_mod(kstep, (uint32_t)j.CB, j.inv_CB, cb);
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t) {
+        const uint32_t slot = slot0 + (uint32_t)t;
+        bool ok;
+        if (j.pack_KW) {                                    // one step per kernel row; slot kw * C + c inside it
+            uint32_t c;
+            const uint32_t kw = div_mod(slot, (uint32_t)j.pack_C, j.inv_pack_C, c);
+            k[t] = c * (uint32_t)j.KHW + kstep * (uint32_t)j.pack_KW + kw;
+            ok = kw < (uint32_t)j.pack_KW;
+        } else {
+            const uint32_t c = cb * 32u + slot;
+            k[t] = c * (uint32_t)j.KHW + r;
+            ok = c < (uint32_t)j.C;
+        }
+        wt[t] = make_uint2(0u, 0u);
+        if (ok) wt[t] = j.tile[(uint64_t)k[t] * (uint32_t)j.oc_pad + oc];
+    }
+
+    Keys key;
+#pragma unroll
+    for (int i = 0; i < 10; ++i) {
+        key.k0[i] = j.key0 + (uint32_t)i * kWeyl0;
+        key.k1[i] = j.key1 + (uint32_t)i * kWeyl1;
+        if (i >= 3) {                                       // see k_layer_oc_lane
+            asm("v_mov_b32 %0, %1" : "=v"(key.k0[i]) : "s"(key.k0[i]));
+            asm("v_mov_b32 %0, %1" : "=v"(key.k1[i]) : "s"(key.k1[i]));
+        }
+    }
+    PixelHoist h;
+    uint32_t hi_a, lo_b1;
+    mulhilo(kMulA, oc, hi_a, h.lo_a);
+    mulhilo(kMulB, hi_a ^ j.layer_id ^ key.k1[0], h.hi_b1, lo_b1);
+    h.y2k = lo_b1 ^ key.k0[2];
+    uint32_t n[TAPS];
+#pragma unroll
+    for (int t = 0; t < TAPS; ++t) n[t] = (uint32_t)(j.to - j.from);
+    for (int b = j.from / kPer; kPer * b < j.to; ++b) {
+        uint32_t s_hib, hz, lo2;
+        block_setup(h, key, b, s_hib, hz, lo2);
+        if (kPer * b >= j.from && kPer * (b + 1) <= j.to) {
+#pragma unroll
+            for (int t = 0; t < TAPS; ++t) {
+                n[t] = sample_block<4, P7>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);     // one call after the other (eight waves per SIMD)
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < TAPS; ++t)
+                n[t] = sample_block<0, P7>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, j.from, j.to);
+        }
+    }
+
+    const uint32_t ocb32 = ocb * 2u + (uint32_t)(lane >> 5);
+    if (ocb32 * 32u >= (uint32_t)j.OC) return;              // an operand block that does not exist
+    // Balanced base-256 digits d_b in [-128, 127] with v = sum d_b 256^b modulo 2^32, all four at once: adding 128 to every
+    // digit gives the ordinary digits (0..255) of v + 0x80808080, and subtracting 128 from a byte flips its top bit.
+    uint32_t word[TAPS / 4][4];                             // [group of four slots][plane]
+#pragma unroll
+    for (int q = 0; q < TAPS / 4; ++q) {
+        uint32_t d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[i] = (wt[4 * q + i].y * n[4 * q + i] + 0x80808080u) ^ 0x80808080u;     // modulo 2^32
+        transpose_bytes_4x4(d, word[q]);
+    }
+    int8_t* const at = j.planes + ((uint64_t)(ocb32 * (uint32_t)j.n_ksteps + kstep) * (kMaxPlanes * kPlaneStride) +
+                                   (((uint32_t)lane & 31u) + 32u * (slot0 >> 4)) * 16u + (slot0 & 15u));
+#pragma unroll
+    for (int b = 0; b < kMaxPlanes; ++b) {
+        if (b >= j.n_planes) break;                         // uniform
+        if constexpr (TAPS == 4) *reinterpret_cast<uint32_t*>(at + b * kPlaneStride) = word[0][b];
+        else *reinterpret_cast<uint2*>(at + b * kPlaneStride) = make_uint2(word[0][b], word[1][b]);
+    }
+}
+
+// Slots per wave of a launch that samples `steps` (blocks of 64 channels x reduction steps).  Eight share the set-up of a wave
+// better (all 21 layers of a ResNet-18 shape at S = 8, 3135 steps: 36.2 us, 42.3 with four), four give a small launch twice the
+// waves (us with four : eight slots, S = 8 - 18 steps 4.8:5.8, 288 steps 6.2:6.8, 576 steps 8.5:8.5, 1152 steps 12.3:12.0; S = 32 - 18
+// steps 7.5:11.2, 1152 steps 27.8:28.7).
+inline int plane_taps(int64_t steps) { return steps >= 576 ? 8 : 4; }
 
 __device__ __forceinline__ void sample_planes_block(const FilterJob& j, uint32_t block)
 {
-    const uint32_t t = (block & 3u) * 256u + threadIdx.x;
-    const int cl = (int)(t & 15u) + 16 * (int)((t >> 9) & 1u);
-    const int ocl = (int)(t >> 4) & 31;
-    const uint32_t n_blk = (uint32_t)((j.OC + 31) >> 5) * (uint32_t)j.n_ksteps;
-    const uint32_t blk0 = (block >> 2) * kPlaneGroup;
-    uint32_t word[kPlaneGroup];
-    int oc_[kPlaneGroup], k_[kPlaneGroup];
-    bool valid[kPlaneGroup];
-#pragma unroll
-    for (int g = 0; g < kPlaneGroup; ++g) {
-        const uint32_t blk = min(blk0 + g, n_blk - 1);     // past the end: the last block again (not stored)
-        uint32_t kstep;
-        const uint32_t ocb = div_mod(blk, (uint32_t)j.n_ksteps, j.inv_ksteps, kstep);
-        const int oc = (int)ocb * 32 + ocl;
-        int c, r;
-        bool ok = oc < j.OC;
-        if (j.pack_KW) {                               // one step per kernel row; slot kw * C + c inside it
-            uint32_t cu;
-            const int kw = (int)div_mod((uint32_t)cl, (uint32_t)j.pack_C, j.inv_pack_C, cu);
-            c = (int)cu;
-            r = (int)kstep * j.pack_KW + kw;
-            ok = ok && kw < j.pack_KW;
-        } else {
-            uint32_t cb;
-            r = (int)div_mod(kstep, (uint32_t)j.CB, j.inv_CB, cb);
-            c = (int)cb * 32 + cl;
-            ok = ok && c < j.C;
-        }
-        oc_[g] = oc;
-        k_[g] = c * j.KHW + r;
-        valid[g] = ok;
-        word[g] = ok ? j.packed[(int64_t)oc * j.K + k_[g]] : kDeadWord;
-    }
-    const int plane = (int)(t & 3);
-    const RoundKeys rk = round_keys(j.key0, j.key1);
-    const int blocks = (j.to - j.from) >> 2;
-    const int whole_blocks = (j.prob_bits > 7 && ((j.from | j.to) & 3) == 0 && blocks <= 4) ? blocks : 0;           // uniform
-#pragma unroll
-    for (int g = 0; g < kPlaneGroup; ++g) {
-        // Balanced base-256 digits d_b in [-128, 127] with v = sum d_b 256^b modulo 2^32, all four at once: adding 128
-        // to every digit gives the ordinary digits (0..255) of v + 0x80808080, and subtracting 128 from a byte
-        // flips its top bit.
-        const uint32_t v = valid[g] ? (uint32_t)sample_word(j, word[g], oc_[g], k_[g], whole_blocks, &rk) : 0u;
-        const uint32_t digits = (v + 0x80808080u) ^ 0x80808080u;
-        const uint32_t out = quad_transpose_bytes(digits);
-        if (plane < j.n_planes && blk0 + g < n_blk)
-            *reinterpret_cast<uint32_t*>(j.planes + (((int64_t)(blk0 + g) * kMaxPlanes + plane) * 64 + ocl + 32 * (cl >> 4)) * 16 +
-                                         (cl & 12)) = out;
+    if (j.prob_bits <= 7) {                                  // uniform, like j.taps
+        if (j.taps == 8) sample_planes_slots<8, true>(j, block);
+        else sample_planes_slots<4, true>(j, block);
+    } else {
+        if (j.taps == 8) sample_planes_slots<8, false>(j, block);
+        else sample_planes_slots<4, false>(j, block);
     }
 }
 
@@ -361,13 +376,8 @@ __device__ __forceinline__ void channels_last_tile_wide(const TransposeJob& j, i
     for (int r = 0; r < 2; ++r) {
         const int unit = r * 256 + (int)threadIdx.x;
         const int cq = unit >> 6, pq = unit & 63;
-        // byte b of w[r][i] = channel i, position b  ->  byte i of out[b]
-        const uint32_t t0 = __builtin_amdgcn_perm(w[r][1], w[r][0], 0x05010400u);
-        const uint32_t t1 = __builtin_amdgcn_perm(w[r][3], w[r][2], 0x05010400u);
-        const uint32_t t2 = __builtin_amdgcn_perm(w[r][1], w[r][0], 0x07030602u);
-        const uint32_t t3 = __builtin_amdgcn_perm(w[r][3], w[r][2], 0x07030602u);
-        const uint32_t out[4] = {__builtin_amdgcn_perm(t1, t0, 0x05040100u), __builtin_amdgcn_perm(t1, t0, 0x07060302u),
-                                 __builtin_amdgcn_perm(t3, t2, 0x05040100u), __builtin_amdgcn_perm(t3, t2, 0x07060302u)};
+        uint32_t out[4];                                   // byte b of w[r][i] = channel i, position b
+        transpose_bytes_4x4(w[r], out);
 #pragma unroll
         for (int b = 0; b < 4; ++b)
             *reinterpret_cast<uint32_t*>(tile + (pq * 4 + b) * kWideTileRow + cq * 4) = out[b];
@@ -393,7 +403,7 @@ struct FilterBatch {
     unsigned first_block[kMaxBatchJobs + 1];
 };
 
-__global__ void __launch_bounds__(256) k_sample_planes_batch(const FilterBatch b)
+__global__ void __launch_bounds__(256, 8) k_sample_planes_batch(const FilterBatch b)
 {
     // the job of this workgroup = number of later jobs' first workgroups it has reached; without a loop over
     // dependent loads (the table arrives in a few wide scalar loads, the rest is scalar compares)

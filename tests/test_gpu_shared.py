@@ -36,6 +36,31 @@ def test_sampled_filter_matches_oracle(psb, orc, prob_bits):
         assert ei.value.code == psb.ERR_VALUE
 
 
+@pytest.mark.parametrize("cin,oc,k,prob_bits", [
+    (1, 1, 1, 23), (33, 31, 1, 4), (32, 33, 3, 23), (40, 64, 3, 7), (70, 65, 3, 23), (3, 97, 5, 23), (4, 40, 7, 4),   # a few slots a wave
+    (32 * 287 + 1, 66, 1, 23), (32 * 288, 66, 1, 4), (32 * 287, 128, 1, 23), (64 * 32, 65, 3, 23)])                     # launches around the line to more
+def test_digit_planes_hold_the_sampled_filter(psb, cin, oc, k, prob_bits):
+    """The filter the matrix cores contract against the int32 filter of psb_sample_filter, over ranges that begin and end inside a
+    generator block (one output pixel per image, no activation zero; integers, so exact in 64 bits)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(cin * 1000 + oc)
+    w = torch.randn((oc, cin, k, k), generator=gen, device="cuda") * 0.05
+    w[torch.rand(w.shape, generator=gen, device="cuda") < 0.2] = 0.0
+    q = psb.Weights(w, s_max=40, prob_bits=prob_bits)
+    x = torch.randint(1, 128, (5, cin, k, k), generator=gen, device="cuda", dtype=torch.int8)
+    x = torch.where(torch.rand(x.shape, generator=gen, device="cuda") < 0.5, x, -x)
+    for a, b in ((0, 8), (0, 40), (0, 3), (4, 8), (5, 6), (3, 37), (16, 32), (31, 34)):
+        full = lambda v: torch.full((5, 1, 1), v, dtype=torch.uint8, device="cuda")
+        acc = torch.zeros((5, oc, 1, 1), dtype=torch.int32, device="cuda")
+        if a == 0:
+            psb.conv2d(q, x, b, seed=7, layer_id=2, acc=acc, shared=True)
+        else:
+            psb.conv2d_progressive(q, x, full(b), full(a), seed=7, layer_id=2, acc=acc, shared=True)
+        f = psb.sample_filter(q, b, a, seed=7, layer_id=2)
+        ref = x.view(5, -1).double().cpu() @ f.view(oc, -1).double().cpu().t()
+        assert torch.equal(acc.view(5, oc).cpu().double(), ref), (a, b)
+
+
 def _cases():
     rng = np.random.default_rng(900)
     c = []
