@@ -15,6 +15,7 @@
 #include "psb_kernels_oc.hip.h"
 #include "psb_kernels_list.hip.h"
 #include "psb_kernels_shared.hip.h"
+#include "psb_kernels_resident.hip.h"
 #include "psb_kernels_glue.hip.h"
 #include "psb_choice.h"
 #include "psb_workspace.h"
@@ -244,6 +245,13 @@ int resident_workgroups()
         return 2 * n;
     }();
     return resident_wgs;
+}
+
+// The contraction of a shared-filter call on the matrix cores.
+void launch_contraction(const psb::SharedParams& p, int planes, int half_tiles, hipStream_t stream)
+{
+    if (psb::launch_conv3x3_resident(p, planes, psb::oc_lane_cus(), stream)) return;
+    psb::launch_conv_shared_mfma(p, planes, resident_workgroups(), half_tiles, stream);
 }
 
 // Which kernel serves a call on this layer under the current mapping switch (1, 2, 3), or a psb_status: a call with S samples
@@ -659,7 +667,7 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         int slot = 0;
         const bool timed = profile_begin(stream, &slot);
         if (mfma) {
-            psb::launch_conv_shared_mfma(p, psb::planes_needed(max_shift, n_samples), resident_workgroups(), half_tiles, stream);
+            launch_contraction(p, psb::planes_needed(max_shift, n_samples), half_tiles, stream);
         } else {
             const int64_t columns = (npix + 255) / 256;
             if (p.Cg == 1 && p.KH == 3 && p.KW == 3) {
@@ -725,7 +733,7 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         p.masked = 0;
         int slot = 0;
         const bool timed = profile_begin(stream, &slot);
-        psb::launch_conv_shared_mfma(p, n_planes, resident_workgroups(), half_tiles, stream);
+        launch_contraction(p, n_planes, half_tiles, stream);
         if (timed) profile_end(stream, slot);
         PSB_HIP_TRY(hipGetLastError());
         return PSB_OK;

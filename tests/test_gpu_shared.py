@@ -371,3 +371,63 @@ def test_rescale_matches_oracle(psb, orc, mapping):
     assert np.array_equal(accp, refp)
     assert np.array_equal(yp, orc.rescale(refp, qo.e_min, s_max=16, budget_to=to))
     psb.set_mapping(psb.MAPPING_AUTO)
+
+
+@pytest.mark.parametrize("n,cin,oc,hw,S", [
+    (1, 64, 16, (5, 6), 8),          # four groups of pixels, the reduction in four or eight parts, one pixel tile
+    (3, 40, 33, (9, 7), 4),          # channels that fill neither an instruction nor a block, tiles across images
+    (2, 160, 70, (14, 13), 8),       # an odd number of channel blocks, planes no multiple of four bytes
+    (1, 256, 64, (40, 36), 8),       # part of the pixels per wave
+    (8, 64, 64, (56, 56), 8),        # seven groups
+    (17, 64, 64, (56, 52), 8),       # thirteen groups, a last tile in part
+    (33, 512, 48, (7, 7), 2),        # two digit planes, long reduction
+    (40, 64, 200, (4, 4), 8)])       # tiles of many small images, many channel groups
+@pytest.mark.parametrize("residual", [None, "f32", "i8"])
+def test_window_of_all_channels(psb, n, cin, oc, hw, S, residual):
+    """3 x 3 layers whose input window stays in LDS: accumulators against a 64-bit convolution with the sampled filter (exact), and
+    every form of the fused outputs against the library's separate requantisation of the rescaled values (exact)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(n * 1000 + cin + oc)
+    h, w = hw
+    x = (torch.rand((n, cin, h, w), generator=gen, device="cuda") * 255 - 128).to(torch.int8)
+    q = psb.Weights(torch.randn((oc, cin, 3, 3), generator=gen, device="cuda") * 0.05, s_max=2 * S)
+    mult = torch.rand(oc, generator=gen, device="cuda") * 2e-5 + 1e-6
+    bias = torch.randn(oc, generator=gen, device="cuda") * 0.1
+    geo = dict(stride=(1, 1), pad=(1, 1), seed=3, layer_id=4, mult=mult, bias=bias)
+    acc = torch.empty((n, oc, h, w), dtype=torch.int32, device="cuda")
+    y = torch.empty((n, oc, h, w), dtype=torch.float32, device="cuda")
+    psb.conv2d(q, x, S, acc=acc, y=y, shared=True, **geo)
+    f = psb.sample_filter(q, S, seed=3, layer_id=4).view(oc, cin, 3, 3).double().cpu()
+    for i in {0, n // 2, n - 1}:
+        assert torch.equal(acc[i:i + 1].cpu().double(), torch.nn.functional.conv2d(x[i:i + 1].double().cpu(), f, padding=1)), i
+    res = {}
+    if residual == "f32":
+        res = dict(res_f32=torch.randn((n, oc, h, w), generator=gen, device="cuda"))
+    elif residual == "i8":
+        res = dict(res_i8=(torch.rand((n, oc, h, w), generator=gen, device="cuda") * 255 - 128).to(torch.int8), res_step=0.01)
+    for relu, lo in ((True, 0), (False, -128), (True, -5)):
+        want = psb.requantize(y, 30.0, relu=relu, lo=lo, **res)
+        got = psb.conv2d_requant(q, x, 30.0, S=S, relu=relu, lo=lo, shared=True, want_acc=False, **geo, **res)
+        assert torch.equal(got, want)
+
+    def blocked(t):
+        cb = (t.shape[1] + 31) // 32
+        p = torch.zeros((n, cb * 32, h, w), dtype=t.dtype, device="cuda")
+        p[:, :t.shape[1]] = t
+        return p.view(n, cb, 32, h, w).permute(0, 3, 1, 4, 2).contiguous()
+    layout = psb.BLOCKED_IN | psb.BLOCKED_OUT
+    if residual == "i8":
+        res = dict(res_i8=blocked(res["res_i8"]), res_step=0.01)
+        layout |= psb.BLOCKED_RES
+    want = blocked(psb.requantize(y, 30.0, **({} if residual is None else dict(res_f32=res["res_f32"]) if residual == "f32" else
+                                              dict(res_i8=res["res_i8"].permute(0, 2, 4, 1, 3).reshape(n, -1, h, w)[:, :oc].contiguous(), res_step=0.01))))
+    got = psb.conv2d_shared_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, S, layout=layout, **geo, **res)
+    assert torch.equal(got, want)
+    # two budget levels in one launch: a pixel's value is that of a call with its own sample count
+    budget = torch.where(torch.rand((n, h, w), generator=gen, device="cuda") < 0.4, 2 * S, S).to(torch.uint8)
+    budget[:, 0, 0] = S // 2                       # below every level
+    both = [psb.conv2d_shared_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, s, layout=layout, **geo, **res) for s in (S, 2 * S)]
+    got = psb.conv2d_shared_budget_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, budget, (S, 2 * S), layout=layout, **geo, **res)
+    at = budget.view(n, h, 1, w, 1).expand_as(got)
+    assert torch.equal(torch.where(at == S, both[0], torch.where(at == 2 * S, both[1], got)), got)
+
