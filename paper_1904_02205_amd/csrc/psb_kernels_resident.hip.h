@@ -463,17 +463,23 @@ inline bool resident_plan(const SharedParams& p, int planes, int n_cus, Resident
             const int64_t oc_tiles = (n_oc16 + (1 << log_wo) - 1) >> log_wo;
             for (int ng : {4, 7, 13}) {
                 if (ng > 7 && (log_wk > 0 || p.n_seg > 0)) continue;         // (segments would spill)
-                // the fewest rounds of one workgroup per CU, and inside them the smallest equal parts
+                // The fewest rounds of one workgroup per CU, and inside them the smallest equal parts.  Not more than two: nothing of a
+                // round lies under the next one, which the kernels of two workgroups per CU do better (384->96 at 28x95, batch 16,
+                // five rounds: 64.6 us against 40.2; two rounds 0.95 to 1.4 times as fast).
                 const int64_t most = 16 * ng;
                 int64_t rounds = std::max<int64_t>(1, ((npix + (most << log_wp) - 1) / (most << log_wp) * oc_tiles + n_cus - 1) / n_cus);
                 int64_t part = 0, px_tiles = 0;
-                for (;; ++rounds) {
+                for (; rounds <= 2; ++rounds) {
                     const int64_t tiles = rounds * n_cus / oc_tiles;
                     if (tiles == 0) continue;
                     part = (((npix + tiles - 1) / tiles + (1 << log_wp) - 1) >> log_wp);
                     part = (part + 3) / 4 * 4;
                     if (part <= most) break;
                 }
+                // microseconds of a round: start and end, matrix instructions of two waves per SIMD, the end of a wave; then the window
+                const double least_us = rounds * (4.0 + (double)((steps + (1 << log_wk) - 1) >> log_wk) * ng * planes * 2 * 16 / 2400.0 / 0.7 +
+                                                  0.15 * ng / (1 << log_wk) + 0.05 * ng * (log_wk > 0));
+                if (rounds > 2 || least_us >= best_us) continue;
                 px_tiles = (npix + (part << log_wp) - 1) / (part << log_wp);
                 const int64_t slots = resident_slots(part << log_wp, p.tH, p.tW);
                 const int64_t pad = (slots + 15) / 16 * 16;
@@ -484,13 +490,7 @@ inline bool resident_plan(const SharedParams& p, int planes, int n_cus, Resident
                 const bool stage_res = ng > 7 && p.rq.x_out && p.rq.res_i8 && p.rq.res_blocked && ((uintptr_t)p.rq.res_i8 & 15u) == 0 && res_at + res <= kResidentLds;
                 const int64_t lds = stage_res ? res_at + res : res_at;
                 if (slots > kResidentSlots || lds > kResidentLds) continue;
-                // More than two rounds: nothing of a round lies under the next one, which the kernels of two workgroups per CU
-                // do better (384->96 at 28x95, batch 16, five rounds: 64.6 us against 40.2; two rounds 0.95 to 1.4 times as fast).
-                if (rounds > 2) continue;
-                if (px_tiles * oc_tiles >= (1ll << 31)) continue;
-                // microseconds of a round: start and end, matrix instructions of two waves per SIMD, the end of a wave
-                const double us = rounds * (4.0 + (double)((steps + (1 << log_wk) - 1) >> log_wk) * ng * planes * 2 * 16 / 2400.0 / 0.7 +
-                                            0.15 * ng / (1 << log_wk) + 0.05 * ng * (log_wk > 0) + (double)window / 60000.0);
+                const double us = least_us + rounds * (double)window / 60000.0;
                 if (us < best_us) {
                     best_us = us;
                     best.log_wo = log_wo; best.log_wp = log_wp; best.log_wk = log_wk; best.ng = ng; best.part = (int)part;

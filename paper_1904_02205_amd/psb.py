@@ -5,6 +5,7 @@ libpsb_hip.so.  PyTorch supplies device memory (tensor.data_ptr()) and the strea
 There is no fallback: if the library is missing or a call fails, PsbError is raised.
 """
 import ctypes as C
+import functools
 import os
 
 import torch
@@ -128,8 +129,15 @@ def _check(rc, where):
         raise PsbError(rc, where)
 
 
+# a small call is bound by what happens here: the stream's address without a Stream object around it, where torch has it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Address of the current stream of the current device."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ptr(t, dtype, name):
@@ -137,12 +145,12 @@ def _ptr(t, dtype, name):
         return None
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype):
         raise TypeError(f"{name}: expected a contiguous CUDA tensor of dtype {dtype}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _expect(t, shape, name):
     """The library cannot see tensor shapes behind the raw pointers it is given: a wrong one is refused here."""
-    if t is not None and tuple(t.shape) != tuple(shape):
+    if t is not None and t.shape != shape and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
@@ -207,6 +215,11 @@ def profile_read():
 
 def conv2d_out_dims(wshape, geom):
     """wshape = (oc, cin, kh, kw, groups); geom = (n, h, w, stride_h, stride_w, pad_h, pad_w)."""
+    return _out_dims(tuple(wshape), tuple(geom))
+
+
+@functools.lru_cache(maxsize=256)
+def _out_dims(wshape, geom):
     oh, ow = C.c_int32(0), C.c_int32(0)
     rc = lib().psb_conv2d_out_dims(C.byref(WShape(*wshape)), C.byref(ConvGeom(*geom)), C.byref(oh), C.byref(ow))
     _check(rc, "psb_conv2d_out_dims")
@@ -334,8 +347,8 @@ def conv2d_requant(q, x, inv_step, S=None, budget_to=None, stride=(1, 1), pad=(0
     _expect_layer_io(q, shape, acc=acc, y=y, mult=mult, bias=bias, budget_to=budget_to, x_out=x_out, res_f32=res_f32,
                      res_i8=res_i8)
     rq = Requant(1 if relu else 0, inv_step, lo, hi,
-                 None if res_f32 is None else _ptr(res_f32, torch.float32, "res_f32").value,
-                 None if res_i8 is None else _ptr(res_i8, torch.int8, "res_i8").value, res_step)
+                 _ptr(res_f32, torch.float32, "res_f32"),
+                 _ptr(res_i8, torch.int8, "res_i8"), res_step)
     rc = lib().psb_conv2d_requant(q._h, _ptr(x, torch.int8, "x"), C.byref(g), 0 if S is None else S,
                                   _ptr(budget_to, torch.uint8, "budget_to"), seed, layer_id,
                                   _ptr(acc, torch.int32, "acc"), _ptr(y, torch.float32, "y"),
@@ -357,8 +370,8 @@ def conv2d_requant_static(q, x, inv_step, x_out, S=None, budget_to=None, stride=
     _expect_layer_io(q, shape, y=y, mult=mult, bias=bias, budget_to=budget_to, x_out=x_out, res_f32=res_f32,
                      res_i8=res_i8)
     rq = Requant(1 if relu else 0, inv_step, lo, hi,
-                 None if res_f32 is None else _ptr(res_f32, torch.float32, "res_f32").value,
-                 None if res_i8 is None else _ptr(res_i8, torch.int8, "res_i8").value, res_step)
+                 _ptr(res_f32, torch.float32, "res_f32"),
+                 _ptr(res_i8, torch.int8, "res_i8"), res_step)
     rc = lib().psb_conv2d_requant_static(q._h, _ptr(x, torch.int8, "x"), C.byref(g), 0 if S is None else S,
                                          _ptr(budget_to, torch.uint8, "budget_to"), seed, layer_id,
                                          _ptr(y, torch.float32, "y"), _ptr(mult, torch.float32, "mult"),
@@ -399,8 +412,8 @@ def conv2d_shared_requant_blocked(q, x, x_shape, inv_step, S, stride=(1, 1), pad
                      x_out_shape=blocked_shape(n, oc, oh, ow) if layout & BLOCKED_OUT else None, res_f32=res_f32,
                      res_i8=res_i8, res_i8_shape=blocked_shape(n, oc, oh, ow) if layout & BLOCKED_RES else None)
     rq = Requant(1 if relu else 0, inv_step, lo, hi,
-                 None if res_f32 is None else _ptr(res_f32, torch.float32, "res_f32").value,
-                 None if res_i8 is None else _ptr(res_i8, torch.int8, "res_i8").value, res_step)
+                 _ptr(res_f32, torch.float32, "res_f32"),
+                 _ptr(res_i8, torch.int8, "res_i8"), res_step)
     rc = lib().psb_conv2d_shared_requant_blocked(q._h, _ptr(x, torch.int8, "x"), C.byref(g), S, seed, layer_id,
                                                  _ptr(y, torch.float32, "y"), _ptr(mult, torch.float32, "mult"),
                                                  _ptr(bias, torch.float32, "bias"), C.byref(rq),
@@ -441,8 +454,8 @@ def conv2d_shared_budget_requant_blocked(q, x, x_shape, inv_step, budget_to, lev
         raise ValueError("budget_to: a budget map is required")
     lv, n_lv = _levels_array(levels)
     rq = Requant(1 if relu else 0, inv_step, lo, hi,
-                 None if res_f32 is None else _ptr(res_f32, torch.float32, "res_f32").value,
-                 None if res_i8 is None else _ptr(res_i8, torch.int8, "res_i8").value, res_step)
+                 _ptr(res_f32, torch.float32, "res_f32"),
+                 _ptr(res_i8, torch.int8, "res_i8"), res_step)
     rc = lib().psb_conv2d_shared_budget_requant_blocked(
         q._h, _ptr(x, torch.int8, "x"), C.byref(g), _ptr(budget_to, torch.uint8, "budget_to"), lv, n_lv, seed, layer_id,
         _ptr(y, torch.float32, "y"), _ptr(mult, torch.float32, "mult"), _ptr(bias, torch.float32, "bias"), C.byref(rq),
