@@ -708,9 +708,10 @@ __device__ __forceinline__ void tile_epilogue(const SharedParams& p, v16i (&acc)
             }
             // The integers of requantize_one() with fewer instructions (32 outputs per lane make this loop a third
             // of a short layer's time): the bias and the residual are added unconditionally (they are 0.0 when
-            // absent; that can only turn a -0.0 into +0.0, which rounds to the same integer), the ReLU gate and
-            // the clamp are max/min (a NaN ends at lo either way, as inv_step is not negative - checked by the
-            // host), and the conversion adds 1.5 * 2^23, which leaves the two's-complement byte in the low bits.
+            // absent; that can only turn a -0.0 into +0.0, which rounds to the same integer), the ReLU gate is a maximum, the
+            // clamp comes before the rounding (its bounds are integers) and is the median of three (a NaN ends at lo either
+            // way, as inv_step is not negative - checked by the host), and adding 1.5 * 2^23 rounds to the nearest integer, ties
+            // to even, and leaves its two's-complement byte in the low bits.
             const float floor_t = relu ? 0.0f : -__builtin_huge_valf();
 #pragma unroll
             for (int qq = 0; qq < 4; ++qq) {
@@ -722,8 +723,7 @@ __device__ __forceinline__ void tile_epilogue(const SharedParams& p, v16i (&acc)
                     float t = __fmul_rn(__fmul_rn(__int2float_rn((int32_t)sum_of(h, q)), s_mult[ocl]), inv_s);
                     t = __fadd_rn(__fadd_rn(t, s_bias[ocl]), res[q]);
                     t = __builtin_fmaxf(t, floor_t);
-                    float v = rintf(__fmul_rn(t, p.rq.inv_step));
-                    v = __builtin_fminf(__builtin_fmaxf(v, p.rq.lo), p.rq.hi);
+                    const float v = __builtin_amdgcn_fmed3f(__fmul_rn(t, p.rq.inv_step), p.rq.lo, p.rq.hi);
                     w[i] = __float_as_uint(__fadd_rn(v, 12582912.0f));
                     if (!FULL && oc_first + 8 * qq + i >= p.OC) w[i] = 0;   // padding channels of the blocked layout
                 }

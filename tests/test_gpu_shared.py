@@ -403,6 +403,7 @@ def test_window_of_all_channels(psb, n, cin, oc, hw, S, residual):
     res = {}
     if residual == "f32":
         res = dict(res_f32=torch.randn((n, oc, h, w), generator=gen, device="cuda"))
+        res["res_f32"].view(-1)[:6] = torch.tensor([float("nan"), float("inf"), -float("inf"), -0.0, 1e30, -1e30])
     elif residual == "i8":
         res = dict(res_i8=(torch.rand((n, oc, h, w), generator=gen, device="cuda") * 255 - 128).to(torch.int8), res_step=0.01)
     for relu, lo in ((True, 0), (False, -128), (True, -5)):
