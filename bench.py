@@ -217,10 +217,10 @@ def prepare(workload, args, torch, psb, dev):
         geom = (L.x.shape[0], L.x.shape[2], L.x.shape[3]) + L.stride + L.pad
         name = KERNEL_NAMES[psb.query_mapping(q, geom, S=L.S, budget_map=L.budget_to is not None)]
         if shared:
-            # matrix-core contraction: 3 x 3 / stride 1 / padding 1 layers normally run in k_conv3x3_window (both operands
-            # from LDS), the others in k_conv_shared_mfma; the library's timer covers whichever it launched
+            # matrix-core contraction: 3 x 3 / stride 1 / padding 1 layers normally run in k_conv3x3_resident or
+            # k_conv3x3_window (window in LDS), the others in k_conv_shared_mfma; the library's timer covers whichever it launched
             window = L.w.shape[2:] == (3, 3) and L.stride == (1, 1) and L.pad == (1, 1)
-            name = ("k_conv3x3_window" if window else "k_conv_shared_mfma") if L.groups == 1 and args.mapping != 1 \
+            name = ("k_conv3x3_resident" if window else "k_conv_shared_mfma") if L.groups == 1 and args.mapping != 1 \
                 else "k_conv_shared_direct"
             a, b = shared_ops(L, q)
             P.mfma_ops += a

@@ -44,3 +44,9 @@ def test_persistent_shared_kernel_without_segments_does_not_spill(tmp_path):
     for planes in (1, 2, 3):
         for half_tiles in (1, 2):
             assert found["<%d, 1, %d, false>" % (planes, half_tiles)] == (0, 0)
+
+
+def test_resident_window_kernel_does_not_spill(tmp_path):
+    """Two and three digit planes, both kinds of output, 4, 7 and 13 groups of pixels (13 without segments of the sample axis)."""
+    found = _resources(tmp_path, "psb_kernels_resident.hip.h", "k_conv3x3_resident", 20)
+    assert len(found) == 20 and set(found.values()) == {(0, 0)}, found
