@@ -11,10 +11,10 @@
 //
 // Time stamps of a workgroup, batch 32, us - 64->64 at 56x56 (13 groups): staged 3.3, loop of the older / younger four waves
 // 5.9 / 8.2, end of a wave 3.0; 128->128 at 28x28 and 256->256 at 14x14 (7 groups): 2.1, 7.0 / 9.2, 2.4.  The matrix instructions alone
-// need 5.9 and 6.3 us of the loop at the 1.9 GHz the chip holds in it (2.4 without them).  A launch 20.5 -> 15, 17 -> 13.8 us and
-// 17.5 -> 14 (k_conv3x3_window against this kernel, from the time of a whole network pass).  Without effect: weights or
-// activations left out of the loop (-0.7 us), wave priorities, the residual requested a few steps before the end (it
-// delays the weights behind it by as much).
+// need 5.9 and 6.3 us of the loop at the 1.9 GHz the chip holds in it (2.4 without them).  A launch, in the kernel trace of a
+// whole network pass: 23.3 us in k_conv3x3_window, 17.7 here (64->64); 18.6 and 16.1 (the later stages).  Without effect: weights
+// and activations left out of the loop (-0.7 to -1.1 us), wave priorities, the residual requested a few steps before the end
+// (it delays the weights behind it by as much).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
