@@ -113,10 +113,11 @@ __device__ __forceinline__ void finish_tile(const SharedParams& p, const uint32_
     if (p.y) each([&](int g, int i, uint32_t o) { p.y[o] = rescaled(g, i); });
     if constexpr (OUT == kOutRequant) {
         // words of four channels of a pixel (blocked), or of four pixels of one channel ([N][OC][OH][OW]; see tile_epilogue)
-        // The integers of requantize_one() as in tile_epilogue with fewer instructions: the gate is a lower bound of zero (the
-        // host keeps the scales for which it is not away), the bounds are integers, so clamping before rounding gives the
-        // same (a NaN ends at the lower bound: the minimum of three), and adding 1.5 * 2^23 rounds to the nearest integer, ties to even.
-        const float lo = p.rq.relu ? __builtin_fmaxf(p.rq.lo, 0.0f) : p.rq.lo;
+        // The integers of requantize_one() as in tile_epilogue with fewer instructions: the gate is a lower bound of zero, or of hi
+        // where that is below zero and every result is hi (the host keeps the scales for which it is not away), the bounds are
+        // integers, so clamping before rounding gives the same (a NaN ends at the lower bound: the minimum of three), and adding
+        // 1.5 * 2^23 rounds to the nearest integer, ties to even.
+        const float lo = p.rq.relu ? __builtin_fminf(__builtin_fmaxf(p.rq.lo, 0.0f), p.rq.hi) : p.rq.lo;
         uint32_t word[NG];
         auto requantised = [&](auto res) {             // res(g, i): the residual
 #pragma unroll

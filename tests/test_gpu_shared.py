@@ -406,10 +406,12 @@ def test_window_of_all_channels(psb, n, cin, oc, hw, S, residual):
         res["res_f32"].view(-1)[:6] = torch.tensor([float("nan"), float("inf"), -float("inf"), -0.0, 1e30, -1e30])
     elif residual == "i8":
         res = dict(res_i8=(torch.rand((n, oc, h, w), generator=gen, device="cuda") * 255 - 128).to(torch.int8), res_step=0.01)
-    for relu, lo in ((True, 0), (False, -128), (True, -5)):
-        want = psb.requantize(y, 30.0, relu=relu, lo=lo, **res)
-        got = psb.conv2d_requant(q, x, 30.0, S=S, relu=relu, lo=lo, shared=True, want_acc=False, **geo, **res)
-        assert torch.equal(got, want)
+    # (a gate with bounds below zero, where every result is the upper one, and scales that turn infinities or zeros into NaN among them)
+    for relu, lo, hi, inv in ((True, 0, 127, 30.0), (False, -128, 127, 30.0), (True, -5, 127, 30.0), (True, -5, -3, 30.0), (True, -1, -1, 30.0),
+                              (True, -100, -5, 30.0), (True, -128, -1, 0.0), (True, -9, -4, float("inf")), (False, -9, -4, 30.0)):
+        want = psb.requantize(y, inv, relu=relu, lo=lo, hi=hi, **res)
+        got = psb.conv2d_requant(q, x, inv, S=S, relu=relu, lo=lo, hi=hi, shared=True, want_acc=False, **geo, **res)
+        assert torch.equal(got, want), (relu, lo, hi, inv)
 
     def blocked(t):
         cb = (t.shape[1] + 31) // 32
