@@ -510,10 +510,8 @@ template <int P, int OUT, int NG, bool SEG>
 inline bool launch_resident_one(const SharedParams& p, const ResidentPlan& plan, hipStream_t stream)
 {
     auto kernel = k_conv3x3_resident<P, OUT, NG, SEG>;
-    // more than 64 KB of dynamic LDS has to be asked for once
-    static const bool usable = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   kResidentLds) == hipSuccess;
-    if (!usable) return false;
+    static LdsGrant grant;
+    if (!grant(kResidentLds, LdsOf{reinterpret_cast<const void*>(kernel)})) return false;
     const unsigned wgs = plan.px_tiles * plan.oc_tiles;
     hipLaunchKernelGGL(kernel, dim3(plan.by_channels ? wgs : (wgs + 7) / 8 * 8), dim3(kResidentWaves * 64), (size_t)plan.lds_bytes, stream, p, plan);
     return true;

@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "psb_kernels.hip.h"
+#include "psb_device_lds.h"
 #include "psb_kernels_oc.hip.h"
 
 namespace psb {
@@ -1449,6 +1450,14 @@ inline WindowPlan window_plan(const SharedParams& p, int planes, int half_tiles,
     return w;
 }
 
+// LdsGrant's runtime for one kernel
+struct LdsOf {
+    const void* kernel;
+    bool device(int* d) const { return hipGetDevice(d) == hipSuccess; }
+    bool request(size_t bytes) const { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess; }
+    void clear_error() const { (void)hipGetLastError(); }
+};
+
 template <int P, int OUT, int HT, int TEAMS, int WS>
 inline bool launch_window_one(const SharedParams& p, dim3 grid, hipStream_t stream)
 {
@@ -1456,10 +1465,8 @@ inline bool launch_window_one(const SharedParams& p, dim3 grid, hipStream_t stre
     constexpr size_t lds = (size_t)TEAMS * (kAregs + 2 * WS) * 4096;
     static_assert(TEAMS == 1 || (size_t)(TEAMS - 1) * 4 * HT * P * 4 * 64 * 16 <= lds, "the teams' sums must fit the operand area");
     auto kernel = k_conv3x3_window<P, OUT, HT, TEAMS, WS>;
-    // more than 64 KB of dynamic LDS has to be asked for once
-    static const bool usable = lds <= 65536 || hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
-    if (!usable) return false;
+    static LdsGrant grant;
+    if (!grant(lds, LdsOf{reinterpret_cast<const void*>(kernel)})) return false;
     hipLaunchKernelGGL(kernel, grid, dim3(256 * TEAMS), lds, stream, p);
     return true;
 }
