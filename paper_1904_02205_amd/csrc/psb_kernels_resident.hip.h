@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(kResidentWaves * 64, 2) k_conv3x3_resident(con
 {
     constexpr bool kStageRes = OUT == kOutRequant && NG > 7;
     extern __shared__ v4i win[];                   // entries of the tile's pixels; [chunk of 64 channels][quarter of 16][slot]; zeros
-    __shared__ float s_mult[128], s_bias[128];
+    __shared__ __align__(16) float s_mult[128], s_bias[128];            // read four at a time
     int8_t* const lds = reinterpret_cast<int8_t*>(win);
     PixelEntry* const entries = reinterpret_cast<PixelEntry*>(win);      // [pixel of the tile]
 
