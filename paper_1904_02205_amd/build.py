@@ -19,6 +19,7 @@ DEPS = [SRC,
         os.path.join(HERE, "csrc", "psb_philox.hip.h"),
         os.path.join(HERE, "csrc", "psb_workspace.h"),
         os.path.join(HERE, "csrc", "psb_device_lds.h"),
+        os.path.join(HERE, "csrc", "psb_resident_plan.h"),
         os.path.join(HERE, "csrc", "psb_choice.h"),
         os.path.join(os.path.dirname(HERE), "include", "psb.h")]
 
