@@ -250,7 +250,7 @@ int resident_workgroups()
 // The contraction of a shared-filter call on the matrix cores.
 void launch_contraction(const psb::SharedParams& p, int planes, int half_tiles, hipStream_t stream)
 {
-    if (psb::launch_conv3x3_resident(p, planes, psb::oc_lane_cus(), stream)) return;
+    if (psb::launch_conv3x3_resident(p, planes, half_tiles, psb::oc_lane_cus(), stream)) return;
     psb::launch_conv_shared_mfma(p, planes, resident_workgroups(), half_tiles, stream);
 }
 

@@ -414,14 +414,14 @@ __global__ void __launch_bounds__(kResidentWaves * 64, 2) k_conv3x3_resident(con
 }
 
 // The cut of a call, or false: not for this kernel.
-inline bool resident_plan(const SharedParams& p, int planes, int n_cus, ResidentPlan& plan)
+inline bool resident_plan(const SharedParams& p, int planes, int half_tiles, int n_cus, ResidentPlan& plan)
 {
     if (p.tKH != 3 || p.tKW != 3 || p.t_stride_h != 1 || p.t_stride_w != 1 || p.t_pad_h != 1 || p.t_pad_w != 1 ||
         p.OH != p.tH || p.OW != p.tW || p.ksplit != 1 || p.masked || planes < 2 || planes > 3)
         return false;
     // (a gate below which the bounds reach, with a scale that turns zero or infinity into NaN: see finish_tile)
     if (p.rq.x_out && p.rq.relu && p.rq.lo < 0.0f && !(p.rq.inv_step > 0.0f && p.rq.inv_step <= 3.0e38f)) return false;
-    const ResidentLayer l{(int64_t)p.N * p.OH * p.OW, p.OH, p.OW, p.OC, p.C_pad >> 5, planes, p.n_seg,
+    const ResidentLayer l{(int64_t)p.N * p.OH * p.OW, p.OH, p.OW, p.OC, p.C_pad >> 5, planes, p.n_seg, half_tiles,
                           p.rq.x_out && p.rq.res_i8 && p.rq.res_blocked && ((uintptr_t)p.rq.res_i8 & 15u) == 0};
     if (!resident_plan(l, n_cus, plan)) return false;
     plan.inv_oc_tiles = inverse_of(plan.oc_tiles);
@@ -440,10 +440,10 @@ inline bool launch_resident_one(const SharedParams& p, const ResidentPlan& plan,
 }
 
 // False: not launched, the call goes to the other kernels.
-inline bool launch_conv3x3_resident(const SharedParams& p, int planes, int n_cus, hipStream_t stream)
+inline bool launch_conv3x3_resident(const SharedParams& p, int planes, int half_tiles, int n_cus, hipStream_t stream)
 {
     ResidentPlan plan;
-    if (!resident_plan(p, planes, n_cus, plan)) return false;
+    if (!resident_plan(p, planes, half_tiles, n_cus, plan)) return false;
     auto with_seg = [&](auto p_c, auto out_c, auto ng_c) {
         constexpr int P = decltype(p_c)::value, OUT = decltype(out_c)::value, NG = decltype(ng_c)::value;
         return p.n_seg > 0 ? launch_resident_one<P, OUT, NG, true>(p, plan, stream) : launch_resident_one<P, OUT, NG, false>(p, plan, stream);

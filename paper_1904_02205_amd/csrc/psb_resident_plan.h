@@ -35,6 +35,7 @@ struct ResidentLayer {
     int H, W, OC;
     int blocks;                             // of 32 input channels
     int planes, n_seg;                      // digit planes (2 or 3); segments of the sample axis, 0: no announced levels
+    int half_tiles;                         // of a wave in the kernels that take the layer otherwise, shared_half_tiles()
     bool residual;                          // a residual that a workgroup can stage: int8, blocked, on a 16-byte address
 };
 
@@ -66,7 +67,7 @@ inline bool resident_plan(const ResidentLayer& l, int n_cus, ResidentPlan& best)
                 if (ng > 7 && (log_wk > 0 || l.n_seg > 0)) continue;         // (segments would spill)
                 // The fewest rounds of one workgroup per CU, and inside them the smallest equal parts.  Not more than two: nothing of a
                 // round lies under the next one, which the kernels of two workgroups per CU do better (384->96 at 28x95, batch 16,
-                // five rounds: 64.6 us against 40.2; two rounds 0.95 to 1.4 times as fast).
+                // five rounds: 64.6 us against 40.2).
                 const int64_t most = 16 * ng;
                 int64_t rounds = std::max<int64_t>(1, ((npix + (most << log_wp) - 1) / (most << log_wp) * oc_tiles + n_cus - 1) / n_cus);
                 int64_t part = 0, px_tiles = 0;
@@ -102,6 +103,23 @@ inline bool resident_plan(const ResidentLayer& l, int n_cus, ResidentPlan& best)
             }
         }
     if (best_us >= 1e30) return false;
+    // Equal shares of a layer need not be whole groups of pixels or blocks of channels, and LDS may not hold the window of larger
+    // ones: then a part of the matrix instructions multiplies padding.  What counts is their number on the busiest CU, against that of
+    // the kernels of 32 channels x 128 or 256 pixels.  Random layers, times as fast as in those, by the quotient theirs / ours: one
+    // round, below 0.7 0.84 to 1.10 (five layers, four of them slower; 768->128 at 56x56, one image, parts of 16 pixels in four groups:
+    // 35.6 us against 29.7), from 0.7 on 0.95 to 2.5 (6234 layers, mean 1.33); two rounds, below 0.9 0.81 to 1.10 (53 layers, 40 of them
+    // slower: 256->128 at 10x93, batch 64, parts of 120 pixels in thirteen groups: 77.0 us against 62.1), from 0.9 on 0.94 to 1.38 (194
+    // layers, mean 1.14) ...
+    const int64_t rounds = ((int64_t)best.px_tiles * best.oc_tiles + n_cus - 1) / n_cus, wg_pixels = 128 * l.half_tiles;
+    const int64_t ours = rounds * kResidentWaves * best.ng * ((steps + (1 << best.log_wk) - 1) >> best.log_wk);
+    const int64_t their_wgs = (npix + wg_pixels - 1) / wg_pixels * (n_oc16 / 2);
+    const int64_t theirs = (their_wgs + n_cus - 1) / n_cus * 8 * l.half_tiles * 9 * l.blocks;
+    if (10 * theirs < (rounds == 1 ? 7 : 9) * ours) return false;
+    // ... but for two forms that two rounds do not pay for: parts of the reduction that meet in LDS, which the second round waits for
+    // (69 layers, 0.89 to 1.23, mean 1.02, a third of them slower; 256->16 at 14x106, batch 64: 29.3 us against 26.0), and four groups of
+    // two planes, whose operands take all that L2 and LDS deliver to a CU (twelve layers, 0.86 to 0.99; 640->512 at 56x56, two images:
+    // 121.9 us against 108.2).
+    if (rounds > 1 && (best.log_wk > 0 || (best.ng == 4 && planes == 2))) return false;
     const int64_t n_steps = (int64_t)9 * l.blocks;
     best.by_channels = best.oc_tiles % 8 == 0 && (int64_t)n_oc16 * 16 * n_steps * 32 * planes > 2 * npix * 32 * l.blocks;
     return true;

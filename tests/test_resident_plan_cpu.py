@@ -25,6 +25,7 @@ int main(int argc, char** argv)
         ResidentLayer l{};
         l.npix = (int64_t)N * H * W; l.H = H; l.W = W; l.OC = OC; l.blocks = (C + 31) / 32;
         l.planes = 2 + rng() % 2; l.n_seg = rng() % 3 ? 0 : 2; l.residual = rng() % 2;
+        l.half_tiles = (l.npix + 63) / 64 * ((OC + 31) / 32) <= 1024 ? 1 : 2;
         if (l.npix > 300000) continue;
         ResidentPlan r{};
         if (!resident_plan(l, 256, r)) continue;
@@ -70,3 +71,50 @@ def test_every_cut_stays_inside_what_it_reserves(tmp_path):
     for seed in (1, 2):
         r = subprocess.run([exe, str(seed), "20000"], capture_output=True, text=True)
         assert r.returncode == 0, r.stdout
+
+
+# stdin: layers, one a line; prints whether the kernel takes them on a device with 256 CUs, and its cut
+CHOICE = r"""
+#include "psb_resident_plan.h"
+#include <cstdio>
+int main()
+{
+    int n, c, h, w, oc, planes, n_seg, residual;
+    while (std::scanf("%d %d %d %d %d %d %d %d", &n, &c, &h, &w, &oc, &planes, &n_seg, &residual) == 8) {
+        const int64_t npix = (int64_t)n * h * w;
+        const int half_tiles = (npix + 63) / 64 * ((oc + 31) / 32) <= 1024 ? 1 : 2;
+        psb::ResidentLayer l{npix, h, w, oc, (c + 31) / 32, planes, n_seg, half_tiles, residual != 0};
+        psb::ResidentPlan r{};
+        const bool taken = psb::resident_plan(l, 256, r);
+        std::printf("%d %d %d %d\n", taken, r.ng, 1 << r.log_wk, (int)((r.px_tiles * r.oc_tiles + 255) / 256));
+    }
+}
+"""
+
+# images, input channels, height, width, output channels, digit planes, levels, int8 residual: us in this kernel and in the others
+# (of a call with its sampling, or as noted), and the form of the cut (pixel groups, reduction parts, rounds)
+MEASURED = [
+    ((64, 256, 10, 93, 128, 3, 0, 1), 76.95, 62.14, (13, 1, 2)),       # parts of 120 pixels in groups of 208
+    ((16, 512, 112, 22, 96, 2, 0, 0), 67.96, 55.01, (7, 1, 2)),
+    ((32, 160, 56, 56, 96, 3, 0, 0), 63.98, 52.57, (13, 1, 2)),
+    ((1, 768, 56, 56, 128, 2, 0, 0), 35.60, 29.74, (4, 1, 1)),         # parts of 16 pixels, the window of more does not fit
+    ((16, 64, 56, 65, 64, 3, 0, 0), 24.91, 22.46, (13, 1, 1)),
+    ((4, 768, 28, 45, 512, 2, 0, 1), 78.24, 67.46, (4, 1, 2)),         # four groups of two planes, two rounds
+    ((2, 640, 56, 56, 512, 2, 2, 0), 121.90, 108.15, (4, 1, 2)),
+    ((64, 256, 14, 106, 16, 2, 0, 1), 29.32, 26.04, (7, 2, 2)),        # the reduction in parts, two rounds
+    ((8, 384, 80, 80, 48, 2, 0, 1), 38.31, 36.13, (7, 2, 2)),
+    ((32, 64, 56, 56, 64, 3, 0, 1), 15.0, 20.5, (13, 1, 1)),              # a launch, from the time of a network pass; this line and the next
+    ((32, 128, 28, 28, 128, 3, 0, 0), 13.8, 17.0, (7, 1, 1)),
+    ((8, 64, 56, 88, 128, 3, 0, 1), 19.27, 28.70, (13, 1, 1)),
+    ((64, 128, 28, 28, 200, 3, 0, 0), 47.89, 51.18, (13, 1, 2)),
+    ((2, 256, 56, 72, 512, 3, 0, 0), 35.14, 39.14, (4, 1, 2)),         # four groups of three planes
+]
+
+
+def test_layers_go_to_the_faster_kernels(tmp_path):
+    out = subprocess.run([build(tmp_path, CHOICE)], input="\n".join(" ".join(map(str, m[0])) for m in MEASURED), capture_output=True, text=True,
+                         check=True).stdout.split("\n")
+    for (layer, here, there, form), line in zip(MEASURED, out):
+        taken, *cut = map(int, line.split())
+        assert tuple(cut) == form, (layer, line)
+        assert taken == (here < there), (layer, line)
