@@ -462,12 +462,35 @@ int psb_query_mapping(const psb_weights_t* q, const psb_conv_geom* geom);
  * 0 before the first. */
 int psb_last_mapping(void);
 
+/* Shared-filter mode, for tests and benchmarks: the kernel and the shape of the last contraction that the calling thread launched (or
+ * captured); kernel = 0 before the first.  Members that the kernel does not have are 0. */
+enum {
+    PSB_SHARED_DIRECT = 1,      /* int32 filter */
+    PSB_SHARED_DEPTHWISE = 2,   /* int32 filter, 3 x 3 depthwise */
+    PSB_SHARED_MFMA = 3,        /* matrix cores, operands from memory */
+    PSB_SHARED_PERSISTENT = 4,  /* ... the weights of a workgroup in LDS, many pixel tiles */
+    PSB_SHARED_WINDOW = 5,      /* ... 3 x 3: the input window in LDS, 32 channels at a time */
+    PSB_SHARED_RESIDENT = 6     /* ... 3 x 3: the input window in LDS, all channels */
+};
+typedef struct psb_shared_launch {
+    int32_t kernel;
+    int32_t planes;             /* digit planes */
+    int32_t half_tiles;         /* MFMA, PERSISTENT, WINDOW: 32 pixels each, of a wave */
+    int32_t teams;              /* WINDOW: teams of four waves that share the channel blocks */
+    int32_t by_channels;        /* WINDOW, RESIDENT: an XCD takes an eighth of the channels instead of the pixels */
+    int32_t pixel_groups;       /* RESIDENT, and all below: groups of 16 pixels compiled into a wave */
+    int32_t channel_waves, pixel_waves, reduction_waves;    /* the eight waves of a workgroup */
+    int32_t pixels_per_wave;    /* of its groups */
+    int32_t residual_staged;    /* the residual comes through LDS */
+} psb_shared_launch;
+int psb_last_shared_launch(psb_shared_launch* out);
+
 /* Shared-filter mode, host only (no device work; for tests): the number of 16-byte slots per half plane that the
- * 3 x 3 kernel with both operands in LDS reserves for the input window of one pixel tile (128 * half_tiles consecutive
+ * 3 x 3 kernel with 32 channels at a time in LDS (PSB_SHARED_WINDOW) reserves for the input window of one pixel tile (128 * half_tiles consecutive
  * output pixels, half_tiles = 1 or 2) of a layer with this geometry - an upper bound on
  *     vpos(last pixel) - vpos(first pixel) + 2 (w + 1) + 3,   vpos(n, oy, ox) = (n (h + 1) + oy) (w + 1) + ox,
  * over all tiles and batch sizes - or 0 when that kernel does not take the geometry (not 3 x 3 / stride 1 / padding 1,
- * or more than 512 slots) and the call runs in the plain matrix-core kernel.  SHAPE for non-positive sizes. */
+ * or more than 512 slots) and the call runs in another matrix-core kernel.  SHAPE for non-positive sizes. */
 int psb_shared_window_slots(int32_t kh, int32_t kw, const psb_conv_geom* geom, int32_t half_tiles);
 
 /* Timing of the sampling kernels, for benchmarks.  While enabled, every layer call

@@ -676,9 +676,11 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
                 while (channels > 2 && columns * ((p.OC + channels - 1) / channels) < 2048) channels /= 2;
                 const dim3 grid((unsigned)columns, (unsigned)((p.OC + channels - 1) / channels));
                 hipLaunchKernelGGL((psb::k_conv_shared_depthwise<3, 3>), grid, dim3(256), 0, stream, p, channels);
+                psb::tl_shared_launch = {psb::kLaunchDepthwise};
             } else {
                 const dim3 grid((unsigned)columns, (unsigned)p.OC);
                 hipLaunchKernelGGL(psb::k_conv_shared_direct, grid, dim3(256), 0, stream, p);
+                psb::tl_shared_launch = {psb::kLaunchDirect};
             }
         }
         if (timed) profile_end(stream, slot);
@@ -821,6 +823,15 @@ int psb_query_mapping(const psb_weights_t* q, const psb_conv_geom* geom)
 }
 
 int psb_last_mapping(void) { return tl_last_mapping; }
+
+int psb_last_shared_launch(psb_shared_launch* out)
+{
+    if (!out) return PSB_ERR_NULL;
+    const psb::SharedLaunch& l = psb::tl_shared_launch;
+    *out = {l.kernel, l.planes, l.half_tiles, l.teams, l.by_channels, l.pixel_groups, l.channel_waves, l.pixel_waves, l.reduction_waves,
+            l.pixels_per_wave, l.residual_staged};
+    return PSB_OK;
+}
 
 int psb_query_mapping_call(const psb_weights_t* q, const psb_conv_geom* geom, int32_t S, int32_t budget_map)
 {

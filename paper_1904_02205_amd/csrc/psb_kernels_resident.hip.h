@@ -436,6 +436,7 @@ inline bool launch_resident_one(const SharedParams& p, const ResidentPlan& plan,
     if (!grant(kResidentLds, LdsOf{reinterpret_cast<const void*>(kernel)})) return false;
     const unsigned wgs = plan.px_tiles * plan.oc_tiles;
     hipLaunchKernelGGL(kernel, dim3(plan.by_channels ? wgs : (wgs + 7) / 8 * 8), dim3(kResidentWaves * 64), (size_t)plan.lds_bytes, stream, p, plan);
+    tl_shared_launch = {kLaunchResident, P, 0, 0, plan.by_channels, NG, 1 << plan.log_wo, 1 << plan.log_wp, 1 << plan.log_wk, plan.part, plan.lds_res > 0};
     return true;
 }
 

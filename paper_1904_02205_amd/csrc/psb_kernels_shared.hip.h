@@ -89,6 +89,14 @@ struct SharedParams {
     int quad_res;              // ... res_i8
 };
 
+// The last contraction this thread launched, for psb_last_shared_launch() (psb_shared_launch in psb.h).
+struct SharedLaunch {
+    int kernel, planes, half_tiles, teams, by_channels;
+    int pixel_groups, channel_waves, pixel_waves, reduction_waves, pixels_per_wave, residual_staged;
+};
+enum { kLaunchDirect = 1, kLaunchDepthwise, kLaunchMfma, kLaunchPersistent, kLaunchWindow, kLaunchResident };
+inline thread_local SharedLaunch tl_shared_launch{};
+
 // Filter sampling: count and filter value of one weight; digit planes for the matrix cores.
 struct FilterJob {
     const uint32_t* packed;   // [OC][K]                         (int32 filter)
@@ -1510,7 +1518,10 @@ inline void launch_conv_shared_mfma(const SharedParams& p, int planes, int resid
         const bool done = p.masked ? launch_window_out<kOutPartial>(pw, planes, half_tiles, win, grid, stream)
                         : p.rq.x_out ? launch_window_out<kOutRequant>(pw, planes, half_tiles, win, grid, stream)
                                      : launch_window_out<kOutAcc>(pw, planes, half_tiles, win, grid, stream);
-        if (done) return;
+        if (done) {
+            tl_shared_launch = {kLaunchWindow, planes, half_tiles, win.teams, pw.xcd_by_channels};
+            return;
+        }
     }
     // worth it when a workgroup gets more than one tile: staging the whole block before the first matrix instruction
     // costs more than the chunked start of the plain kernel
@@ -1526,16 +1537,19 @@ inline void launch_conv_shared_mfma(const SharedParams& p, int planes, int resid
             const unsigned wgs1 = lds <= 36864 ? 2u * (unsigned)resident_wgs : 3u * (unsigned)resident_wgs / 2u;
             const unsigned fit1 = std::max(8u, wgs1 / n_ocb / 8u * 8u);
             const dim3 grid(std::min(fit1, columns1), n_ocb);
+            tl_shared_launch = {kLaunchPersistent, planes, 1};
             if (p.rq.x_out) launch_conv_shared_mfma_resident<kOutRequant, 1>(p, planes, grid, columns1, lds, stream);
             else launch_conv_shared_mfma_resident<kOutAcc, 1>(p, planes, grid, columns1, lds, stream);
             return;
         }
         const dim3 grid(fit, n_ocb);
+        tl_shared_launch = {kLaunchPersistent, planes, 2};
         if (p.rq.x_out) launch_conv_shared_mfma_resident<kOutRequant, 2>(p, planes, grid, columns, lds, stream);
         else launch_conv_shared_mfma_resident<kOutAcc, 2>(p, planes, grid, columns, lds, stream);
         return;
     }
     const dim3 grid(columns, n_ocb, (unsigned)p.ksplit);
+    tl_shared_launch = {kLaunchMfma, planes, half_tiles};
     if (half_tiles == 1) {
         if (p.masked || p.ksplit > 1) launch_conv_shared_mfma_out<kOutPartial, 1>(p, planes, grid, stream);
         else if (p.rq.x_out) launch_conv_shared_mfma_out<kOutRequant, 1>(p, planes, grid, stream);

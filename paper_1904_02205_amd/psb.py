@@ -17,13 +17,14 @@ ERR_NULL, ERR_SHAPE, ERR_VALUE, ERR_OVERFLOW_UNSAFE, ERR_TOO_LARGE, ERR_DEVICE, 
 _NAMES = {0: "PSB_OK", -1: "PSB_ERR_NULL", -2: "PSB_ERR_SHAPE", -3: "PSB_ERR_VALUE",
           -4: "PSB_ERR_OVERFLOW_UNSAFE", -5: "PSB_ERR_TOO_LARGE", -6: "PSB_ERR_DEVICE", -7: "PSB_ERR_ALLOC"}
 
+SHARED_DIRECT, SHARED_DEPTHWISE, SHARED_MFMA, SHARED_PERSISTENT, SHARED_WINDOW, SHARED_RESIDENT = 1, 2, 3, 4, 5, 6
 MAPPING_AUTO, MAPPING_PIXEL_LANE, MAPPING_CHANNEL_LANE, MAPPING_PRODUCT_LIST = 0, 1, 2, 3
 
 SYMBOLS = ["psb_quantize_weights", "psb_weights_info", "psb_weights_export", "psb_weights_destroy",
            "psb_conv2d_out_dims", "psb_linear", "psb_conv2d", "psb_conv2d_progressive",
            "psb_sample_filter", "psb_linear_shared", "psb_conv2d_shared", "psb_conv2d_progressive_shared",
            "psb_conv2d_requant", "psb_conv2d_requant_static", "psb_conv2d_shared_requant_blocked", "psb_shared_prepare_filters", "psb_shared_prepare_filters_levels", "psb_conv2d_shared_budget_requant_blocked", "psb_shared_budget_levels", "psb_requantize", "psb_maxpool2d_i8", "psb_maxpool2d_i8_blocked", "psb_global_avgpool_requantize", "psb_budget_resample",
-           "psb_attention_budget", "psb_last_device_error", "psb_build_id", "psb_set_mapping", "psb_query_mapping", "psb_query_mapping_call", "psb_last_mapping", "psb_shared_window_slots", "psb_profile_enable",
+           "psb_attention_budget", "psb_last_device_error", "psb_build_id", "psb_set_mapping", "psb_query_mapping", "psb_query_mapping_call", "psb_last_mapping", "psb_last_shared_launch", "psb_shared_window_slots", "psb_profile_enable",
            "psb_profile_read"]
 
 
@@ -48,6 +49,11 @@ class ConvGeom(C.Structure):
 class Requant(C.Structure):
     _fields_ = [("relu", C.c_int32), ("inv_step", C.c_float), ("lo", C.c_int32), ("hi", C.c_int32),
                 ("res_f32_dev", C.c_void_p), ("res_i8_dev", C.c_void_p), ("res_step", C.c_float)]
+
+
+class SharedLaunch(C.Structure):
+    _fields_ = [(k, C.c_int32) for k in ("kernel", "planes", "half_tiles", "teams", "by_channels", "pixel_groups", "channel_waves",
+                                         "pixel_waves", "reduction_waves", "pixels_per_wave", "residual_staged")]
 
 
 class WInfo(C.Structure):
@@ -108,6 +114,7 @@ def lib():
         L.psb_query_mapping.argtypes = [vp, C.POINTER(ConvGeom)]
         L.psb_query_mapping_call.argtypes = [vp, C.POINTER(ConvGeom), i32, i32]
         L.psb_last_mapping.argtypes = []
+        L.psb_last_shared_launch.argtypes = [C.POINTER(SharedLaunch)]
         L.psb_shared_window_slots.argtypes = [i32, i32, C.POINTER(ConvGeom), i32]
         L.psb_profile_enable.argtypes = [C.c_int]
         L.psb_profile_read.argtypes = [C.POINTER(C.c_double), C.POINTER(C.c_int64)]
@@ -193,8 +200,15 @@ def last_mapping():
     return lib().psb_last_mapping()
 
 
+def last_shared_launch():
+    """Kernel (SHARED_*) and shape of this thread's last shared-filter contraction; kernel = 0 before the first."""
+    out = SharedLaunch()
+    _check(lib().psb_last_shared_launch(C.byref(out)), "psb_last_shared_launch")
+    return out
+
+
 def shared_window_slots(kernel, geom, half_tiles):
-    """LDS window slots of the 3 x 3 shared-filter kernel for kernel = (kh, kw) and geom = (n, h, w, stride_h, stride_w,
+    """LDS window slots of the 3 x 3 shared-filter kernel with 32 channels at a time in LDS for kernel = (kh, kw) and geom = (n, h, w, stride_h, stride_w,
     pad_h, pad_w) with pixel tiles of 128 * half_tiles outputs; 0 when that kernel does not take the layer.  Host only."""
     rc = lib().psb_shared_window_slots(int(kernel[0]), int(kernel[1]), C.byref(ConvGeom(*geom)), int(half_tiles))
     if rc < 0:

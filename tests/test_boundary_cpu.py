@@ -149,6 +149,7 @@ def test_query_mapping_null_arguments(psb):
     assert L.psb_query_mapping_call(None, C.byref(g), 8, 0) == psb.ERR_NULL
     assert L.psb_query_mapping_call(C.c_void_p(16), None, 8, 0) == psb.ERR_NULL
     assert L.psb_last_mapping() == 0
+    assert psb.last_shared_launch().kernel == 0 and L.psb_last_shared_launch(None) == psb.ERR_NULL
 
 
 def test_mapping_switch(psb):

@@ -373,30 +373,48 @@ def test_rescale_matches_oracle(psb, orc, mapping):
     psb.set_mapping(psb.MAPPING_AUTO)
 
 
-@pytest.mark.parametrize("n,cin,oc,hw,S", [
-    (1, 64, 16, (5, 6), 8),          # four groups of pixels, the reduction in four or eight parts, one pixel tile
-    (3, 40, 33, (9, 7), 4),          # channels that fill neither an instruction nor a block, tiles across images
-    (2, 160, 70, (14, 13), 8),       # an odd number of channel blocks, planes no multiple of four bytes
-    (1, 256, 64, (40, 36), 8),       # part of the pixels per wave
-    (8, 64, 64, (56, 56), 8),        # seven groups
-    (17, 64, 64, (56, 52), 8),       # thirteen groups, a last tile in part
-    (33, 512, 48, (7, 7), 2),        # two digit planes, long reduction
-    (40, 64, 200, (4, 4), 8)])       # tiles of many small images, many channel groups
+# planes: digit planes at S samples (four exponent bits, of which a long reduction leaves fewer, or two).  cut: pixel groups of a wave,
+# waves of a workgroup (channel groups, pixel parts, reduction parts), whether an XCD takes an eighth of the channels; groups_seg: pixel
+# groups with two budget levels, 0 for a layer that another kernel takes then.
+@pytest.mark.parametrize("n,cin,oc,hw,S,exp_bits,planes,cut,groups_seg", [
+    (1, 64, 16, (5, 6), 8, 4, 3, (4, (2, 1, 4), 0), 4),              # four pixels a wave
+    (3, 40, 33, (9, 7), 4, 4, 3, (4, (2, 1, 4), 0), 4),              # channels that fill neither an instruction nor a block, tiles across images
+    (2, 160, 70, (14, 13), 8, 4, 3, (4, (1, 1, 8), 0), 4),           # an odd number of channel blocks, planes no multiple of four bytes
+    (1, 256, 64, (40, 36), 8, 4, 2, (4, (1, 1, 8), 0), 4),
+    (8, 64, 64, (56, 56), 8, 4, 3, (4, (4, 2, 1), 0), 4),
+    (40, 64, 200, (4, 4), 8, 4, 3, (4, (2, 1, 4), 0), 4),            # tiles of many small images, many channel groups
+    (33, 512, 48, (7, 7), 2, 4, 2, (4, (1, 1, 8), 0), 4),            # two digit planes, long reduction
+    (4, 512, 512, (7, 7), 2, 4, 2, (4, (1, 1, 8), 1), 4),            # more weights than activations: XCDs by channels
+    (18, 256, 512, (7, 7), 8, 4, 3, (4, (2, 1, 4), 1), 4),
+    (17, 64, 64, (56, 52), 8, 4, 3, (7, (4, 2, 1), 0), 7),
+    (17, 64, 64, (56, 52), 8, 2, 2, (7, (4, 2, 1), 0), 7),
+    (16, 128, 128, (28, 27), 8, 4, 3, (7, (4, 1, 2), 0), 7),         # seven groups, two of whose waves share a reduction
+    (32, 512, 512, (7, 7), 2, 4, 2, (7, (2, 1, 4), 1), 7),
+    (26, 64, 64, (55, 53), 8, 4, 3, (13, (4, 2, 1), 0), 0),          # thirteen groups, a last tile in part, planes no multiple of four bytes
+    (40, 64, 70, (56, 56), 8, 2, 2, (13, (2, 4, 1), 0), 0),          # ... two rounds, padding channels
+    (45, 128, 128, (28, 28), 8, 4, 3, (13, (8, 1, 1), 0), 0)])
 @pytest.mark.parametrize("residual", [None, "f32", "i8"])
-def test_window_of_all_channels(psb, n, cin, oc, hw, S, residual):
+def test_window_of_all_channels(psb, n, cin, oc, hw, S, exp_bits, planes, cut, groups_seg, residual):
     """3 x 3 layers whose input window stays in LDS: accumulators against a 64-bit convolution with the sampled filter (exact), and
     every form of the fused outputs against the library's separate requantisation of the rescaled values (exact)."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(n * 1000 + cin + oc)
     h, w = hw
     x = (torch.rand((n, cin, h, w), generator=gen, device="cuda") * 255 - 128).to(torch.int8)
-    q = psb.Weights(torch.randn((oc, cin, 3, 3), generator=gen, device="cuda") * 0.05, s_max=2 * S)
-    mult = torch.rand(oc, generator=gen, device="cuda") * 2e-5 + 1e-6
+    q = psb.Weights(torch.randn((oc, cin, 3, 3), generator=gen, device="cuda") * 0.05, exp_bits=exp_bits, s_max=2 * S)
+
+    def ran_here(groups=cut[0], staged=False):
+        at = psb.last_shared_launch()
+        assert (at.kernel, at.pixel_groups, at.residual_staged) == (psb.SHARED_RESIDENT, groups, staged)
+        assert groups != cut[0] or ((at.channel_waves, at.pixel_waves, at.reduction_waves), at.by_channels) == cut[1:]
+        assert at.planes == planes
+    mult = torch.rand(oc, generator=gen, device="cuda") * (2e-5 if exp_bits == 4 else 2e-3) + 1e-6
     bias = torch.randn(oc, generator=gen, device="cuda") * 0.1
     geo = dict(stride=(1, 1), pad=(1, 1), seed=3, layer_id=4, mult=mult, bias=bias)
     acc = torch.empty((n, oc, h, w), dtype=torch.int32, device="cuda")
     y = torch.empty((n, oc, h, w), dtype=torch.float32, device="cuda")
     psb.conv2d(q, x, S, acc=acc, y=y, shared=True, **geo)
+    ran_here()
     f = psb.sample_filter(q, S, seed=3, layer_id=4).view(oc, cin, 3, 3).double().cpu()
     for i in {0, n // 2, n - 1}:
         assert torch.equal(acc[i:i + 1].cpu().double(), torch.nn.functional.conv2d(x[i:i + 1].double().cpu(), f, padding=1)), i
@@ -412,6 +430,8 @@ def test_window_of_all_channels(psb, n, cin, oc, hw, S, residual):
         want = psb.requantize(y, inv, relu=relu, lo=lo, hi=hi, **res)
         got = psb.conv2d_requant(q, x, inv, S=S, relu=relu, lo=lo, hi=hi, shared=True, want_acc=False, **geo, **res)
         assert torch.equal(got, want), (relu, lo, hi, inv)
+        if inv == 30.0:
+            ran_here()
 
     def blocked(t):
         cb = (t.shape[1] + 31) // 32
@@ -426,11 +446,16 @@ def test_window_of_all_channels(psb, n, cin, oc, hw, S, residual):
                                               dict(res_i8=res["res_i8"].permute(0, 2, 4, 1, 3).reshape(n, -1, h, w)[:, :oc].contiguous(), res_step=0.01))))
     got = psb.conv2d_shared_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, S, layout=layout, **geo, **res)
     assert torch.equal(got, want)
+    ran_here(staged=cut[0] == 13 and residual == "i8")
     # two budget levels in one launch: a pixel's value is that of a call with its own sample count
     budget = torch.where(torch.rand((n, h, w), generator=gen, device="cuda") < 0.4, 2 * S, S).to(torch.uint8)
     budget[:, 0, 0] = S // 2                       # below every level
     both = [psb.conv2d_shared_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, s, layout=layout, **geo, **res) for s in (S, 2 * S)]
     got = psb.conv2d_shared_budget_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, budget, (S, 2 * S), layout=layout, **geo, **res)
+    if groups_seg:
+        ran_here(groups_seg)
+    else:
+        assert psb.last_shared_launch().kernel == psb.SHARED_WINDOW
     at = budget.view(n, h, 1, w, 1).expand_as(got)
     assert torch.equal(torch.where(at == S, both[0], torch.where(at == 2 * S, both[1], got)), got)
 
