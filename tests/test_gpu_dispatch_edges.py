@@ -237,10 +237,13 @@ def test_shared_levels_of_long_reductions(psb, orc, cin, k, oc, hw):
         assert torch.equal(psb.conv2d_shared_budget_requant_blocked(q, x, tuple(x.shape), 4.0, bt, (3, 8, 16), **kw), one_by_one)
 
 
-@pytest.mark.parametrize("cin,oc,hw", [(160, 9, (7, 7)), (192, 9, (7, 7)), (224, 9, (7, 7)), (352, 484, (5, 6)), (384, 484, (5, 6)), (416, 484, (5, 6))])
-def test_shared_two_digit_planes(psb, orc, cin, oc, hw):
-    """3 x 3 layers whose filter needs two digit planes, around the numbers of channel blocks from which the window kernel with a
-    single team leaves them to the plain one (even numbers have two teams)."""
+@pytest.mark.parametrize("cin,oc,hw,refined", [(160, 9, (7, 7), ("WINDOW", 1)), (192, 9, (7, 7), ("WINDOW", 2)), (224, 9, (7, 7), ("MFMA", 0)),
+                                               (352, 484, (5, 6), ("WINDOW", 1)), (384, 484, (5, 6), ("WINDOW", 2)), (416, 484, (5, 6), ("MFMA", 0))])
+def test_shared_two_digit_planes(psb, orc, cin, oc, hw, refined):
+    """3 x 3 layers whose filter needs two digit planes.  A whole call keeps all channels of its window in LDS; a refinement call adds to
+    accumulators, which the kernels with 32 channels at a time do - around the numbers of channel blocks from which the one with a single
+    team leaves the layer to the one with operands from memory (even numbers have two teams)."""
+    import torch
     rng = np.random.default_rng(cin)
     L = synth.Layer("planes", synth.he_normal((oc, cin, 3, 3), rng), synth.sparse_relu_int8((1, cin) + hw, rng), pad=(1, 1), S=8, s_max=8,
                     seed=6, layer_id=1)
@@ -249,4 +252,14 @@ def test_shared_two_digit_planes(psb, orc, cin, oc, hw):
     points = np.sort(rng.choice(oc * hw[0] * hw[1], 441, replace=False)).astype(np.int64)
     ref, over, _ = helpers.oracle_layer(orc, L, qo, shared=True, points=points)
     acc, _ = helpers.gpu_layer(psb, L, qg, shared=True)
+    at = psb.last_shared_launch()
+    assert (at.kernel, at.planes) == (psb.SHARED_RESIDENT, 2)
     assert over == 0 and np.array_equal(acc.ravel()[points], ref)
+    kw = dict(pad=(1, 1), seed=6, layer_id=1, shared=True)
+    x = torch.from_numpy(L.x).cuda()
+    low, high = (torch.full((1,) + hw, v, dtype=torch.uint8, device="cuda") for v in (3, 8))
+    part = psb.conv2d(qg, x, 3, **kw)
+    psb.conv2d_progressive(qg, x, high, low, acc=part, **kw)
+    at = psb.last_shared_launch()
+    assert (at.kernel, at.teams, at.planes) == (getattr(psb, "SHARED_" + refined[0]), refined[1], 2)
+    assert np.array_equal(part.cpu().numpy(), acc)

@@ -88,16 +88,16 @@ def _cases():
     c.append(("many_tiles_row_packed", _layer(rng, 1, 3, 33, (530, 540), 5, stride=2, pad=2, S=4, xkind="signed"), (0,)))
     # two half tiles per wave without the persistent variant: many channel blocks, few pixel tiles per block
     c.append(("two_half_tiles_many_blocks", _layer(rng, 1, 32, 250, (100, 120), 3, pad=1, S=4), (0,)))
-    # 3 x 3, stride 1, padding 1 with both operands in LDS, in each of its shapes: two teams that split the channel
-    # blocks (narrow and wide window), one team (ragged sizes, channel padding), one channel block on a wide image,
-    # two half tiles per wave with a tile that crosses an image boundary, and tiles that span many tiny images
+    # 3 x 3, stride 1, padding 1 with the input window in LDS, 32 channels at a time (one block of channels) or all of them: ragged sizes,
+    # channel padding, a wide image, two half tiles per wave with a tile that crosses an image boundary, tiles that span many tiny images
+    # (test_window_of_all_channels and test_window_of_32_channels check which kernel and shape runs)
     c.append(("window_two_teams", _layer(rng, 2, 128, 64, 14, 3, pad=1, S=8), (0,)))
     c.append(("window_two_teams_wide", _layer(rng, 1, 128, 32, 40, 3, pad=1, S=4), (0,)))
     c.append(("window_ragged", _layer(rng, 3, 64, 40, (13, 11), 3, pad=1, S=8), (0,)))
     c.append(("window_one_block_wide", _layer(rng, 1, 20, 33, (37, 45), 3, pad=1, S=4), (0,)))
     c.append(("window_two_half_tiles", _layer(rng, 2, 32, 480, 50, 3, pad=1, S=4), (0,)))
     c.append(("window_many_small_images", _layer(rng, 40, 128, 32, 4, 3, pad=1, S=8, xkind="signed"), (0,)))
-    # ... and a weight-heavy layer (every XCD takes an eighth of the channel blocks instead of the pixel tiles)
+    # ... and layers with many weights for their pixels
     c.append(("window_many_channel_blocks", _layer(rng, 3, 128, 250, 6, 3, pad=1, S=8, xkind="signed"), (0,)))
     c.append(("window_sixteen_channel_blocks", _layer(rng, 2, 64, 512, 9, 3, pad=1, S=4), (0,)))
     c.append(("window_one_pixel_images", _layer(rng, 70, 64, 32, 1, 3, pad=1, S=8, xkind="signed"), (0,)))
@@ -373,42 +373,22 @@ def test_rescale_matches_oracle(psb, orc, mapping):
     psb.set_mapping(psb.MAPPING_AUTO)
 
 
-# planes: digit planes at S samples (four exponent bits, of which a long reduction leaves fewer, or two).  cut: pixel groups of a wave,
-# waves of a workgroup (channel groups, pixel parts, reduction parts), whether an XCD takes an eighth of the channels; groups_seg: pixel
-# groups with two budget levels, 0 for a layer that another kernel takes then.
-@pytest.mark.parametrize("n,cin,oc,hw,S,exp_bits,planes,cut,groups_seg", [
-    (1, 64, 16, (5, 6), 8, 4, 3, (4, (2, 1, 4), 0), 4),              # four pixels a wave
-    (3, 40, 33, (9, 7), 4, 4, 3, (4, (2, 1, 4), 0), 4),              # channels that fill neither an instruction nor a block, tiles across images
-    (2, 160, 70, (14, 13), 8, 4, 3, (4, (1, 1, 8), 0), 4),           # an odd number of channel blocks, planes no multiple of four bytes
-    (1, 256, 64, (40, 36), 8, 4, 2, (4, (1, 1, 8), 0), 4),
-    (8, 64, 64, (56, 56), 8, 4, 3, (4, (4, 2, 1), 0), 4),
-    (40, 64, 200, (4, 4), 8, 4, 3, (4, (2, 1, 4), 0), 4),            # tiles of many small images, many channel groups
-    (33, 512, 48, (7, 7), 2, 4, 2, (4, (1, 1, 8), 0), 4),            # two digit planes, long reduction
-    (4, 512, 512, (7, 7), 2, 4, 2, (4, (1, 1, 8), 1), 4),            # more weights than activations: XCDs by channels
-    (18, 256, 512, (7, 7), 8, 4, 3, (4, (2, 1, 4), 1), 4),
-    (17, 64, 64, (56, 52), 8, 4, 3, (7, (4, 2, 1), 0), 7),
-    (17, 64, 64, (56, 52), 8, 2, 2, (7, (4, 2, 1), 0), 7),
-    (16, 128, 128, (28, 27), 8, 4, 3, (7, (4, 1, 2), 0), 7),         # seven groups, two of whose waves share a reduction
-    (32, 512, 512, (7, 7), 2, 4, 2, (7, (2, 1, 4), 1), 7),
-    (26, 64, 64, (55, 53), 8, 4, 3, (13, (4, 2, 1), 0), 0),          # thirteen groups, a last tile in part, planes no multiple of four bytes
-    (40, 64, 70, (56, 56), 8, 2, 2, (13, (2, 4, 1), 0), 0),          # ... two rounds, padding channels
-    (45, 128, 128, (28, 28), 8, 4, 3, (13, (8, 1, 1), 0), 0)])
-@pytest.mark.parametrize("residual", [None, "f32", "i8"])
-def test_window_of_all_channels(psb, n, cin, oc, hw, S, exp_bits, planes, cut, groups_seg, residual):
-    """3 x 3 layers whose input window stays in LDS: accumulators against a 64-bit convolution with the sampled filter (exact), and
-    every form of the fused outputs against the library's separate requantisation of the rescaled values (exact)."""
+def _check_3x3(psb, n, cin, oc, hw, S, exp_bits, residual, ran, mult_to, x_absmax=128):
+    """Accumulators against a 64-bit convolution with the sampled filter (exact), and every form of the fused outputs against the
+    library's separate requantisation of the rescaled values (exact).  ran(launch, levels, residual): checks what the call ran in."""
     import torch
     gen = torch.Generator(device="cuda").manual_seed(n * 1000 + cin + oc)
     h, w = hw
-    x = (torch.rand((n, cin, h, w), generator=gen, device="cuda") * 255 - 128).to(torch.int8)
-    q = psb.Weights(torch.randn((oc, cin, 3, 3), generator=gen, device="cuda") * 0.05, exp_bits=exp_bits, s_max=2 * S)
+    if x_absmax == 1:
+        x = torch.randint(-1, 2, (n, cin, h, w), generator=gen, device="cuda", dtype=torch.int8)
+    else:
+        x = (torch.rand((n, cin, h, w), generator=gen, device="cuda") * 255 - 128).to(torch.int8)
+    q = psb.Weights(torch.randn((oc, cin, 3, 3), generator=gen, device="cuda") * 0.05, exp_bits=exp_bits, s_max=2 * S,
+                    x_absmax=min(x_absmax, 127))
 
-    def ran_here(groups=cut[0], staged=False):
-        at = psb.last_shared_launch()
-        assert (at.kernel, at.pixel_groups, at.residual_staged) == (psb.SHARED_RESIDENT, groups, staged)
-        assert groups != cut[0] or ((at.channel_waves, at.pixel_waves, at.reduction_waves), at.by_channels) == cut[1:]
-        assert at.planes == planes
-    mult = torch.rand(oc, generator=gen, device="cuda") * (2e-5 if exp_bits == 4 else 2e-3) + 1e-6
+    def ran_here(levels=False, blocked_residual=False):
+        ran(psb.last_shared_launch(), levels, blocked_residual)
+    mult = torch.rand(oc, generator=gen, device="cuda") * mult_to + mult_to / 20
     bias = torch.randn(oc, generator=gen, device="cuda") * 0.1
     geo = dict(stride=(1, 1), pad=(1, 1), seed=3, layer_id=4, mult=mult, bias=bias)
     acc = torch.empty((n, oc, h, w), dtype=torch.int32, device="cuda")
@@ -446,16 +426,65 @@ def test_window_of_all_channels(psb, n, cin, oc, hw, S, exp_bits, planes, cut, g
                                               dict(res_i8=res["res_i8"].permute(0, 2, 4, 1, 3).reshape(n, -1, h, w)[:, :oc].contiguous(), res_step=0.01))))
     got = psb.conv2d_shared_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, S, layout=layout, **geo, **res)
     assert torch.equal(got, want)
-    ran_here(staged=cut[0] == 13 and residual == "i8")
+    ran_here(blocked_residual=residual == "i8")
     # two budget levels in one launch: a pixel's value is that of a call with its own sample count
     budget = torch.where(torch.rand((n, h, w), generator=gen, device="cuda") < 0.4, 2 * S, S).to(torch.uint8)
     budget[:, 0, 0] = S // 2                       # below every level
     both = [psb.conv2d_shared_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, s, layout=layout, **geo, **res) for s in (S, 2 * S)]
     got = psb.conv2d_shared_budget_requant_blocked(q, blocked(x), (n, cin, h, w), 30.0, budget, (S, 2 * S), layout=layout, **geo, **res)
-    if groups_seg:
-        ran_here(groups_seg)
-    else:
-        assert psb.last_shared_launch().kernel == psb.SHARED_WINDOW
+    ran_here(levels=True, blocked_residual=residual == "i8")
     at = budget.view(n, h, 1, w, 1).expand_as(got)
     assert torch.equal(torch.where(at == S, both[0], torch.where(at == 2 * S, both[1], got)), got)
 
+
+# planes: digit planes at S samples (four exponent bits, of which a long reduction leaves fewer, or two).  cut: pixel groups of a wave,
+# waves of a workgroup (channel groups, pixel parts, reduction parts), whether an XCD takes an eighth of the channels; groups_seg: pixel
+# groups with two budget levels, 0 for a layer that another kernel takes then.
+@pytest.mark.parametrize("n,cin,oc,hw,S,exp_bits,planes,cut,groups_seg", [
+    (1, 64, 16, (5, 6), 8, 4, 3, (4, (2, 1, 4), 0), 4),              # four pixels a wave
+    (3, 40, 33, (9, 7), 4, 4, 3, (4, (2, 1, 4), 0), 4),              # channels that fill neither an instruction nor a block, tiles across images
+    (2, 160, 70, (14, 13), 8, 4, 3, (4, (1, 1, 8), 0), 4),           # an odd number of channel blocks, planes no multiple of four bytes
+    (1, 256, 64, (40, 36), 8, 4, 2, (4, (1, 1, 8), 0), 4),
+    (8, 64, 64, (56, 56), 8, 4, 3, (4, (4, 2, 1), 0), 4),
+    (40, 64, 200, (4, 4), 8, 4, 3, (4, (2, 1, 4), 0), 4),            # tiles of many small images, many channel groups
+    (33, 512, 48, (7, 7), 2, 4, 2, (4, (1, 1, 8), 0), 4),            # two digit planes, long reduction
+    (4, 512, 512, (7, 7), 2, 4, 2, (4, (1, 1, 8), 1), 4),            # more weights than activations: XCDs by channels
+    (18, 256, 512, (7, 7), 8, 4, 3, (4, (2, 1, 4), 1), 4),
+    (17, 64, 64, (56, 52), 8, 4, 3, (7, (4, 2, 1), 0), 7),
+    (17, 64, 64, (56, 52), 8, 2, 2, (7, (4, 2, 1), 0), 7),
+    (16, 128, 128, (28, 27), 8, 4, 3, (7, (4, 1, 2), 0), 7),         # seven groups, two of whose waves share a reduction
+    (32, 512, 512, (7, 7), 2, 4, 2, (7, (2, 1, 4), 1), 7),
+    (26, 64, 64, (55, 53), 8, 4, 3, (13, (4, 2, 1), 0), 0),          # thirteen groups, a last tile in part, planes no multiple of four bytes
+    (40, 64, 70, (56, 56), 8, 2, 2, (13, (2, 4, 1), 0), 0),          # ... two rounds, padding channels
+    (45, 128, 128, (28, 28), 8, 4, 3, (13, (8, 1, 1), 0), 0)])
+@pytest.mark.parametrize("residual", [None, "f32", "i8"])
+def test_window_of_all_channels(psb, n, cin, oc, hw, S, exp_bits, planes, cut, groups_seg, residual):
+    """3 x 3 layers whose input window stays in LDS with all its channels."""
+    def ran(at, levels, blocked_residual):
+        if levels and not groups_seg:
+            assert at.kernel == psb.SHARED_WINDOW
+            return
+        groups = groups_seg if levels else cut[0]
+        assert (at.kernel, at.planes, at.pixel_groups) == (psb.SHARED_RESIDENT, planes, groups)
+        assert at.residual_staged == (groups == 13 and blocked_residual)
+        assert groups != cut[0] or ((at.channel_waves, at.pixel_waves, at.reduction_waves), at.by_channels) == cut[1:]
+    _check_3x3(psb, n, cin, oc, hw, S, exp_bits, residual, ran, 2e-5 if exp_bits == 4 else 2e-3)
+
+
+# The layers that are left to the kernels with 32 channels at a time: shape = (kernel, digit planes, half tiles, teams).
+@pytest.mark.parametrize("n,cin,oc,hw,S,exp_bits,x_absmax,shape", [
+    (1, 20, 33, (37, 45), 4, 4, 128, ("WINDOW", 3, 1, 1)),         # one block of channels on a wide image
+    (2, 96, 40, (9, 11), 4, 4, 128, ("WINDOW", 3, 1, 1)),          # three blocks, padding channels
+    (2, 32, 480, (50, 50), 4, 4, 128, ("WINDOW", 3, 2, 1)),        # two half tiles a wave, a tile that crosses images
+    (2, 615, 2, (1, 85), 8, 2, 128, ("WINDOW", 2, 1, 2)),          # two teams: windows of more than 256 slots ...
+    (6, 1068, 1, (41, 39), 8, 2, 128, ("WINDOW", 2, 1, 2)),        # ... and of less
+    (2, 684, 2, (1, 94), 8, 4, 1, ("WINDOW", 3, 1, 2)),            # three planes (a long reduction of small activations)
+    (6, 1068, 1, (41, 39), 8, 4, 1, ("WINDOW", 3, 1, 2)),
+    (2, 775, 1, (1, 78), 8, 2, 128, ("MFMA", 2, 1, 0)),            # two planes, a lone team and many blocks: the plain kernel
+    (3, 390, 1, (17, 108), 8, 2, 128, ("MFMA", 2, 1, 0))])
+@pytest.mark.parametrize("residual", [None, "f32", "i8"])
+def test_window_of_32_channels(psb, n, cin, oc, hw, S, exp_bits, x_absmax, shape, residual):
+    """3 x 3 layers with 32 channels at a time, or operands from memory."""
+    def ran(at, levels, blocked_residual):
+        assert (at.kernel, at.planes, at.half_tiles, at.teams) == (getattr(psb, "SHARED_" + shape[0]),) + shape[1:]
+    _check_3x3(psb, n, cin, oc, hw, S, exp_bits, residual, ran, 2e-5 if exp_bits == 4 else 2e-3, x_absmax)
