@@ -172,11 +172,11 @@ __device__ __forceinline__ void sample_planes_slots(const FilterJob& j, uint32_t
     static_assert(TAPS == 4 || TAPS == 8, "a lane stores one or two words per plane");
     constexpr uint32_t kWgs = 32 / (4 * TAPS);              // workgroups per (channel block, reduction step)
     constexpr int kPer = P7 ? 16 : 4;                       // samples of a generator block
-    const int lane = threadIdx.x & 63;
+    const uint32_t lane = threadIdx.x & 63u;
     const uint32_t slot0 = ((block % kWgs) * 4u + uniform_u32(threadIdx.x >> 6)) * TAPS;      // scalar, like all but the lane's channel
     uint32_t kstep;
     const uint32_t ocb = div_mod(block / kWgs, (uint32_t)j.n_ksteps, j.inv_ksteps, kstep);
-    const uint32_t oc = ocb * 64u + (uint32_t)lane;
+    const uint32_t oc = ocb * 64u + lane;
     uint32_t k[TAPS];
     uint2 wt[TAPS];
     uint32_t cb = 0;
@@ -233,7 +233,10 @@ __device__ __forceinline__ void sample_planes_slots(const FilterJob& j, uint32_t
         }
     }
 
-    const uint32_t ocb32 = ocb * 2u + (uint32_t)(lane >> 5);
+    // The lane again where the calls leave no register for it (eight waves per SIMD): spilled, it cost the 7-bit form 2 %.  Not in the
+    // others, whose loop came out 2 % slower with it (S = 64).
+    const uint32_t lane_here = P7 && TAPS == 8 ? __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : lane;
+    const uint32_t ocb32 = ocb * 2u + (lane_here >> 5);
     if (ocb32 * 32u >= (uint32_t)j.OC) return;              // an operand block that does not exist
     // Balanced base-256 digits d_b in [-128, 127] with v = sum d_b 256^b modulo 2^32, all four at once: adding 128 to every
     // digit gives the ordinary digits (0..255) of v + 0x80808080, and subtracting 128 from a byte flips its top bit.
@@ -246,7 +249,7 @@ __device__ __forceinline__ void sample_planes_slots(const FilterJob& j, uint32_t
         transpose_bytes_4x4(d, word[q]);
     }
     int8_t* const at = j.planes + ((uint64_t)(ocb32 * (uint32_t)j.n_ksteps + kstep) * (kMaxPlanes * kPlaneStride) +
-                                   (((uint32_t)lane & 31u) + 32u * (slot0 >> 4)) * 16u + (slot0 & 15u));
+                                   ((lane_here & 31u) + 32u * (slot0 >> 4)) * 16u + (slot0 & 15u));
 #pragma unroll
     for (int b = 0; b < kMaxPlanes; ++b) {
         if (b >= j.n_planes) break;                         // uniform
@@ -419,6 +422,9 @@ __global__ void __launch_bounds__(256, 8) k_sample_planes_batch(const FilterBatc
     int i = 0;
 #pragma unroll
     for (int k = 1; k < kMaxBatchJobs; ++k) i += (blockIdx.x >= b.first_block[k]) ? 1 : 0;
+    // Where the calls' straight-line code lies modulo 32 bytes makes up to 4 % of a launch (S = 64): with 0 to 12 of these in front, 0.96 to
+    // 1.00 of the best with 23-bit probabilities and 0.98 to 1.00 with 7-bit ones; seven are good for both.
+    asm volatile("s_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0");
     sample_planes_block(b.jobs[i], blockIdx.x - b.first_block[i]);
 }
 

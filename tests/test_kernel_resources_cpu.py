@@ -1,52 +1,70 @@
 """Registers of the kernels as hipcc reports them: the ones that are built to stay out of scratch memory do."""
+import functools
+import os
 import re
 import shutil
 import subprocess
+import tempfile
 
 import pytest
 
 from paper_1904_02205_amd import build
 
 
-def _resources(tmp_path, header, kernel, instances):
-    """{template arguments: (scratch bytes per lane, spilled vector registers)} of the instances of a kernel that the header's
-    launcher can launch, e.g. "<1, true, false>"; `instances` = how many there have to be at least."""
+@functools.lru_cache(maxsize=None)
+def _remarks(header):
+    """What hipcc reports for the kernels of a header, compiled once."""
     if shutil.which("hipcc") is None:
         pytest.skip("no hipcc")
-    src = tmp_path / "kernels.hip"
-    src.write_text('#include "%s"\n' % header)
-    flags = [f for f in build.FLAGS if f not in ("-shared", "-Wall")]
-    r = subprocess.run(["hipcc", *flags, "-I", build.HERE + "/csrc", "--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage",
-                        str(src), "-o", "/dev/null"], capture_output=True, text=True, check=True)
-    names = re.findall(r"Function Name: (\S+)", r.stderr)
-    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)]
-    spills = [int(v) for v in re.findall(r"VGPRs Spill: (\d+)", r.stderr)]
+    with tempfile.TemporaryDirectory() as tmp:
+        src = os.path.join(tmp, "kernels.hip")
+        with open(src, "w") as f:
+            f.write('#include "%s"\n' % header)
+        flags = [f for f in build.FLAGS if f not in ("-shared", "-Wall")]
+        return subprocess.run(["hipcc", *flags, "-I", build.HERE + "/csrc", "--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage",
+                               src, "-o", "/dev/null"], capture_output=True, text=True, check=True).stderr
+
+
+def _resources(header, kernel, instances):
+    """{template arguments: (scratch bytes per lane, spilled vector registers)} of the instances of a kernel that the header's
+    launcher can launch, e.g. "<1, true, false>" ("" for a kernel that is no template); `instances` = how many there have to be at
+    least."""
+    remarks = _remarks(header)
+    names = re.findall(r"Function Name: (\S+)", remarks)
+    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", remarks)]
+    spills = [int(v) for v in re.findall(r"VGPRs Spill: (\d+)", remarks)]
     assert len(names) == len(scratch) == len(spills)
     found = {}
     for name, s, v in zip(names, scratch, spills):
-        m = re.match(r"_ZN3psb\d+%sI((?:L[ib]\d+E)+)E" % kernel, name)
+        m = re.match(r"_ZN3psb\d+%s(?:I((?:L[ib]\d+E)+)E)?E" % kernel, name)
         if m:
-            args = [("false", "true")[int(n)] if t == "b" else n for t, n in re.findall(r"L([ib])(\d+)E", m.group(1))]
-            found["<%s>" % ", ".join(args)] = (s, v)
+            args = [("false", "true")[int(n)] if t == "b" else n for t, n in re.findall(r"L([ib])(\d+)E", m.group(1) or "")]
+            found["<%s>" % ", ".join(args) if args else ""] = (s, v)
     assert len(found) >= instances, names
     return found
 
 
-def test_product_list_of_one_and_two_blocks_does_not_spill(tmp_path):
-    found = _resources(tmp_path, "psb_kernels_list.hip.h", "k_layer_product_list", 68)
+def test_product_list_of_one_and_two_blocks_does_not_spill():
+    found = _resources("psb_kernels_list.hip.h", "k_layer_product_list", 68)
     few = {k: v for k, v in found.items() if k.startswith(("<1,", "<2,"))}
     assert len(few) == 16 and set(few.values()) == {(0, 0)}, few
 
 
-def test_persistent_shared_kernel_without_segments_does_not_spill(tmp_path):
+def test_persistent_shared_kernel_without_segments_does_not_spill():
     """Calls that write accumulators, one to three digit planes, one and two half tiles, no segments of the sample axis."""
-    found = _resources(tmp_path, "psb_kernels_shared.hip.h", "k_conv_shared_mfma_resident", 24)
+    found = _resources("psb_kernels_shared.hip.h", "k_conv_shared_mfma_resident", 24)
     for planes in (1, 2, 3):
         for half_tiles in (1, 2):
             assert found["<%d, 1, %d, false>" % (planes, half_tiles)] == (0, 0)
 
 
-def test_resident_window_kernel_does_not_spill(tmp_path):
+def test_resident_window_kernel_does_not_spill():
     """Two and three digit planes, both kinds of output, 4, 7 and 13 groups of pixels (13 without segments of the sample axis)."""
-    found = _resources(tmp_path, "psb_kernels_resident.hip.h", "k_conv3x3_resident", 20)
+    found = _resources("psb_kernels_resident.hip.h", "k_conv3x3_resident", 20)
     assert len(found) == 20 and set(found.values()) == {(0, 0)}, found
+
+
+def test_filter_sampling_does_not_spill():
+    """The launch that samples the filters of a whole network, and the one of a single call."""
+    assert _resources("psb_kernels_shared.hip.h", "k_sample_planes_batch", 1) == {"": (0, 0)}
+    assert _resources("psb_kernels_shared.hip.h", "k_shared_prologue", 1) == {"": (0, 0)}
