@@ -1459,6 +1459,8 @@ inline WindowPlan window_plan(const SharedParams& p, int planes, int half_tiles,
     // than the plain kernel's operand loads when the blocks are many.  Plain : window, us, 7x7, batch 17 - 5 / 9 / 13 / 15 / 25 blocks, 64
     // channels 14.2:14.2 / 17.6:17.7 / 20.7:22.0 / 22.7:24.4 / 31.6:34.8 (two budget segments 20.5:20.3 / 28.4:29.3 / 34.5:37.9); 512 channels, whose
     // workgroups of a pixel tile share an XCD's cache, 7 / 11 / 13 blocks 19.5:18.2 / 26.8:25.3 / 29.3:28.4 (33.5:32.4 / 45.6:45.9 / 50.7:52.0).
+    // (k_conv3x3_resident takes such layers where their window fits; left here are wide images and calls that add to accumulators.  On
+    // random ones of those, window / plain: 127 whole calls 0.95 to 1.17, mean 1.08; 106 refinement calls 0.97 to 1.10, mean 1.04.)
     if (planes == 2 && w.teams == 1 && wgs <= n_cus && CB > (p.OC > 480 ? 11 : 5)) return w;
     w.ok = true;
     return w;
