@@ -15,9 +15,10 @@
 //     consecutive memory; the reduction index is ordered (kh, kw, channel), which no result depends on;
 //   * the digit planes are written directly in the operand order of the instruction
 //     [block of 32 channels][k-step][plane][lane][16 bytes]: an operand is one coalesced 1 KB read.
-// One wave computes 32 output channels x 64 (or 32) output pixels.  Three kernels share the pieces below: the
+// One wave computes 32 output channels x 64 (or 32) output pixels.  Four kernels share the pieces below: the
 // plain one (weights staged through LDS chunk by chunk), a persistent one for short reductions (all weights of a
-// channel block resident in LDS) and the direct one for grouped layers.
+// channel block resident in LDS), one for 3 x 3 layers with the input window in LDS, 32 channels at a time, and the
+// direct one for grouped layers.  Most 3 x 3 layers go to psb_kernels_resident.hip.h: all channels of the window in LDS.
 //
 // Per-pixel budgets: the distinct budget values cut the sample axis into segments; each segment is one
 // filter (built from exactly its samples, so budgets nest) and one masked, accumulating contraction over

@@ -229,7 +229,9 @@ def profile_read():
 
 def conv2d_out_dims(wshape, geom):
     """wshape = (oc, cin, kh, kw, groups); geom = (n, h, w, stride_h, stride_w, pad_h, pad_w)."""
-    return _out_dims(tuple(wshape), tuple(geom))
+    wshape, geom = tuple(wshape), tuple(geom)
+    # only whole numbers are looked up: 56.0 is equal to 56 as a key, but the library's structures refuse it
+    return (_out_dims if {*map(type, wshape), *map(type, geom)} == {int} else _out_dims.__wrapped__)(wshape, geom)
 
 
 @functools.lru_cache(maxsize=256)
@@ -313,7 +315,7 @@ def _geom(q, x, stride, pad):
         raise ValueError(f"x: shape {tuple(x.shape)}, expected (N, {q.wshape[1]}, H, W)")
     n, _, h, w = x.shape
     g = ConvGeom(n, h, w, stride[0], stride[1], pad[0], pad[1])
-    oh, ow = conv2d_out_dims(q.wshape, (g.n, g.h, g.w, g.stride_h, g.stride_w, g.pad_h, g.pad_w))
+    oh, ow = _out_dims(q.wshape, (g.n, g.h, g.w, g.stride_h, g.stride_w, g.pad_h, g.pad_w))
     return g, (n, q.wshape[0], oh, ow)
 
 
@@ -412,7 +414,7 @@ def conv2d_shared_requant_blocked(q, x, x_shape, inv_step, S, stride=(1, 1), pad
     values are computed, into y [N, OC, OH, OW] (allocated if None), which is returned."""
     n, c, h, w = x_shape
     g = ConvGeom(n, h, w, stride[0], stride[1], pad[0], pad[1])
-    oh, ow = conv2d_out_dims(q.wshape, (g.n, g.h, g.w, g.stride_h, g.stride_w, g.pad_h, g.pad_w))
+    oh, ow = _out_dims(q.wshape, (g.n, g.h, g.w, g.stride_h, g.stride_w, g.pad_h, g.pad_w))
     oc = q.wshape[0]
     if want_x and x_out is None:
         shape = blocked_shape(n, oc, oh, ow) if layout & BLOCKED_OUT else (n, oc, oh, ow)
@@ -450,7 +452,7 @@ def conv2d_shared_budget_requant_blocked(q, x, x_shape, inv_step, budget_to, lev
     `levels` (at most four distinct values): all sample segments in one launch, epilogue fused."""
     n, c, h, w = x_shape
     g = ConvGeom(n, h, w, stride[0], stride[1], pad[0], pad[1])
-    oh, ow = conv2d_out_dims(q.wshape, (g.n, g.h, g.w, g.stride_h, g.stride_w, g.pad_h, g.pad_w))
+    oh, ow = _out_dims(q.wshape, (g.n, g.h, g.w, g.stride_h, g.stride_w, g.pad_h, g.pad_w))
     oc = q.wshape[0]
     if want_x and x_out is None:
         shape = blocked_shape(n, oc, oh, ow) if layout & BLOCKED_OUT else (n, oc, oh, ow)

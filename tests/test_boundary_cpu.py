@@ -35,6 +35,9 @@ def test_out_dims_and_shape_errors(psb):
     assert psb.conv2d_out_dims((64, 3, 7, 7, 1), (32, 224, 224, 2, 2, 3, 3)) == (112, 112)
     assert psb.conv2d_out_dims((128, 64, 1, 1, 1), (2, 56, 56, 2, 2, 0, 0)) == (28, 28)
     assert psb.conv2d_out_dims((8, 8, 2, 3, 2), (1, 6, 8, 1, 2, 0, 2)) == (5, 5)
+    for wshape, geom in (((64, 64, 3, 3, 1), (1, 56.0, 56, 1, 1, 1, 1)), ((64.0, 64, 3, 3, 1), (1, 56, 56, 1, 1, 1, 1))):
+        with pytest.raises(TypeError):           # sizes that are no whole numbers, also when equal ones have been asked for before
+            psb.conv2d_out_dims(wshape, geom)
     bad = [((0, 64, 3, 3, 1), (1, 8, 8, 1, 1, 1, 1), psb.ERR_SHAPE),
            ((64, 64, 3, 3, 3), (1, 8, 8, 1, 1, 1, 1), psb.ERR_SHAPE),       # groups do not divide
            ((64, 64, 3, 3, 1), (1, 8, 8, 0, 1, 1, 1), psb.ERR_SHAPE),       # stride 0
