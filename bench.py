@@ -64,6 +64,8 @@ CALL_UNITS_7BIT = 15 * WIDE + 17 + 1                                       # 48 
 WORD_UNITS_7BIT = 4                                                        # ... + 4 per word of four samples it needs
 PRODUCT_UNITS = 2 * WIDE                                                   # v_mul_i32_i24 + v_mad_i32_i24
 KERNEL_NAMES = {1: "k_layer_pixel_lane", 2: "k_layer_oc_lane", 3: "k_layer_product_list"}
+SHARED_KERNEL_NAMES = {1: "k_conv_shared_direct", 2: "k_conv_shared_depthwise", 3: "k_conv_shared_mfma",
+                       4: "k_conv_shared_mfma_resident", 5: "k_conv3x3_window", 6: "k_conv3x3_resident"}
 PEAK_INT8_TOPS = 5000.0    # dense int8 MFMA, MI355X
 
 
@@ -215,18 +217,6 @@ def prepare(workload, args, torch, psb, dev):
         w = torch.from_numpy(L.w).to(dev)
         q = psb.Weights(w, groups=L.groups, x_absmax=L.x_absmax, s_max=L.s_max, prob_bits=args.prob_bits)
         geom = (L.x.shape[0], L.x.shape[2], L.x.shape[3]) + L.stride + L.pad
-        name = KERNEL_NAMES[psb.query_mapping(q, geom, S=L.S, budget_map=L.budget_to is not None)]
-        if shared:
-            # matrix-core contraction: 3 x 3 / stride 1 / padding 1 layers normally run in k_conv3x3_resident or
-            # k_conv3x3_window (window in LDS), the others in k_conv_shared_mfma; the library's timer covers whichever it launched
-            window = L.w.shape[2:] == (3, 3) and L.stride == (1, 1) and L.pad == (1, 1)
-            name = ("k_conv3x3_resident" if window else "k_conv_shared_mfma") if L.groups == 1 and args.mapping != 1 \
-                else "k_conv_shared_direct"
-            a, b = shared_ops(L, q)
-            P.mfma_ops += a
-            P.mfma_plane_ops += b
-        if name not in P.kernels:
-            P.kernels.append(name)
         x = torch.from_numpy(L.x).to(dev)
         n, oc = L.x.shape[0], L.w.shape[0]
         oh, ow = L.out_hw
@@ -243,11 +233,35 @@ def prepare(workload, args, torch, psb, dev):
         P.layer_smac.append(a)
         P.layer_work.append((b, c, f))
         P.calls.append((L, q, x, acc, y, bt))
+        if shared:
+            a, b = shared_ops(L, q)
+            P.mfma_ops += a
+            P.mfma_plane_ops += b
+            run_layer(P.calls[-1], shared, psb)
+            name = SHARED_KERNEL_NAMES[psb.last_shared_launch().kernel]
+        else:
+            name = KERNEL_NAMES[psb.query_mapping(q, geom, S=L.S, budget_map=L.budget_to is not None)]
+        if name not in P.kernels:
+            P.kernels.append(name)
     torch.cuda.synchronize()
     P.graph = None
     if P.model is not None and args.graph:
         P.graph, _ = P.model.capture(S=8, shared=shared)
     return P
+
+
+def run_layer(call, shared, psb):
+    L, q, x, acc, y, bt = call
+    if bt is not None:
+        psb.conv2d_progressive(q, x, bt, None, stride=L.stride, pad=L.pad, seed=L.seed, layer_id=L.layer_id,
+                               acc=acc, y=y, shared=shared)
+    elif L.linear:
+        psb.linear(q, x.reshape(x.shape[0], -1), L.S, seed=L.seed, layer_id=L.layer_id,
+                   acc=acc.reshape(acc.shape[0], -1), y=None if y is None else y.reshape(y.shape[0], -1),
+                   shared=shared)
+    else:
+        psb.conv2d(q, x, L.S, stride=L.stride, pad=L.pad, seed=L.seed, layer_id=L.layer_id, acc=acc, y=y,
+                   shared=shared)
 
 
 def measure(P, steps, warmup, torch, psb):
@@ -261,17 +275,8 @@ def measure(P, steps, warmup, torch, psb):
         if P.model is not None:
             P.model.forward(S=8, shared=shared)
             return
-        for L, q, x, acc, y, bt in P.calls:
-            if bt is not None:
-                psb.conv2d_progressive(q, x, bt, None, stride=L.stride, pad=L.pad, seed=L.seed, layer_id=L.layer_id,
-                                       acc=acc, y=y, shared=shared)
-            elif L.linear:
-                psb.linear(q, x.reshape(x.shape[0], -1), L.S, seed=L.seed, layer_id=L.layer_id,
-                           acc=acc.reshape(acc.shape[0], -1), y=None if y is None else y.reshape(y.shape[0], -1),
-                           shared=shared)
-            else:
-                psb.conv2d(q, x, L.S, stride=L.stride, pad=L.pad, seed=L.seed, layer_id=L.layer_id, acc=acc, y=y,
-                           shared=shared)
+        for call in P.calls:
+            run_layer(call, shared, psb)
 
     for _ in range(warmup):
         step()
