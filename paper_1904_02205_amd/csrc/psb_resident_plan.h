@@ -50,8 +50,8 @@ inline int64_t resident_slots(int64_t tile, int H, int W)
 inline bool resident_plan(const ResidentLayer& l, int n_cus, ResidentPlan& best)
 {
     // An instruction takes 64 channels: with one or three blocks of 32 half or a quarter of them are padding, which the kernels of
-    // 32 channels do not multiply.  Against those kernels, over 390 random layers of 1 to 64 images: 2 and 4 blocks and more 1.26
-    // times as fast (geometric mean), 1 block 0.85 to 1.1 times, 3 blocks 0.94 to 1.46 times.
+    // 32 channels do not multiply.  Over random layers of 1 to 64 images, times as fast as in those: 1 block 0.85 to 1.1, 3 blocks 0.94
+    // to 1.46; the others below.
     if (l.blocks == 1 || l.blocks == 3) return false;
     const int64_t npix = l.npix;
     const int planes = l.planes;
