@@ -10,8 +10,9 @@
 // The weights of a tap x 64 channels are {threshold, +-2^shift} pairs, 512 consecutive bytes.
 //
 // Bound by the issue of vector instructions: a generator call takes 41 of them (15 wide multiplies, 14 three-input and 3
-// two-input xors, 4 compares, 4 counts, a share of the product's 4), which a SIMD issues in 63 ns at best (a loop of
-// nothing else, eight waves).  3x3 128->128 at 28x28, batch 32, S = 8: 53.7 k calls per SIMD in 3.38 ms, 63 ns each.
+// two-input xors, 4 compares, 4 counts, a share of the product's 4), which a SIMD issues in 58 ns at best (a loop of
+// nothing else, eight waves).  3x3 128->128 at 28x28, batch 32, S = 8: 53.7 k calls per SIMD in 3.09 ms, 57.5 ns each (the
+// calls of blocks 0 and 1 share two multiplies; 3.36 ms before the empty slots between the rounds, issue_gap()).
 //
 // The reduction over taps is split into chunks; with more than one chunk the partial
 // sums are combined with int32 atomic adds, which is exact in any order because the
@@ -67,10 +68,15 @@ struct Keys {
 };
 
 // Rounds 3..9.
+template <bool GAPS>
 __device__ __forceinline__ u32x4 philox_rounds_3_to_9(u32x4 c, const Keys& key)
 {
+    if (GAPS) issue_gap();
 #pragma unroll
-    for (int r = 3; r < 10; ++r) c = philox_round(c, key.k0[r], key.k1[r]);
+    for (int r = 3; r < 10; ++r) {
+        c = philox_round(c, key.k0[r], key.k1[r]);
+        if (GAPS) issue_gap();
+    }
     return c;
 }
 
@@ -90,7 +96,8 @@ __device__ __forceinline__ TapScalars tap_scalars(uint32_t s_x1, const Keys& key
 // 4 VALID (whole words) with 7-bit uniforms (the last block of a range that starts on a block boundary);
 // 0: the range [from,to) is checked at run time.
 // state after round 1: (.., .., ts.sz ^ lo_a, ts.s_lo); words 0 and 1 were used in the per-pixel set-up.
-template <int VALID, bool P7>
+// GAPS: see issue_gap().
+template <int VALID, bool P7, bool GAPS = true>
 __device__ __forceinline__ uint32_t sample_block(uint32_t n, uint32_t thr, TapScalars ts, const PixelHoist& h, uint32_t hz,
                                                  uint32_t lo2, const Keys& key, int j, int from, int to)
 {
@@ -103,7 +110,7 @@ __device__ __forceinline__ uint32_t sample_block(uint32_t n, uint32_t thr, TapSc
     c.y = lo_b2;
     c.z = hz ^ ts.s_lo;
     c.w = lo2;
-    c = philox_rounds_3_to_9(c, key);
+    c = philox_rounds_3_to_9<GAPS>(c, key);
     if constexpr (P7) {
         if constexpr (VALID > 0) {       // the first 4 VALID samples of the block: its first VALID words, whole
             const uint32_t all = 0x80808080u;
@@ -150,7 +157,7 @@ __device__ __forceinline__ void block_setup(const PixelHoist& h, const Keys& key
 struct Step {
     unsigned long long mask;      // taps whose product needs sampling (scalar)
     int32_t xv;                   // lane t: activation of tap t of the step
-    const char* w;                // weights of the step's first tap and of the ticket's first channel (scalar)
+    __amdgpu_buffer_rsrc_t w;     // the weights from the step's first tap and the ticket's first channel on (scalar)
     uint32_t w_stride;            // bytes between the weights of consecutive taps (scalar)
     uint32_t k0;                  // the step's first tap (scalar)
 };
@@ -162,7 +169,7 @@ struct Step {
 // Nothing is compacted: the next product's tap is the lowest bit left in the mask, its activation that lane's value,
 // and its weights - 512 consecutive bytes, which the waves of a CU share through L1 and L2 - are requested one product
 // ahead.  One generator call after the other: eight waves per SIMD hide each other's latencies, and a call costs a
-// SIMD 63 ns then, against 69 ns with four waves that interleave two or four calls each.
+// SIMD 57.5 ns then (69 ns with four waves that interleave two or four calls each, when it was 63).
 template <int NB, int VALID, bool P7>
 __device__ __forceinline__ int32_t process_step(const Step& s, int lane, int j0, int from, int to, const PixelHoist& h,
                                                 const Keys& key)
@@ -181,14 +188,10 @@ __device__ __forceinline__ int32_t process_step(const Step& s, int lane, int j0,
         asm("s_ff1_i32_b64 %0, %1" : "=s"(f) : "s"(rest));
         last = rest != 0ull ? f : last;
         asm("s_bitset0_b64 %0, %1" : "+s"(rest) : "s"(last));
-        // a scalar address and the lane's constant offset: no address arithmetic in vector registers
-        typedef const __attribute__((address_space(1))) char* GlobalPtr;
-        typedef const __attribute__((address_space(1))) unsigned long long* GlobalEntry;
-        GlobalPtr row = (GlobalPtr)s.w + (uint64_t)last * s.w_stride;
-        uint32_t at = (uint32_t)lane * 8u;
-        asm("" : "+s"(row), "+v"(at));
-        const unsigned long long e = *(GlobalEntry)(row + at);
-        return Product{last, make_uint2((uint32_t)e, (uint32_t)(e >> 32))};
+        // a buffer load: scalar row offset (below 2^31: oc_lane_chunks) and the lane's constant one, no address arithmetic
+        typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+        const v2u e = __builtin_amdgcn_raw_buffer_load_b64(s.w, lane * 8, (int)(last * s.w_stride), 0);
+        return Product{last, make_uint2(e.x, e.y)};
     };
     auto sample = [&](const Product& q) {
         const int32_t x = __builtin_amdgcn_readlane(s.xv, (int)q.t);
@@ -299,7 +302,7 @@ __global__ void __launch_bounds__(kOcWaves * 64, 8) k_layer_oc_lane(const OcArgs
         // of channel 0, and its row and column; the same for every pixel of the ticket
         const bool has_tap = k_begin + lane < k_end;
         uint32_t tap_off, tap_at;
-        const char* weights;
+        __amdgpu_buffer_rsrc_t weights;
         {
             const OcArgs& a = reload_args();
             uint32_t r, kw;
@@ -307,7 +310,8 @@ __global__ void __launch_bounds__(kOcWaves * 64, 8) k_layer_oc_lane(const OcArgs
             const uint32_t kh = div_mod(r, (uint32_t)a.p.KW, a.plan.inv_KW, kw);
             tap_off = (ci * (uint32_t)a.p.H + kh) * (uint32_t)a.p.W + kw;
             tap_at = kh | (kw << 16);                               // below 2^15 each
-            weights = reinterpret_cast<const char*>(a.p.tile + ((int64_t)k_begin * a.p.oc_pad + (int64_t)ocb * 64));
+            weights = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint2*>(a.p.tile + ((int64_t)k_begin * a.p.oc_pad + (int64_t)ocb * 64)), 0, -1, 0x00020000);
         }
 
         for (int pp = 0; pp < ppw; ++pp) {
@@ -528,7 +532,8 @@ constexpr int kOcWavesPerCu = 32;
 struct OcChunks { int n_chunks, kc; };
 inline OcChunks oc_lane_chunks(const LayerParams& p, bool budget_map)
 {
-    int max_taps = oc_tuning().max_taps;
+    // the rows of a chunk's weights are addressed with offsets below 2^31
+    int max_taps = std::max(1, (int)std::min<int64_t>(oc_tuning().max_taps, ((1ll << 31) - 1) / ((int64_t)p.oc_pad * 8)));
     const int64_t n_ocb = p.oc_pad / 64;
     const int64_t npix = (int64_t)p.N * p.OH * p.OW;
     OcChunks c;

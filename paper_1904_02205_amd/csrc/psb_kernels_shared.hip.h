@@ -224,13 +224,13 @@ __device__ __forceinline__ void sample_planes_slots(const FilterJob& j, uint32_t
         if (kPer * b >= j.from && kPer * (b + 1) <= j.to) {
 #pragma unroll
             for (int t = 0; t < TAPS; ++t) {
-                n[t] = sample_block<4, P7>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, 0, 0);
+                n[t] = sample_block<4, P7, false>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);     // one call after the other (eight waves per SIMD)
             }
         } else {
 #pragma unroll
             for (int t = 0; t < TAPS; ++t)
-                n[t] = sample_block<0, P7>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, j.from, j.to);
+                n[t] = sample_block<0, P7, false>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, j.from, j.to);
         }
     }
 
