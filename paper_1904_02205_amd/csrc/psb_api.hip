@@ -256,14 +256,13 @@ void launch_contraction(const psb::SharedParams& p, int planes, int half_tiles, 
 
 // Which kernel serves a call on this layer under the current mapping switch (1, 2, 3), or a psb_status: a call with S samples
 // everywhere, or (budget_map) with a budget per pixel.
-int pick_mapping(const psb_weights* q, const psb::LayerParams& p, int32_t S, bool budget_map)
+int pick_mapping(const psb_weights* q, const psb::LayerParams& p, int32_t S, bool budget_map, const psb::OcChunks& chunks)
 {
     int mapping = g_mapping;
     if (mapping == 2 && q->shape.groups != 1) return PSB_ERR_SHAPE;
     if (mapping == 0) {
         const int per_block = p.prob_bits <= 7 ? 16 : 4;
         const int samples = budget_map ? p.s_max : std::min(S, p.s_max);
-        const psb::OcChunks chunks = psb::oc_lane_chunks(p, budget_map);
         psb::LayerWork work;
         work.K = p.K; work.OC = p.OC; work.n_live = q->info.n_live;
         work.pixels = (double)p.N * p.OH * p.OW;
@@ -272,6 +271,7 @@ int pick_mapping(const psb_weights* q, const psb::LayerParams& p, int32_t S, boo
         work.lane_chunks = chunks.n_chunks; work.lane_taps = chunks.kc;
         work.list_channels = psb::list_channels_per_wg(p.K);
         work.list_pixels = psb::kListPixels; work.list_taps = psb::kListTaps;
+        work.packed_pixels = chunks.pack_log ? 64 >> chunks.pack_log : 0;
         const bool mostly_pruned = 3 * q->info.n_live < (int64_t)q->shape.oc * q->K;
         // (the list's grid holds 65535 channels)
         const bool lanes = (!mostly_pruned && psb::prefer_channel_lanes(work, psb::oc_lane_cus())) || p.OC > 65535;
@@ -318,10 +318,11 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
     PSB_HIP_TRY(hipGetDevice(&dev));
     if (dev != q->device) return PSB_ERR_DEVICE;
 
-    int mapping = pick_mapping(q, p, S, budget_to != nullptr);
+    const psb::OcChunks chunks = psb::oc_lane_chunks(p, budget_to != nullptr);
+    int mapping = pick_mapping(q, p, S, budget_to != nullptr, chunks);
     if (mapping < 0) return mapping;
     // the channel-lane kernel combines the partial sums of a split tap reduction in scratch accumulators
-    bool split = mapping == 2 && psb::oc_lane_chunks(p, budget_to != nullptr).n_chunks > 1;
+    bool split = mapping == 2 && chunks.n_chunks > 1;
     bool capturing = false;
     if (use_static_scratch) {           // the accumulators lie in the static array: nothing is allocated
         uint32_t* base = nullptr;
@@ -351,7 +352,7 @@ int launch_layer(const psb_weights* q, const int8_t* x, const psb_conv_geom* g, 
     }
 
     if (mapping == 2) {
-        rc = psb::launch_oc_lane(p, stream, profile_begin, profile_end);
+        rc = psb::launch_oc_lane(p, chunks, stream, profile_begin, profile_end);
         if (rc != 0) { tl_last_device_error = rc; return PSB_ERR_DEVICE; }
         if (split && !use_static_scratch && !capturing) q->ws->acc_cl_clean = true;
     } else if (mapping == 3) {
@@ -842,7 +843,8 @@ int psb_query_mapping_call(const psb_weights_t* q, const psb_conv_geom* geom, in
     if (rc != PSB_OK) return rc;
     psb::LayerParams p;
     fill_geometry(q, geom, OH, OW, p);
-    return pick_mapping(q, p, S, budget_map != 0);
+    p.S = S;
+    return pick_mapping(q, p, S, budget_map != 0, psb::oc_lane_chunks(p, budget_map != 0));
 }
 
 int psb_profile_enable(int on)

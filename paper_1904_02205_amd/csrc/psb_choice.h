@@ -4,8 +4,11 @@
 // list also has a chain of latencies per ten taps and work per tap and pixel that is there whatever the activations are.
 // How many of them are zero is not known on the host, and with a budget map neither is the number of samples.  So the rule
 // compares the estimates at both ends, a quarter of the activations not zero and all of them, and departs from the plain
-// answer - channel lanes for dense layers that fill at least half of the lanes of their last block, else the list - only if
-// the other kernel is not slower at either end by more than 15 % and faster by 5 % in the mean of the two.
+// answer - channel lanes for dense layers that fill at least half of the lanes of their last block (or pack it for four or eight
+// pixels, with three quarters of the weights live), else the list - only if
+// the other kernel is not slower at either end by more than 15 % and faster by 5 % in the mean of the two.  (Lanes packed for
+// two pixels have to be 5 % faster at either end: a tap is skipped there only if both pixels have a zero, so what they gain
+// depends most on what the host does not know.  3x3 24->20 on 3360 pixels, S = 32, lanes : list, estimates 95:96 and 194:251: list.)
 // 3x3 on 64 channels, 4704 pixels, lanes : list in us, 8 channels, S = 4: 59:131 with a quarter, 188:229 with all (lanes); S = 8:
 // 96:140 and 331:255 (list); 70 channels, S = 8: 177:292, 644:691 (lanes); 37->70, 5x5, 324 pixels, S = 10: 71:504 with half (lanes).
 // Host code only (no HIP types), so that the rule can be tested against measured times without a GPU.
@@ -26,6 +29,7 @@ struct LayerWork {
     int lane_chunks, lane_taps; // channel lanes: chunks of the tap reduction, taps per chunk
     int list_channels;          // product list: channels of a workgroup, and its pixels
     int list_pixels, list_taps; // ... and live taps per chunk
+    int packed_pixels = 0;      // channel lanes: pixels of a packed ticket of the last channel block (0: none)
 };
 
 // The estimates, in us, with the share `density` of the activations not zero and `blocks` generator blocks per product.  Their
@@ -33,14 +37,23 @@ struct LayerWork {
 // 32 and 7 bits, budget maps): the root mean square of the relative error is 9 % for the lanes, 13 % for the list.
 
 // Channel lanes: a ticket (one pixel, 64 channels, a chunk of taps) takes 0.24 us of a SIMD, and 58 ns per generator call of its
-// wave; the last ticket of a wave runs alone.  A split reduction has a second launch.
+// wave; the last ticket of a wave runs alone.  A split reduction has a second launch.  A packed ticket (several pixels of the last
+// channels) takes another 0.075 us a pixel, and a call wherever one of its pixels has an activation.
 inline double channel_lane_us(const LayerWork& w, double density, double blocks, int n_cus)
 {
-    const bool split = w.lane_chunks > 1;
-    const double calls_us = 0.063 * density * w.lane_taps * blocks;
-    const double tickets = w.pixels * w.lane_chunks * ((w.OC + 63) / 64) / (4.0 * n_cus);      // per SIMD
-    const double us = 4.9 + (split ? 3.9 : 0.0) + tickets * (0.24 + 0.925 * calls_us) + 1.3 * calls_us;
-    return std::max(us, split ? 14.5 : 12.0);                                                 // what launching takes
+    const bool split = w.lane_chunks > 1, packed = w.packed_pixels > 1;
+    const double call_us = 0.061 * w.lane_taps * blocks;
+    const double plain_blocks = (w.OC + 63) / 64 - (packed ? 1 : 0), per_simd = w.lane_chunks / (4.0 * n_cus);
+    double us = 4.9 + (split ? 3.9 : 0.0) + w.pixels * plain_blocks * per_simd * (0.24 + 0.925 * density * call_us);
+    double last = plain_blocks > 0 ? density : 0.0;
+    if (packed) {
+        double none = 1.0 - density;                     // a tap has no activation at any of the 2, 4 or 8 pixels
+        for (int n = 1; n < w.packed_pixels; n *= 2) none *= none;
+        const double any = 1.0 - none;
+        us += std::ceil(w.pixels / w.packed_pixels) * per_simd * (0.24 + 0.075 * w.packed_pixels + 0.925 * any * call_us);
+        last = any;
+    }
+    return std::max(us + 1.3 * last * call_us, split ? 14.5 : 12.0);                          // what launching takes
 }
 
 // Product list: a workgroup walks its live taps ten at a time, up to eight blocks a pass; a chunk takes 1.9 us alone on its CU (table,
@@ -64,13 +77,15 @@ inline double product_list_us(const LayerWork& w, double density, double blocks,
 inline bool prefer_channel_lanes(const LayerWork& w, int n_cus)
 {
     const int last = w.OC % 64;
-    const bool plain = 2 * w.n_live >= (int64_t)w.OC * w.K && (last == 0 || last >= 32 || w.OC >= 256);
+    const bool plain = 2 * w.n_live >= (int64_t)w.OC * w.K && (last == 0 || last >= 32 || w.OC >= 256 ||
+                                                                     (w.packed_pixels > 2 && 4 * w.n_live >= 3 * (int64_t)w.OC * w.K));
     auto list_over_lanes = [&](double density, double blocks) {
         return std::log(product_list_us(w, density, blocks, n_cus) / channel_lane_us(w, density, blocks, n_cus));
     };
     const double sparse = list_over_lanes(0.25, w.budget_map ? 1.0 : w.blocks), full = list_over_lanes(1.0, w.blocks);
     const double sign = plain ? -1.0 : 1.0;               // > 0: the other kernel is the faster one
-    const bool other = std::min(sign * sparse, sign * full) >= -std::log(1.15) && sign * (sparse + full) > 0.1;
+    const bool two_pixels = !plain && w.packed_pixels == 2;
+    const bool other = std::min(sign * sparse, sign * full) >= (two_pixels ? 0.05 : -std::log(1.15)) && sign * (sparse + full) > 0.1;
     return plain != other;
 }
 

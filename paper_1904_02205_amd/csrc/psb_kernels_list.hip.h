@@ -73,11 +73,10 @@ __global__ void __launch_bounds__(256) k_live_index(const uint32_t* __restrict__
 // NB = 0: per-pixel ranges [from, to), any values.
 // P7: 7-bit uniforms, 16 samples per block; otherwise 32-bit uniforms, 4 per block.
 // INSIDE: every tap of every output pixel lies inside the image (1 x 1 layers, unpadded layers): no bounds checks.
-template <int NB, bool P7, bool INSIDE, bool MULTI>
-__global__ void __launch_bounds__(kListPixels, NB > 6 ? 5 : NB > 4 ? 4 : 6) k_layer_product_list(const LayerParams p,
-                                                                    const uint32_t* __restrict__ live_idx,
-                                                                    const uint32_t* __restrict__ live_cnt,
-                                                                    int channels_per_wg)
+// GAPS: issue_gap() between the rounds, for calls with several workgroups for every CU.
+template <int NB, bool P7, bool INSIDE, bool MULTI, bool GAPS>
+__device__ __forceinline__ void product_list(const LayerParams& p, const uint32_t* __restrict__ live_idx,
+                                             const uint32_t* __restrict__ live_cnt, int channels_per_wg)
 {
     static_assert(NB <= 8, "table rows are kept for eight blocks");
     constexpr bool HOIST = NB >= 1;      // the tap- and the pixel-independent parts of rounds 0..2 come from tables
@@ -276,9 +275,9 @@ __global__ void __launch_bounds__(kListPixels, NB > 6 ? 5 : NB > 4 ? 4 : 6) k_la
                             const uint2 tb = tap_blk[slot][j];
                             if (!WHOLE && kPer * (j0 + j) >= s_uniform) break;          // uniform
                             if (WHOLE || kPer * (j0 + j + 1) <= s_uniform)               // uniform
-                                cnt[u] = sample_block<4, P7>(cnt[u], thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j0 + j, 0, 0);
+                                cnt[u] = sample_block<4, P7, GAPS>(cnt[u], thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j0 + j, 0, 0);
                             else
-                                cnt[u] = sample_block<0, P7>(cnt[u], thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j0 + j, 0, s_uniform);
+                                cnt[u] = sample_block<0, P7, GAPS>(cnt[u], thr, TapScalars{tb.x, tb.y}, h, pb.x, pb.y, key, j0 + j, 0, s_uniform);
                         }
                     }
 #pragma unroll
@@ -320,6 +319,21 @@ __global__ void __launch_bounds__(kListPixels, NB > 6 ? 5 : NB > 4 ? 4 : 6) k_la
     }   // channels of this workgroup (acc_s and o_s are only touched by their own lane between the barriers)
 }
 
+constexpr int list_wgs(int nb) { return nb > 6 ? 5 : nb > 4 ? 4 : 6; }
+
+template <int NB, bool P7, bool INSIDE, bool MULTI>
+__global__ void __launch_bounds__(kListPixels, list_wgs(NB)) k_layer_product_list(const LayerParams p, const uint32_t* __restrict__ live_idx,
+                                                                                  const uint32_t* __restrict__ live_cnt, int channels_per_wg)
+{
+    product_list<NB, P7, INSIDE, MULTI, false>(p, live_idx, live_cnt, channels_per_wg);
+}
+template <int NB, bool P7, bool INSIDE, bool MULTI>
+__global__ void __launch_bounds__(kListPixels, list_wgs(NB)) k_layer_product_list_gaps(const LayerParams p, const uint32_t* __restrict__ live_idx,
+                                                                                       const uint32_t* __restrict__ live_cnt, int channels_per_wg)
+{
+    product_list<NB, P7, INSIDE, MULTI, true>(p, live_idx, live_cnt, channels_per_wg);
+}
+
 // enough channels per workgroup for about 64 taps of work per pixel, at most 8
 inline int list_channels_per_wg(int K) { return std::min(8, std::max(1, 64 / std::max(1, K))); }
 
@@ -352,9 +366,14 @@ inline int launch_product_list(const LayerParams& p, const uint32_t* live_idx, c
     const bool timed = prof_begin(stream, &slot);
     const bool inside = p.pad_h == 0 && p.pad_w == 0 && (int64_t)(p.OH - 1) * p.stride_h + p.KH <= p.H &&
                         (int64_t)(p.OW - 1) * p.stride_w + p.KW <= p.W;
+    // (with fewer workgroups the gaps are waiting time: 1x1 200->4 on 6272 pixels, S = 16, 100 workgroups, 72 us without, 87 with)
+    const bool gaps = gx * gy >= 4ll * oc_lane_cus();
     auto launch = [&](auto nb_c, auto p7_c, auto inside_c, auto multi_c) {
-        hipLaunchKernelGGL((k_layer_product_list<decltype(nb_c)::value, decltype(p7_c)::value, decltype(inside_c)::value, decltype(multi_c)::value>),
-                           grid, block, 0, stream, p, live_idx, live_cnt, channels_per_wg);
+        constexpr int NB = decltype(nb_c)::value;
+        constexpr bool P7 = decltype(p7_c)::value, INSIDE = decltype(inside_c)::value, MULTI = decltype(multi_c)::value;
+        auto kernel = k_layer_product_list<NB, P7, INSIDE, MULTI>;
+        if constexpr (NB > 0) kernel = gaps ? k_layer_product_list_gaps<NB, P7, INSIDE, MULTI> : kernel;
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, p, live_idx, live_cnt, channels_per_wg);
     };
     auto with_inside = [&](auto nb_c, auto p7_c, auto multi_c) {
         if (inside) launch(nb_c, p7_c, std::true_type{}, multi_c);

@@ -30,14 +30,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "psb_kernels.hip.h"
+#include "psb_oc_plan.h"
 
 namespace psb {
-
-constexpr int kOcWaves = 16;    // waves per workgroup
-constexpr int kOcMaxTaps = 64;  // taps per step of a wave: one activation per lane
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
@@ -47,6 +47,12 @@ __device__ __forceinline__ int32_t mul24(int32_t x /* scalar */, int32_t n)
 {
     int32_t d;
     asm("v_mul_i32_i24 %0, %1, %2" : "=v"(d) : "s"(x), "v"(n));
+    return d;
+}
+__device__ __forceinline__ int32_t mul24_lanes(int32_t x, int32_t n)
+{
+    int32_t d;
+    asm("v_mul_i32_i24 %0, %1, %2" : "=v"(d) : "v"(x), "v"(n));
     return d;
 }
 __device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c)
@@ -157,6 +163,11 @@ __device__ __forceinline__ void block_setup(const PixelHoist& h, const Keys& key
 struct Step {
     unsigned long long mask;      // taps whose product needs sampling (scalar)
     int32_t xv;                   // lane t: activation of tap t of the step
+    // packed steps (2, 4 or 8 pixels): lane t has the activations of tap t at pixels 0..3 in the bytes of xv, at 4..7 in xv_more
+    int32_t xv_more;
+    uint32_t x_shift;             // this lane's pixel: 8 (pixel mod 4) ...
+    bool x_more;                  // ... and whether it is one of 4..7
+    bool eight;                   // eight pixels (scalar)
     __amdgpu_buffer_rsrc_t w;     // the weights from the step's first tap and the ticket's first channel on (scalar)
     uint32_t w_stride;            // bytes between the weights of consecutive taps (scalar)
     uint32_t k0;                  // the step's first tap (scalar)
@@ -170,7 +181,9 @@ struct Step {
 // and its weights - 512 consecutive bytes, which the waves of a CU share through L1 and L2 - are requested one product
 // ahead.  One generator call after the other: eight waves per SIMD hide each other's latencies, and a call costs a
 // SIMD 57.5 ns then (69 ns with four waves that interleave two or four calls each, when it was 63).
-template <int NB, int VALID, bool P7>
+// PACKED: the lanes are groups of channels of several pixels, see Step; lane is the channel then, and a tap is skipped only if
+// all of these pixels have a zero there.
+template <int NB, int VALID, bool P7, bool PACKED, bool GAPS>
 __device__ __forceinline__ int32_t process_step(const Step& s, int lane, int j0, int from, int to, const PixelHoist& h,
                                                 const Keys& key)
 {
@@ -194,14 +207,22 @@ __device__ __forceinline__ int32_t process_step(const Step& s, int lane, int j0,
         return Product{last, make_uint2(e.x, e.y)};
     };
     auto sample = [&](const Product& q) {
-        const int32_t x = __builtin_amdgcn_readlane(s.xv, (int)q.t);
+        int32_t x = __builtin_amdgcn_readlane(s.xv, (int)q.t);
         uint32_t n = nsamp;
 #pragma unroll
         for (int jj = 0; jj < NB; ++jj) {
-            n = sample_block<VALID, P7>(n, q.wt.x, tap_scalars(s_hib[jj] ^ (s.k0 + q.t), key), h, hz[jj], lo2[jj], key, j0 + jj, from, to);
+            n = sample_block<VALID, P7, GAPS>(n, q.wt.x, tap_scalars(s_hib[jj] ^ (s.k0 + q.t), key), h, hz[jj], lo2[jj], key, j0 + jj, from, to);
             __builtin_amdgcn_sched_barrier(0);     // one call after the other: interleaved calls only take more registers
         }
-        acc = mad24(mul24(x, (int32_t)n), (int32_t)q.wt.y, acc);
+        if constexpr (PACKED) {
+            if (s.eight) {
+                const int32_t more = __builtin_amdgcn_readlane(s.xv_more, (int)q.t);
+                x = s.x_more ? more : x;
+            }
+            acc = mad24(mul24_lanes(__builtin_amdgcn_sbfe(x, s.x_shift, 8u), (int32_t)n), (int32_t)q.wt.y, acc);
+        } else {
+            acc = mad24(mul24(x, (int32_t)n), (int32_t)q.wt.y, acc);
+        }
     };
     int left = __popcll(s.mask);
     Product a = take();
@@ -215,15 +236,48 @@ __device__ __forceinline__ int32_t process_step(const Step& s, int lane, int j0,
     return acc;
 }
 
-// How the launcher cuts a call into tickets.
-struct OcPlan {
-    int n_chunks, kc;             // the taps are cut into n_chunks chunks of kc taps, none empty
-    int ppw;                      // consecutive pixels of a ticket
-    uint32_t pixel_groups;        // groups of ppw pixels
-    uint32_t n_tickets;           // pixel_groups * n_chunks * channel blocks
-    uint32_t rounds;              // rounds in which every workgroup takes a whole batch of tickets
-    uint32_t inv_groups, inv_chunks, inv_KHW, inv_KW;     // inverse_of()
-};
+// All samples of a step in [from, to); see k_layer_oc_lane for the template parameters.
+template <int FIXED_NB, bool FIXED_P7, int FIXED_VALID, bool PACKED, bool GAPS>
+__device__ __forceinline__ int32_t walk_step(const Step& step, int lane, int from, int to, const PixelHoist& h, const Keys& key)
+{
+    int32_t total = 0;
+#define PSB_STEP(NB_, VALID_, J0_, FROM_, TO_) total += process_step<NB_, VALID_, FIXED_P7, PACKED, GAPS>(step, lane, J0_, FROM_, TO_, h, key)
+    if constexpr (FIXED_NB > 0) {
+        PSB_STEP(FIXED_NB, FIXED_VALID, 0, 0, 0);
+    } else {
+        // Any range: a first block that is not drawn from its start, whole blocks, a last block that is not
+        // drawn to its end.  Every part is compiled for its number of blocks and goes over the mask once.
+        constexpr int kPer = FIXED_P7 ? 16 : 4;       // samples of a generator block
+        int at = from;
+        if (at & (kPer - 1)) {
+            const int end = min(to, (at | (kPer - 1)) + 1);
+            PSB_STEP(1, 0, at / kPer, at, end);
+            at = end;
+        }
+        if (at == 0 && to >= 2 * kPer) {               // blocks 0 and 1 share two multiplies and two xors
+            PSB_STEP(2, 4, 0, 0, 0);
+            at = 2 * kPer;
+        }
+        for (; to - at >= 2 * kPer; at += 2 * kPer) PSB_STEP(2, 4, at / kPer, 0, 0);
+        if (to - at >= kPer) {
+            PSB_STEP(1, 4, at / kPer, 0, 0);
+            at += kPer;
+        }
+        const int left = to - at;                      // the first samples of block at / kPer
+        if constexpr (FIXED_P7) {
+            if (left & 3) PSB_STEP(1, 0, at / kPer, at, to);
+            else if (left == 4) PSB_STEP(1, 1, at / kPer, 0, 0);
+            else if (left == 8) PSB_STEP(1, 2, at / kPer, 0, 0);
+            else if (left == 12) PSB_STEP(1, 3, at / kPer, 0, 0);
+        } else {
+            if (left == 1) PSB_STEP(1, 1, at / kPer, 0, 0);
+            else if (left == 2) PSB_STEP(1, 2, at / kPer, 0, 0);
+            else if (left == 3) PSB_STEP(1, 3, at / kPer, 0, 0);
+        }
+    }
+#undef PSB_STEP
+    return total;
+}
 
 // Workgroup b of a grid of n runs on XCD b mod 8: its position when the workgroups of an XCD are next to each other.
 __device__ __forceinline__ uint32_t xcd_grouped(uint32_t b, uint32_t n)
@@ -246,6 +300,66 @@ __device__ __forceinline__ const OcArgs& reload_args()
     return *(const OcArgs*)ptr;
 }
 
+// A packed ticket: 64 >> pack_log consecutive pixels and a chunk of taps of the last channel block, which has at most
+// 1 << pack_log channels.  Lane = (pixel, channel); see oc_chunks().
+template <int FIXED_NB, bool FIXED_P7, int FIXED_VALID, bool GAPS>
+__device__ __forceinline__ void packed_ticket(const Keys& key, int lane, uint32_t pgroup, uint32_t ocb, int k_begin, bool has_tap,
+                                              uint32_t tap_off, uint32_t tap_at, __amdgpu_buffer_rsrc_t weights)
+{
+    const OcArgs& a = reload_args();
+    const LayerParams& p = a.p;
+    const int pack_log = a.plan.pack_log;
+    const uint32_t pixels = 64u >> pack_log, hw = (uint32_t)(p.OH * p.OW), npix = (uint32_t)p.N * hw;
+    const uint32_t pix_first = pgroup * pixels;
+    // activations: lane = tap, the pixels one after the other (scalar geometry), four to a word
+    int32_t xv[2] = {0, 0};
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        if ((uint32_t)(4 * half) >= pixels) break;           // uniform
+        int32_t byte[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t pix = pix_first + (uint32_t)(4 * half + i);
+            uint32_t ox, oy;
+            const uint32_t row = div_mod(pix, (uint32_t)p.OW, p.inv_OW, ox);
+            const uint32_t n = div_mod(row, (uint32_t)p.OH, p.inv_OH, oy);
+            const int iy0 = (int)oy * p.stride_h - p.pad_h, ix0 = (int)ox * p.stride_w - p.pad_w;
+            const uint32_t x_base = (n * (uint32_t)(p.C * p.H) + (uint32_t)iy0) * (uint32_t)p.W + (uint32_t)ix0;
+            byte[i] = 0;
+            if ((uint32_t)(4 * half + i) < pixels && pix < npix && has_tap && (unsigned)(iy0 + (int)(tap_at & 0xFFFFu)) < (unsigned)p.H &&
+                (unsigned)(ix0 + (int)(tap_at >> 16)) < (unsigned)p.W)
+                byte[i] = (int32_t)(uint8_t)p.x[x_base + tap_off];
+        }
+        xv[half] = byte[0] | (byte[1] << 8) | (byte[2] << 16) | (byte[3] << 24);
+    }
+    const uint32_t sub = (uint32_t)lane >> pack_log, channel = (uint32_t)lane & ((1u << pack_log) - 1u);
+    const uint32_t pix = pix_first + sub, oc = ocb * 64u + channel;
+    uint32_t ox, oy;
+    const uint32_t row = div_mod(pix, (uint32_t)p.OW, p.inv_OW, ox);
+    const uint32_t n = div_mod(row, (uint32_t)p.OH, p.inv_OH, oy);
+    const uint32_t o = pix + n * (uint32_t)(p.OC - 1) * hw + oc * hw;
+    PixelHoist h;
+    uint32_t hi_a, lo_b1;
+    mulhilo(kMulA, o, hi_a, h.lo_a);
+    mulhilo(kMulB, hi_a ^ p.layer_id ^ key.k1[0], h.hi_b1, lo_b1);
+    h.y2k = lo_b1 ^ key.k0[2];
+    const int to = min(p.S, p.s_max);
+    int32_t total = 0;
+    const Step step{__ballot((xv[0] | xv[1]) != 0), xv[0], xv[1], 8u * (sub & 3u), sub >= 4u, pixels == 8u,
+                    weights, (uint32_t)p.oc_pad * 8u, (uint32_t)k_begin};
+    if (to > 0 && step.mask != 0ull)
+        total = walk_step<FIXED_NB, FIXED_P7, FIXED_VALID, true, GAPS>(step, (int)channel, 0, to, h, key);
+    const OcArgs& b = reload_args();
+    if (oc < (uint32_t)b.p.OC && pix < npix) {
+        if (b.plan.n_chunks == 1) {
+            if (b.p.acc) b.p.acc[o] = total;
+            emit(b.p, o, (int)oc, total, to);
+        } else if (total != 0) {
+            atomicAdd(&b.p.acc_cl[(int64_t)pix * b.p.oc_pad + oc], total);
+        }
+    }
+}
+
 // Persistent kernel of independent waves: two workgroups of sixteen per CU, eight waves per SIMD.  A ticket is one
 // (channel block, tap chunk, group of ppw pixels); tickets are numbered so that consecutive tickets are consecutive pixel
 // groups of the same (channel block, chunk), whose weights all waves then share in the caches.  Sixteen consecutive
@@ -259,7 +373,9 @@ __device__ __forceinline__ const OcArgs& reload_args()
 // a whole number of blocks).  Only that path of the sampling loop is compiled then.
 // FIXED_VALID < 4 (with FIXED_NB = 1, 7-bit uniforms): every pixel draws the first 4 FIXED_VALID samples of block 0
 // (S = 4, 8 or 12: a 16-sample block is more than such a call needs).
-template <int FIXED_NB = 0, bool FIXED_P7 = false, int FIXED_VALID = 4>
+// PACK: the last channel block has at most 32 channels and goes to packed tickets (no budget maps).
+// GAPS: issue_gap() between the rounds, for calls that fill the chip.
+template <int FIXED_NB, bool FIXED_P7, int FIXED_VALID, bool PACK, bool GAPS>
 __global__ void __launch_bounds__(kOcWaves * 64, 8) k_layer_oc_lane(const OcArgs args)
 {
     const int lane = threadIdx.x & 63;
@@ -281,18 +397,24 @@ __global__ void __launch_bounds__(kOcWaves * 64, 8) k_layer_oc_lane(const OcArgs
         uint32_t drawn = 0;
         if (lane == 0) drawn = atomicAdd(&s_next, 1u);
         drawn = uniform_u32(drawn);
-        const uint32_t mine = xcd_grouped(blockIdx.x, gridDim.x), rounds = args.plan.rounds;
-        const uint32_t ticket = drawn < rounds * kOcWaves
-                                    ? ((drawn / kOcWaves) * gridDim.x + mine) * kOcWaves + drawn % kOcWaves
-                                    : (rounds * kOcWaves + (drawn - rounds * kOcWaves)) * gridDim.x + mine;
-        if (ticket >= args.plan.n_tickets) break;            // later draws of this workgroup lie beyond it, too
+        const OcTicket t = oc_ticket<PACK>(drawn, xcd_grouped(blockIdx.x, args.plan.grid), args.plan.grid, args.plan.rounds, args.plan.n_tickets,
+                                           args.plan.packed_rounds, args.plan.packed_left);
+        if (t.kind == 0u) break;                             // later draws of this workgroup lie beyond it, too
+        const uint32_t ticket = t.at;
+        const bool packed = PACK && t.kind == 2u;
 
         uint32_t pgroup, chunk, ocb;
         int k_begin, k_end, ppw;
         {
             const OcArgs& a = reload_args();
-            const uint32_t combo = div_mod(ticket, a.plan.pixel_groups, a.plan.inv_groups, pgroup);
-            ocb = div_mod(combo, (uint32_t)a.plan.n_chunks, a.plan.inv_chunks, chunk);
+            if constexpr (PACK) {
+                if (packed) chunk = div_mod(ticket, a.plan.pack_groups, a.plan.inv_pack_groups, pgroup);
+                ocb = (uint32_t)(a.p.oc_pad >> 6) - 1u;
+            }
+            if (!packed) {
+                const uint32_t combo = div_mod(ticket, a.plan.pixel_groups, a.plan.inv_groups, pgroup);
+                ocb = div_mod(combo, (uint32_t)a.plan.n_chunks, a.plan.inv_chunks, chunk);
+            }
             k_begin = (int)chunk * a.plan.kc;
             k_end = min(k_begin + a.plan.kc, a.p.K);
             ppw = a.plan.ppw;
@@ -314,6 +436,12 @@ __global__ void __launch_bounds__(kOcWaves * 64, 8) k_layer_oc_lane(const OcArgs
                 const_cast<uint2*>(a.p.tile + ((int64_t)k_begin * a.p.oc_pad + (int64_t)ocb * 64)), 0, -1, 0x00020000);
         }
 
+        if constexpr (PACK) {
+            if (packed) {
+                packed_ticket<FIXED_NB, FIXED_P7, FIXED_VALID, GAPS>(key, lane, pgroup, ocb, k_begin, has_tap, tap_off, tap_at, weights);
+                continue;
+            }
+        }
         for (int pp = 0; pp < ppw; ++pp) {
             // everything about a pixel but its activations is scalar
             const LayerParams& p = reload_args().p;
@@ -346,40 +474,9 @@ __global__ void __launch_bounds__(kOcWaves * 64, 8) k_layer_oc_lane(const OcArgs
                 int32_t xv = 0;
                 if (has_tap && (unsigned)(iy0 + (int)(tap_at & 0xFFFFu)) < (unsigned)p.H && (unsigned)(ix0 + (int)(tap_at >> 16)) < (unsigned)p.W)
                     xv = p.x[x_base + tap_off];                     // modulo 2^32: the element exists
-                const Step step{__ballot(xv != 0), xv, weights, (uint32_t)p.oc_pad * 8u, (uint32_t)k_begin};
+                const Step step{__ballot(xv != 0), xv, 0, 0u, false, false, weights, (uint32_t)p.oc_pad * 8u, (uint32_t)k_begin};
                 if (step.mask != 0ull) {
-#define PSB_STEP(NB_, VALID_, J0_, FROM_, TO_) \
-    total += process_step<NB_, VALID_, FIXED_P7>(step, lane, J0_, FROM_, TO_, h, key)
-                    if constexpr (FIXED_NB > 0) {
-                        PSB_STEP(FIXED_NB, FIXED_VALID, 0, 0, 0);
-                    } else {
-                        // Any range: a first block that is not drawn from its start, whole blocks, a last block that is not
-                        // drawn to its end.  Every part is compiled for its number of blocks and goes over the mask once.
-                        constexpr int kPer = FIXED_P7 ? 16 : 4;       // samples of a generator block
-                        int at = from;
-                        if (at & (kPer - 1)) {
-                            const int end = min(to, (at | (kPer - 1)) + 1);
-                            PSB_STEP(1, 0, at / kPer, at, end);
-                            at = end;
-                        }
-                        for (; to - at >= 2 * kPer; at += 2 * kPer) PSB_STEP(2, 4, at / kPer, 0, 0);
-                        if (to - at >= kPer) {
-                            PSB_STEP(1, 4, at / kPer, 0, 0);
-                            at += kPer;
-                        }
-                        const int left = to - at;                      // the first samples of block at / kPer
-                        if constexpr (FIXED_P7) {
-                            if (left & 3) PSB_STEP(1, 0, at / kPer, at, to);
-                            else if (left == 4) PSB_STEP(1, 1, at / kPer, 0, 0);
-                            else if (left == 8) PSB_STEP(1, 2, at / kPer, 0, 0);
-                            else if (left == 12) PSB_STEP(1, 3, at / kPer, 0, 0);
-                        } else {
-                            if (left == 1) PSB_STEP(1, 1, at / kPer, 0, 0);
-                            else if (left == 2) PSB_STEP(1, 2, at / kPer, 0, 0);
-                            else if (left == 3) PSB_STEP(1, 3, at / kPer, 0, 0);
-                        }
-                    }
-#undef PSB_STEP
+                    total = walk_step<FIXED_NB, FIXED_P7, FIXED_VALID, false, GAPS>(step, lane, from, to, h, key);
                 }
             }
             const OcArgs& a = reload_args();
@@ -519,37 +616,17 @@ inline int oc_lane_cus()
     return cus;
 }
 
-// resident waves per CU: the kernel is built for eight per SIMD
-constexpr int kOcWavesPerCu = 32;
-
-// How the launcher cuts the tap reduction of a layer: n_chunks chunks of kc taps (at most kOcMaxTaps), as equal as
-// possible, none empty; a layer too small to give every resident wave a ticket gets shorter chunks (down to 16
-// taps) instead of leaving part of the chip idle.  (Shorter chunks beyond that cost more set-up than they even out: 3x3
-// 64->64 at 56x56, 3.4 tickets of 64 taps per wave, 238 us with 64 and 32 taps, 241 with 24 and 16; 512->512 at 7x7, 7-bit,
-// 1577 / 1663 / 1864 us with 64 / 32 / 16.)  With a budget map the tickets of a call differ by the ratio of its budgets,
-// and 32 taps are better up to 32 tickets per wave (128->128 at 28x28, budgets 2..32, 28 of them: 898 -> 854 us).
-// With more than one chunk the partial sums meet in LayerParams::acc_cl, which the caller provides.
-struct OcChunks { int n_chunks, kc; };
-inline OcChunks oc_lane_chunks(const LayerParams& p, bool budget_map)
+// A call as the plan sees it; S is LayerParams::S.
+inline OcLayer oc_layer(const LayerParams& p, bool budget_map)
 {
-    // the rows of a chunk's weights are addressed with offsets below 2^31
-    int max_taps = std::max(1, (int)std::min<int64_t>(oc_tuning().max_taps, ((1ll << 31) - 1) / ((int64_t)p.oc_pad * 8)));
-    const int64_t n_ocb = p.oc_pad / 64;
-    const int64_t npix = (int64_t)p.N * p.OH * p.OW;
-    OcChunks c;
-    for (;;) {
-        c.n_chunks = (p.K + max_taps - 1) / max_taps;
-        c.kc = (p.K + c.n_chunks - 1) / c.n_chunks;
-        c.n_chunks = (p.K + c.kc - 1) / c.kc;
-        const int64_t waves = (int64_t)oc_lane_cus() * kOcWavesPerCu;
-        const int64_t want = budget_map && max_taps > 32 ? 32 * waves : waves;
-        if (npix * c.n_chunks * n_ocb >= want || max_taps <= 16) break;
-        max_taps /= 2;
-    }
-    return c;
+    const int per_block = p.prob_bits <= 7 ? 16 : 4;
+    return OcLayer{(int64_t)p.N * p.OH * p.OW, p.K, p.OC, (p.S + per_block - 1) / per_block, budget_map, oc_lane_cus(), oc_tuning().max_taps,
+                   std::max(1, oc_tuning().ppw)};
 }
+inline OcChunks oc_lane_chunks(const LayerParams& p, bool budget_map) { return oc_chunks(oc_layer(p, budget_map)); }
 
-inline int launch_oc_lane(const LayerParams& p, hipStream_t stream, ProfileBegin prof_begin, ProfileEnd prof_end)
+// chunks: oc_lane_chunks() of the call
+inline int launch_oc_lane(const LayerParams& p, const OcChunks& chunks, hipStream_t stream, ProfileBegin prof_begin, ProfileEnd prof_end)
 {
     if (!oc_lane_supported(p)) return (int)hipErrorInvalidValue;
     // one S everywhere, a whole number of generator blocks for which a specialised kernel is built (0: none)
@@ -565,34 +642,30 @@ inline int launch_oc_lane(const LayerParams& p, hipStream_t stream, ProfileBegin
     }
     const int n_ocb = p.oc_pad / 64;
     const int64_t npix = (int64_t)p.N * p.OH * p.OW;
-    const OcChunks chunks = oc_lane_chunks(p, p.budget_to != nullptr);
-    const int n_chunks = chunks.n_chunks;
+    OcPlan plan = oc_plan(oc_layer(p, p.budget_to != nullptr), chunks);
+    const int n_chunks = plan.n_chunks;
     if (n_chunks > 1 && !p.acc_cl) return (int)hipErrorInvalidValue;
-    const int64_t waves = (int64_t)oc_lane_cus() * kOcWavesPerCu;
-    OcPlan plan;
-    plan.n_chunks = n_chunks;
-    plan.kc = chunks.kc;
-    // one pixel per ticket (3x3 128->128 at 28x28, batch 8, S = 16: 1686 / 1705 / 1734 / 1759 us with 1 / 2 / 4 / 8), more only
-    // where the ticket numbers would not fit 31 bits
-    plan.ppw = std::max(1, oc_tuning().ppw);
-    while ((npix + plan.ppw - 1) / plan.ppw * n_chunks * n_ocb >= (1ll << 31)) plan.ppw *= 2;
-    const int64_t pixel_groups = (npix + plan.ppw - 1) / plan.ppw;
-    const int64_t n_tickets = pixel_groups * n_chunks * n_ocb;
-    plan.pixel_groups = (uint32_t)pixel_groups;
-    plan.n_tickets = (uint32_t)n_tickets;
     plan.inv_groups = inverse_of(plan.pixel_groups);
     plan.inv_chunks = inverse_of((uint32_t)n_chunks);
+    plan.inv_pack_groups = inverse_of(plan.pack_groups);
     plan.inv_KHW = inverse_of((uint32_t)(p.KH * p.KW));
     plan.inv_KW = inverse_of((uint32_t)p.KW);
-    // Two workgroups per CU; when one per CU is enough, one on every CU, though it has tickets for some of its waves only
-    // (as few full workgroups as possible would leave CUs idle: 1x1 128->32 at 14x14, S = 32, 1568 tickets, 29.1 -> 21.1 us).
-    const int64_t grid = std::min<int64_t>(n_tickets, n_tickets > waves / 2 ? waves / kOcWaves : waves / kOcWaves / 2);
-    plan.rounds = (uint32_t)(n_tickets / (grid * kOcWaves));
 
     int slot = 0;
     const bool timed = prof_begin(stream, &slot);
-#define PSB_OC_LAUNCH(NB_, P7_, VALID_)                                                                            \
-    hipLaunchKernelGGL((k_layer_oc_lane<NB_, P7_, VALID_>), dim3((unsigned)grid), dim3(kOcWaves * 64), 0, stream, OcArgs{p, plan})
+    auto launch_one = [&](auto nb_c, auto p7_c, auto valid_c, auto pack_c, auto gaps_c) {
+        hipLaunchKernelGGL((k_layer_oc_lane<decltype(nb_c)::value, decltype(p7_c)::value, decltype(valid_c)::value, decltype(pack_c)::value,
+                                            decltype(gaps_c)::value>),
+                           dim3(plan.grid), dim3(kOcWaves * 64), 0, stream, OcArgs{p, plan});
+    };
+    auto launch = [&](auto nb_c, auto p7_c, auto valid_c) {
+        if (plan.pack_log && plan.gaps) launch_one(nb_c, p7_c, valid_c, std::true_type{}, std::true_type{});
+        else if (plan.pack_log) launch_one(nb_c, p7_c, valid_c, std::true_type{}, std::false_type{});
+        else if (plan.gaps) launch_one(nb_c, p7_c, valid_c, std::false_type{}, std::true_type{});
+        else launch_one(nb_c, p7_c, valid_c, std::false_type{}, std::false_type{});
+    };
+#define PSB_OC_LAUNCH(NB_, P7_, VALID_) \
+    launch(std::integral_constant<int, NB_>{}, std::integral_constant<bool, P7_>{}, std::integral_constant<int, VALID_>{})
     if (p7) {
         if (fixed_nb == 0) PSB_OC_LAUNCH(0, true, 4);
         else if (fixed_nb == 2) PSB_OC_LAUNCH(2, true, 4);

@@ -1,0 +1,137 @@
+// How the channel-lane kernel cuts a call into tickets, and which workgroup takes which.  No HIP types, so that it can be
+// tested without a GPU; oc_ticket() is what the kernel itself runs.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+
+#ifdef __HIPCC__
+#define PSB_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define PSB_HOST_DEVICE inline
+#endif
+
+namespace psb {
+
+constexpr int kOcWaves = 16;         // waves per workgroup
+constexpr int kOcMaxTaps = 64;       // taps per step of a wave: one activation per lane
+constexpr int kOcWavesPerCu = 32;    // resident waves per CU: the kernel is built for eight per SIMD
+
+// A call, as the plan sees it.
+struct OcLayer {
+    int64_t npix;                    // output pixels
+    int K, OC;                       // taps of an output channel, channels
+    int blocks;                      // generator blocks of a product
+    bool budget_map;                 // per-pixel sample ranges
+    int n_cus;
+    int max_taps = kOcMaxTaps, ppw = 1;      // benchmark overrides
+};
+
+// The taps are cut into n_chunks chunks of kc taps, none empty.  pack_log: log2 of the channel slots of packed tickets (8, 16 or
+// 32, for 8, 4 or 2 pixels), 0: none.
+struct OcChunks { int n_chunks, kc, pack_log; };
+
+struct OcPlan {
+    int n_chunks, kc;
+    int ppw;                      // consecutive pixels of a ticket
+    uint32_t pixel_groups;        // groups of ppw pixels
+    uint32_t n_tickets;           // pixel_groups * n_chunks * channel blocks (without the packed one)
+    uint32_t rounds;              // rounds in which every workgroup takes a whole batch of tickets
+    uint32_t inv_groups, inv_chunks, inv_KHW, inv_KW;     // inverse_of(), set by the launcher
+    // packed tickets, for a last channel block of few channels: pack_groups groups of 64 >> pack_log pixels and a chunk each.
+    // They are the longer ones: every workgroup starts with packed_rounds of them, the first packed_left with one more
+    int pack_log;
+    uint32_t pack_groups, inv_pack_groups, packed_rounds, packed_left;
+    uint32_t grid;                // workgroups
+    bool gaps;                    // issue_gap() between the rounds of the generator
+};
+
+// n_chunks chunks of kc taps (at most kOcMaxTaps), as equal as possible, none empty; a layer too small to give every resident
+// wave a ticket gets shorter chunks (down to 16 taps) instead of leaving part of the chip idle.  (Shorter chunks beyond that
+// cost more set-up than they even out: 3x3 64->64 at 56x56, 3.4 tickets of 64 taps per wave, 238 us with 64 and 32 taps, 241 with
+// 24 and 16; 512->512 at 7x7, 7-bit, 1577 / 1663 / 1864 us with 64 / 32 / 16.)  With a budget map the tickets of a call differ by the
+// ratio of its budgets, and 32 taps are better up to 32 tickets per wave (128->128 at 28x28, budgets 2..32, 28 of them: 898 -> 854 us).
+// With more than one chunk the partial sums meet in LayerParams::acc_cl, which the caller provides.
+//
+// Packed tickets, for a last channel block of at most 32 channels: lane = (pixel, channel), so that a ticket of 5x5 37->70 on 324
+// pixels at S = 10 computes its last six channels for eight pixels at a time (66.8 -> 45.0 us).  A tap costs a call wherever one of
+// the pixels has an activation, so they are longer, and there are fewer: not in calls with less than two plain tickets of sixteen taps
+// for every resident wave (us, plain and packed - 1x1 128->134, 14x14, S = 5: 15.9, 19.7; 3x3 24->90, 18x18, S = 10: 18.0, 19.5; 3x3
+// 16->14, 1886 pixels, S = 8, all activations live: 46.6, 21.8), nor where they would split a reduction that is whole without them.  To
+// even them out a call of long tickets gets two of them and more for every wave (the call above: 51 us with one).
+inline OcChunks oc_chunks(const OcLayer& l)
+{
+    const int64_t waves = (int64_t)l.n_cus * kOcWavesPerCu;
+    const int64_t channel_blocks = ((int64_t)l.OC + 63) / 64;
+    // the rows of a chunk's weights are addressed with offsets below 2^31
+    const int longest = std::max(1, (int)std::min<int64_t>(l.max_taps, ((1ll << 31) - 1) / (channel_blocks * 512)));
+    auto cut = [&](int64_t tickets, int pack_log) {
+        OcChunks c{0, 0, pack_log};
+        for (int taps = longest;; taps /= 2) {
+            c.n_chunks = (l.K + taps - 1) / taps;
+            c.kc = (l.K + c.n_chunks - 1) / c.n_chunks;
+            c.n_chunks = (l.K + c.kc - 1) / c.kc;
+            const int64_t want = l.budget_map && taps > 32 ? 32 * waves : pack_log && c.kc * l.blocks >= 128 ? 2 * waves : waves;
+            if (tickets * c.n_chunks >= want || taps <= 16) return c;
+        }
+    };
+    const OcChunks plain = cut(l.npix * channel_blocks, 0);
+    const int last = l.OC % 64;
+    if (l.budget_map || l.ppw != 1 || last == 0 || last > 32 || l.npix * channel_blocks * ((l.K + 15) / 16) < 2 * waves) return plain;
+    const int pack_log = last <= 8 ? 3 : last <= 16 ? 4 : 5, pixels = 64 >> pack_log;
+    const OcChunks packed = cut(l.npix * (channel_blocks - 1) + (l.npix + pixels - 1) / pixels, pack_log);
+    // (ticket numbers fit 31 bits with one pixel per ticket, see oc_plan)
+    const bool fits = l.npix * packed.n_chunks * channel_blocks < (1ll << 31);
+    return (plain.n_chunks == 1 && packed.n_chunks > 1) || !fits ? plain : packed;
+}
+
+inline OcPlan oc_plan(const OcLayer& l, const OcChunks& chunks)
+{
+    const int64_t waves = (int64_t)l.n_cus * kOcWavesPerCu, channel_blocks = ((int64_t)l.OC + 63) / 64;
+    OcPlan plan{};
+    plan.n_chunks = chunks.n_chunks;
+    plan.kc = chunks.kc;
+    plan.pack_log = chunks.pack_log;
+    // one pixel per ticket (3x3 128->128 at 28x28, batch 8, S = 16: 1686 / 1705 / 1734 / 1759 us with 1 / 2 / 4 / 8), more only
+    // where the ticket numbers would not fit 31 bits
+    plan.ppw = std::max(1, l.ppw);
+    while ((l.npix + plan.ppw - 1) / plan.ppw * plan.n_chunks * channel_blocks >= (1ll << 31)) plan.ppw *= 2;
+    const int64_t pixel_groups = (l.npix + plan.ppw - 1) / plan.ppw;
+    const int pixels = plan.pack_log ? 64 >> plan.pack_log : 1;
+    const int64_t pack_groups = (l.npix + pixels - 1) / pixels;
+    const int64_t n_packed = plan.pack_log ? pack_groups * plan.n_chunks : 0;
+    const int64_t n_plain = pixel_groups * plan.n_chunks * (channel_blocks - (plan.pack_log ? 1 : 0)), n_all = n_plain + n_packed;
+    plan.pixel_groups = (uint32_t)pixel_groups;
+    plan.pack_groups = (uint32_t)pack_groups;
+    plan.n_tickets = (uint32_t)n_plain;
+    // Two workgroups per CU; when one per CU is enough, one on every CU, though it has tickets for some of its waves only
+    // (as few full workgroups as possible would leave CUs idle: 1x1 128->32 at 14x14, S = 32, 1568 tickets, 29.1 -> 21.1 us).
+    const int64_t grid = std::min<int64_t>(n_all, n_all > waves / 2 ? waves / kOcWaves : waves / kOcWaves / 2);
+    plan.grid = (uint32_t)grid;
+    // Alone on its SIMD, or nearly, a wave just waits in the gaps (1x1 67->26 on 64 pixels, S = 16, 9.7 us without, 12.2 with).
+    plan.gaps = n_all > waves / 2;
+    plan.rounds = (uint32_t)(n_plain / (grid * kOcWaves));
+    plan.packed_rounds = (uint32_t)(n_packed / grid);
+    plan.packed_left = (uint32_t)(n_packed % grid);
+    return plan;
+}
+
+// The ticket of draw number `drawn` of workgroup `mine` of `grid`: packed ones first, then sixteen at a time in turn with the other
+// workgroups, then (what does not fill a round) one by one.  kind 0: there is none, nor for later draws; 1: plain, 2: packed.
+struct OcTicket { uint32_t kind, at; };
+template <bool PACK>
+PSB_HOST_DEVICE OcTicket oc_ticket(uint32_t drawn, uint32_t mine, uint32_t grid, uint32_t rounds, uint32_t n_tickets, uint32_t packed_rounds,
+                                   uint32_t packed_left)
+{
+    if (PACK) {
+        const uint32_t first = packed_rounds + (mine < packed_left ? 1u : 0u);
+        if (drawn < first) return OcTicket{2u, drawn * grid + mine};
+        drawn -= first;
+    }
+    const uint32_t in_rounds = rounds * (uint32_t)kOcWaves;
+    const uint32_t at = drawn < in_rounds ? ((drawn / kOcWaves) * grid + mine) * kOcWaves + drawn % kOcWaves
+                                          : (in_rounds + (drawn - in_rounds)) * grid + mine;
+    return OcTicket{at < n_tickets ? 1u : 0u, at};
+}
+
+}  // namespace psb

@@ -1,0 +1,78 @@
+"""The cuts of the channel-lane kernel (csrc/psb_oc_plan.h): every ticket is drawn once, and packing changes no call that was whole."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1904_02205_amd", "csrc")
+
+PROGRAM = r"""
+#include "psb_oc_plan.h"
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+using namespace psb;
+static unsigned long long state = 12345;
+static unsigned below(unsigned n) { state = state * 6364136223846793005ull + 1442695040888963407ull; return (unsigned)(state >> 33) % n; }
+static int spread(int hi) { return std::max(1, (int)std::lround(std::exp(std::log((double)hi) * below(10001) / 10000.0))); }
+#define CHECK(c) do { if (!(c)) { std::printf("%s: npix %lld K %d OC %d blocks %d map %d cus %d\n", #c, (long long)l.npix, l.K, l.OC, l.blocks, \
+                                              (int)l.budget_map, l.n_cus); return 1; } } while (0)
+int main()
+{
+    int packed_calls = 0, whole = 0;
+    for (int i = 0; i < 20000; ++i) {
+        OcLayer l{spread(40000), spread(5000), spread(700), 1 + (int)below(8), below(4) == 0, below(3) ? 256 : 1 + (int)below(300)};
+        if (below(8) == 0) { l.ppw = 1 << below(3); l.max_taps = 1 + (int)below(64); }
+        const OcPlan p = oc_plan(l, oc_chunks(l));
+        const long long blocks = (l.OC + 63) / 64;
+        CHECK(p.n_chunks >= 1 && p.kc >= 1 && p.kc <= kOcMaxTaps && (long long)(p.n_chunks - 1) * p.kc < l.K && (long long)p.n_chunks * p.kc >= l.K);
+        CHECK((long long)p.kc * blocks * 512 < (1ll << 31));
+        CHECK(p.grid >= 1 && p.grid <= (unsigned)l.n_cus * 2);
+        if (p.pack_log) {
+            ++packed_calls;
+            const int last = l.OC % 64;
+            CHECK(!l.budget_map && p.ppw == 1 && last >= 1 && last <= (1 << p.pack_log) && p.pack_log >= 3 && p.pack_log <= 5);
+        }
+        OcLayer plain = l;                     // the same call if its last block could not be packed
+        plain.OC = (int)blocks * 64;
+        if (oc_chunks(plain).n_chunks == 1) { ++whole; CHECK(p.n_chunks == 1); }
+        const long long n_packed = p.pack_log ? (long long)p.pack_groups * p.n_chunks : 0;
+        CHECK((long long)p.n_tickets == (long long)p.pixel_groups * p.n_chunks * (blocks - (p.pack_log ? 1 : 0)));
+        if (p.n_tickets + n_packed > 2000000) continue;
+        std::vector<char> seen[2] = {std::vector<char>(p.n_tickets), std::vector<char>(n_packed)};
+        long long drawn_all = 0;
+        for (unsigned mine = 0; mine < p.grid; ++mine)
+            for (unsigned d = 0;; ++d) {
+                const OcTicket t = p.pack_log ? oc_ticket<true>(d, mine, p.grid, p.rounds, p.n_tickets, p.packed_rounds, p.packed_left)
+                                              : oc_ticket<false>(d, mine, p.grid, p.rounds, p.n_tickets, p.packed_rounds, p.packed_left);
+                if (t.kind == 0) {             // and the draws after it have none either
+                    for (unsigned e = d; e < d + 40; ++e)
+                        CHECK((p.pack_log ? oc_ticket<true>(e, mine, p.grid, p.rounds, p.n_tickets, p.packed_rounds, p.packed_left)
+                                          : oc_ticket<false>(e, mine, p.grid, p.rounds, p.n_tickets, p.packed_rounds, p.packed_left)).kind == 0);
+                    break;
+                }
+                std::vector<char>& s = seen[t.kind - 1];
+                CHECK(t.at < s.size() && !s[t.at]);
+                s[t.at] = 1;
+                ++drawn_all;
+            }
+        CHECK(drawn_all == (long long)p.n_tickets + n_packed);
+    }
+    std::printf("ok %d %d\n", packed_calls, whole);
+    return 0;
+}
+"""
+
+
+def test_every_ticket_is_drawn_once(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    (tmp_path / "plan.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-Werror", "-I", CSRC, str(tmp_path / "plan.cpp"), "-o", str(tmp_path / "plan")],
+                   check=True)
+    out = subprocess.run([str(tmp_path / "plan")], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    word, packed, whole = out.stdout.split()
+    assert word == "ok" and int(packed) > 1000 and int(whole) > 1000
