@@ -108,8 +108,9 @@ inline OcPlan oc_plan(const OcLayer& l, const OcChunks& chunks)
     // (as few full workgroups as possible would leave CUs idle: 1x1 128->32 at 14x14, S = 32, 1568 tickets, 29.1 -> 21.1 us).
     const int64_t grid = std::min<int64_t>(n_all, n_all > waves / 2 ? waves / kOcWaves : waves / kOcWaves / 2);
     plan.grid = (uint32_t)grid;
-    // Alone on its SIMD, or nearly, a wave just waits in the gaps (1x1 67->26 on 64 pixels, S = 16, 9.7 us without, 12.2 with).
-    plan.gaps = n_all > waves / 2;
+    // With two waves per SIMD and more the gaps between the rounds pay, alone on its SIMD a wave just waits in them (1x1 67->26 on 64
+    // pixels, S = 16, 320 tickets, 9.7 us without, 12.2 with; 1x1 253->64 at 14x14, S = 16, 3136 tickets, 22.4 without, 21.8 with).
+    plan.gaps = n_all >= waves / 4;
     plan.rounds = (uint32_t)(n_plain / (grid * kOcWaves));
     plan.packed_rounds = (uint32_t)(n_packed / grid);
     plan.packed_left = (uint32_t)(n_packed % grid);
