@@ -211,17 +211,21 @@ struct LayerParams {
 };
 
 // Asks for all of a kernel's arguments at once, first thing: a wave that reads them where it needs them waits for each 64-byte
-// line of the argument segment separately, and no cache has them when a launch begins (linear 512->256, batch 64: 21.1 -> 20.8 us,
-// other short calls 0.3 to 0.5 us).
-template <class Args>
-__device__ __forceinline__ void touch_arguments()
+// line of the argument segment separately, and no cache has them when a launch begins.  linear 512->256, batch 64: 21.1 -> 20.8 us,
+// other short calls 0.3 to 0.5 us a launch; the 25 launches of a ResNet-18-shaped shared-filter pass at batch 32: 392 -> 379 us.
+typedef const __attribute__((address_space(4))) uint32_t* ArgumentWords;
+template <int BYTES>
+__device__ __forceinline__ void touch_words(ArgumentWords words)
 {
-    typedef const __attribute__((address_space(4))) uint32_t* Words;
-    const Words words = (Words)__builtin_amdgcn_kernarg_segment_ptr();
     uint32_t all = 0;
 #pragma unroll
-    for (int i = 0; i < (int)((sizeof(Args) + 63) / 64); ++i) all ^= words[16 * i];
+    for (int i = 0; i < (BYTES + 63) / 64; ++i) all ^= words[16 * i];
     asm volatile("" : : "s"(all));
+}
+template <class... Args>
+__device__ __forceinline__ void touch_arguments()
+{
+    touch_words<(int)(sizeof(Args) + ...)>((ArgumentWords)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 // Number of samples i in [from,to) of product (o,k) whose uniform is below thr.

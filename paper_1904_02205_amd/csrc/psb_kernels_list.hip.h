@@ -325,12 +325,14 @@ template <int NB, bool P7, bool INSIDE, bool MULTI>
 __global__ void __launch_bounds__(kListPixels, list_wgs(NB)) k_layer_product_list(const LayerParams p, const uint32_t* __restrict__ live_idx,
                                                                                   const uint32_t* __restrict__ live_cnt, int channels_per_wg)
 {
+    touch_arguments<LayerParams>();
     product_list<NB, P7, INSIDE, MULTI, false>(p, live_idx, live_cnt, channels_per_wg);
 }
 template <int NB, bool P7, bool INSIDE, bool MULTI>
 __global__ void __launch_bounds__(kListPixels, list_wgs(NB)) k_layer_product_list_gaps(const LayerParams p, const uint32_t* __restrict__ live_idx,
                                                                                        const uint32_t* __restrict__ live_cnt, int channels_per_wg)
 {
+    touch_arguments<LayerParams>();
     product_list<NB, P7, INSIDE, MULTI, true>(p, live_idx, live_cnt, channels_per_wg);
 }
 

@@ -533,6 +533,7 @@ __global__ void __launch_bounds__(256) k_rescale(const LayerParams p)
 template <int PX>
 __global__ void __launch_bounds__(256) k_rescale_channels_last(const LayerParams p)
 {
+    touch_arguments<LayerParams>();
     __shared__ int32_t tile[64][PX + 1];
     const uint32_t hw = (uint32_t)(p.OH * p.OW);
     const uint32_t npix = (uint32_t)p.N * hw;                    // the number of outputs fits 32 bits
@@ -574,6 +575,7 @@ __global__ void __launch_bounds__(256) k_rescale_channels_last(const LayerParams
 // The same for 1 x 1 outputs (linear layers), where [N*OH*OW][oc] and [N][OC][OH][OW] run in the same order.
 __global__ void __launch_bounds__(256) k_rescale_rows(const LayerParams p)
 {
+    touch_arguments<LayerParams>();
     const uint32_t oc = blockIdx.y * 64u + (threadIdx.x & 63u), n = blockIdx.x * 4u + (threadIdx.x >> 6);
     if (n >= (uint32_t)p.N) return;
     int32_t* const at = p.acc_cl + ((uint64_t)n * (uint32_t)p.oc_pad + oc);

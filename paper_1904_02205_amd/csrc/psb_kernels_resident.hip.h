@@ -157,6 +157,7 @@ __device__ __forceinline__ void finish_tile(const SharedParams& p, const uint32_
 template <int P, int OUT, int NG, bool SEG>
 __global__ void __launch_bounds__(kResidentWaves * 64, 2) k_conv3x3_resident(const SharedParams p, const ResidentPlan plan)
 {
+    touch_arguments<SharedParams, ResidentPlan>();
     constexpr bool kStageRes = OUT == kOutRequant && NG > 7;
     extern __shared__ v4i win[];                   // entries of the tile's pixels; [chunk of 64 channels][quarter of 16][slot]; zeros
     __shared__ __align__(16) float s_mult[128], s_bias[128];            // read four at a time

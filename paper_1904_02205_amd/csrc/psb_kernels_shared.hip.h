@@ -411,7 +411,7 @@ __device__ __forceinline__ void channels_last_tile_wide(const TransposeJob& j, i
 // The digit planes of several layers in one launch (a network pass samples all its filters at once): job i owns
 // the workgroups [first_block[i], first_block[i + 1]); entries past the last job hold 0xFFFFFFFF.
 constexpr int kMaxBatchJobs = 32;
-struct FilterBatch {
+struct FilterBatch {                                         // jobs first: see k_sample_planes_batch
     FilterJob jobs[kMaxBatchJobs];
     unsigned first_block[kMaxBatchJobs + 1];
 };
@@ -426,6 +426,7 @@ __global__ void __launch_bounds__(256, 8) k_sample_planes_batch(const FilterBatc
     // Where the calls' straight-line code lies modulo 32 bytes makes up to 4 % of a launch (S = 64): with 0 to 12 of these in front, 0.96 to
     // 1.00 of the best with 23-bit probabilities and 0.98 to 1.00 with 7-bit ones; seven are good for both.
     asm volatile("s_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0\ns_nop 0");
+    touch_words<sizeof(FilterJob)>((ArgumentWords)((uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + (uint32_t)i * sizeof(FilterJob)));
     sample_planes_block(b.jobs[i], blockIdx.x - b.first_block[i]);
 }
 
@@ -438,6 +439,7 @@ __global__ void __launch_bounds__(256) k_sample_filter(const FilterJob j)
 // the rest transpose the activations.  The two jobs are independent of each other.
 __global__ void __launch_bounds__(256) k_shared_prologue(const FilterJob f, const TransposeJob t, unsigned filter_blocks)
 {
+    touch_arguments<FilterJob, TransposeJob, unsigned>();
     __shared__ __align__(16) int8_t tile[kWideTilePositions * kWideTileRow];
     if (blockIdx.x < filter_blocks) {        // uniform over the workgroup
         if (f.planes) sample_planes_block(f, blockIdx.x);
@@ -774,6 +776,7 @@ __device__ __forceinline__ void tile_epilogue(const SharedParams& p, v16i (&acc)
 template <int P, int OUT, int HT>
 __global__ void __launch_bounds__(256, (P == 4 && HT == 2) ? 1 : 2) k_conv_shared_mfma(const SharedParams p)
 {
+    touch_arguments<SharedParams>();
     __shared__ v4i a_lds[kStageSteps * P * 64];
     __shared__ float s_mult[32], s_bias[32];       // rescale factors of this block of channels (read after the loop)
     __shared__ int s_takes_part[4];                // per wave: one of its pixels takes part in the segment voted on
@@ -939,6 +942,7 @@ __global__ void __launch_bounds__(256, (P == 4 && HT == 2) ? 1 : 2) k_conv_share
 template <int P, int OUT, int HT, bool SEG>
 __global__ void __launch_bounds__(256, HT == 1 ? 4 : 2) k_conv_shared_mfma_resident(const SharedParams p, unsigned columns)
 {
+    touch_arguments<SharedParams, unsigned>();
     extern __shared__ v4i a_all[];                 // [n_steps][P][64]
     __shared__ float s_mult[32], s_bias[32];
 
@@ -1053,6 +1057,7 @@ __global__ void __launch_bounds__(256, HT == 1 ? 4 : 2) k_conv_shared_mfma_resid
 template <int P, int OUT, int HT, int TEAMS, int WS>
 __global__ void __launch_bounds__(256 * TEAMS, 2) k_conv3x3_window(const SharedParams p)
 {
+    touch_arguments<SharedParams>();
     extern __shared__ v4i win_lds[];
     __shared__ float s_mult[32], s_bias[32];
     __shared__ int s_segments;                     // segments of the sample axis that some pixel of the workgroup reaches
@@ -1281,6 +1286,7 @@ __global__ void __launch_bounds__(256 * TEAMS, 2) k_conv3x3_window(const SharedP
 // scalar work per tap than the loop counters; 3 x 3 depthwise layers have the unrolled kernel below instead.)
 __global__ void __launch_bounds__(256) k_conv_shared_direct(const SharedParams p)
 {
+    touch_arguments<SharedParams>();
     const int oc = blockIdx.y;
     const int64_t npix = (int64_t)p.N * p.OH * p.OW;
     const int64_t pix = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1325,6 +1331,7 @@ __global__ void __launch_bounds__(256) k_conv_shared_direct(const SharedParams p
 template <int KH, int KW>
 __global__ void __launch_bounds__(256) k_conv_shared_depthwise(const SharedParams p, int channels)
 {
+    touch_arguments<SharedParams, int>();
     const int64_t npix = (int64_t)p.N * p.OH * p.OW;
     const int64_t pix = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (pix >= npix) return;
