@@ -171,6 +171,7 @@ template <int TAPS, bool P7>
 __device__ __forceinline__ void sample_planes_slots(const FilterJob& j, uint32_t block)
 {
     static_assert(TAPS == 4 || TAPS == 8, "a lane stores one or two words per plane");
+    constexpr bool GAPS = TAPS == 8;                        // launches that fill the chip, see plane_taps()
     constexpr uint32_t kWgs = 32 / (4 * TAPS);              // workgroups per (channel block, reduction step)
     constexpr int kPer = P7 ? 16 : 4;                       // samples of a generator block
     const uint32_t lane = threadIdx.x & 63u;
@@ -218,19 +219,32 @@ __device__ __forceinline__ void sample_planes_slots(const FilterJob& j, uint32_t
     uint32_t n[TAPS];
 #pragma unroll
     for (int t = 0; t < TAPS; ++t) n[t] = (uint32_t)(j.to - j.from);
-    for (int b = j.from / kPer; kPer * b < j.to; ++b) {
+    int b = j.from / kPer;
+    if (j.from == 0 && j.to >= 2 * kPer) {                  // blocks 0 and 1 share two multiplies and two xors
+        uint32_t s_hib[2], hz[2], lo2[2];
+        block_setup(h, key, 0, s_hib[0], hz[0], lo2[0]);
+        block_setup(h, key, 1, s_hib[1], hz[1], lo2[1]);
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) {
+            n[t] = sample_block<4, P7, GAPS>(n[t], wt[t].x, tap_scalars(s_hib[0] ^ k[t], key), h, hz[0], lo2[0], key, 0, 0, 0);
+            n[t] = sample_block<4, P7, GAPS>(n[t], wt[t].x, tap_scalars(s_hib[1] ^ k[t], key), h, hz[1], lo2[1], key, 1, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        b = 2;
+    }
+    for (; kPer * b < j.to; ++b) {
         uint32_t s_hib, hz, lo2;
         block_setup(h, key, b, s_hib, hz, lo2);
         if (kPer * b >= j.from && kPer * (b + 1) <= j.to) {
 #pragma unroll
             for (int t = 0; t < TAPS; ++t) {
-                n[t] = sample_block<4, P7, false>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, 0, 0);
+                n[t] = sample_block<4, P7, GAPS>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);     // one call after the other (eight waves per SIMD)
             }
         } else {
 #pragma unroll
             for (int t = 0; t < TAPS; ++t)
-                n[t] = sample_block<0, P7, false>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, j.from, j.to);
+                n[t] = sample_block<0, P7, GAPS>(n[t], wt[t].x, tap_scalars(s_hib ^ k[t], key), h, hz, lo2, key, b, j.from, j.to);
         }
     }
 
@@ -260,7 +274,8 @@ __device__ __forceinline__ void sample_planes_slots(const FilterJob& j, uint32_t
 }
 
 // Slots per wave of a launch that samples `steps` (blocks of 64 channels x reduction steps).  Eight share the set-up of a wave
-// better (all 21 layers of a ResNet-18 shape at S = 8, 3135 steps: 36.2 us, 42.3 with four), four give a small launch twice the
+// better (all 21 layers of a ResNet-18 shape at S = 8, 3135 steps: 36.2 us, 42.3 with four; 34.3 since blocks 0 and 1 are drawn
+// together and the rounds have gaps), four give a small launch twice the
 // waves (us with four : eight slots, S = 8 - 18 steps 4.8:5.8, 288 steps 6.2:6.8, 576 steps 8.5:8.5, 1152 steps 12.3:12.0; S = 32 - 18
 // steps 7.5:11.2, 1152 steps 27.8:28.7).
 inline int plane_taps(int64_t steps) { return steps >= 576 ? 8 : 4; }
