@@ -639,7 +639,10 @@ int launch_shared(const psb_weights* q, const int8_t* x, const psb_conv_geom* g,
         transpose_blocks = (int64_t)tj.tiles_p * g->n * CB;
         if (rowpack) {
             tj.pack_KW = q->shape.kw; tj.OW = OW; tj.stride_w = g->stride_w; tj.pad_w = g->pad_w;
-            transpose_blocks = (tj.rows * OW + 255) / 256;
+            tj.pack = psb::row_pack_tiles(tj.rows, OW, g->stride_w, p.C, q->shape.kw);
+            tj.inv_outputs = psb::inverse_of((uint32_t)tj.pack.outputs); tj.inv_segments = psb::inverse_of((uint32_t)tj.pack.segments);
+            tj.inv_C = psb::inverse_of((uint32_t)p.C); tj.inv_H = psb::inverse_of((uint32_t)p.H);
+            transpose_blocks = (tj.rows + tj.pack.rows - 1) / tj.pack.rows * tj.pack.segments;
         }
     }
     auto prepare = [&](int from, int to) -> int {

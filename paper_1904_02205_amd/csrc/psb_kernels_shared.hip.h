@@ -37,6 +37,7 @@
 #include "psb_kernels.hip.h"
 #include "psb_device_lds.h"
 #include "psb_kernels_oc.hip.h"
+#include "psb_row_pack.h"
 
 namespace psb {
 
@@ -302,41 +303,78 @@ struct TransposeJob {
     int wide;             // H * W and the address of x are multiples of 4: the copy moves 32-bit words
     int64_t rows;         // N * H
     // row packing (pack_KW > 0): xt[n][iy][ox][kw * C + c] = x[n][c][iy][ox * stride_w - pad_w + kw], zero outside
-    // the row and in the unused slots; one thread per (n, iy, ox)
+    // the row and in the unused slots
     int pack_KW, OW, stride_w, pad_w;
+    RowPackTiles pack;
+    uint32_t inv_outputs, inv_segments, inv_C, inv_H;     // inverse_of() the divisors of the packing
 };
 
-__device__ __forceinline__ void row_pack_block(const TransposeJob& j, int64_t block)
+// One tile of packed rows, see RowPackTiles.  The image rows go to LDS with their channels interleaved (a wave copies the columns of
+// one row and channel at a time, everything else is scalar), where the kw x C values of a packed pixel are consecutive bytes: five
+// words for each half, shifted by the position's last two bits.  Bound by the 25.7 MB that it writes at 7x7, stride 2, 3 x 224 x 224, batch 32:
+// 10.4 us.  Threads that fetched their 32 bytes from the planes one by one spent 15.5 us there on addresses and byte loads; with one
+// copy of a row in flight to a wave and a whole packed pixel to a thread (stores of 16 in every 32 bytes) 13.6.
+__device__ __forceinline__ void row_pack_tile(const TransposeJob& j, uint32_t block, int8_t* tile)
 {
-    const int64_t i = block * 256 + threadIdx.x;          // (n * H + iy) * OW + ox
-    if (i >= j.rows * j.OW) return;
-    const uint32_t i32 = (uint32_t)i;                     // rows * OW is below 2^31 (xt has 32 bytes per element)
-    const uint32_t row = i32 / (uint32_t)j.OW;
-    const int ox = (int)(i32 - row * (uint32_t)j.OW);
-    const int n = (int)(row / (uint32_t)j.H), iy = (int)(row - (uint32_t)n * (uint32_t)j.H);
-    const int ix0 = ox * j.stride_w - j.pad_w;
-    // All 32 slots in straight-line code: slot s = kw * C + c; a slot outside the row (or beyond kw * C) reads
-    // element 0 of the tensor instead and is masked, so the loads do not wait for each other.
-    const uint32_t plane = (uint32_t)(j.H * j.W);
-    const uint32_t base = ((uint32_t)n * (uint32_t)j.C * (uint32_t)j.H + (uint32_t)iy) * (uint32_t)j.W;   // x[n][0][iy][0]
-    const int n_slots = j.pack_KW * j.C;
-    uint32_t v[32];
-    int kw = 0, c = 0;                                    // uniform, stepped on the scalar unit
+    const RowPackTiles& t = j.pack;
+    uint32_t segment;
+    const uint32_t group = div_mod(block, (uint32_t)t.segments, j.inv_segments, segment);
+    const int64_t row0 = (int64_t)group * t.rows;
+    const int n_rows = (int)min((int64_t)t.rows, j.rows - row0);
+    const int ox0 = (int)segment * t.outputs, ix0 = ox0 * j.stride_w - j.pad_w;
+    const int lane = (int)(threadIdx.x & 63u), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int n_copies = n_rows * j.C;                    // (row of the tile, channel); a wave has two of them in flight
+    for (int col0 = lane; col0 < t.cols; col0 += 256) {
+        for (int q = wave; q < n_copies; q += 8) {
+            int8_t v[2][4];
+            int dst[2];
 #pragma unroll
-    for (int s = 0; s < 32; ++s) {
-        const int ix = ix0 + kw;
-        const bool ok = (s < n_slots) & ((unsigned)ix < (unsigned)j.W);
-        const uint32_t at = ok ? base + (uint32_t)c * plane + (uint32_t)ix : 0u;
-        const uint32_t b = (uint8_t)j.x[at];
-        v[s] = ok ? b : 0u;
-        if (++c == j.C) { c = 0; ++kw; }
+            for (int u = 0; u < 2; ++u) {
+                const int copy = min(q + 4 * u, n_copies - 1);       // the second may be one that another wave has, too
+                uint32_t c, iy;
+                const uint32_t r = div_mod((uint32_t)copy, (uint32_t)j.C, j.inv_C, c);
+                const uint32_t n = div_mod((uint32_t)row0 + r, (uint32_t)j.H, j.inv_H, iy);
+                const int8_t* const src = j.x + (((int64_t)n * j.C + c) * j.H + iy) * j.W;
+                dst[u] = (int)r * t.row_bytes + (int)c;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int ix = ix0 + col0 + 64 * i;
+                    v[u][i] = 0;
+                    if (col0 + 64 * i < t.cols && (unsigned)ix < (unsigned)j.W) v[u][i] = src[ix];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (col0 + 64 * i < t.cols) tile[dst[u] + (col0 + 64 * i) * j.C] = v[u][i];
+        }
     }
-    uint32_t w[8];
+    __syncthreads();
+    // thread = half a packed pixel, so that a wave stores 1024 consecutive bytes
+    const uint32_t half = threadIdx.x & 1u;
+    const int used = j.pack_KW * j.C - 16 * (int)half;    // slots of this half; what lies behind them belongs to the next pixels
+    uint32_t keep[4];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) w[q] = v[4 * q] | (v[4 * q + 1] << 8) | (v[4 * q + 2] << 16) | (v[4 * q + 3] << 24);
-    uint4* dst = reinterpret_cast<uint4*>(j.xt + i * 32);
-    dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+    for (int i = 0; i < 4; ++i) {
+        const int bytes = used - 4 * i;
+        keep[i] = bytes >= 4 ? 0xFFFFFFFFu : bytes <= 0 ? 0u : (1u << (8 * bytes)) - 1u;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        uint32_t o;
+        const int r = (int)div_mod((threadIdx.x >> 1) + 128u * k, (uint32_t)t.outputs, j.inv_outputs, o);
+        const int ox = ox0 + (int)o;
+        if (r >= n_rows || ox >= j.OW) return;
+        const uint32_t at = (uint32_t)(r * t.row_bytes) + o * (uint32_t)(j.stride_w * j.C);
+        const uint32_t* const words = reinterpret_cast<const uint32_t*>(tile) + (at >> 2) + 4u * half;
+        uint32_t in[5], w[4];
+#pragma unroll
+        for (int i = 0; i < 5; ++i) in[i] = words[i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_alignbyte(in[i + 1], in[i], at & 3u) & keep[i];
+        *reinterpret_cast<uint4*>(j.xt + ((row0 + r) * j.OW + ox) * 32 + 16 * half) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
 }
 
 __device__ __forceinline__ void channels_last_tile(const TransposeJob& j, int64_t tile_index, int8_t (*tile)[64 + 4])
@@ -456,11 +494,12 @@ __global__ void __launch_bounds__(256) k_shared_prologue(const FilterJob f, cons
 {
     touch_arguments<FilterJob, TransposeJob, unsigned>();
     __shared__ __align__(16) int8_t tile[kWideTilePositions * kWideTileRow];
+    static_assert(sizeof(tile) >= kRowPackLds, "holds the image rows of a packed tile, too");
     if (blockIdx.x < filter_blocks) {        // uniform over the workgroup
         if (f.planes) sample_planes_block(f, blockIdx.x);
         else sample_filter_thread(f, (int64_t)blockIdx.x * 256 + threadIdx.x);
     } else if (t.pack_KW)
-        row_pack_block(t, (int64_t)(blockIdx.x - filter_blocks));
+        row_pack_tile(t, blockIdx.x - filter_blocks, tile);
     else if (t.wide)
         channels_last_tile_wide(t, (int64_t)(blockIdx.x - filter_blocks), tile);
     else

@@ -1,0 +1,72 @@
+"""The tiles of a first layer's row packing (csrc/psb_row_pack.h): every packed pixel is in one tile, the image rows fit the LDS, and
+32 bytes read from there are those of the definition xt[row][ox][kw * C + c] = x[c][row][ox * stride - pad + kw]."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1904_02205_amd", "csrc")
+
+PROGRAM = r"""
+#include "psb_row_pack.h"
+#include <cmath>
+#include <cstdio>
+#include <vector>
+using namespace psb;
+static unsigned long long state = 777;
+static unsigned below(unsigned n) { state = state * 6364136223846793005ull + 1442695040888963407ull; return (unsigned)(state >> 33) % n; }
+static int spread(int hi) { return std::max(1, (int)std::lround(std::exp(std::log((double)hi) * below(10001) / 10000.0))); }
+#define CHECK(c) do { if (!(c)) { std::printf("%s: rows %lld OW %d W %d stride %d pad %d C %d KW %d\n", #c, rows, OW, W, stride, pad, C, KW); return 1; } } while (0)
+int main()
+{
+    int cut = 0, several = 0;
+    for (int i = 0; i < 4000; ++i) {
+        const int KW = 2 + (int)below(31), C = 1 + (int)below(32 / KW), stride = below(8) ? 1 + (int)below(4) : spread(15000), pad = (int)below(KW + 2);
+        const int W = std::max(KW, spread(below(2) ? 300 : 30000)), OW = (W + 2 * pad - KW) / stride + 1;
+        const long long rows = spread(300);
+        const RowPackTiles t = row_pack_tiles(rows, OW, stride, C, KW);
+        CHECK(t.outputs >= 1 && t.segments >= 1 && t.rows >= 1 && t.rows <= rows && (t.rows == 1 || t.segments == 1));
+        CHECK(t.rows * t.outputs <= kRowPackOutputs && t.rows * t.row_bytes <= kRowPackLds && t.row_bytes % 4 == 0);
+        CHECK((long long)t.segments * t.outputs >= OW && (long long)(t.segments - 1) * t.outputs < OW);
+        cut += t.segments > 1;
+        several += t.rows > 1;
+        // one row: the bytes of a segment as the kernel writes them (what it does not write is 0x55), and what a pixel reads
+        std::vector<signed char> x((size_t)C * W);
+        for (auto& v : x) v = (signed char)below(256);
+        const int segments[] = {0, t.segments - 1};
+        for (int s : segments) {
+            const int ox0 = s * t.outputs, ix0 = ox0 * stride - pad;
+            std::vector<unsigned char> lds((size_t)t.row_bytes, 0x55);
+            for (int c = 0; c < C; ++c)
+                for (int col = 0; col < t.cols; ++col) {
+                    CHECK(col * C + c < t.row_bytes);
+                    const int ix = ix0 + col;
+                    lds[(size_t)(col * C + c)] = (unsigned char)(ix >= 0 && ix < W ? x[(size_t)c * W + ix] : 0);
+                }
+            for (int o = 0; o < t.outputs && ox0 + o < OW; ++o) {
+                const int at = o * stride * C;
+                CHECK(at / 4 * 4 + 36 <= t.row_bytes);
+                for (int slot = 0; slot < KW * C; ++slot) {
+                    const int ix = (ox0 + o) * stride - pad + slot / C;
+                    CHECK(lds[(size_t)(at + slot)] == (unsigned char)(ix >= 0 && ix < W ? x[(size_t)(slot % C) * W + ix] : 0));
+                }
+            }
+        }
+    }
+    std::printf("ok %d %d\n", cut, several);
+    return 0;
+}
+"""
+
+
+def test_tiles_of_the_row_packing(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    (tmp_path / "pack.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-Werror", "-I", CSRC, str(tmp_path / "pack.cpp"), "-o", str(tmp_path / "pack")],
+                   check=True)
+    out = subprocess.run([str(tmp_path / "pack")], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    word, cut, several = out.stdout.split()
+    assert word == "ok" and int(cut) > 500 and int(several) > 500
