@@ -1358,6 +1358,13 @@ int psb_maxpool2d_i8_blocked(const int8_t* x_dev, int32_t n, int32_t c, int32_t 
     if ((int64_t)n * cb * 32 * h * w >= (1ll << 40) || OH > 2147483647ll || OW > 2147483647ll || cb > 2147483647ll)
         return PSB_ERR_TOO_LARGE;
     const int64_t total = (int64_t)n * OH * cb * OW * 2;
+    if (kh == 3 && kw == 3 && total < (1ll << 31)) {
+        hipLaunchKernelGGL(psb::k_maxpool3x3_blocked_i8, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, (hipStream_t)hip_stream, x_dev,
+                           (uint32_t)total, (uint32_t)cb, h, w, stride_h, stride_w, pad_h, pad_w, (uint32_t)OH, (uint32_t)OW,
+                           psb::inverse_of((uint32_t)cb), psb::inverse_of((uint32_t)OH), psb::inverse_of((uint32_t)OW), out_dev);
+        PSB_HIP_TRY(hipGetLastError());
+        return PSB_OK;
+    }
     const int blocks = (int)std::min<int64_t>((total + 255) / 256, 65536);
     hipLaunchKernelGGL(psb::k_maxpool_blocked_i8, dim3(blocks), dim3(256), 0, (hipStream_t)hip_stream, x_dev, n, (int)cb, h, w,
                        kh, kw, stride_h, stride_w, pad_h, pad_w, (int)OH, (int)OW, out_dev);
